@@ -494,3 +494,51 @@ def tolerance(case):
     and 1.7e-3 (max 3.9e-3) with bf16 results; the bounds are four times that."""
     return {"i8": "exact", "f32": {"rel": 1.2e-6, "max": 6.5e-6}, "f16": {"rel": 8.5e-4, "max": 2e-3},
             "bf16": {"rel": 7e-3, "max": 1.6e-2}}[case["dtype"]]
+
+
+def exact(case, seed):
+    """What `run` returns for these inputs, from the operator's definition in float64."""
+    f, r = case["family"], case.get("instances", 1)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    x, *rest = [t.double().reshape((r, t.numel() // r)) for t in _inputs(case, g)]
+    shapes = _in_shapes(case)
+    shape, _ = _out_shape(case)
+    x = x.reshape((r,) + shapes[0])
+    if f == "softmax":
+        y = torch.softmax(x, -1)
+    else:
+        w = rest[0].reshape((r,) + shapes[1])
+        if f in ("gemm_f32", "gemm_rows", "gemm", "gemm_i8"):
+            y = torch.stack([p @ q for p, q in zip(x, w)])
+        elif f == "bmm":
+            w = w.transpose(-1, -2).contiguous() if case["trans_b"] else w
+            y = torch.stack([a @ b for p, q in zip(x, w) for a, b in zip(p, q)]).reshape((r,) + shape)
+        else:
+            bias = rest[1] if len(rest) > 1 else None
+            y = torch.stack([_exact_conv(case, x[i], w[i], shape) for i in range(r)])
+            if bias is not None:
+                y = torch.relu(y + bias.reshape((r,) + (1,) * (len(shape) - 1) + (shape[-1],)))
+    y = y.to(torch.int32) if f == "gemm_i8" else y
+    return y if r > 1 else y[0]
+
+
+def _exact_conv(case, x, w, shape):
+    """Sum over the filter's taps; x [N, (D,) H, W, C], w [(KD,) KH, KW, C(, Cout)], result of `shape`."""
+    f, s, p = case["family"], case["stride"], _pad(case)
+    if f == "conv_transposed":
+        # every tap writes a grid of pixels `stride` apart into an image that has the padding still around it
+        k, n = case["kernel"], case["size"]
+        y = torch.zeros((shape[0], shape[1] + 2 * p, shape[2] + 2 * p, shape[3]), dtype=torch.float64, device=x.device)
+        for kh in range(k):
+            for kw in range(k):
+                y[:, kh:kh + (n - 1) * s + 1:s, kw:kw + (n - 1) * s + 1:s] += x @ w[kh, kw]
+        return y[:, p:p + shape[1], p:p + shape[2]]
+    dims = len(shape) - 2
+    x = torch.nn.functional.pad(x, (0, 0) + (p, p) * dims)
+    y = torch.zeros(shape, dtype=torch.float64, device=x.device)
+    for tap in torch.cartesian_prod(*[torch.arange(case["kernel"])] * dims).tolist():
+        at = [t * case.get("dilation", 1) for t in tap]
+        part = x[(slice(None),) + tuple(slice(a, a + (o - 1) * s + 1, s) for a, o in zip(at, shape[1:-1]))]
+        y += part * w[tuple(tap)] if f == "depthwise" else part @ w[tuple(tap)]
+    return y
