@@ -104,6 +104,24 @@
 #endif
 #endif
 
+// Phase form of the transposed convolution (CV_PHASES 1).  An output pixel meets only the taps with
+// (oh + pad - kh) mod S = 0 (same for the columns), one in S^2 of them; the plain row order mixes the S^2 phases in
+// every tile, so each tile walks all KH*KW taps and multiplies zeros for the rest.  Here the rows are ordered so that
+// a tile lies in one phase, and the k loop covers that phase's (KH/S)*(KW/S) taps only: S^2 times fewer k steps and
+// activation loads, the same products.  Taken where every tile keeps to one phase and every k step to one tap;
+// elsewhere (filters that the stride does not divide, tiles wider than a phase) all taps are walked as before.
+// 16 x 16 x 256 -> 128, 4 x 4, stride 2, batch 64 in bf16: 77.8 -> 25.9 us.
+#if IS_CONV && CV_TRANSPOSED
+#define CV_BM_ (I1 * I2 * I3 * MI_M)
+#define CV_BK_ (K1 * K2 * K3 * MI_K)
+#define CV_PHASES (CV_STRIDE > 1 && DIM_B == 1 && CACHE_READ <= 4 && CV_KH % CV_STRIDE == 0 && CV_KW % CV_STRIDE == 0 && \
+                   CV_OH % CV_STRIDE == 0 && CV_OW % CV_STRIDE == 0 && (CV_N * (CV_OH / CV_STRIDE) * (CV_OW / CV_STRIDE)) % CV_BM_ == 0 && \
+                   CV_CIN % CV_BK_ == 0 && K0 * CV_BK_ == CV_KH * CV_KW * CV_CIN && K0 % (CV_STRIDE * CV_STRIDE * RFACTOR) == 0)
+#define K0_WALK (CV_PHASES ? K0 / (CV_STRIDE * CV_STRIDE) : K0) // k0 steps of a whole reduction
+#else
+#define CV_PHASES 0
+#define K0_WALK K0
+#endif
 #define B_KMAJOR (!IS_CONV && SB_K == 1 && SB_J != 1)
 // LDS_PAD 3 (j-contiguous B of a GEMM, register staging): B lies in LDS as in global memory, row-major k-rows of BN
 // elements, and the fragments come out of the transposing LDS loads; A as with LDS_PAD 2.  LDS_PAD 4: the same without
@@ -298,6 +316,45 @@ static_assert(!CV_TAPROWS || (CV_KR % MI_K == 0 && CV_KR >= CV_RUN && !K_PADDED 
 static_assert(!K_PADDED || COMPUTE_AT == 0, "a padded reduction needs the im2col loader");
 static_assert(!CV_TRANSPOSED || (COMPUTE_AT == 0 && CV_DIL == 1), "the transposed convolution exists in the im2col loader only");
 static_assert((CV_D == 1 && CV_KD == 1) || (COMPUTE_AT == 0 && !CV_TRANSPOSED), "3-D convolution exists in the im2col loader only");
+#if CV_PHASES
+// Phase form of the transposed convolution (see CV_PHASES above): row v of the launch's row order is output pixel
+// (n, a * S + ph, b * S + pw), where the workgroup's (ph, pw) = i0 mod S^2 and (n, a, b) counts inside the phase.
+constexpr int PH_N = CV_STRIDE * CV_STRIDE;
+constexpr int PH_H = CV_OH / CV_STRIDE, PH_W = CV_OW / CV_STRIDE;      // pixels of one phase of one image
+constexpr int PH_TH = CV_KH / CV_STRIDE, PH_TW = CV_KW / CV_STRIDE;    // taps that meet a phase
+// row of the output [n][oh][ow] that row `lr` of tile i0 is
+__device__ __forceinline__ long out_row(int i0, int lr)
+{
+    const int cls = i0 % PH_N, u = (i0 / PH_N) * BM + lr;
+    const int b = u % PH_W, a = (u / PH_W) % PH_H, n = u / (PH_W * PH_H);
+    return ((long)n * CV_OH + a * CV_STRIDE + cls / CV_STRIDE) * CV_OW + b * CV_STRIDE + cls % CV_STRIDE;
+}
+// filter row (kh) and column (kw) of the phase's tap `t` for an output offset ph (or pw): kh = r + S * t, r = (ph + pad) mod S;
+// it reads input row a + (ph + pad) / S - t
+__device__ __forceinline__ int phase_tap(int ph, int pad, int t) { return (ph + pad) % CV_STRIDE + CV_STRIDE * t; }
+// row of W [KH*KW*Cin] at which k step k0 of tile i0 starts (a step never leaves its tap: Cin is a multiple of BK)
+__device__ __forceinline__ long phase_w_row(int i0, int k0)
+{
+    const int cls = i0 % PH_N, k = k0 * BK, t = k / CV_CIN;
+    return (long)(phase_tap(cls / CV_STRIDE, CV_PAD_H, t / PH_TW) * CV_KW + phase_tap(cls % CV_STRIDE, CV_PAD, t % PH_TW)) * CV_CIN + k % CV_CIN;
+}
+// V channels from channel offset `kk` of k step k0 on, for row `lr` of tile i0
+template <int V> __device__ __forceinline__ vec_t<in_t, V> load_phase_a(const in_t *__restrict__ X, int i0, int lr, int k0, int kk)
+{
+    const int cls = i0 % PH_N, u = (i0 / PH_N) * BM + lr;
+    const int b = u % PH_W, a = (u / PH_W) % PH_H, n = u / (PH_W * PH_H);
+    const int k = k0 * BK, t = k / CV_CIN, ci = k % CV_CIN + kk;
+    const int ih = a + (cls / CV_STRIDE + CV_PAD_H) / CV_STRIDE - t / PH_TW, iw = b + (cls % CV_STRIDE + CV_PAD) / CV_STRIDE - t % PH_TW;
+    vec_t<in_t, V> x;
+    if ((unsigned)ih < (unsigned)CV_H && (unsigned)iw < (unsigned)CV_W) {
+        x = *reinterpret_cast<const vec_t<in_t, V> *>(X + (((long)n * CV_H + ih) * CV_W + iw) * CV_XC + ci);
+    } else {
+#pragma unroll
+        for (int q = 0; q < V; ++q) x.v[q] = 0;
+    }
+    return x;
+}
+#endif
 // im2col on the fly: row = output pixel, k = (kh, kw, ci)
 template <int V> __device__ __forceinline__ vec_t<in_t, V> load_conv_a(const in_t *__restrict__ X, int row, int k)
 {
@@ -352,7 +409,11 @@ __device__ __forceinline__ void kmajor_load(kmajor_stage<ROWS, V> &st, const in_
             const int row = idx / KV, kv = idx % KV;
 #if IS_CONV
             if (CONV_A) {
+#if CV_PHASES
+                st.r[it] = load_phase_a<V>(src, (int)row0 / BM, row, (int)k0e / BK, kv * V);
+#else
                 st.r[it] = load_conv_a<V>(src, (int)row0 + row, (int)k0e + kv * V);
+#endif
                 continue;
             }
 #endif
@@ -761,7 +822,11 @@ __device__ __forceinline__ void stage_load(tile_stage &st, const in_t *__restric
 #elif B_ROWMAJOR
     rowmajor_load(st.b, B, (long)j0 * BN, k0e, SB_K, tid, u0 - tile_stage::UNITS_A, u1 - tile_stage::UNITS_A);
 #else
+#if CV_PHASES
+    jmajor_load(st.b, B, (long)j0 * BN, phase_w_row(i0, k0), SB_K, tid, u0 - tile_stage::UNITS_A, u1 - tile_stage::UNITS_A);
+#else
     jmajor_load(st.b, B, (long)j0 * BN, k0e, SB_K, tid, u0 - tile_stage::UNITS_A, u1 - tile_stage::UNITS_A);
+#endif
 #endif
 }
 
@@ -1110,6 +1175,11 @@ __device__ __forceinline__ void dl_read_frags(frag_t (&fa)[K3][TM], frag_t (&fb)
 #endif // CACHE_READ >= 5
 
 
+#if !CV_PHASES
+// row of the output that row `lr` of tile i0 is
+__device__ __forceinline__ long out_row(int i0, int lr) { return (long)i0 * BM + lr; }
+#endif
+
 constexpr int CROW = BN * (int)sizeof(out_t) + 16; // bytes of one staged output row (cache-write)
 
 // second half of the CACHE_WRITE epilogue: NT threads (t = 0 .. NT-1) write the staged tile as whole rows
@@ -1123,7 +1193,7 @@ __device__ __forceinline__ void flush_cstage(out_t *__restrict__ C, int i0, int 
     for (int idx = t; idx < TOTAL; idx += NT) {
         const int row = idx / CHUNKS_PER_ROW, ch = idx % CHUNKS_PER_ROW;
         const chunk_t v = *reinterpret_cast<const chunk_t *>(cstage + row * CROW + ch * 16);
-        char *dst = (char *)(C + ((long)i0 * BM + row) * LDC + (long)j0 * BN) + ch * 16;
+        char *dst = (char *)(C + out_row(i0, row) * LDC + (long)j0 * BN) + ch * 16;
         *reinterpret_cast<chunk_t *>(dst) = v;
     }
 }
@@ -1171,7 +1241,7 @@ __device__ __forceinline__ void write_tile(accv_t (&acc)[TM][TN], out_t *__restr
 #if CACHE_WRITE
                         *reinterpret_cast<vec_t<out_t, 4> *>(cstage + lr * CROW + lc * (int)sizeof(out_t)) = o;
 #else
-                        *reinterpret_cast<vec_t<out_t, 4> *>(C + ((long)i0 * BM + lr) * LDC + col) = o;
+                        *reinterpret_cast<vec_t<out_t, 4> *>(C + out_row(i0, lr) * LDC + col) = o;
 #endif
                     }
                 }
@@ -1709,8 +1779,8 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
 }
 #endif // CONV_HELPERS
 #else // REORDER != 3
-constexpr int K0L = K0 / RFACTOR; // k0 steps of one workgroup
-static_assert(K0 % RFACTOR == 0, "rfactor divides the k0 loop");
+constexpr int K0L = K0_WALK / RFACTOR; // k0 steps of one workgroup
+static_assert(K0_WALK % RFACTOR == 0, "rfactor divides the k0 loop");
 static_assert(RFACTOR == 1 || (!CACHE_WRITE && !CONV_RESIDENT), "rfactor: partial sums leave straight from the accumulators");
 
 #if RFACTOR > 1
@@ -1726,7 +1796,7 @@ __device__ __forceinline__ void write_partial(accv_t (&acc)[TM][TN], acc_t *__re
 #pragma unroll
                 for (int c3 = 0; c3 < J3; ++c3) {
                     const int trow = (r1 * I2 + wi) * I3 + r3, tcol = (c1 * J2 + wj) * J3 + c3;
-                    const long row = (long)i0 * BM + trow * MI_M + lrow;
+                    const long row = out_row(i0, trow * MI_M + lrow);
 #pragma unroll
                     for (int g = 0; g < ACC_N / 4; ++g) {
                         const long col = (long)j0 * BN + tcol * MI_N + (MI_M == 16 ? 4 * lgrp : 8 * g + 4 * lgrp);

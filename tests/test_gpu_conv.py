@@ -290,6 +290,38 @@ def test_transposed_conv_exact(stride, pad, k, H, W_):
         assert np.array_equal(got[0], ref) and np.array_equal(got[1], ref), "trace %d" % n
 
 
+@pytest.mark.parametrize("stride,pad,k,N,H,W_,flags", [(2, 1, 4, 2, 8, 8, 0xFF), (2, 0, 2, 1, 4, 8, 0x4FF), (4, 0, 4, 2, 8, 4, 0xFF),
+                                                         (2, 2, 6, 2, 8, 4, 0x4FF), (3, 0, 3, 1, 8, 6, 0xFF)])
+def test_transposed_conv_phases_exact(stride, pad, k, N, H, W_, flags):
+    """Traces whose tiles keep to one phase of the output grid and whose k steps keep to one tap: the kernel walks that
+    phase's taps only.  Integer-valued inputs, 2 instances: bit-equal fp32 outputs in every staging mode drawn."""
+    Cin, Cout = 64, 32
+    g = I.rng(75)
+    X = I.small_ints(g, (N, H, W_, Cin), -2, 2, "f16")
+    Wt = I.small_ints(g, (k, k, Cin, Cout), -2, 2, "f16")
+    bias = g.integers(-3, 4, size=Cout).astype(np.float32)
+    ref = O.conv2d_transposed_nhwc(X, Wt, bias=bias, relu=True, stride=stride, pad=pad)
+    assert ref.shape[1:3] == (H * stride, W_ * stride)
+    op = B.conv2d_transposed_op(N, H, W_, Cin, Cout, k, k, stride=stride, pad=pad, out_dtype="f32")
+    space = op.space(flags)
+    modes = {}
+    for idx in range(3000):
+        t = B.trace_sample_valid(op, space, 76, idx)
+        p = B.trace_validate(op, space, t)
+        if (N * H * W_) % p.block_m or Cin % p.block_k or p.tk[0] % (stride * stride * p.rfactor) or p.block_m < 32:
+            continue
+        mode = (p.cache_read, p.cache_write, p.rfactor > 1)
+        if mode in modes:
+            continue
+        modes[mode] = True
+        print("trace", idx, t.decisions(), flush=True)
+        got = run_variant(op, space, t, [X, Wt, bias], "f32", ref.shape, instances=2)
+        if got is None:
+            continue
+        assert np.array_equal(got[0], ref) and np.array_equal(got[1], ref), "trace %d" % idx
+    assert len({m[0] for m in modes}) >= 3 and (flags == 0xFF or any(m[2] for m in modes)), modes
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_t2d_config_transposed_conv_4x4x512(dtype):
     """The paper's T2D shape: 4 x 4 x 512 -> 8 x 8 x 256, 4 x 4 filter, stride 2, padding 1 (K = 8192)."""
