@@ -519,6 +519,17 @@ static std::string def(const char *name, int64_t v)
 
 static int dt_code(int32_t dt) { return dt; }
 
+// Elements per vector of the whole-vector row kernel (reduce.hip), 0 = the kernel that the factors spell out.
+// Taken for a softmax whose lane groups read less than a 128-byte line per access, or read the row once per pass
+// (cache_read 0), where a row is whole 16-byte vectors and at most 64 values per lane of a wavefront.
+static int row_vectors(const ms_op *op, const ms_variant_params *p)
+{
+    if (op->d.kind != MS_OP_SOFTMAX) return 0;
+    const int v = 16 / std::max(op->in_size, op->out_size);
+    if (op->K % v || op->K > 64 * 64) return 0;
+    return !p->cache_read || (int64_t)p->tk[2] * p->tk[3] * op->in_size < 128 ? v : 0;
+}
+
 int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec *out)
 {
     const ms_op_desc &d = op->d;
@@ -622,6 +633,17 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
         D.push_back(def("RD_OP", d.kind == MS_OP_NORM ? 1 : 0));
         D.push_back(def("RD_ROWS", op->M));
         D.push_back(def("RD_LEN", op->K));
+        if (const int v = row_vectors(op, p)) {
+            int lanes = 1;
+            while (lanes < 64 && lanes * v < op->K) lanes *= 2;
+            const int waves = 4;
+            D.push_back(def("ROW_VEC", v));
+            D.push_back(def("ROW_LANES", lanes));
+            D.push_back(def("ROW_WAVES", waves));
+            const int64_t rows = waves * (64 / lanes);
+            k.block[0] = (unsigned)(waves * 64);
+            k.grid[0] = (unsigned)((op->M + rows - 1) / rows);
+        }
     } else {
         k.template_name = "dwconv.hip";
         D.push_back(def("CV_N", d.dims[0]));

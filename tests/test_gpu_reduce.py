@@ -87,6 +87,28 @@ def test_groups_wider_than_a_wavefront_and_exact_cases():
         assert np.array_equal(got[0], got[1])
 
 
+@pytest.mark.parametrize("dtype,out", [("f32", "f32"), ("f16", "f16"), ("bf16", "f32")])
+@pytest.mark.parametrize("cols", [8, 24, 136, 1000, 1896, 4096])
+def test_softmax_whole_vector_rows(cols, dtype, out):
+    """Rows of whole 16-byte vectors under narrow lane groups: one lane group of a wavefront holds the row, the last
+    vectors masked.  Row counts that no workgroup's rows divide, elements at -inf, a maximum in the last element."""
+    g = I.rng(53)
+    X = I.normal(g, (1, 24, cols), 2.0, dtype)
+    X[0, 3, ::2] = -np.inf if dtype != "bf16" else X[0, 3, 1]
+    X[0, 5, cols - 1] = X[0, 4, cols - 1] = X[0].max()
+    ref = O.softmax(X) if dtype != "bf16" else O.softmax(X, bf16=True)
+    op = B.softmax_op(1, 24, cols, dtype, out)
+    space = op.space()
+    for vals in ([[3, 1, 8, 1], [cols // 8, 1, 8, 1], [0]], [[1, 3, 8, 1], [1, cols // 8, 8, 1], [1]]):
+        if vals[2] == [1] and cols > 8 * 64:
+            continue
+        got = run_variant(op, space, B.make_trace(space, vals), [X], out, ref.shape, instances=2)
+        if got is None:
+            continue
+        compare.assert_float_close(got[0], ref, compare.RTOL_F32 if out == dtype == "f32" else compare.RTOL_HALF if out != "f32" else 1e-5, "softmax %d" % cols)
+        assert np.array_equal(got[0], got[1])
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_softmax_and_norm_half_inputs_odd_shapes(dtype):
     """Extents with factors 3 and 5; the softmax output is rounded once to the input type."""
