@@ -13,6 +13,71 @@
 //           register copy of its input patch; 1: rolled, every tap re-reads its input)
 #include "common.h"
 
+#ifndef STRIP
+#define STRIP 0
+#endif
+#if STRIP
+// Strips (STRIP S > 0; the host's rule is dw_strip() in ms_interp.cpp): images whose extents have no small divisor but 2,
+// so that no perfect tile gives a thread a compact output patch.  A thread makes S x S output pixels of one channel;
+// threads count the channels first, then the strips of the image, and the last strips of a row or column are masked.
+// What bounds the general kernel there is the L1: a 1 x 29 patch of one thread reads 6 values per output, lane groups of 16
+// channels read half lines, and its 188 registers leave one workgroup per compute unit.  The halo costs no branch: a
+// buffer load beyond the image's bytes returns zero, and pixels outside the image ask for such an offset.
+// 57 x 57 x 144, stride 2, batch 128: 75.1 -> 50.4 us (6.0 TB/s); of one channel 4 x 4 was the fastest (2 x 4: 53.1,
+// 6 x 6: 51.4, 8 x 8: 64.3), 2 and 4 channels per thread read more lines per output (2 x 4 of 2: 55.6, of 4: 49.8 but
+// 327 against 300 us on 112 x 112 x 32, stride 1).
+constexpr int SP_H = (STRIP - 1) * CV_STRIDE + CV_KH, SP_W = (STRIP - 1) * CV_STRIDE + CV_KW; // input patch of a strip
+constexpr int S_OH = (CV_OH + STRIP - 1) / STRIP, S_OW = (CV_OW + STRIP - 1) / STRIP;           // strips of an image
+constexpr int IMG_BYTES = CV_H * CV_W * CV_C * 4;
+
+extern "C" __global__ void __launch_bounds__(STRIP_THREADS)
+ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *__restrict__ unused_, void *__restrict__ y_, int instances)
+{
+    (void)unused_;
+    int z = blockIdx.z * gridDim.y + blockIdx.y; // instance * N + n
+    int wg = blockIdx.x;
+    const long total = (long)gridDim.x * gridDim.y * gridDim.z;
+    if (total % 8 == 0) { // workgroup order grouped per XCD: strips that share input rows meet in one L2
+        const long f = wg + (long)gridDim.x * z;
+        const long g = (f % 8) * (total / 8) + f / 8;
+        wg = (int)(g % gridDim.x);
+        z = (int)(g / gridDim.x);
+    }
+    if (z >= instances * CV_N) return;
+    const int item = wg * STRIP_THREADS + threadIdx.x;
+    if (item >= S_OH * S_OW * CV_C) return;
+    const int c = item % CV_C, ow = item / CV_C % S_OW * STRIP, oh = item / (CV_C * S_OW) * STRIP;
+    const float *X = (const float *)x_ + (long)z * (CV_H * CV_W * CV_C);
+    const float *__restrict__ Wt = (const float *)w_ + (long)(z / CV_N) * CV_KH * CV_KW * CV_C + c;
+    float *__restrict__ Y = (float *)y_ + (long)z * CV_OH * CV_OW * CV_C + c;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(X), 0, IMG_BYTES, 0x00020000);
+
+    float x[SP_H][SP_W], w[CV_KH][CV_KW];
+#pragma unroll
+    for (int ph = 0; ph < SP_H; ++ph)
+#pragma unroll
+        for (int pw = 0; pw < SP_W; ++pw) {
+            const int ih = oh * CV_STRIDE - CV_PAD + ph, iw = ow * CV_STRIDE - CV_PAD + pw;
+            const bool in = (unsigned)ih < (unsigned)CV_H && (unsigned)iw < (unsigned)CV_W;
+            x[ph][pw] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, in ? ((ih * CV_W + iw) * CV_C + c) * 4 : IMG_BYTES, 0, 0));
+        }
+#pragma unroll
+    for (int kh = 0; kh < CV_KH; ++kh)
+#pragma unroll
+        for (int kw = 0; kw < CV_KW; ++kw) w[kh][kw] = Wt[(kh * CV_KW + kw) * CV_C];
+#pragma unroll
+    for (int a = 0; a < STRIP; ++a)
+#pragma unroll
+        for (int b = 0; b < STRIP; ++b) {
+            float acc = 0.f;
+#pragma unroll
+            for (int kh = 0; kh < CV_KH; ++kh)
+#pragma unroll
+                for (int kw = 0; kw < CV_KW; ++kw) acc += x[a * CV_STRIDE + kh][b * CV_STRIDE + kw] * w[kh][kw];
+            if (oh + a < CV_OH && ow + b < CV_OW) Y[((oh + a) * CV_OW + ow + b) * CV_C] = acc;
+        }
+}
+#else
 constexpr int BOH = I1 * I2 * I3;
 constexpr int BOW = J1 * J2 * J3;
 constexpr int BC = C1 * C2 * C3;
@@ -159,3 +224,4 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
                 }
             }
 }
+#endif // STRIP

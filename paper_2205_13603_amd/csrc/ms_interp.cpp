@@ -530,6 +530,26 @@ static int row_vectors(const ms_op *op, const ms_variant_params *p)
     return !p->cache_read || (int64_t)p->tk[2] * p->tk[3] * op->in_size < 128 ? v : 0;
 }
 
+// Output pixels per side of a thread's strip in the strip kernel (dwconv.hip), 0 = the kernel that the factors spell out.
+// Taken where an output extent above 2 has no divisor from 3 to 8: perfect tiles then leave a thread a row, a column or a
+// single pixel, which reads its inputs several times over (57 x 57 x 144, stride 2, batch 128: 75 against 50 us; 73 x 73 x 32,
+// batch 22: 119 against 6).  Elsewhere the factors can say better what fits.
+static int dw_strip(const ms_op *op)
+{
+    const ms_op_desc &d = op->d;
+    auto stubborn = [](int64_t e) {
+        for (int64_t f = 3; f <= 8; ++f)
+            if (e % f == 0) return false;
+        return e > 2;
+    };
+    if (!stubborn(op->OH) && !stubborn(op->OW)) return 0;
+    const int64_t strip = 4, regs = ((strip - 1) * d.stride + d.dims[4]) * ((strip - 1) * d.stride + d.dims[5]) + d.dims[4] * d.dims[5];
+    if (regs > 256) return 0; // the thread's input patch and taps stay in registers
+    // 32-bit byte offsets inside an image, 32-bit counts of its strips
+    if (d.dims[1] * d.dims[2] * d.dims[3] > 0x7ffffff0 / 4 || op->OH * op->OW * d.dims[3] > 0x7ffffff0) return 0;
+    return (int)strip;
+}
+
 int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec *out)
 {
     const ms_op_desc &d = op->d;
@@ -656,6 +676,14 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
         D.push_back(def("CV_OW", op->OW));
         D.push_back(def("CV_STRIDE", d.stride));
         D.push_back(def("CV_PAD", d.pad));
+        if (const int strip = dw_strip(op)) {
+            const int64_t items = ((op->OH + strip - 1) / strip) * ((op->OW + strip - 1) / strip) * d.dims[3];
+            const int64_t threads = std::min<int64_t>(256, (items + 63) / 64 * 64);
+            D.push_back(def("STRIP", strip));
+            D.push_back(def("STRIP_THREADS", threads));
+            k.block[0] = (unsigned)threads;
+            k.grid[0] = (unsigned)((items + threads - 1) / threads);
+        }
     }
     *out = k;
     return MS_OK;

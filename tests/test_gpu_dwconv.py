@@ -55,3 +55,22 @@ def test_depthwise_instances_with_distinct_inputs():
             continue
         for r in range(3):
             compare.assert_float_close(got[r], refs[r], compare.RTOL_F32, "instance %d trace %d" % (r, n))
+
+
+@pytest.mark.parametrize("H,W_,Cc,stride,pad,k", [(11, 13, 12, 1, 1, 3), (57, 23, 7, 2, 1, 3), (29, 16, 24, 1, 2, 5), (4, 38, 1, 1, 0, 2),
+                                                  (71, 22, 8, 2, 3, 5), (11, 44, 65, 1, 3, 7)])
+def test_depthwise_strips_exact(H, W_, Cc, stride, pad, k):
+    """Output extents without a divisor from 3 to 8: strips of 4 x 4 outputs per thread, the last ones masked, halo pixels
+    by buffer loads beyond the image.  Batch 3, 2 instances with their own filters; integer-valued inputs -> exact."""
+    g = I.rng(5)
+    ins = [[I.small_ints(g, (3, H, W_, Cc), -3, 3, "f32"), I.small_ints(g, (k, k, Cc), -3, 3, "f32")] for _ in range(2)]
+    refs = [O.dwconv2d_nhwc(x, w, stride=stride, pad=pad) for x, w in ins]
+    op = B.dwconv2d_op(3, H, W_, Cc, k, k, stride=stride, pad=pad)
+    space = op.space()
+    t = B.trace_sample_valid(op, space, 15, 0)
+    assert "-DSTRIP=4" in B.variant_kernel_text(op, B.trace_validate(op, space, t))
+    got = run_variant_distinct(op, space, t, ins, "f32", refs[0].shape)
+    if got is None:
+        return
+    for r in range(2):
+        assert np.array_equal(got[r], refs[r]), "instance %d" % r
