@@ -1,0 +1,234 @@
+// First-layer convolution (2-D or 3-D, 1 to 4 channels per pixel, + bias + ReLU) on the CDNA4 matrix cores, straight
+// from image rows; which variants run here says conv_rows() in ms_interp.cpp.
+//
+// What bounds the im2col form of such a layer is its loader: a matrix-core operand of 8 k values crosses taps and rows,
+// so every value is a 2-byte load with its own index arithmetic.  Here the reduction is laid out by filter rows: for one
+// filter plane kd, the KW * Cin elements that a filter row meets are contiguous in an image row, and a lane's 8 k values
+// are one 16-byte piece ("chunk") of them.  A run takes CPR chunks of 8; the lane groups of an intrinsic take two
+// consecutive chunks of the whole plane, which need not belong to the same filter row, so that only runs are padded
+// (7 x 3 channels: 22 of 24) and not k steps.
+//
+// A workgroup makes CR_WAVES x CR_TM x 32 consecutive pixels of one output plane for CR_TN x 32 output channels.  Per
+// filter plane it stages the image rows that its pixels meet and the plane's weights in LDS, and while it multiplies
+// them the next plane's rows and weights are on their way into registers.  Filter planes outside the input are skipped.
+// A wavefront holds CR_TM x CR_TN accumulator tiles: LDS reads 8 * (TM + TN) clocks per k step on each of four SIMDs
+// against 32 * TM * TN of the matrix cores.  8 x 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2 in fp16: 572 -> 144 us
+// (735 TFLOP/s); 128 x 224 x 224 x 3 -> 64, 7 x 7: 117 -> 75 us (3.3 TB/s).
+#include "common.h"
+
+typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 b8_t __attribute__((ext_vector_type(8)));
+typedef short tr4_t __attribute__((ext_vector_type(4)));
+typedef float accv_t __attribute__((ext_vector_type(16)));
+typedef unsigned u4_t __attribute__((ext_vector_type(4)));
+
+constexpr int TM = CR_TM, TN = CR_TN, NT = CR_WAVES * 64;
+constexpr int PX = CR_WAVES * TM * 32;                    // output pixels of a workgroup
+constexpr int BN = TN * 32, JB = DIM_N / BN;              // output channels of a workgroup, column blocks
+constexpr int OHW = CV_OH * CV_OW, TILES = (OHW + PX - 1) / PX;
+constexpr int LEAD = CV_PAD * CV_CIN % 2;                 // runs start at even elements: 4-byte LDS reads
+constexpr int RUN = CV_KW * CV_CIN, CPR = (LEAD + RUN + 7) / 8; // elements of a filter row, its chunks
+constexpr int NCH = CV_KH * CPR, STEPS = (NCH + 1) / 2;   // chunks of a filter plane, matrix-core steps of two chunks
+constexpr int ROW_E = CV_W * CV_CIN, CPW = ROW_E / 8;     // elements of an image row, its 16-byte vectors
+static_assert(ROW_E % 8 == 0 && CV_STRIDE * CV_CIN % 2 == 0 && DIM_N % BN == 0, "whole vectors per row, even pixel steps");
+
+// LDS: image rows with their zero columns, then the weights row-major, rows padded by 32 bytes for the transposing reads
+constexpr int LHALO = ((CV_PAD * CV_CIN + LEAD) * 2 + 15) / 16 * 16;
+constexpr int ORG = LHALO - (CV_PAD * CV_CIN + LEAD) * 2; // byte of pixel 0's run in its row
+constexpr int READ_END = ORG + (CV_OW - 1) * CV_STRIDE * CV_CIN * 2 + CPR * 16, IMG_END = LHALO + ROW_E * 2;
+constexpr int PRS = ((READ_END > IMG_END ? READ_END : IMG_END) + 15) / 16 * 16;
+constexpr int P_OUT_ = PX % CV_OW == 0 ? PX / CV_OW : (CV_OW + PX - 2) / CV_OW + 1;
+constexpr int P_OUT = P_OUT_ < CV_OH ? P_OUT_ : CV_OH;    // output rows that a workgroup can touch
+constexpr int PR = (P_OUT - 1) * CV_STRIDE + CV_KH;       // input rows
+constexpr int RMB = BN * 2 + 32;                          // bytes of a weight row
+constexpr int PATCH_B = PR * PRS, WT_B = STEPS * 16 * RMB;
+constexpr int SROW = BN * (int)sizeof(out_t) + 16, STG_B = CR_WAVES * 32 * SROW; // staged output rows, 32 per wavefront
+constexpr int LDS_B = PATCH_B + WT_B > STG_B ? PATCH_B + WT_B : STG_B;
+constexpr int cr_gcd(int a, int b) { return b ? cr_gcd(b, a % b) : a; }
+constexpr int AL = cr_gcd(16, cr_gcd(ORG, CV_STRIDE * CV_CIN * 2)); // alignment of a fragment in its row
+
+// inputs are aligned to their elements only: 16 bytes at any address
+struct __attribute__((packed, aligned(2))) raw16_t {
+    u4_t v;
+};
+constexpr int XI = (PR * CPW + NT - 1) / NT;              // vectors of the image rows per thread
+constexpr int WROWS = CV_KH * RUN, WCB = BN / 8;          // weight rows of a filter plane, 16-byte vectors of one
+constexpr int WI = (WROWS * WCB + NT - 1) / NT;
+
+// byte of chunk c relative to a pixel's run; the chunk behind the last one (odd counts) meets zero weights and is masked
+constexpr int koff(int c) { return c < NCH ? c / CPR * PRS + c % CPR * 16 : koff(c - 1); }
+// bits of dword d of chunk c that belong to the run: the others are neighbours, which may be infinite or NaN
+constexpr unsigned kmask(int c, int d)
+{
+    unsigned m = 0;
+    for (int h = 0; h < 2; ++h) {
+        const int q = c % CPR * 8 + d * 2 + h;
+        if (c < NCH && q >= LEAD && q < LEAD + RUN) m |= 0xffffu << (16 * h);
+    }
+    return m;
+}
+
+__device__ __forceinline__ accv_t mfma(const u4_t &a, const u4_t &b, accv_t c)
+{
+#if IN_DT == DT_F16
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8_t, a), __builtin_bit_cast(h8_t, b), c, 0, 0, 0);
+#else
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(b8_t, a), __builtin_bit_cast(b8_t, b), c, 0, 0, 0);
+#endif
+}
+
+struct stage_t {
+    u4_t x[XI], w[WI];
+};
+
+__device__ __forceinline__ void stage_fetch(stage_t &st, const in_t *__restrict__ plane, const in_t *__restrict__ wt, int ih_lo, int tid)
+{
+#pragma unroll
+    for (int i = 0; i < XI; ++i) {
+        const int idx = i * NT + tid, row = idx / CPW, ih = ih_lo + row;
+        const bool ok = (unsigned)ih < (unsigned)CV_H && row < PR;
+        // rows outside the image read the plane's first vector (always there) and become zero
+        const u4_t v = reinterpret_cast<const raw16_t *>(plane + (ok ? ih * ROW_E + idx % CPW * 8 : 0))->v;
+        st.x[i] = ok ? v : u4_t{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int i = 0; i < WI; ++i) {
+        const int idx = i * NT + tid;
+        if (WROWS * WCB % NT == 0 || idx < WROWS * WCB) st.w[i] = reinterpret_cast<const raw16_t *>(wt + (long)(idx / WCB) * DIM_N + idx % WCB * 8)->v;
+    }
+}
+
+__device__ __forceinline__ void stage_commit(const stage_t &st, char *__restrict__ patch, char *__restrict__ wts, int tid)
+{
+#pragma unroll
+    for (int i = 0; i < XI; ++i) {
+        const int idx = i * NT + tid;
+        if (PR * CPW % NT == 0 || idx < PR * CPW) *reinterpret_cast<u4_t *>(patch + idx / CPW * PRS + LHALO + idx % CPW * 16) = st.x[i];
+    }
+#pragma unroll
+    for (int i = 0; i < WI; ++i) {
+        const int idx = i * NT + tid, r = idx / WCB;
+        if (WROWS * WCB % NT == 0 || idx < WROWS * WCB)
+            *reinterpret_cast<u4_t *>(wts + (r / RUN * CPR * 8 + LEAD + r % RUN) * RMB + idx % WCB * 16) = st.w[i];
+    }
+}
+
+extern "C" __global__ void __launch_bounds__(NT, 2)
+ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *__restrict__ bias_, void *__restrict__ y_, int instances)
+{
+    __shared__ __attribute__((aligned(16))) char smem[LDS_B];
+    int wg = blockIdx.x, z = blockIdx.z * gridDim.y + blockIdx.y; // z = instance
+    const long total = (long)gridDim.x * gridDim.y * gridDim.z;
+    if (total % 8 == 0) { // workgroup order grouped per XCD: tiles that share input rows and planes meet in one L2
+        const long f = wg + (long)gridDim.x * z, g = (f % 8) * (total / 8) + f / 8;
+        wg = (int)(g % gridDim.x);
+        z = (int)(g / gridDim.x);
+    }
+    if (z >= instances) return;
+    const int jb = wg % JB, od = wg / JB % CV_OD, tile = wg / (JB * CV_OD) % TILES, n = wg / (JB * CV_OD * TILES);
+    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, lrow = lane % 32, lgrp = lane / 32;
+    const int p0 = tile * PX, oh_lo = p0 / CV_OW, ih_lo = oh_lo * CV_STRIDE - CV_PAD_H;
+    const in_t *X = (const in_t *)x_ + (long)z * A_INST + (long)n * CV_D * CV_H * ROW_E;
+    const in_t *Wt = (const in_t *)w_ + (long)z * B_INST + jb * BN;
+    char *patch = smem, *wts = smem + PATCH_B;
+
+    // filter planes that lie inside the input
+    const int id0 = CV_D > 1 || CV_KD > 1 ? od * CV_STRIDE - CV_PAD : 0;
+    const int kd_lo = id0 < 0 ? -id0 : 0, kd_hi = CV_D - id0 < CV_KD ? CV_D - id0 : CV_KD;
+
+    stage_t st;
+    if (kd_lo < kd_hi) stage_fetch(st, X + (long)(id0 + kd_lo) * CV_H * ROW_E, Wt + (long)kd_lo * WROWS * DIM_N, ih_lo, tid);
+    // zero columns of the image rows and padding rows of the weights: written once, no plane overwrites them
+    for (int i = tid; i < (PATCH_B + WT_B) / 16; i += NT) *reinterpret_cast<u4_t *>(smem + i * 16) = u4_t{0, 0, 0, 0};
+
+    accv_t acc[TM][TN];
+    int pix[TM];
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = accv_t{};
+        int p = p0 + (wave * TM + tm) * 32 + lrow;
+        p = p < OHW ? p : OHW - 1; // pixels behind the plane repeat its last one and are not stored
+        pix[tm] = (p / CV_OW - oh_lo) * CV_STRIDE * PRS + ORG + p % CV_OW * (CV_STRIDE * CV_CIN * 2);
+    }
+    const int li = lane % 16;
+    const char *wl = wts + (lgrp * 8 + li / 4) * RMB + lrow / 16 * 32 + li % 4 * 8;
+
+#pragma unroll 1
+    for (int kd = kd_lo; kd < kd_hi; ++kd) {
+        __syncthreads();
+        stage_commit(st, patch, wts, tid);
+        __syncthreads();
+        if (kd + 1 < kd_hi) stage_fetch(st, X + (long)(id0 + kd + 1) * CV_H * ROW_E, Wt + (long)(kd + 1) * WROWS * DIM_N, ih_lo, tid);
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            u4_t fa[TM], fb[TN];
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) {
+                union {
+                    u4_t u;
+                    tr4_t h[2];
+                } b;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    b.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) tr4_t *)(wl + (s * 16 + h * 4) * RMB + tn * 64));
+                fb[tn] = b.u;
+            }
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) {
+                const unsigned *src = reinterpret_cast<const unsigned *>(
+                    __builtin_assume_aligned(patch + (pix[tm] + lgrp * (koff(2 * s + 1) - koff(2 * s)) + koff(2 * s)), AL));
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const unsigned m0 = kmask(2 * s, d), m1 = kmask(2 * s + 1, d);
+                    fa[tm][d] = m0 == ~0u && m1 == ~0u ? src[d] : src[d] & (lgrp ? m1 : m0);
+                }
+            }
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = mfma(fb[tn], fa[tm], acc[tm][tn]);
+        }
+    }
+
+    // epilogue: + bias, ReLU, one rounding; a wavefront turns 32 pixels at a time in its own LDS rows and stores whole rows
+    __syncthreads();
+    out_t *Y = (out_t *)y_ + (((long)z * CV_N + n) * CV_OD + od) * OHW * DIM_N + jb * BN;
+    char *stg = smem + wave * 32 * SROW;
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int col = tn * 32 + 8 * g + 4 * lgrp;
+                vec_t<out_t, 4> o;
+#if HAS_BIAS
+                const vec_t<float, 4> bias = *reinterpret_cast<const vec_t<float, 4> *>((const float *)bias_ + (long)z * DIM_N + jb * BN + col);
+#endif
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float v = acc[tm][tn][4 * g + e];
+#if HAS_BIAS
+                    v += bias.v[e];
+#endif
+#if RELU
+                    v = v > 0 ? v : 0;
+#endif
+                    o.v[e] = from_acc(v);
+                }
+                *reinterpret_cast<vec_t<out_t, 4> *>(stg + lrow * SROW + col * (int)sizeof(out_t)) = o;
+            }
+        __builtin_amdgcn_wave_barrier();
+        constexpr int OV = 16 / sizeof(out_t), OCB = BN / OV; // 16-byte vectors of a row
+        const int pw = p0 + (wave * TM + tm) * 32;
+#pragma unroll
+        for (int i = 0; i < 32 * OCB / 64; ++i) {
+            const int idx = i * 64 + lane, r = idx / OCB, c = idx % OCB;
+            const u4_t v = *reinterpret_cast<const u4_t *>(stg + r * SROW + c * 16);
+            if (pw + r < OHW) *reinterpret_cast<u4_t *>(Y + (long)(pw + r) * DIM_N + c * OV) = v;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    (void)bias_;
+}

@@ -550,6 +550,49 @@ static int dw_strip(const ms_op *op)
     return (int)strip;
 }
 
+// Tiles of the image-row kernel for first layers (conv_rows.hip): waves of tm x tn intrinsic tiles; tm = 0 = the kernel
+// that the factors spell out.  Taken for 1 to 4 channels per pixel where the cache-read of X is not shared by several tiles
+// (compute_at 0, 1): the im2col loader and the patch of single elements lose on every size tried (3-D: 572 -> 144 us for
+// 8 x 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2, and 9.6 -> 7.7 us for one 8 x 64 x 64 x 1, 5 x 5 x 5; 2-D in filter rows:
+// 117 -> 75 us for 128 x 224 x 224 x 3 -> 64, 7 x 7, and 7.8 us on both sides, which is a launch, for one 64 x 64 x 3).
+struct ConvRows {
+    int tm, tn;
+    int64_t groups; // workgroups of one instance
+};
+static ConvRows conv_rows(const ms_op *op, const ms_variant_params *p)
+{
+    const ms_op_desc &d = op->d;
+    const ConvRows no = {0, 0, 0};
+    if (d.kind != MS_OP_CONV2D_NHWC || p->family != MS_FAM_GEMM_MFMA || p->compute_at > 1 || p->rfactor > 1) return no;
+    const int64_t H = d.dims[1], W = d.dims[2], Cin = d.dims[3], Cout = d.dims[4], KH = d.dims[5], KW = d.dims[6], S = d.stride;
+    if (op->nb != 1 || d.dilation != 1 || Cin > 4 || (d.in_dtype != MS_F16 && d.in_dtype != MS_BF16)) return no;
+    // whole 16-byte vectors per image row, runs at even elements, whole intrinsic columns
+    if (W * Cin % 8 || S * Cin % 2 || Cout % 32) return no;
+    if (op->depth * H * W * Cin > 0x7fffffff / 2 || op->OH * op->OW > 0x7fffffff / 2) return no;
+    const int64_t waves = 4, nt = waves * 64, ohw = op->OH * op->OW, lead = d.pad * Cin % 2, run = KW * Cin, cpr = (lead + run + 7) / 8;
+    const int tn = Cout / 32 % 2 == 0 ? 2 : Cout / 32 % 3 == 0 ? 3 : 1;
+    const int64_t bn = tn * 32, steps = (KH * cpr + 1) / 2, halo = ((d.pad * Cin + lead) * 2 + 15) / 16 * 16;
+    const int64_t row = std::max(halo + W * Cin * 2, halo - (d.pad * Cin + lead) * 2 + (op->OW - 1) * S * Cin * 2 + cpr * 16);
+    ConvRows best = no;
+    double cost = 0;
+    for (int tm : {4, 2, 1}) {
+        if (tm * tn > 8) continue;
+        const int64_t px = waves * tm * 32;
+        const int64_t rows = (std::min(px % op->OW ? (op->OW + px - 2) / op->OW + 1 : px / op->OW, op->OH) - 1) * S + KH;
+        const int64_t lds = std::max(rows * ((row + 15) / 16 * 16) + steps * 16 * (bn * 2 + 32), waves * 32 * (bn * op->out_size + 16));
+        if (lds > g_limits.max_lds_bytes || nt > g_limits.max_threads || tm * tn * 16 > g_limits.max_acc_per_thread) continue;
+        // a staging round trip costs a wavefront about three tiles' time; two workgroups per compute unit.  One instance of the
+        // 3-D layer above takes 29.6, 23.5, 26.7 us with tm = 1, 2, 4, eight 165, 144, 133: instances are not known here
+        const int64_t groups = (ohw + px - 1) / px * (Cout / bn) * op->OD * d.dims[0];
+        const double c = (double)((groups + 511) / 512) * (3 + tm * tn);
+        if (!best.tm || c < cost) {
+            best = {tm, tn, groups};
+            cost = c;
+        }
+    }
+    return best;
+}
+
 int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec *out)
 {
     const ms_op_desc &d = op->d;
@@ -645,6 +688,16 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             D.push_back(def("MI_M", p->tile_unit[0]));
             D.push_back(def("MI_N", p->tile_unit[1]));
             D.push_back(def("MI_K", p->tile_unit[2]));
+            const ConvRows cr = conv_rows(op, p);
+            if (cr.tm) {
+                k.template_name = "conv_rows.hip";
+                D.push_back(def("CR_TM", cr.tm));
+                D.push_back(def("CR_TN", cr.tn));
+                D.push_back(def("CR_WAVES", 4));
+                k.block[0] = 256;
+                k.grid[0] = (unsigned)cr.groups;
+                k.grid[1] = k.grid[2] = 1;
+            }
         } else {
             k.template_name = "gemm_alu.hip";
         }

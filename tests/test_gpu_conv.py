@@ -525,6 +525,33 @@ def test_conv3d_exact(Cin, k, stride, pad, dil, D, H, W_):
             continue
         assert np.array_equal(got[0], ref) and np.array_equal(got[1], ref), "trace %d" % n
 
+@pytest.mark.parametrize("D,H,W_,Cin,Cout,k,stride,pad,dtype,out", [(6, 16, 16, 3, 64, 7, 2, 3, "f16", "f32"), (4, 9, 24, 1, 32, 3, 2, 1, "bf16", "f32"),
+                                                                   (5, 13, 16, 4, 96, 5, 2, 2, "f16", "f16"), (4, 12, 8, 2, 32, 3, 1, 0, "f16", "f32"),
+                                                                   (1, 40, 56, 3, 64, 7, 2, 3, "bf16", "f32"), (1, 33, 72, 4, 128, 3, 1, 1, "f16", "f32"),
+                                                                   (1, 59, 104, 3, 32, 5, 2, 4, "f16", "f32")])
+def test_first_layer_image_rows_exact(D, H, W_, Cin, Cout, k, stride, pad, dtype, out):
+    """Im2col traces of first layers on the image-row kernel: runs with and without a leading element, odd and even chunk
+    counts, tiles that end behind the plane, every accumulator shape.  Batch 2, 2 instances with their own weights;
+    integer-valued inputs -> exact.  An infinite pixel reaches the outputs whose windows hold it and no others."""
+    g = I.rng(97)
+    shape, wshape = ((2, D, H, W_, Cin), (k, k, k, Cin, Cout)) if D > 1 else ((2, H, W_, Cin), (k, k, Cin, Cout))
+    ref_of = O.conv3d_ndhwc if D > 1 else O.conv2d_nhwc
+    ins = [[I.small_ints(g, shape, -2, 2, dtype), I.small_ints(g, wshape, 1, 2, dtype), g.integers(-3, 4, size=Cout).astype(np.float32)] for _ in range(2)]
+    for x, _, _ in ins:
+        x[(1,) + tuple(e // 2 for e in x.shape[1:])] = np.inf if dtype == "f16" else 0x7F80
+    kw = {"bf16": True} if dtype == "bf16" else {}
+    refs = [ref_of(x, w, bias=b, relu=True, stride=stride, pad=pad, **kw) for x, w, b in ins]
+    op = (B.conv3d_op(2, D, H, W_, Cin, Cout, k, stride=stride, pad=pad, in_dtype=dtype, out_dtype=out) if D > 1 else
+          B.conv2d_op(2, H, W_, Cin, Cout, k, k, stride=stride, pad=pad, in_dtype=dtype, out_dtype=out))
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 98, n) for n in range(200))
+             if B.trace_validate(op, space, t).compute_at == 0 and B.trace_validate(op, space, t).family == B.FAM_GEMM_MFMA)
+    assert "conv_rows.hip" in B.variant_kernel_text(op, B.trace_validate(op, space, t))
+    got = run_variant_distinct(op, space, t, ins, out, refs[0].shape)
+    if got is not None:
+        for r in range(2):
+            assert np.array_equal(got[r], refs[r]), "instance %d" % r
+
 
 def test_c3d_config_conv3d_16x224x224x3():
     """The paper's C3D shape: 16 x 224 x 224 x 3 -> 8 x 112 x 112 x 64, 7 x 7 x 7, stride 2, padding 3; fp16 (K = 1029)."""
