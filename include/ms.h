@@ -391,6 +391,19 @@ int32_t ms_trace_from_text(const ms_space *space, const char *text, ms_trace *ou
 
 /* ------------------------------------------------------------------ g(e0,tau) */
 
+/* The program that a trace resolves to.  MS_BODY_NEST: the loop nest that the decisions spell out.  Where no decisions can
+ * spell out a good kernel the interpreter gives the trace another body, which reads the operator and its own tile (and, of
+ * the decisions, nothing): all traces that a rule takes to one body are one kernel and share one key. */
+typedef enum ms_body {
+    MS_BODY_NEST = 0,
+    MS_BODY_ROW_VECTORS = 1, /* softmax: whole rows as 16-byte vectors in the registers of one wavefront's lane group;
+                                body_tile = elements per vector */
+    MS_BODY_STRIPS = 2,      /* depthwise: square strips of output pixels per thread, masked at the border;
+                                body_tile = pixels per side */
+    MS_BODY_IMAGE_ROWS = 3   /* conv with 1 to 4 channels per pixel: image rows and one filter plane's weights in LDS;
+                                body_tile = 32-pixel tiles of a wavefront */
+} ms_body;
+
 /* What the trace interpreter derives.  Unused fields are zero. */
 typedef struct ms_variant_params {
     int32_t family;
@@ -414,7 +427,9 @@ typedef struct ms_variant_params {
     int32_t compute_at;     /* 0 .. 4 as in MS_SLOT_COMPUTE_AT */
     int32_t tap_rows;       /* 1: the reduction of the MS_SPACE_TAP_ROWS layout (tile_unit[2] * the k split = KH * run) */
     int32_t rfactor;        /* workgroups that share the reduction of one output tile (1 = no workspace) */
-    int32_t reserved[3];
+    int32_t body;           /* ms_body */
+    int32_t body_tile;      /* as ms_body says, 0 for the nest */
+    int32_t reserved;
     uint64_t key;           /* hash of everything that selects the kernel */
 } ms_variant_params;
 

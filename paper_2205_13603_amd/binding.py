@@ -26,6 +26,7 @@ SPACE_RFACTOR = 0x400  # opt-in: sample the split of the reduction across workgr
 SPACE_DEFAULT = 0xFF
 STATIC_WORKSPACE_BYTES = 32 << 20
 FAM_GEMM_ALU, FAM_GEMM_MFMA, FAM_DWCONV, FAM_REDUCE = range(4)
+BODY_NEST, BODY_ROW_VECTORS, BODY_STRIPS, BODY_IMAGE_ROWS = range(4)
 MAX_SLOTS, MAX_FACTORS, MAX_CANDS, MAX_LOOPS = 16, 4, 12, 8
 
 F8E4M3 = 5
@@ -88,8 +89,8 @@ class ms_variant_params(C.Structure):
                 ("block_n", C.c_int32), ("block_k", C.c_int32), ("grid", C.c_int32 * 3), ("threads", C.c_int32),
                 ("waves", C.c_int32), ("acc_per_thread", C.c_int32), ("lds_bytes", C.c_int32),
                 ("cache_read", C.c_int32), ("vec", C.c_int32), ("unroll", C.c_int32), ("unroll_k1", C.c_int32),
-                ("unroll_k2", C.c_int32), ("lds_pad", C.c_int32), ("reorder", C.c_int32), ("vec_b", C.c_int32), ("cache_write", C.c_int32), ("compute_at", C.c_int32), ("tap_rows", C.c_int32), ("rfactor", C.c_int32), ("reserved", C.c_int32 * 3),
-                ("key", C.c_uint64)]
+                ("unroll_k2", C.c_int32), ("lds_pad", C.c_int32), ("reorder", C.c_int32), ("vec_b", C.c_int32), ("cache_write", C.c_int32), ("compute_at", C.c_int32), ("tap_rows", C.c_int32), ("rfactor", C.c_int32),
+                ("body", C.c_int32), ("body_tile", C.c_int32), ("reserved", C.c_int32), ("key", C.c_uint64)]
 
     def as_dict(self):
         out = {}

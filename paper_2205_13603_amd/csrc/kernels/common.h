@@ -59,6 +59,7 @@ __device__ __forceinline__ out_t from_acc(acc_t x)
 #endif
 }
 
+#ifdef I0 // kernels built from the factors of a trace
 // Workgroup -> (z, i0, j0): z = instance * batch + batch index, (i0, j0) = the two outer spatial loops.
 // REORDER 0: i outer.  1: j outer.  2: i outer, after a permutation of the launch-wide workgroup
 // id that undoes the round-robin of workgroups over the 8 XCDs: the hardware sends workgroup f
@@ -95,3 +96,4 @@ __device__ __forceinline__ void block_to_tile(int &z, int &i0, int &j0, int &ks)
     j0 = wg % J0;
 #endif
 }
+#endif

@@ -46,6 +46,104 @@ bool get_tile(const ms_space *sp, const ms_trace *t, int32_t slot_id, int32_t *f
     return true;
 }
 
+// ---------------------------------------------------------------- bodies
+//
+// Where no choice of factors spells out a good kernel, a rule gives the trace another body (ms_variant_params.body).  Such
+// a body reads the operator and its own tile only, so every trace that a rule takes is one kernel with one key.
+
+// MS_BODY_ROW_VECTORS: elements per vector of the whole-vector row kernel (reduce.hip), 0 = not taken.
+// Taken for a softmax whose lane groups read less than a 128-byte line per access, or read the row once per pass
+// (cache_read 0), where a row is whole 16-byte vectors and at most 64 values per lane of a wavefront.
+int row_vectors(const ms_op *op, const ms_variant_params *p)
+{
+    if (op->d.kind != MS_OP_SOFTMAX) return 0;
+    const int v = 16 / std::max(op->in_size, op->out_size);
+    if (op->K % v || op->K > 64 * 64) return 0;
+    return !p->cache_read || (int64_t)p->tk[2] * p->tk[3] * op->in_size < 128 ? v : 0;
+}
+
+// MS_BODY_STRIPS: output pixels per side of a thread's strip in the strip kernel (dwconv.hip), 0 = not taken.
+// Taken where an output extent above 2 has no divisor from 3 to 8: perfect tiles then leave a thread a row, a column or a
+// single pixel, which reads its inputs several times over (57 x 57 x 144, stride 2, batch 128: 75 against 50 us; 73 x 73 x 32,
+// batch 22: 119 against 6).  Elsewhere the factors can say better what fits.
+int dw_strip(const ms_op *op)
+{
+    const ms_op_desc &d = op->d;
+    auto stubborn = [](int64_t e) {
+        for (int64_t f = 3; f <= 8; ++f)
+            if (e % f == 0) return false;
+        return e > 2;
+    };
+    if (!stubborn(op->OH) && !stubborn(op->OW)) return 0;
+    const int64_t strip = 4, regs = ((strip - 1) * d.stride + d.dims[4]) * ((strip - 1) * d.stride + d.dims[5]) + d.dims[4] * d.dims[5];
+    if (regs > 256) return 0; // the thread's input patch and taps stay in registers
+    // 32-bit byte offsets inside an image, 32-bit counts of its strips
+    if (d.dims[1] * d.dims[2] * d.dims[3] > 0x7ffffff0 / 4 || op->OH * op->OW * d.dims[3] > 0x7ffffff0) return 0;
+    return (int)strip;
+}
+
+// The image-row kernel for first layers (conv_rows.hip): workgroups of four wavefronts of tm x tn intrinsic tiles.
+struct ConvRows {
+    int tm, tn;
+    int64_t groups; // workgroups of one instance
+    int64_t lds;    // bytes of a workgroup
+};
+ConvRows conv_rows_tiles(const ms_op *op, int tm)
+{
+    const ms_op_desc &d = op->d;
+    const int64_t W = d.dims[2], Cin = d.dims[3], Cout = d.dims[4], KH = d.dims[5], KW = d.dims[6], S = d.stride;
+    const int64_t waves = 4, px = waves * tm * 32, ohw = op->OH * op->OW, lead = d.pad * Cin % 2, run = KW * Cin, cpr = (lead + run + 7) / 8;
+    ConvRows c;
+    c.tm = tm;
+    c.tn = Cout / 32 % 2 == 0 ? 2 : Cout / 32 % 3 == 0 ? 3 : 1;
+    const int64_t bn = c.tn * 32, steps = (KH * cpr + 1) / 2, halo = ((d.pad * Cin + lead) * 2 + 15) / 16 * 16;
+    const int64_t row = std::max(halo + W * Cin * 2, halo - (d.pad * Cin + lead) * 2 + (op->OW - 1) * S * Cin * 2 + cpr * 16);
+    const int64_t rows = (std::min(px % op->OW ? (op->OW + px - 2) / op->OW + 1 : px / op->OW, op->OH) - 1) * S + KH;
+    c.lds = std::max(rows * ((row + 15) / 16 * 16) + steps * 16 * (bn * 2 + 32), waves * 32 * (bn * op->out_size + 16));
+    c.groups = (ohw + px - 1) / px * (Cout / bn) * op->OD * d.dims[0];
+    return c;
+}
+
+// MS_BODY_IMAGE_ROWS: tm of the image-row kernel, 0 = not taken.  Taken for 1 to 4 channels per pixel where the cache-read
+// of X is not shared by several tiles (compute_at 0, 1): the im2col loader and the patch of single elements lose on every
+// size tried (3-D: 572 -> 144 us for 8 x 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2, and 9.6 -> 7.7 us for one
+// 8 x 64 x 64 x 1, 5 x 5 x 5; 2-D in filter rows: 117 -> 75 us for 128 x 224 x 224 x 3 -> 64, 7 x 7, and 7.8 us on both
+// sides, which is a launch, for one 64 x 64 x 3).
+int conv_rows(const ms_op *op, const ms_variant_params *p)
+{
+    const ms_op_desc &d = op->d;
+    if (d.kind != MS_OP_CONV2D_NHWC || p->family != MS_FAM_GEMM_MFMA || p->compute_at > 1 || p->rfactor > 1) return 0;
+    const int64_t H = d.dims[1], W = d.dims[2], Cin = d.dims[3], Cout = d.dims[4], S = d.stride;
+    if (op->nb != 1 || d.dilation != 1 || Cin > 4 || (d.in_dtype != MS_F16 && d.in_dtype != MS_BF16)) return 0;
+    // whole 16-byte vectors per image row, runs at even elements, whole intrinsic columns
+    if (W * Cin % 8 || S * Cin % 2 || Cout % 32) return 0;
+    if (op->depth * H * W * Cin > 0x7fffffff / 2 || op->OH * op->OW > 0x7fffffff / 2) return 0;
+    int best = 0;
+    double cost = 0;
+    for (int tm : {4, 2, 1}) {
+        const ConvRows t = conv_rows_tiles(op, tm);
+        if (tm * t.tn > 8 || t.groups > 0x7fffffff) continue;
+        if (t.lds > g_limits.max_lds_bytes || 256 > g_limits.max_threads || tm * t.tn * 16 > g_limits.max_acc_per_thread) continue;
+        // a staging round trip costs a wavefront about three tiles' time; two workgroups per compute unit.  One instance of the
+        // 3-D layer above takes 29.6, 23.5, 26.7 us with tm = 1, 2, 4, eight 165, 144, 133: instances are not known here
+        const double c = (double)((t.groups + 511) / 512) * (3 + tm * t.tn);
+        if (!best || c < cost) {
+            best = tm;
+            cost = c;
+        }
+    }
+    return best;
+}
+
+// fills p->body and p->body_tile
+void resolve_body(const ms_op *op, ms_variant_params *p)
+{
+    p->body = MS_BODY_NEST;
+    if ((p->body_tile = row_vectors(op, p))) p->body = MS_BODY_ROW_VECTORS;
+    else if (p->family == MS_FAM_DWCONV && (p->body_tile = dw_strip(op))) p->body = MS_BODY_STRIPS;
+    else if ((p->body_tile = conv_rows(op, p))) p->body = MS_BODY_IMAGE_ROWS;
+}
+
 uint64_t hash_params(const ms_op *op, const ms_variant_params *p)
 {
     uint64_t h = 0x243F6A8885A308D3ull;
@@ -70,6 +168,11 @@ uint64_t hash_params(const ms_op *op, const ms_variant_params *p)
         add((uint64_t)d.b_strides[i]);
     }
     add((uint64_t)p->family);
+    if (p->body) { // the operator and the body's own tile are all that such a kernel reads
+        add(0xB0D7000000ull + (uint64_t)p->body);
+        add((uint64_t)p->body_tile);
+        return h;
+    }
     add((uint64_t)p->mfma);
     for (int i = 0; i < 4; ++i) {
         add((uint64_t)p->ti[i]);
@@ -503,6 +606,7 @@ extern "C" int32_t ms_trace_validate(const ms_op *op, const ms_space *space, con
     } else {
         return fail(MS_ERR_BAD_ARG, "ms_trace_validate: unknown family %d", space->family);
     }
+    resolve_body(op, &p);
     p.key = hash_params(op, &p);
     if (out) *out = p;
     return MS_OK;
@@ -519,94 +623,9 @@ static std::string def(const char *name, int64_t v)
 
 static int dt_code(int32_t dt) { return dt; }
 
-// Elements per vector of the whole-vector row kernel (reduce.hip), 0 = the kernel that the factors spell out.
-// Taken for a softmax whose lane groups read less than a 128-byte line per access, or read the row once per pass
-// (cache_read 0), where a row is whole 16-byte vectors and at most 64 values per lane of a wavefront.
-static int row_vectors(const ms_op *op, const ms_variant_params *p)
+// the -D options of the loop nest that the factors spell out
+static void push_schedule(std::vector<std::string> &D, const ms_variant_params *p)
 {
-    if (op->d.kind != MS_OP_SOFTMAX) return 0;
-    const int v = 16 / std::max(op->in_size, op->out_size);
-    if (op->K % v || op->K > 64 * 64) return 0;
-    return !p->cache_read || (int64_t)p->tk[2] * p->tk[3] * op->in_size < 128 ? v : 0;
-}
-
-// Output pixels per side of a thread's strip in the strip kernel (dwconv.hip), 0 = the kernel that the factors spell out.
-// Taken where an output extent above 2 has no divisor from 3 to 8: perfect tiles then leave a thread a row, a column or a
-// single pixel, which reads its inputs several times over (57 x 57 x 144, stride 2, batch 128: 75 against 50 us; 73 x 73 x 32,
-// batch 22: 119 against 6).  Elsewhere the factors can say better what fits.
-static int dw_strip(const ms_op *op)
-{
-    const ms_op_desc &d = op->d;
-    auto stubborn = [](int64_t e) {
-        for (int64_t f = 3; f <= 8; ++f)
-            if (e % f == 0) return false;
-        return e > 2;
-    };
-    if (!stubborn(op->OH) && !stubborn(op->OW)) return 0;
-    const int64_t strip = 4, regs = ((strip - 1) * d.stride + d.dims[4]) * ((strip - 1) * d.stride + d.dims[5]) + d.dims[4] * d.dims[5];
-    if (regs > 256) return 0; // the thread's input patch and taps stay in registers
-    // 32-bit byte offsets inside an image, 32-bit counts of its strips
-    if (d.dims[1] * d.dims[2] * d.dims[3] > 0x7ffffff0 / 4 || op->OH * op->OW * d.dims[3] > 0x7ffffff0) return 0;
-    return (int)strip;
-}
-
-// Tiles of the image-row kernel for first layers (conv_rows.hip): waves of tm x tn intrinsic tiles; tm = 0 = the kernel
-// that the factors spell out.  Taken for 1 to 4 channels per pixel where the cache-read of X is not shared by several tiles
-// (compute_at 0, 1): the im2col loader and the patch of single elements lose on every size tried (3-D: 572 -> 144 us for
-// 8 x 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2, and 9.6 -> 7.7 us for one 8 x 64 x 64 x 1, 5 x 5 x 5; 2-D in filter rows:
-// 117 -> 75 us for 128 x 224 x 224 x 3 -> 64, 7 x 7, and 7.8 us on both sides, which is a launch, for one 64 x 64 x 3).
-struct ConvRows {
-    int tm, tn;
-    int64_t groups; // workgroups of one instance
-};
-static ConvRows conv_rows(const ms_op *op, const ms_variant_params *p)
-{
-    const ms_op_desc &d = op->d;
-    const ConvRows no = {0, 0, 0};
-    if (d.kind != MS_OP_CONV2D_NHWC || p->family != MS_FAM_GEMM_MFMA || p->compute_at > 1 || p->rfactor > 1) return no;
-    const int64_t H = d.dims[1], W = d.dims[2], Cin = d.dims[3], Cout = d.dims[4], KH = d.dims[5], KW = d.dims[6], S = d.stride;
-    if (op->nb != 1 || d.dilation != 1 || Cin > 4 || (d.in_dtype != MS_F16 && d.in_dtype != MS_BF16)) return no;
-    // whole 16-byte vectors per image row, runs at even elements, whole intrinsic columns
-    if (W * Cin % 8 || S * Cin % 2 || Cout % 32) return no;
-    if (op->depth * H * W * Cin > 0x7fffffff / 2 || op->OH * op->OW > 0x7fffffff / 2) return no;
-    const int64_t waves = 4, nt = waves * 64, ohw = op->OH * op->OW, lead = d.pad * Cin % 2, run = KW * Cin, cpr = (lead + run + 7) / 8;
-    const int tn = Cout / 32 % 2 == 0 ? 2 : Cout / 32 % 3 == 0 ? 3 : 1;
-    const int64_t bn = tn * 32, steps = (KH * cpr + 1) / 2, halo = ((d.pad * Cin + lead) * 2 + 15) / 16 * 16;
-    const int64_t row = std::max(halo + W * Cin * 2, halo - (d.pad * Cin + lead) * 2 + (op->OW - 1) * S * Cin * 2 + cpr * 16);
-    ConvRows best = no;
-    double cost = 0;
-    for (int tm : {4, 2, 1}) {
-        if (tm * tn > 8) continue;
-        const int64_t px = waves * tm * 32;
-        const int64_t rows = (std::min(px % op->OW ? (op->OW + px - 2) / op->OW + 1 : px / op->OW, op->OH) - 1) * S + KH;
-        const int64_t lds = std::max(rows * ((row + 15) / 16 * 16) + steps * 16 * (bn * 2 + 32), waves * 32 * (bn * op->out_size + 16));
-        if (lds > g_limits.max_lds_bytes || nt > g_limits.max_threads || tm * tn * 16 > g_limits.max_acc_per_thread) continue;
-        // a staging round trip costs a wavefront about three tiles' time; two workgroups per compute unit.  One instance of the
-        // 3-D layer above takes 29.6, 23.5, 26.7 us with tm = 1, 2, 4, eight 165, 144, 133: instances are not known here
-        const int64_t groups = (ohw + px - 1) / px * (Cout / bn) * op->OD * d.dims[0];
-        const double c = (double)((groups + 511) / 512) * (3 + tm * tn);
-        if (!best.tm || c < cost) {
-            best = {tm, tn, groups};
-            cost = c;
-        }
-    }
-    return best;
-}
-
-int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec *out)
-{
-    const ms_op_desc &d = op->d;
-    KernelSpec k;
-    k.entry = "ms_kernel";
-    k.block[0] = (unsigned)p->threads;
-    k.block[1] = k.block[2] = 1;
-    k.grid[0] = (unsigned)p->grid[0];
-    k.grid[1] = (unsigned)p->grid[1];
-    k.grid[2] = (unsigned)p->grid[2];
-    k.lds_dynamic = 0;
-    auto &D = k.defines;
-    D.push_back(def("IN_DT", dt_code(d.in_dtype)));
-    D.push_back(def("OUT_DT", dt_code(d.out_dtype)));
     const char *tn[4] = {"I", "J", "C", "K"};
     const int32_t *tl[4] = {p->ti, p->tj, p->tc, p->tk};
     for (int l = 0; l < 4; ++l)
@@ -627,6 +646,23 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
     D.push_back(def("COMPUTE_AT", p->compute_at));
     D.push_back(def("HELPER_WAVES", p->compute_at == 3 ? 4 : 0));
     D.push_back(def("RFACTOR", p->rfactor > 1 ? p->rfactor : 1));
+}
+
+int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec *out)
+{
+    const ms_op_desc &d = op->d;
+    KernelSpec k;
+    k.entry = "ms_kernel";
+    k.block[0] = (unsigned)p->threads;
+    k.block[1] = k.block[2] = 1;
+    k.grid[0] = (unsigned)p->grid[0];
+    k.grid[1] = (unsigned)p->grid[1];
+    k.grid[2] = (unsigned)p->grid[2];
+    k.lds_dynamic = 0;
+    auto &D = k.defines;
+    D.push_back(def("IN_DT", dt_code(d.in_dtype)));
+    D.push_back(def("OUT_DT", dt_code(d.out_dtype)));
+    if (p->body == MS_BODY_NEST) push_schedule(D, p);
     if (p->family == MS_FAM_GEMM_ALU || p->family == MS_FAM_GEMM_MFMA) {
         D.push_back(def("DIM_B", op->nb));
         D.push_back(def("DIM_M", op->M));
@@ -655,8 +691,10 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             D.push_back(def("CV_OD", op->OD));
             D.push_back(def("CV_DIL", d.dilation));
             D.push_back(def("CV_TRANSPOSED", d.kind == MS_OP_CONV2D_TRANSPOSED_NHWC ? 1 : 0));
-            D.push_back(def("CV_TAPROWS", p->tap_rows));
-            D.push_back(def("CV_KR", (d.dims[6] * d.dims[3] + p->tile_unit[2] - 1) / p->tile_unit[2] * p->tile_unit[2]));
+            if (p->body == MS_BODY_NEST) {
+                D.push_back(def("CV_TAPROWS", p->tap_rows));
+                D.push_back(def("CV_KR", (d.dims[6] * d.dims[3] + p->tile_unit[2] - 1) / p->tile_unit[2] * p->tile_unit[2]));
+            }
             D.push_back(def("HAS_BIAS", d.has_bias ? 1 : 0));
             D.push_back(def("RELU", d.relu ? 1 : 0));
             // implicit GEMM view: A rows are output pixels, B = W as [K][N]
@@ -683,21 +721,20 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             D.push_back(def("A_INST", ab / op->in_size));
             D.push_back(def("B_INST", bb / op->in_size));
         }
-        if (p->family == MS_FAM_GEMM_MFMA) {
+        if (p->body == MS_BODY_IMAGE_ROWS) {
+            const ConvRows cr = conv_rows_tiles(op, p->body_tile);
+            k.template_name = "conv_rows.hip";
+            D.push_back(def("CR_TM", cr.tm));
+            D.push_back(def("CR_TN", cr.tn));
+            D.push_back(def("CR_WAVES", 4));
+            k.block[0] = 256;
+            k.grid[0] = (unsigned)cr.groups;
+            k.grid[1] = k.grid[2] = 1;
+        } else if (p->family == MS_FAM_GEMM_MFMA) {
             k.template_name = "gemm_mfma.hip";
             D.push_back(def("MI_M", p->tile_unit[0]));
             D.push_back(def("MI_N", p->tile_unit[1]));
             D.push_back(def("MI_K", p->tile_unit[2]));
-            const ConvRows cr = conv_rows(op, p);
-            if (cr.tm) {
-                k.template_name = "conv_rows.hip";
-                D.push_back(def("CR_TM", cr.tm));
-                D.push_back(def("CR_TN", cr.tn));
-                D.push_back(def("CR_WAVES", 4));
-                k.block[0] = 256;
-                k.grid[0] = (unsigned)cr.groups;
-                k.grid[1] = k.grid[2] = 1;
-            }
         } else {
             k.template_name = "gemm_alu.hip";
         }
@@ -706,7 +743,8 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
         D.push_back(def("RD_OP", d.kind == MS_OP_NORM ? 1 : 0));
         D.push_back(def("RD_ROWS", op->M));
         D.push_back(def("RD_LEN", op->K));
-        if (const int v = row_vectors(op, p)) {
+        if (p->body == MS_BODY_ROW_VECTORS) {
+            const int v = p->body_tile;
             int lanes = 1;
             while (lanes < 64 && lanes * v < op->K) lanes *= 2;
             const int waves = 4;
@@ -729,7 +767,8 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
         D.push_back(def("CV_OW", op->OW));
         D.push_back(def("CV_STRIDE", d.stride));
         D.push_back(def("CV_PAD", d.pad));
-        if (const int strip = dw_strip(op)) {
+        if (p->body == MS_BODY_STRIPS) {
+            const int strip = p->body_tile;
             const int64_t items = ((op->OH + strip - 1) / strip) * ((op->OW + strip - 1) / strip) * d.dims[3];
             const int64_t threads = std::min<int64_t>(256, (items + 63) / 64 * 64);
             D.push_back(def("STRIP", strip));

@@ -581,6 +581,41 @@ def test_equal_kernel_text_means_equal_key(mk):
     assert len(by_text) > 20
 
 
+BODY_OPS = [
+    (lambda: B.softmax_op(1, 4096, 1000), B.SPACE_DEFAULT, B.BODY_ROW_VECTORS),
+    (lambda: B.dwconv2d_op(4, 57, 57, 144, stride=2), B.SPACE_DEFAULT, B.BODY_STRIPS),
+    (lambda: B.conv2d_op(1, 224, 224, 3, 64, 7, 7, stride=2, pad=3), B.SPACE_DEFAULT | B.SPACE_TAP_ROWS, B.BODY_IMAGE_ROWS),
+    (lambda: B.conv3d_op(1, 16, 64, 64, 3, 64, 7, stride=2, pad=3), B.SPACE_DEFAULT, B.BODY_IMAGE_ROWS),
+]
+
+
+@pytest.mark.parametrize("mk,flags,body", BODY_OPS)
+def test_traces_of_one_body_are_one_kernel_with_one_key(mk, flags, body):
+    """A body other than the nest reads the operator and its own tile: whatever the decisions, one text and one key, and
+    no text with two keys or key with two texts across the bodies of a space."""
+    op = mk()
+    sp = op.space(flags)
+    by_text, by_key, of_body = {}, {}, set()
+    for idx in range(300):
+        p = B.trace_validate(op, sp, B.trace_sample_valid(op, sp, 34, idx))
+        text = B.variant_kernel_text(op, p)
+        assert by_text.setdefault(text, p.key) == p.key and by_key.setdefault(p.key, text) == text
+        if p.body != B.BODY_NEST:
+            assert p.body == body
+            of_body.add(p.key)
+    assert len(of_body) == 1
+
+
+def test_a_search_measures_a_body_once():
+    """Every trace of this operator resolves to the strip kernel: one measurement, the rest are duplicates."""
+    op = B.dwconv2d_op(1, 57, 57, 16, stride=2)
+    sp = op.space()
+    cfg = B.search_cfg_default()
+    cfg.seed, cfg.trials = 3, 64
+    res = B.search(op, sp, cfg, fake_latency=lambda p: 1.0)
+    assert res.n_measured == 1 and res.n_duplicate > 0
+
+
 def test_unroll_budgets_that_resolve_alike_share_a_key():
     op = B.dwconv2d_op(1, 28, 28, 12)
     sp = op.space()
