@@ -393,7 +393,8 @@ int32_t ms_trace_from_text(const ms_space *space, const char *text, ms_trace *ou
 
 /* The program that a trace resolves to.  MS_BODY_NEST: the loop nest that the decisions spell out.  Where no decisions can
  * spell out a good kernel the interpreter gives the trace another body, which reads the operator and its own tile (and, of
- * the decisions, nothing): all traces that a rule takes to one body are one kernel and share one key. */
+ * the decisions, nothing): all traces that a rule takes to one body are one kernel and share one key.  The rules keep to
+ * ms_limits; where a body would exceed them the trace stays with its nest. */
 typedef enum ms_body {
     MS_BODY_NEST = 0,
     MS_BODY_ROW_VECTORS = 1, /* softmax: whole rows as 16-byte vectors in the registers of one wavefront's lane group;
@@ -404,7 +405,11 @@ typedef enum ms_body {
                                 body_tile = 32-pixel tiles of a wavefront */
 } ms_body;
 
-/* What the trace interpreter derives.  Unused fields are zero. */
+/* What the trace interpreter derives.  Unused fields are zero.  With another body than the nest, block_*, grid, threads,
+ * waves, acc_per_thread, lds_bytes, vec and vec_b are those of the kernel that runs, and so are the splits ti, tj, tc and tk
+ * of MS_BODY_ROW_VECTORS and MS_BODY_STRIPS (their products may exceed the extents: the rest is masked; block_k of the
+ * strips = threads, one per strip and channel); block_k of MS_BODY_IMAGE_ROWS = k values per filter plane.  All other
+ * fields then repeat decisions that the kernel does not read. */
 typedef struct ms_variant_params {
     int32_t family;
     int32_t mfma;           /* MS_MFMA_CODE or MS_MFMA_NONE */
@@ -527,7 +532,7 @@ int32_t ms_variant_launch_static(ms_variant *v, const void *const *inputs, void 
 
 /*
  * Host-side coverage check of the interpreted loop nest (no GPU): walks the
- * grid / thread / register loops the parameters describe and counts, for
+ * grid / thread / register loops of the parameters' body and counts, for
  * every output element, how often it is produced.  counts: host pointer to
  * out_elems int32 (one instance).  A correct split/bind visits each exactly
  * once.  This executes index arithmetic only, never the operator.

@@ -1042,11 +1042,18 @@ extern "C" int32_t ms_trace_to_text(const ms_op *op, const ms_space *space, cons
     // transformation instructions they parameterise (informational on read-back)
     ms_variant_params p;
     if (ms_trace_validate(op, space, trace, &p) == MS_OK) {
-        if (p.mfma) appendf(s, "tensorize(block=C, intrin=mfma_%dx%dx%d)\n", p.tile_unit[0], p.tile_unit[1], p.tile_unit[2]);
+        const bool image_rows = p.body == MS_BODY_IMAGE_ROWS, strips = p.body == MS_BODY_STRIPS, row_vectors = p.body == MS_BODY_ROW_VECTORS;
+        if (row_vectors) s += "# body=row-vectors: this operator's own split, the last rows and vectors masked\n";
+        if (strips) appendf(s, "# body=strips: %d x %d output pixels per thread, masked at the border\n", p.body_tile, p.body_tile);
+        if (image_rows)
+            appendf(s, "# body=image-rows: %d pixels x %d channels per workgroup, %d k values per filter plane; the decisions do not act\n"
+                       "tensorize(block=C, intrin=mfma_32x32x16)\ncache-read(buffers=[X, W], scope=lds, compute-at=filter plane, prefetch_distance=1)\n"
+                       "cache-write(buffer=C, scope=lds, per wavefront)\n", p.block_m, p.block_n, p.block_k);
+        if (p.mfma && !image_rows) appendf(s, "tensorize(block=C, intrin=mfma_%dx%dx%d)\n", p.tile_unit[0], p.tile_unit[1], p.tile_unit[2]);
         const char *nm[4] = {"i", "j", "c", "k"};
         const int32_t *tl[4] = {p.ti, p.tj, p.tc, p.tk};
         for (int l = 0; l < 4; ++l) {
-            if (!tl[l][0]) continue;
+            if (!tl[l][0] || image_rows) continue;
             appendf(s, "%s0, %s1, %s2, %s3 = split(loop=%s, factors=[%d, %d, %d, %d])\n", nm[l], nm[l], nm[l], nm[l], nm[l],
                     tl[l][0], tl[l][1], tl[l][2], tl[l][3]);
         }
@@ -1055,9 +1062,13 @@ extern "C" int32_t ms_trace_to_text(const ms_op *op, const ms_space *space, cons
             appendf(s, "bind(fuse(i2, k2), threadIdx.x)  # k2: cross-thread reduction over %d lanes (wavefront shuffles%s)\n", p.tk[2],
                     p.tk[2] > 64 ? ", LDS across wavefronts" : "");
             appendf(s, "vectorize(k3)\nunroll(k1)\n");
-            if (p.cache_read) appendf(s, "cache-read(buffer=X, scope=registers, compute-at=i3)  # one pass over global memory\n");
+            if (p.cache_read || row_vectors) appendf(s, "cache-read(buffer=X, scope=registers, compute-at=i3)  # one pass over global memory\n");
             appendf(s, "# workgroup=%d threads, grid=%d, lds=%d B, values/lane=%d\n", p.threads, p.grid[0] * p.grid[1] * p.grid[2], p.lds_bytes,
                     p.acc_per_thread);
+        } else if (image_rows) {
+            // everything was said above
+        } else if (strips) {
+            s += "bind(fuse(i0, j0, c0), fuse(blockIdx.x, threadIdx.x))\n";
         } else if (p.family == MS_FAM_DWCONV) {
             s += "reorder(i0, j0, c0, i1, j1, c1, i2, j2, c2, i3, j3, c3, kh, kw)\n";
             s += "bind(fuse(i0, j0, c0), blockIdx.x)\nbind(fuse(i2, j2, c2), threadIdx.x)\nvectorize(c3)\n";
@@ -1070,6 +1081,7 @@ extern "C" int32_t ms_trace_to_text(const ms_op *op, const ms_space *space, cons
         if (p.family == MS_FAM_REDUCE) {
             // everything was said above
         } else {
+        if (p.body == MS_BODY_NEST) {
         if (p.cache_read) {
             if (p.cache_read >= 8)
                 appendf(s, "cache-read(buffers=[A, B], scope=lds, at=k0, stages=%d, prefetch_distance=%d, direct_to_lds=1)\n"
@@ -1099,6 +1111,7 @@ extern "C" int32_t ms_trace_to_text(const ms_op *op, const ms_space *space, cons
         if (p.vec > 1) appendf(s, "vectorize(global loads of A, width=%d)\n", p.vec);
         if (p.vec_b > 1) appendf(s, "vectorize(global loads of B, width=%d)\n", p.vec_b);
         appendf(s, "unroll(k1, factor=%d)\nunroll(k2, factor=%d)\n", p.unroll_k1, p.unroll_k2);
+        }
         appendf(s, "# workgroup=%d threads, grid=%d, lds=%d B, acc/lane=%d\n", p.threads, p.grid[0] * p.grid[1] * p.grid[2], p.lds_bytes,
                 p.acc_per_thread);
         }

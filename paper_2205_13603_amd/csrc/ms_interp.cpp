@@ -51,6 +51,20 @@ bool get_tile(const ms_space *sp, const ms_trace *t, int32_t slot_id, int32_t *f
 // Where no choice of factors spells out a good kernel, a rule gives the trace another body (ms_variant_params.body).  Such
 // a body reads the operator and its own tile only, so every trace that a rule takes is one kernel with one key.
 
+// Split of the whole-vector row kernel: lanes of a wavefront that share a row, vectors of each (the last one masked),
+// rows and threads of a workgroup of four wavefronts.
+struct RowVectors {
+    int lanes, vectors, rows, threads;
+};
+RowVectors row_vectors_split(const ms_op *op, int v)
+{
+    RowVectors r = {1, 0, 0, 256};
+    while (r.lanes < 64 && r.lanes * v < op->K) r.lanes *= 2;
+    r.vectors = (int)((op->K / v + r.lanes - 1) / r.lanes);
+    r.rows = r.threads / r.lanes;
+    return r;
+}
+
 // MS_BODY_ROW_VECTORS: elements per vector of the whole-vector row kernel (reduce.hip), 0 = not taken.
 // Taken for a softmax whose lane groups read less than a 128-byte line per access, or read the row once per pass
 // (cache_read 0), where a row is whole 16-byte vectors and at most 64 values per lane of a wavefront.
@@ -59,8 +73,14 @@ int row_vectors(const ms_op *op, const ms_variant_params *p)
     if (op->d.kind != MS_OP_SOFTMAX) return 0;
     const int v = 16 / std::max(op->in_size, op->out_size);
     if (op->K % v || op->K > 64 * 64) return 0;
+    const RowVectors r = row_vectors_split(op, v);
+    if (r.threads > g_limits.max_threads || r.threads / 64 > g_limits.max_waves || r.vectors * v > g_limits.max_acc_per_thread) return 0;
     return !p->cache_read || (int64_t)p->tk[2] * p->tk[3] * op->in_size < 128 ? v : 0;
 }
+
+// Threads of the strip kernel: one per strip and channel of an image, at most 256 in a workgroup.
+int64_t dw_strip_items(const ms_op *op, int64_t strip) { return ((op->OH + strip - 1) / strip) * ((op->OW + strip - 1) / strip) * op->d.dims[3]; }
+int64_t dw_strip_threads(const ms_op *op, int64_t strip) { return std::min<int64_t>(256, (dw_strip_items(op, strip) + 63) / 64 * 64); }
 
 // MS_BODY_STRIPS: output pixels per side of a thread's strip in the strip kernel (dwconv.hip), 0 = not taken.
 // Taken where an output extent above 2 has no divisor from 3 to 8: perfect tiles then leave a thread a row, a column or a
@@ -76,7 +96,7 @@ int dw_strip(const ms_op *op)
     };
     if (!stubborn(op->OH) && !stubborn(op->OW)) return 0;
     const int64_t strip = 4, regs = ((strip - 1) * d.stride + d.dims[4]) * ((strip - 1) * d.stride + d.dims[5]) + d.dims[4] * d.dims[5];
-    if (regs > 256) return 0; // the thread's input patch and taps stay in registers
+    if (regs > g_limits.max_acc_per_thread || dw_strip_threads(op, strip) > g_limits.max_threads) return 0; // patch and taps stay in registers
     // 32-bit byte offsets inside an image, 32-bit counts of its strips
     if (d.dims[1] * d.dims[2] * d.dims[3] > 0x7ffffff0 / 4 || op->OH * op->OW * d.dims[3] > 0x7ffffff0) return 0;
     return (int)strip;
@@ -84,23 +104,30 @@ int dw_strip(const ms_op *op)
 
 // The image-row kernel for first layers (conv_rows.hip): workgroups of four wavefronts of tm x tn intrinsic tiles.
 struct ConvRows {
-    int tm, tn;
-    int64_t groups; // workgroups of one instance
-    int64_t lds;    // bytes of a workgroup
+    int tm, tn, threads;
+    int64_t px, tiles;   // output pixels of a workgroup, workgroups of an output plane
+    int64_t lead, cpr, steps; // unused elements before a run, 8-element chunks of a run, k steps of a filter plane
+    int64_t groups;      // workgroups of one instance
+    int64_t lds;         // bytes of a workgroup
 };
 ConvRows conv_rows_tiles(const ms_op *op, int tm)
 {
     const ms_op_desc &d = op->d;
-    const int64_t W = d.dims[2], Cin = d.dims[3], Cout = d.dims[4], KH = d.dims[5], KW = d.dims[6], S = d.stride;
-    const int64_t waves = 4, px = waves * tm * 32, ohw = op->OH * op->OW, lead = d.pad * Cin % 2, run = KW * Cin, cpr = (lead + run + 7) / 8;
+    const int64_t W = d.dims[2], Cin = d.dims[3], Cout = d.dims[4], KH = d.dims[5], KW = d.dims[6], S = d.stride, waves = 4, ohw = op->OH * op->OW;
     ConvRows c;
     c.tm = tm;
     c.tn = Cout / 32 % 2 == 0 ? 2 : Cout / 32 % 3 == 0 ? 3 : 1;
-    const int64_t bn = c.tn * 32, steps = (KH * cpr + 1) / 2, halo = ((d.pad * Cin + lead) * 2 + 15) / 16 * 16;
-    const int64_t row = std::max(halo + W * Cin * 2, halo - (d.pad * Cin + lead) * 2 + (op->OW - 1) * S * Cin * 2 + cpr * 16);
-    const int64_t rows = (std::min(px % op->OW ? (op->OW + px - 2) / op->OW + 1 : px / op->OW, op->OH) - 1) * S + KH;
-    c.lds = std::max(rows * ((row + 15) / 16 * 16) + steps * 16 * (bn * 2 + 32), waves * 32 * (bn * op->out_size + 16));
-    c.groups = (ohw + px - 1) / px * (Cout / bn) * op->OD * d.dims[0];
+    c.threads = (int)waves * 64;
+    c.px = waves * tm * 32;
+    c.tiles = (ohw + c.px - 1) / c.px;
+    c.lead = d.pad * Cin % 2;
+    c.cpr = (c.lead + KW * Cin + 7) / 8;
+    c.steps = (KH * c.cpr + 1) / 2;
+    const int64_t bn = c.tn * 32, halo = ((d.pad * Cin + c.lead) * 2 + 15) / 16 * 16;
+    const int64_t row = std::max(halo + W * Cin * 2, halo - (d.pad * Cin + c.lead) * 2 + (op->OW - 1) * S * Cin * 2 + c.cpr * 16);
+    const int64_t rows = (std::min(c.px % op->OW ? (op->OW + c.px - 2) / op->OW + 1 : c.px / op->OW, op->OH) - 1) * S + KH;
+    c.lds = std::max(rows * ((row + 15) / 16 * 16) + c.steps * 16 * (bn * 2 + 32), waves * 32 * (bn * op->out_size + 16));
+    c.groups = c.tiles * (Cout / bn) * op->OD * d.dims[0];
     return c;
 }
 
@@ -123,7 +150,9 @@ int conv_rows(const ms_op *op, const ms_variant_params *p)
     for (int tm : {4, 2, 1}) {
         const ConvRows t = conv_rows_tiles(op, tm);
         if (tm * t.tn > 8 || t.groups > 0x7fffffff) continue;
-        if (t.lds > g_limits.max_lds_bytes || 256 > g_limits.max_threads || tm * t.tn * 16 > g_limits.max_acc_per_thread) continue;
+        if (t.lds > g_limits.max_lds_bytes || t.threads > g_limits.max_threads || t.threads / 64 > g_limits.max_waves ||
+            tm * t.tn * 16 > g_limits.max_acc_per_thread)
+            continue;
         // a staging round trip costs a wavefront about three tiles' time; two workgroups per compute unit.  One instance of the
         // 3-D layer above takes 29.6, 23.5, 26.7 us with tm = 1, 2, 4, eight 165, 144, 133: instances are not known here
         const double c = (double)((t.groups + 511) / 512) * (3 + tm * t.tn);
@@ -135,13 +164,61 @@ int conv_rows(const ms_op *op, const ms_variant_params *p)
     return best;
 }
 
-// fills p->body and p->body_tile
+void set4(int32_t *f, int64_t f0, int64_t f1, int64_t f2, int64_t f3)
+{
+    f[0] = (int32_t)f0;
+    f[1] = (int32_t)f1;
+    f[2] = (int32_t)f2;
+    f[3] = (int32_t)f3;
+}
+
+// Chooses the body and, for another one than the nest, makes the launch fields of *p those of that kernel.
 void resolve_body(const ms_op *op, ms_variant_params *p)
 {
+    const ms_op_desc &d = op->d;
     p->body = MS_BODY_NEST;
-    if ((p->body_tile = row_vectors(op, p))) p->body = MS_BODY_ROW_VECTORS;
-    else if (p->family == MS_FAM_DWCONV && (p->body_tile = dw_strip(op))) p->body = MS_BODY_STRIPS;
-    else if ((p->body_tile = conv_rows(op, p))) p->body = MS_BODY_IMAGE_ROWS;
+    if ((p->body_tile = row_vectors(op, p))) {
+        const RowVectors r = row_vectors_split(op, p->body_tile);
+        p->body = MS_BODY_ROW_VECTORS;
+        p->grid[0] = (int32_t)((op->M + r.rows - 1) / r.rows);
+        set4(p->ti, p->grid[0], 1, r.rows, 1);
+        set4(p->tk, 1, r.vectors, r.lanes, p->body_tile);
+        p->block_m = r.rows;
+        p->vec = p->body_tile;
+        p->unroll_k1 = r.vectors;
+        p->threads = r.threads;
+        p->acc_per_thread = r.vectors * p->body_tile;
+        p->lds_bytes = 0;
+    } else if (p->family == MS_FAM_DWCONV && (p->body_tile = dw_strip(op))) {
+        const int64_t strip = p->body_tile;
+        p->body = MS_BODY_STRIPS;
+        p->threads = (int32_t)dw_strip_threads(op, strip);
+        p->grid[0] = (int32_t)((dw_strip_items(op, strip) + p->threads - 1) / p->threads);
+        set4(p->ti, (op->OH + strip - 1) / strip, 1, 1, strip);
+        set4(p->tj, (op->OW + strip - 1) / strip, 1, 1, strip);
+        set4(p->tc, d.dims[3], 1, 1, 1);
+        p->block_m = p->block_n = (int32_t)strip;
+        p->block_k = p->threads;
+        p->vec = 1;
+        p->unroll_k1 = p->unroll_k2 = 0;
+        p->acc_per_thread = (int32_t)(strip * strip);
+        p->lds_bytes = 0;
+    } else if ((p->body_tile = conv_rows(op, p))) {
+        const ConvRows c = conv_rows_tiles(op, p->body_tile);
+        p->body = MS_BODY_IMAGE_ROWS;
+        p->grid[0] = (int32_t)c.groups;
+        p->grid[1] = p->grid[2] = 1;
+        p->block_m = (int32_t)c.px;
+        p->block_n = c.tn * 32;
+        p->block_k = (int32_t)c.steps * 16;
+        p->vec = p->vec_b = 8;
+        p->threads = c.threads;
+        p->acc_per_thread = c.tm * c.tn * 16;
+        p->lds_bytes = (int32_t)c.lds;
+    } else {
+        return;
+    }
+    p->waves = p->threads / 64;
 }
 
 uint64_t hash_params(const ms_op *op, const ms_variant_params *p)
@@ -726,10 +803,7 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             k.template_name = "conv_rows.hip";
             D.push_back(def("CR_TM", cr.tm));
             D.push_back(def("CR_TN", cr.tn));
-            D.push_back(def("CR_WAVES", 4));
-            k.block[0] = 256;
-            k.grid[0] = (unsigned)cr.groups;
-            k.grid[1] = k.grid[2] = 1;
+            D.push_back(def("CR_WAVES", p->waves));
         } else if (p->family == MS_FAM_GEMM_MFMA) {
             k.template_name = "gemm_mfma.hip";
             D.push_back(def("MI_M", p->tile_unit[0]));
@@ -744,16 +818,9 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
         D.push_back(def("RD_ROWS", op->M));
         D.push_back(def("RD_LEN", op->K));
         if (p->body == MS_BODY_ROW_VECTORS) {
-            const int v = p->body_tile;
-            int lanes = 1;
-            while (lanes < 64 && lanes * v < op->K) lanes *= 2;
-            const int waves = 4;
-            D.push_back(def("ROW_VEC", v));
-            D.push_back(def("ROW_LANES", lanes));
-            D.push_back(def("ROW_WAVES", waves));
-            const int64_t rows = waves * (64 / lanes);
-            k.block[0] = (unsigned)(waves * 64);
-            k.grid[0] = (unsigned)((op->M + rows - 1) / rows);
+            D.push_back(def("ROW_VEC", p->body_tile));
+            D.push_back(def("ROW_LANES", p->tk[2]));
+            D.push_back(def("ROW_WAVES", p->waves));
         }
     } else {
         k.template_name = "dwconv.hip";
@@ -768,13 +835,8 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
         D.push_back(def("CV_STRIDE", d.stride));
         D.push_back(def("CV_PAD", d.pad));
         if (p->body == MS_BODY_STRIPS) {
-            const int strip = p->body_tile;
-            const int64_t items = ((op->OH + strip - 1) / strip) * ((op->OW + strip - 1) / strip) * d.dims[3];
-            const int64_t threads = std::min<int64_t>(256, (items + 63) / 64 * 64);
-            D.push_back(def("STRIP", strip));
-            D.push_back(def("STRIP_THREADS", threads));
-            k.block[0] = (unsigned)threads;
-            k.grid[0] = (unsigned)((items + threads - 1) / threads);
+            D.push_back(def("STRIP", p->body_tile));
+            D.push_back(def("STRIP_THREADS", p->threads));
         }
     }
     *out = k;
@@ -813,7 +875,31 @@ extern "C" int32_t ms_variant_coverage(const ms_op *op, const ms_variant_params 
     ms_op_tensor_bytes(op, -1, &ob);
     if (out_elems != ob / op->out_size) return fail(MS_ERR_BAD_ARG, "ms_variant_coverage: out_elems %" PRId64 " != %" PRId64, out_elems, ob / op->out_size);
     memset(counts, 0, sizeof(int32_t) * (size_t)out_elems);
-    if (p->family == MS_FAM_GEMM_ALU || p->family == MS_FAM_GEMM_MFMA) {
+    const ms_op_desc &d = op->d;
+    if (p->body == MS_BODY_IMAGE_ROWS) {
+        const ConvRows c = conv_rows_tiles(op, p->body_tile);
+        const int64_t bn = p->block_n, jbs = op->N / bn, ohw = op->OH * op->OW;
+        for (int64_t wg = 0; wg < p->grid[0]; ++wg) {
+            const int64_t jb = wg % jbs, od = wg / jbs % op->OD, tile = wg / (jbs * op->OD) % c.tiles, n = wg / (jbs * op->OD * c.tiles);
+            for (int64_t p0 = tile * c.px; p0 < (tile + 1) * c.px; ++p0)
+                for (int64_t j = 0; j < bn; ++j) {
+                    if (p0 >= ohw) continue; // pixels behind the plane are not stored
+                    const int64_t at = ((n * op->OD + od) * ohw + p0) * op->N + jb * bn + j;
+                    if (at >= out_elems) return fail(MS_ERR_INVALID_TRACE, "coverage: index out of range");
+                    ++counts[at];
+                }
+        }
+    } else if (p->body == MS_BODY_STRIPS) {
+        const int64_t C = d.dims[3], strip = p->body_tile, sw = p->tj[0];
+        for (int64_t n = 0; n < d.dims[0]; ++n)
+            for (int64_t item = 0; item < (int64_t)p->grid[0] * p->threads; ++item) {
+                if (item >= (int64_t)p->ti[0] * sw * C) continue;
+                const int64_t ch = item % C, ow = item / C % sw * strip, oh = item / (C * sw) * strip;
+                for (int64_t a = 0; a < strip; ++a)
+                    for (int64_t b = 0; b < strip; ++b)
+                        if (oh + a < op->OH && ow + b < op->OW) ++counts[((n * op->OH + oh + a) * op->OW + ow + b) * C + ch];
+            }
+    } else if (p->family == MS_FAM_GEMM_ALU || p->family == MS_FAM_GEMM_MFMA) {
         int um = p->tile_unit[0], un = p->tile_unit[1];
         for (int64_t b = 0; b < op->nb; ++b)
             for (int64_t wg = 0; wg < p->grid[0] / std::max(1, p->rfactor); ++wg) { // output tiles (rfactor workgroups share one)
@@ -844,12 +930,13 @@ extern "C" int32_t ms_variant_coverage(const ms_op *op, const ms_variant_params 
                 }
             }
     } else if (p->family == MS_FAM_REDUCE) {
-        const bool per_element = op->d.kind == MS_OP_SOFTMAX;
+        const bool per_element = op->d.kind == MS_OP_SOFTMAX, masked = p->body == MS_BODY_ROW_VECTORS;
         for (int64_t wg = 0; wg < p->grid[0]; ++wg)
             for (int64_t r1 = 0; r1 < p->ti[1]; ++r1)
                 for (int64_t g = 0; g < p->ti[2]; ++g)
                     for (int64_t r3 = 0; r3 < p->ti[3]; ++r3) {
                         int64_t row = split_index(p->ti, wg, r1, g, r3);
+                        if (masked && row >= op->M) continue;
                         if (row >= op->M) return fail(MS_ERR_INVALID_TRACE, "coverage: index out of range");
                         if (!per_element) {
                             ++counts[row];
@@ -860,12 +947,12 @@ extern "C" int32_t ms_variant_coverage(const ms_op *op, const ms_variant_params 
                                 for (int64_t t = 0; t < p->tk[2]; ++t)
                                     for (int64_t q3 = 0; q3 < p->tk[3]; ++q3) {
                                         int64_t k = split_index(p->tk, q0, q1, t, q3);
+                                        if (masked && k >= op->K) continue;
                                         if (k >= op->K) return fail(MS_ERR_INVALID_TRACE, "coverage: index out of range");
                                         ++counts[row * op->K + k];
                                     }
                     }
     } else {
-        const ms_op_desc &d = op->d;
         int64_t C = d.dims[3];
         for (int64_t n = 0; n < d.dims[0]; ++n)
             for (int64_t wg = 0; wg < p->grid[0]; ++wg) {
@@ -895,12 +982,13 @@ extern "C" int32_t ms_variant_reduction_coverage(const ms_op *op, const ms_varia
     if (!op || !p) return fail(MS_ERR_BAD_ARG, "ms_variant_reduction_coverage: NULL argument");
     const bool dw = p->family == MS_FAM_DWCONV;
     const int unit = dw ? 1 : std::max(1, p->tile_unit[2]);
-    const int64_t len = dw ? (int64_t)op->d.dims[4] * op->d.dims[5] : (int64_t)p->tk[0] * p->tk[1] * p->tk[2] * p->tk[3] * unit;
+    const bool masked = p->body == MS_BODY_ROW_VECTORS || p->body == MS_BODY_IMAGE_ROWS; // positions beyond K are left out
+    const int64_t len = dw ? (int64_t)op->d.dims[4] * op->d.dims[5] : masked ? op->K : (int64_t)p->tk[0] * p->tk[1] * p->tk[2] * p->tk[3] * unit;
     if (needed) *needed = len;
     if (!counts) return needed ? MS_OK : fail(MS_ERR_BAD_ARG, "ms_variant_reduction_coverage: NULL argument");
     if (k_elems != len) return fail(MS_ERR_BAD_ARG, "ms_variant_reduction_coverage: k_elems %" PRId64 " != %" PRId64, k_elems, len);
     // the interpreted reduction covers the operator's K, padded by less than one intrinsic where a convolution rounds it up
-    if (!dw && !p->tap_rows && (len < op->K || len - op->K >= unit))
+    if (!dw && !masked && !p->tap_rows && (len < op->K || len - op->K >= unit))
         return fail(MS_ERR_INVALID_TRACE, "reduction coverage: the split covers %" PRId64 " positions, the operator reduces over %" PRId64, len, op->K);
     memset(counts, 0, sizeof(int32_t) * (size_t)len);
     if (dw) {
@@ -910,6 +998,18 @@ extern "C" int32_t ms_variant_reduction_coverage(const ms_op *op, const ms_varia
                 if (k >= len) return fail(MS_ERR_INVALID_TRACE, "reduction coverage: index out of range");
                 ++counts[k];
             }
+        return MS_OK;
+    }
+    if (p->body == MS_BODY_IMAGE_ROWS) {
+        // per filter plane the chunks of its runs; elements before and behind a run are masked
+        const ConvRows c = conv_rows_tiles(op, p->body_tile);
+        const int64_t KH = op->d.dims[5], run = op->d.dims[6] * op->d.dims[3];
+        for (int64_t kd = 0; kd < op->kd; ++kd)
+            for (int64_t ch = 0; ch < c.steps * 2; ++ch)
+                for (int64_t e = 0; e < 8; ++e) {
+                    const int64_t q = ch % c.cpr * 8 + e - c.lead;
+                    if (ch < KH * c.cpr && q >= 0 && q < run) ++counts[(kd * KH + ch / c.cpr) * run + q];
+                }
         return MS_OK;
     }
     const int rf = std::max(1, p->rfactor);
@@ -922,6 +1022,7 @@ extern "C" int32_t ms_variant_reduction_coverage(const ms_op *op, const ms_varia
                     for (int64_t q3 = 0; q3 < p->tk[3]; ++q3)
                         for (int u = 0; u < unit; ++u) {
                             int64_t k = split_index(p->tk, q0, q1, q2, q3) * unit + u;
+                            if (masked && k >= len) continue;
                             if (k < 0 || k >= len) return fail(MS_ERR_INVALID_TRACE, "reduction coverage: index out of range");
                             ++counts[k];
                         }

@@ -174,6 +174,18 @@ extern "C" int32_t ms_cost_model_predict(const ms_cost_model *m, const double *X
 extern "C" int32_t ms_variant_features(const ms_op *op, const ms_variant_params *p, double *out, int32_t cap, int32_t *n_out)
 {
     if (!op || !p || !n_out) return fail(MS_ERR_BAD_ARG, "ms_variant_features: NULL argument");
+    ms_variant_params of_body = *p;
+    if (p->body != MS_BODY_NEST) { // decisions that such a kernel does not read are no features of it
+        of_body.cache_read = of_body.cache_write = of_body.unroll = of_body.lds_pad = of_body.reorder = of_body.compute_at = 0;
+        if (p->body == MS_BODY_IMAGE_ROWS) {
+            memset(of_body.ti, 0, sizeof of_body.ti);
+            memset(of_body.tj, 0, sizeof of_body.tj);
+            memset(of_body.tk, 0, sizeof of_body.tk);
+            of_body.mfma = of_body.unroll_k1 = of_body.unroll_k2 = 0;
+            for (int32_t &u : of_body.tile_unit) u = 1;
+        }
+        p = &of_body;
+    }
     std::vector<double> f;
     const int32_t *tl[4] = {p->ti, p->tj, p->tc, p->tk};
     for (int l = 0; l < 4; ++l)

@@ -606,6 +606,58 @@ def test_traces_of_one_body_are_one_kernel_with_one_key(mk, flags, body):
     assert len(of_body) == 1
 
 
+@pytest.mark.parametrize("mk,flags,body", [
+    (lambda: B.softmax_op(1, 1024, 1000), B.SPACE_DEFAULT, B.BODY_ROW_VECTORS),
+    (lambda: B.softmax_op(3, 32, 24, "f16"), B.SPACE_DEFAULT, B.BODY_ROW_VECTORS),
+    (lambda: B.dwconv2d_op(2, 57, 23, 7, stride=2), B.SPACE_DEFAULT, B.BODY_STRIPS),
+    (lambda: B.dwconv2d_op(1, 4, 38, 1, 2, 2, pad=0), B.SPACE_DEFAULT, B.BODY_STRIPS),
+    (lambda: B.conv2d_op(2, 59, 104, 3, 96, 5, 5, stride=2, pad=4), B.SPACE_DEFAULT | B.SPACE_TAP_ROWS, B.BODY_IMAGE_ROWS),
+    (lambda: B.conv3d_op(2, 5, 13, 16, 4, 64, 5, stride=2, pad=2), B.SPACE_DEFAULT, B.BODY_IMAGE_ROWS),
+    (lambda: B.conv1d_op(2, 528, 3, 32, 7, stride=2, pad=3), B.SPACE_DEFAULT, B.BODY_IMAGE_ROWS)])
+def test_params_describe_the_body_that_runs(mk, flags, body):
+    """Workgroup, grid, LDS, coverage and features of a body other than the nest are those of the kernel it launches, and
+    the limits hold for that kernel: under tighter ones the trace keeps its nest."""
+    op = mk()
+    sp = op.space(flags)
+    elems = op.tensor_bytes(-1) // {B.F32: 4, B.F16: 2, B.BF16: 2}[op.desc().out_dtype]
+    K = int(np.prod([e for n, e, red in op.loops() if red]))
+    traces = [B.trace_sample_valid(op, sp, 35, idx) for idx in range(60)]
+    traces = [t for t in traces if B.trace_validate(op, sp, t).body == body]
+    assert len(traces) >= 10
+    p = B.trace_validate(op, sp, traces[0])
+    text = B.variant_kernel_text(op, p)
+    d = {k: int(v) for k, v in (line[2:].split("=") for line in text.splitlines()[1:])}
+    threads = {B.BODY_ROW_VECTORS: lambda: d["ROW_WAVES"] * 64, B.BODY_STRIPS: lambda: d["STRIP_THREADS"],
+               B.BODY_IMAGE_ROWS: lambda: d["CR_WAVES"] * 64}[body]()
+    r = B.Variant(op, sp, traces[0]).resources()
+    assert p.threads == threads and p.waves == threads // 64 and p.lds_bytes == r.lds_bytes
+    cov = B.variant_coverage(op, p, elems)
+    assert cov.min() == 1 and cov.max() == 1
+    red = B.variant_reduction_coverage(op, p)
+    assert len(red) == K and red.min() == 1 and red.max() == 1
+    for t in traces[1:]:
+        q = B.trace_validate(op, sp, t)
+        assert (q.threads, q.waves, list(q.grid), q.lds_bytes, q.acc_per_thread) == (p.threads, p.waves, list(p.grid), p.lds_bytes, p.acc_per_thread)
+        assert np.array_equal(B.variant_features(op, q), B.variant_features(op, p))
+    assert "body=" in B.trace_to_text(op, sp, traces[0])
+    assert "workgroup=%d threads, grid=%d" % (p.threads, p.grid[0] * p.grid[1] * p.grid[2]) in B.trace_to_text(op, sp, traces[0])
+    lim = B.get_limits()
+    try:
+        for field, value in (("max_threads", p.threads - 1), ("max_acc_per_thread", p.acc_per_thread - 1)) + (
+                (("max_lds_bytes", p.lds_bytes - 1),) if p.lds_bytes else ()):
+            tight = B.get_limits()
+            setattr(tight, field, value)
+            B.set_limits(tight)
+            for t in traces:
+                try:
+                    q = B.trace_validate(op, sp, t)
+                except B.MsError:
+                    continue
+                assert q.threads <= tight.max_threads and q.lds_bytes <= tight.max_lds_bytes and q.acc_per_thread <= tight.max_acc_per_thread
+    finally:
+        B.set_limits(lim)
+
+
 def test_a_search_measures_a_body_once():
     """Every trace of this operator resolves to the strip kernel: one measurement, the rest are duplicates."""
     op = B.dwconv2d_op(1, 57, 57, 16, stride=2)
