@@ -9,7 +9,8 @@
 // (7 x 3 channels: 22 of 24) and not k steps.
 //
 // A workgroup makes CR_WAVES x CR_TM x 32 consecutive pixels of one output plane for CR_TN x 32 output channels.  Per
-// filter plane it stages the image rows that its pixels meet and the plane's weights in LDS, and while it multiplies
+// filter plane it stages the image rows that its pixels meet (where a row is several tiles long, CR_SPAN, only the columns
+// of those rows) and the plane's weights in LDS, and while it multiplies
 // them the next plane's rows and weights are on their way into registers.  Filter planes outside the input are skipped.
 // A wavefront holds CR_TM x CR_TN accumulator tiles: LDS reads 8 * (TM + TN) clocks per k step on each of four SIMDs
 // against 32 * TM * TN of the matrix cores.  8 x 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2 in fp16: 572 -> 144 us
@@ -25,7 +26,8 @@ typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 constexpr int TM = CR_TM, TN = CR_TN, NT = CR_WAVES * 64;
 constexpr int PX = CR_WAVES * TM * 32;                    // output pixels of a workgroup
 constexpr int BN = TN * 32, JB = DIM_N / BN;              // output channels of a workgroup, column blocks
-constexpr int OHW = CV_OH * CV_OW, TILES = (OHW + PX - 1) / PX;
+// CR_SPAN: a workgroup keeps to one output row and stages the columns that its pixels meet, not whole image rows
+constexpr int OHW = CV_OH * CV_OW, TPR = (CV_OW + PX - 1) / PX, TILES = CR_SPAN ? CV_OH * TPR : (OHW + PX - 1) / PX;
 constexpr int LEAD = CV_PAD * CV_CIN % 2;                 // runs start at even elements: 4-byte LDS reads
 constexpr int RUN = CV_KW * CV_CIN, CPR = (LEAD + RUN + 7) / 8; // elements of a filter row, its chunks
 constexpr int NCH = CV_KH * CPR, STEPS = (NCH + 1) / 2;   // chunks of a filter plane, matrix-core steps of two chunks
@@ -35,10 +37,10 @@ static_assert(ROW_E % 8 == 0 && CV_STRIDE * CV_CIN % 2 == 0 && DIM_N % BN == 0, 
 // LDS: image rows with their zero columns, then the weights row-major, rows padded by 32 bytes for the transposing reads
 constexpr int LHALO = ((CV_PAD * CV_CIN + LEAD) * 2 + 15) / 16 * 16;
 constexpr int ORG = LHALO - (CV_PAD * CV_CIN + LEAD) * 2; // byte of pixel 0's run in its row
-constexpr int READ_END = ORG + (CV_OW - 1) * CV_STRIDE * CV_CIN * 2 + CPR * 16, IMG_END = LHALO + ROW_E * 2;
+constexpr int READ_END = ORG + ((CR_SPAN ? PX : CV_OW) - 1) * CV_STRIDE * CV_CIN * 2 + CPR * 16, IMG_END = CR_SPAN ? 0 : LHALO + ROW_E * 2;
 constexpr int PRS = ((READ_END > IMG_END ? READ_END : IMG_END) + 15) / 16 * 16;
 constexpr int P_OUT_ = PX % CV_OW == 0 ? PX / CV_OW : (CV_OW + PX - 2) / CV_OW + 1;
-constexpr int P_OUT = P_OUT_ < CV_OH ? P_OUT_ : CV_OH;    // output rows that a workgroup can touch
+constexpr int P_OUT = CR_SPAN ? 1 : P_OUT_ < CV_OH ? P_OUT_ : CV_OH; // output rows that a workgroup can touch
 constexpr int PR = (P_OUT - 1) * CV_STRIDE + CV_KH;       // input rows
 constexpr int RMB = BN * 2 + 32;                          // bytes of a weight row
 constexpr int PATCH_B = PR * PRS, WT_B = STEPS * 16 * RMB;
@@ -51,7 +53,8 @@ constexpr int AL = cr_gcd(16, cr_gcd(ORG, CV_STRIDE * CV_CIN * 2)); // alignment
 struct __attribute__((packed, aligned(2))) raw16_t {
     u4_t v;
 };
-constexpr int XI = (PR * CPW + NT - 1) / NT;              // vectors of the image rows per thread
+constexpr int SV = CR_SPAN ? PRS / 16 : CPW;              // staged vectors of an image row
+constexpr int XI = (PR * SV + NT - 1) / NT;               // staged vectors of the image rows per thread
 constexpr int WROWS = CV_KH * RUN, WCB = BN / 8;          // weight rows of a filter plane, 16-byte vectors of one
 constexpr int WI = (WROWS * WCB + NT - 1) / NT;
 
@@ -81,14 +84,14 @@ struct stage_t {
     u4_t x[XI], w[WI];
 };
 
-__device__ __forceinline__ void stage_fetch(stage_t &st, const in_t *__restrict__ plane, const in_t *__restrict__ wt, int ih_lo, int tid)
+__device__ __forceinline__ void stage_fetch(stage_t &st, const in_t *__restrict__ plane, const in_t *__restrict__ wt, int ih_lo, int v_lo, int tid)
 {
 #pragma unroll
     for (int i = 0; i < XI; ++i) {
-        const int idx = i * NT + tid, row = idx / CPW, ih = ih_lo + row;
-        const bool ok = (unsigned)ih < (unsigned)CV_H && row < PR;
-        // rows outside the image read the plane's first vector (always there) and become zero
-        const u4_t v = reinterpret_cast<const raw16_t *>(plane + (ok ? ih * ROW_E + idx % CPW * 8 : 0))->v;
+        const int idx = i * NT + tid, row = idx / SV, ih = ih_lo + row, col = (CR_SPAN ? v_lo : 0) + idx % SV;
+        const bool ok = (unsigned)ih < (unsigned)CV_H && row < PR && (!CR_SPAN || (unsigned)col < (unsigned)CPW);
+        // vectors outside the image read the plane's first one (always there) and become zero
+        const u4_t v = reinterpret_cast<const raw16_t *>(plane + (ok ? ih * ROW_E + col * 8 : 0))->v;
         st.x[i] = ok ? v : u4_t{0, 0, 0, 0};
     }
 #pragma unroll
@@ -103,7 +106,7 @@ __device__ __forceinline__ void stage_commit(const stage_t &st, char *__restrict
 #pragma unroll
     for (int i = 0; i < XI; ++i) {
         const int idx = i * NT + tid;
-        if (PR * CPW % NT == 0 || idx < PR * CPW) *reinterpret_cast<u4_t *>(patch + idx / CPW * PRS + LHALO + idx % CPW * 16) = st.x[i];
+        if (PR * SV % NT == 0 || idx < PR * SV) *reinterpret_cast<u4_t *>(patch + idx / SV * PRS + (CR_SPAN ? 0 : LHALO) + idx % SV * 16) = st.x[i];
     }
 #pragma unroll
     for (int i = 0; i < WI; ++i) {
@@ -127,7 +130,9 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
     if (z >= instances) return;
     const int jb = wg % JB, od = wg / JB % CV_OD, tile = wg / (JB * CV_OD) % TILES, n = wg / (JB * CV_OD * TILES);
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, lrow = lane % 32, lgrp = lane / 32;
-    const int p0 = tile * PX, oh_lo = p0 / CV_OW, ih_lo = oh_lo * CV_STRIDE - CV_PAD_H;
+    const int p0 = CR_SPAN ? tile / TPR * CV_OW + tile % TPR * PX : tile * PX, oh_lo = p0 / CV_OW, ih_lo = oh_lo * CV_STRIDE - CV_PAD_H;
+    const int p_end = CR_SPAN ? (oh_lo + 1) * CV_OW : OHW;        // end of the pixels that a workgroup stores
+    const int v_lo = tile % TPR * (PX * CV_STRIDE * CV_CIN / 8) - LHALO / 16; // CR_SPAN: first staged vector of an image row
     const in_t *X = (const in_t *)x_ + (long)z * A_INST + (long)n * CV_D * CV_H * ROW_E;
     const in_t *Wt = (const in_t *)w_ + (long)z * B_INST + jb * BN;
     char *patch = smem, *wts = smem + PATCH_B;
@@ -137,7 +142,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
     const int kd_lo = id0 < 0 ? -id0 : 0, kd_hi = CV_D - id0 < CV_KD ? CV_D - id0 : CV_KD;
 
     stage_t st;
-    if (kd_lo < kd_hi) stage_fetch(st, X + (long)(id0 + kd_lo) * CV_H * ROW_E, Wt + (long)kd_lo * WROWS * DIM_N, ih_lo, tid);
+    if (kd_lo < kd_hi) stage_fetch(st, X + (long)(id0 + kd_lo) * CV_H * ROW_E, Wt + (long)kd_lo * WROWS * DIM_N, ih_lo, v_lo, tid);
     // zero columns of the image rows and padding rows of the weights: written once, no plane overwrites them
     for (int i = tid; i < (PATCH_B + WT_B) / 16; i += NT) *reinterpret_cast<u4_t *>(smem + i * 16) = u4_t{0, 0, 0, 0};
 
@@ -148,8 +153,9 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = accv_t{};
         int p = p0 + (wave * TM + tm) * 32 + lrow;
-        p = p < OHW ? p : OHW - 1; // pixels behind the plane repeat its last one and are not stored
-        pix[tm] = (p / CV_OW - oh_lo) * CV_STRIDE * PRS + ORG + p % CV_OW * (CV_STRIDE * CV_CIN * 2);
+        p = p < p_end ? p : p_end - 1; // pixels behind the last one repeat it and are not stored
+        pix[tm] = CR_SPAN ? ORG + (p - p0) * (CV_STRIDE * CV_CIN * 2)
+                          : (p / CV_OW - oh_lo) * CV_STRIDE * PRS + ORG + p % CV_OW * (CV_STRIDE * CV_CIN * 2);
     }
     const int li = lane % 16;
     const char *wl = wts + (lgrp * 8 + li / 4) * RMB + lrow / 16 * 32 + li % 4 * 8;
@@ -159,7 +165,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
         __syncthreads();
         stage_commit(st, patch, wts, tid);
         __syncthreads();
-        if (kd + 1 < kd_hi) stage_fetch(st, X + (long)(id0 + kd + 1) * CV_H * ROW_E, Wt + (long)(kd + 1) * WROWS * DIM_N, ih_lo, tid);
+        if (kd + 1 < kd_hi) stage_fetch(st, X + (long)(id0 + kd + 1) * CV_H * ROW_E, Wt + (long)(kd + 1) * WROWS * DIM_N, ih_lo, v_lo, tid);
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
             u4_t fa[TM], fb[TN];
@@ -226,7 +232,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
         for (int i = 0; i < 32 * OCB / 64; ++i) {
             const int idx = i * 64 + lane, r = idx / OCB, c = idx % OCB;
             const u4_t v = *reinterpret_cast<const u4_t *>(stg + r * SROW + c * 16);
-            if (pw + r < OHW) *reinterpret_cast<u4_t *>(Y + (long)(pw + r) * DIM_N + c * OV) = v;
+            if (pw + r < p_end) *reinterpret_cast<u4_t *>(Y + (long)(pw + r) * DIM_N + c * OV) = v;
         }
         __builtin_amdgcn_wave_barrier();
     }

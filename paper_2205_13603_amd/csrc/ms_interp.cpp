@@ -105,7 +105,7 @@ int dw_strip(const ms_op *op)
 // The image-row kernel for first layers (conv_rows.hip): workgroups of four wavefronts of tm x tn intrinsic tiles.
 struct ConvRows {
     int tm, tn, threads;
-    int64_t px, tiles;   // output pixels of a workgroup, workgroups of an output plane
+    int64_t px, tpr, tiles; // output pixels of a workgroup, workgroups of an output row (0: tiles cross rows) and plane
     int64_t lead, cpr, steps; // unused elements before a run, 8-element chunks of a run, k steps of a filter plane
     int64_t groups;      // workgroups of one instance
     int64_t lds;         // bytes of a workgroup
@@ -119,21 +119,27 @@ ConvRows conv_rows_tiles(const ms_op *op, int tm)
     c.tn = Cout / 32 % 2 == 0 ? 2 : Cout / 32 % 3 == 0 ? 3 : 1;
     c.threads = (int)waves * 64;
     c.px = waves * tm * 32;
-    c.tiles = (ohw + c.px - 1) / c.px;
+    // Rows of at least two tiles: a tile keeps to its row and stages the columns it meets.  Whole rows would be read once per
+    // tile and leave one workgroup per compute unit: 64 x 16384 x 4 -> 64, width 7: 73 us with whole rows, 34 so (the im2col
+    // loop 40); 8 x 128 x 2048 x 4 -> 64, 3 x 3: 88 and 67; 128 x 1024 x 4 -> 32, 5 x 5: 6.7 and 5.6.  From one tile per row
+    // on, the masked rest of a row costs more than it saves (8 x 128 x 640 x 4 -> 64: 23.3 and 26.2).
+    c.tpr = op->OW >= 2 * c.px ? (op->OW + c.px - 1) / c.px : 0;
+    c.tiles = c.tpr ? op->OH * c.tpr : (ohw + c.px - 1) / c.px;
     c.lead = d.pad * Cin % 2;
     c.cpr = (c.lead + KW * Cin + 7) / 8;
     c.steps = (KH * c.cpr + 1) / 2;
     const int64_t bn = c.tn * 32, halo = ((d.pad * Cin + c.lead) * 2 + 15) / 16 * 16;
-    const int64_t row = std::max(halo + W * Cin * 2, halo - (d.pad * Cin + c.lead) * 2 + (op->OW - 1) * S * Cin * 2 + c.cpr * 16);
-    const int64_t rows = (std::min(c.px % op->OW ? (op->OW + c.px - 2) / op->OW + 1 : c.px / op->OW, op->OH) - 1) * S + KH;
+    const int64_t last = halo - (d.pad * Cin + c.lead) * 2 + ((c.tpr ? c.px : op->OW) - 1) * S * Cin * 2 + c.cpr * 16; // end of the last run
+    const int64_t row = c.tpr ? last : std::max(halo + W * Cin * 2, last);
+    const int64_t rows = c.tpr ? KH : (std::min(c.px % op->OW ? (op->OW + c.px - 2) / op->OW + 1 : c.px / op->OW, op->OH) - 1) * S + KH;
     c.lds = std::max(rows * ((row + 15) / 16 * 16) + c.steps * 16 * (bn * 2 + 32), waves * 32 * (bn * op->out_size + 16));
     c.groups = c.tiles * (Cout / bn) * op->OD * d.dims[0];
     return c;
 }
 
 // MS_BODY_IMAGE_ROWS: tm of the image-row kernel, 0 = not taken.  Taken for 1 to 4 channels per pixel where the cache-read
-// of X is not shared by several tiles (compute_at 0, 1): the im2col loader and the patch of single elements lose on every
-// size tried (3-D: 572 -> 144 us for 8 x 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2, and 9.6 -> 7.7 us for one
+// of X is not shared by several tiles (compute_at 0, 1), where the im2col loader and the patch of single elements read
+// 2-byte elements (3-D: 572 -> 144 us for 8 x 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2, and 9.6 -> 7.7 us for one
 // 8 x 64 x 64 x 1, 5 x 5 x 5; 2-D in filter rows: 117 -> 75 us for 128 x 224 x 224 x 3 -> 64, 7 x 7, and 7.8 us on both
 // sides, which is a launch, for one 64 x 64 x 3).
 int conv_rows(const ms_op *op, const ms_variant_params *p)
@@ -803,6 +809,7 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             k.template_name = "conv_rows.hip";
             D.push_back(def("CR_TM", cr.tm));
             D.push_back(def("CR_TN", cr.tn));
+            D.push_back(def("CR_SPAN", cr.tpr ? 1 : 0));
             D.push_back(def("CR_WAVES", p->waves));
         } else if (p->family == MS_FAM_GEMM_MFMA) {
             k.template_name = "gemm_mfma.hip";
@@ -881,10 +888,12 @@ extern "C" int32_t ms_variant_coverage(const ms_op *op, const ms_variant_params 
         const int64_t bn = p->block_n, jbs = op->N / bn, ohw = op->OH * op->OW;
         for (int64_t wg = 0; wg < p->grid[0]; ++wg) {
             const int64_t jb = wg % jbs, od = wg / jbs % op->OD, tile = wg / (jbs * op->OD) % c.tiles, n = wg / (jbs * op->OD * c.tiles);
-            for (int64_t p0 = tile * c.px; p0 < (tile + 1) * c.px; ++p0)
+            const int64_t oh = c.tpr ? tile / c.tpr : 0, first = c.tpr ? oh * op->OW + tile % c.tpr * c.px : tile * c.px;
+            const int64_t end = c.tpr ? (oh + 1) * op->OW : ohw;
+            for (int64_t px = first; px < first + c.px; ++px)
                 for (int64_t j = 0; j < bn; ++j) {
-                    if (p0 >= ohw) continue; // pixels behind the plane are not stored
-                    const int64_t at = ((n * op->OD + od) * ohw + p0) * op->N + jb * bn + j;
+                    if (px >= end) continue; // pixels behind the plane, or the row, are not stored
+                    const int64_t at = ((n * op->OD + od) * ohw + px) * op->N + jb * bn + j;
                     if (at >= out_elems) return fail(MS_ERR_INVALID_TRACE, "coverage: index out of range");
                     ++counts[at];
                 }

@@ -528,10 +528,12 @@ def test_conv3d_exact(Cin, k, stride, pad, dil, D, H, W_):
 @pytest.mark.parametrize("D,H,W_,Cin,Cout,k,stride,pad,dtype,out", [(6, 16, 16, 3, 64, 7, 2, 3, "f16", "f32"), (4, 9, 24, 1, 32, 3, 2, 1, "bf16", "f32"),
                                                                    (5, 13, 16, 4, 96, 5, 2, 2, "f16", "f16"), (4, 12, 8, 2, 32, 3, 1, 0, "f16", "f32"),
                                                                    (1, 40, 56, 3, 64, 7, 2, 3, "bf16", "f32"), (1, 33, 72, 4, 128, 3, 1, 1, "f16", "f32"),
-                                                                   (1, 59, 104, 3, 32, 5, 2, 4, "f16", "f32")])
+                                                                   (1, 59, 104, 3, 32, 5, 2, 4, "f16", "f32"),
+                                                                   (1, 5, 304, 4, 64, 3, 1, 1, "f16", "f32"), (1, 6, 528, 3, 32, 7, 2, 3, "bf16", "f32"),
+                                                                   (2, 3, 272, 2, 96, 3, 1, 2, "f16", "f16"), (1, 4, 264, 4, 32, 3, 1, 1, "f16", "f16")])
 def test_first_layer_image_rows_exact(D, H, W_, Cin, Cout, k, stride, pad, dtype, out):
     """Im2col traces of first layers on the image-row kernel: runs with and without a leading element, odd and even chunk
-    counts, tiles that end behind the plane, every accumulator shape.  Batch 2, 2 instances with their own weights;
+    counts, tiles that end behind the plane, tiles that keep to the columns of a row, every accumulator shape.  Batch 2, 2 instances with their own weights;
     integer-valued inputs -> exact.  An infinite pixel reaches the outputs whose windows hold it and no others."""
     g = I.rng(97)
     shape, wshape = ((2, D, H, W_, Cin), (k, k, k, Cin, Cout)) if D > 1 else ((2, H, W_, Cin), (k, k, Cin, Cout))
@@ -551,6 +553,25 @@ def test_first_layer_image_rows_exact(D, H, W_, Cin, Cout, k, stride, pad, dtype
     if got is not None:
         for r in range(2):
             assert np.array_equal(got[r], refs[r]), "instance %d" % r
+
+
+@pytest.mark.parametrize("L_,Cin,Cout,k,stride,pad", [(1056, 4, 64, 7, 1, 3), (4096, 1, 32, 7, 2, 3), (2080, 2, 64, 3, 1, 1)])
+def test_conv1d_image_rows_exact(L_, Cin, Cout, k, stride, pad):
+    """Rows of several tiles, not a whole number of them: a tile stages the columns that it meets.  Batch 2, integer-valued
+    inputs -> exact."""
+    g = I.rng(99)
+    X = I.small_ints(g, (2, L_, Cin), -2, 2, "f16")
+    Wt = I.small_ints(g, (k, Cin, Cout), -2, 2, "f16")
+    bias = g.integers(-3, 4, size=Cout).astype(np.float32)
+    ref = O.conv1d_nwc(X, Wt, bias=bias, relu=True, stride=stride, pad=pad)
+    op = B.conv1d_op(2, L_, Cin, Cout, k, stride=stride, pad=pad, out_dtype="f32")
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 100, n) for n in range(200)) if B.trace_validate(op, space, t).body == B.BODY_IMAGE_ROWS)
+    assert "-DCR_SPAN=1" in B.variant_kernel_text(op, B.trace_validate(op, space, t))
+    got = run_variant(op, space, t, [X, Wt, bias], "f32", ref.shape, instances=2)
+    if got is None:
+        return
+    assert np.array_equal(got[0], ref) and np.array_equal(got[1], ref)
 
 
 def test_c3d_config_conv3d_16x224x224x3():

@@ -613,7 +613,9 @@ def test_traces_of_one_body_are_one_kernel_with_one_key(mk, flags, body):
     (lambda: B.dwconv2d_op(1, 4, 38, 1, 2, 2, pad=0), B.SPACE_DEFAULT, B.BODY_STRIPS),
     (lambda: B.conv2d_op(2, 59, 104, 3, 96, 5, 5, stride=2, pad=4), B.SPACE_DEFAULT | B.SPACE_TAP_ROWS, B.BODY_IMAGE_ROWS),
     (lambda: B.conv3d_op(2, 5, 13, 16, 4, 64, 5, stride=2, pad=2), B.SPACE_DEFAULT, B.BODY_IMAGE_ROWS),
-    (lambda: B.conv1d_op(2, 528, 3, 32, 7, stride=2, pad=3), B.SPACE_DEFAULT, B.BODY_IMAGE_ROWS)])
+    (lambda: B.conv1d_op(2, 528, 3, 32, 7, stride=2, pad=3), B.SPACE_DEFAULT, B.BODY_IMAGE_ROWS),
+    (lambda: B.conv1d_op(1, 2080, 2, 64, 3, stride=1, pad=1), B.SPACE_DEFAULT, B.BODY_IMAGE_ROWS),
+    (lambda: B.conv2d_op(1, 4, 784, 3, 64, 7, 7, stride=2, pad=3), B.SPACE_DEFAULT, B.BODY_IMAGE_ROWS)])
 def test_params_describe_the_body_that_runs(mk, flags, body):
     """Workgroup, grid, LDS, coverage and features of a body other than the nest are those of the kernel it launches, and
     the limits hold for that kernel: under tighter ones the trace keeps its nest."""
@@ -656,6 +658,18 @@ def test_params_describe_the_body_that_runs(mk, flags, body):
                 assert q.threads <= tight.max_threads and q.lds_bytes <= tight.max_lds_bytes and q.acc_per_thread <= tight.max_acc_per_thread
     finally:
         B.set_limits(lim)
+
+
+@pytest.mark.parametrize("mk,elements", [(lambda: B.conv1d_op(1, 65536, 1, 64, 7, stride=2, pad=3), 2 * 512 + 16),
+                                         (lambda: B.conv1d_op(64, 16384, 4, 64, 7, stride=1, pad=3), 4 * 512 + 32),
+                                         (lambda: B.conv2d_op(1, 64, 4096, 4, 64, 3, 3, stride=1, pad=1), 3 * (4 * 512 + 32))])
+def test_image_rows_stage_the_columns_of_a_tile_not_whole_rows(mk, elements):
+    """Rows of many tiles: the LDS beyond the weights holds at most the columns that a tile of 512 pixels meets."""
+    op = mk()
+    sp = op.space()
+    p = next(p for p in (B.trace_validate(op, sp, B.trace_sample_valid(op, sp, 36, n)) for n in range(50)) if p.body == B.BODY_IMAGE_ROWS)
+    weights = p.block_k * (p.block_n * 2 + 32)
+    assert p.lds_bytes <= max(weights + 2 * elements, p.waves * 32 * (p.block_n * 2 + 16))
 
 
 def test_a_search_measures_a_body_once():
