@@ -82,11 +82,27 @@ int row_vectors(const ms_op *op, const ms_variant_params *p)
 int64_t dw_strip_items(const ms_op *op, int64_t strip) { return ((op->OH + strip - 1) / strip) * ((op->OW + strip - 1) / strip) * op->d.dims[3]; }
 int64_t dw_strip_threads(const ms_op *op, int64_t strip) { return std::min<int64_t>(256, (dw_strip_items(op, strip) + 63) / 64 * 64); }
 
+// Whether a nest is worth keeping where strips could run: small launches (at most one strip wavefront per compute unit)
+// that wait for one thread's chain of loads, not for memory.  A nest whose threads make one patch each, unrolled, straight
+// from global memory, no larger than a strip's, neighbours in a row beside each other in a wavefront, is never slower there
+// (137 such nests of 64 operators: 0.48 to 1.00 of the strips' time, 0.73 in the mean; 2 x 211 x 211 x 4, 5 x 5, stride 2:
+// 3.1 against 6.8 us, 57 x 57 x 144, stride 2: 3.0 against 4.6).  From one wavefront per compute unit on strips win, and
+// without these conditions most nests lose at every size.
+bool keeps_small_launch(const ms_op *op, const ms_variant_params *p, int64_t strip)
+{
+    const ms_op_desc &d = op->d;
+    const int64_t sp_h = (strip - 1) * d.stride + d.dims[4], sp_w = (strip - 1) * d.stride + d.dims[5];
+    const int64_t ph = (int64_t)(p->ti[3] - 1) * d.stride + d.dims[4], pw = (int64_t)(p->tj[3] - 1) * d.stride + d.dims[5];
+    return d.dims[0] * dw_strip_items(op, strip) <= 256 * 64 && !p->cache_read && p->unroll > 0 &&
+           (int64_t)p->ti[1] * p->tj[1] * p->tc[1] * (p->tc[3] / p->vec) == 1 && ph * pw <= sp_h * sp_w &&
+           (int64_t)p->tj[2] * p->tc[2] >= 32 && p->threads * 2 >= p->waves * 64;
+}
+
 // MS_BODY_STRIPS: output pixels per side of a thread's strip in the strip kernel (dwconv.hip), 0 = not taken.
 // Taken where an output extent above 2 has no divisor from 3 to 8: perfect tiles then leave a thread a row, a column or a
 // single pixel, which reads its inputs several times over (57 x 57 x 144, stride 2, batch 128: 75 against 50 us; 73 x 73 x 32,
 // batch 22: 119 against 6).  Elsewhere the factors can say better what fits.
-int dw_strip(const ms_op *op)
+int dw_strip(const ms_op *op, const ms_variant_params *p)
 {
     const ms_op_desc &d = op->d;
     auto stubborn = [](int64_t e) {
@@ -99,7 +115,7 @@ int dw_strip(const ms_op *op)
     if (regs > g_limits.max_acc_per_thread || dw_strip_threads(op, strip) > g_limits.max_threads) return 0; // patch and taps stay in registers
     // 32-bit byte offsets inside an image, 32-bit counts of its strips
     if (d.dims[1] * d.dims[2] * d.dims[3] > 0x7ffffff0 / 4 || op->OH * op->OW * d.dims[3] > 0x7ffffff0) return 0;
-    return (int)strip;
+    return keeps_small_launch(op, p, strip) ? 0 : (int)strip;
 }
 
 // The image-row kernel for first layers (conv_rows.hip): workgroups of four wavefronts of tm x tn intrinsic tiles.
@@ -195,7 +211,7 @@ void resolve_body(const ms_op *op, ms_variant_params *p)
         p->threads = r.threads;
         p->acc_per_thread = r.vectors * p->body_tile;
         p->lds_bytes = 0;
-    } else if (p->family == MS_FAM_DWCONV && (p->body_tile = dw_strip(op))) {
+    } else if (p->family == MS_FAM_DWCONV && (p->body_tile = dw_strip(op, p))) {
         const int64_t strip = p->body_tile;
         p->body = MS_BODY_STRIPS;
         p->threads = (int32_t)dw_strip_threads(op, strip);

@@ -672,9 +672,27 @@ def test_image_rows_stage_the_columns_of_a_tile_not_whole_rows(mk, elements):
     assert p.lds_bytes <= max(weights + 2 * elements, p.waves * 32 * (p.block_n * 2 + 16))
 
 
+def test_small_depthwise_launches_keep_a_compact_nest():
+    """A small launch keeps a nest of one compact patch per thread; the same decisions on a launch of many strips, and
+    nests that are rolled, staged or serial, go to the strips."""
+    def body(n, i=(29, 1, 1, 1), j=(29, 1, 1, 1), c=(2, 1, 72, 1), unroll=64, cache_read=0):
+        op = B.dwconv2d_op(n, 57, 57, 144, stride=2)
+        sp = op.space()
+        by = {B.SLOT_TILE_I: list(i), B.SLOT_TILE_J: list(j), B.SLOT_TILE_C: list(c), B.SLOT_UNROLL: [unroll],
+              B.SLOT_CACHE_READ: [cache_read], B.SLOT_REORDER: [0]}
+        return B.trace_validate(op, sp, B.make_trace(sp, [by[sp.slots[k].slot_id] for k in range(sp.n_slots)])).body
+
+    assert body(1) == B.BODY_NEST                     # 8 x 8 x 144 strips: 144 wavefronts
+    assert body(2) == B.BODY_STRIPS                   # 288
+    assert body(1, unroll=0) == B.BODY_STRIPS and body(1, cache_read=1) == B.BODY_STRIPS
+    assert body(1, c=(1, 2, 72, 1)) == B.BODY_STRIPS  # two channels per thread, one after the other
+    assert body(1, j=(1, 1, 1, 29)) == B.BODY_STRIPS  # 3 x 59 input patch against 9 x 9
+    assert body(1, c=(9, 1, 16, 1)) == B.BODY_STRIPS  # 16 of 64 lanes
+
+
 def test_a_search_measures_a_body_once():
     """Every trace of this operator resolves to the strip kernel: one measurement, the rest are duplicates."""
-    op = B.dwconv2d_op(1, 57, 57, 16, stride=2)
+    op = B.dwconv2d_op(32, 57, 57, 48, stride=2)
     sp = op.space()
     cfg = B.search_cfg_default()
     cfg.seed, cfg.trials = 3, 64
