@@ -65,6 +65,16 @@ RowVectors row_vectors_split(const ms_op *op, int v)
     return r;
 }
 
+// Whether a nest that reads its rows once per pass (cache_read 0) is worth keeping: few long rows, each in one trip of a lane
+// group of its own of at least a wavefront.  The passes then meet in the caches, and more lanes than the row kernel's 64
+// share the exponentials of a row: 256 x 4096 in fp32 with 512 lanes 3.5 against 5.7 us, 64 x 2048 with 256 lanes 2.8
+// against 3.5, 1024 x 4096 7.8 against 8.8.  Rows of up to 1024 elements come out even; with more rows in a launch the second
+// and third pass cost bandwidth (16384 x 4096 with 256 lanes: 133 against 105).
+bool keeps_wide_groups(const ms_op *op, const ms_variant_params *p)
+{
+    return op->K > 1024 && op->M <= 1024 && p->ti[1] == 1 && p->ti[2] <= 4 && p->ti[3] == 1 && p->tk[0] == 1 && p->tk[1] <= 16 && p->tk[2] >= 64;
+}
+
 // MS_BODY_ROW_VECTORS: elements per vector of the whole-vector row kernel (reduce.hip), 0 = not taken.
 // Taken for a softmax whose lane groups read less than a 128-byte line per access, or read the row once per pass
 // (cache_read 0), where a row is whole 16-byte vectors and at most 64 values per lane of a wavefront.
@@ -75,7 +85,8 @@ int row_vectors(const ms_op *op, const ms_variant_params *p)
     if (op->K % v || op->K > 64 * 64) return 0;
     const RowVectors r = row_vectors_split(op, v);
     if (r.threads > g_limits.max_threads || r.threads / 64 > g_limits.max_waves || r.vectors * v > g_limits.max_acc_per_thread) return 0;
-    return !p->cache_read || (int64_t)p->tk[2] * p->tk[3] * op->in_size < 128 ? v : 0;
+    if ((int64_t)p->tk[2] * p->tk[3] * op->in_size < 128) return v;
+    return p->cache_read || keeps_wide_groups(op, p) ? 0 : v;
 }
 
 // Threads of the strip kernel: one per strip and channel of an image, at most 256 in a workgroup.

@@ -672,6 +672,24 @@ def test_image_rows_stage_the_columns_of_a_tile_not_whole_rows(mk, elements):
     assert p.lds_bytes <= max(weights + 2 * elements, p.waves * 32 * (p.block_n * 2 + 16))
 
 
+def test_few_long_rows_keep_their_wide_lane_groups():
+    """Softmax without staging: a few long rows keep a lane group of a wavefront or more per row; many rows, short rows and
+    groups that walk a row or several rows in turn go to the row kernel, as do groups narrower than a line."""
+    def body(rows, cols, i, k, cache_read=0):
+        op = B.softmax_op(1, rows, cols)
+        sp = op.space()
+        return B.trace_validate(op, sp, B.make_trace(sp, [i, k, [cache_read]])).body
+
+    assert body(256, 4096, [256, 1, 1, 1], [1, 2, 512, 4]) == B.BODY_NEST
+    assert body(1024, 2048, [256, 1, 4, 1], [1, 8, 64, 4]) == B.BODY_NEST
+    assert body(2048, 4096, [2048, 1, 1, 1], [1, 2, 512, 4]) == B.BODY_ROW_VECTORS
+    assert body(256, 1024, [256, 1, 1, 1], [1, 1, 256, 4]) == B.BODY_ROW_VECTORS
+    assert body(256, 4096, [256, 1, 1, 1], [2, 1, 512, 4]) == B.BODY_ROW_VECTORS
+    assert body(256, 4096, [128, 2, 1, 1], [1, 2, 512, 4]) == B.BODY_ROW_VECTORS
+    assert body(256, 2048, [64, 1, 4, 1], [1, 16, 32, 4]) == B.BODY_ROW_VECTORS
+    assert body(256, 4096, [256, 1, 1, 1], [1, 2, 512, 4], 1) == B.BODY_NEST        # staged: one pass, full lines
+
+
 def test_small_depthwise_launches_keep_a_compact_nest():
     """A small launch keeps a nest of one compact patch per thread; the same decisions on a launch of many strips, and
     nests that are rolled, staged or serial, go to the strips."""
