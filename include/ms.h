@@ -392,8 +392,8 @@ int32_t ms_trace_from_text(const ms_space *space, const char *text, ms_trace *ou
 /* ------------------------------------------------------------------ g(e0,tau) */
 
 /* The program that a trace resolves to.  MS_BODY_NEST: the loop nest that the decisions spell out.  Where no decisions can
- * spell out a good kernel the interpreter gives the trace another body, which reads the operator and its own tile (and, of
- * the decisions, nothing): all traces that a rule takes to one body are one kernel and share one key.  The rules keep to
+ * spell out a good kernel the interpreter gives the trace another body.  Bodies 1 to 3 read the operator and their own tile
+ * (and, of the decisions, nothing): all traces that a rule takes to one of them are one kernel and share one key.  The rules keep to
  * ms_limits; where a body would exceed them the trace stays with its nest. */
 typedef enum ms_body {
     MS_BODY_NEST = 0,
@@ -401,11 +401,13 @@ typedef enum ms_body {
                                 body_tile = elements per vector */
     MS_BODY_STRIPS = 2,      /* depthwise: square strips of output pixels per thread, masked at the border;
                                 body_tile = pixels per side */
-    MS_BODY_IMAGE_ROWS = 3   /* conv with 1 to 4 channels per pixel: image rows and one filter plane's weights in LDS;
+    MS_BODY_IMAGE_ROWS = 3,  /* conv with 1 to 4 channels per pixel: image rows and one filter plane's weights in LDS;
                                 body_tile = 32-pixel tiles of a wavefront */
+    MS_BODY_PHASES = 4       /* transposed conv: the nest, all decisions included, with its rows ordered by output phase and
+                                the k0 loop over the taps that meet a tile's phase; body_tile = phases = stride^2 */
 } ms_body;
 
-/* What the trace interpreter derives.  Unused fields are zero.  With another body than the nest, block_*, grid, threads,
+/* What the trace interpreter derives.  Unused fields are zero.  With bodies 1 to 3, block_*, grid, threads,
  * waves, acc_per_thread, lds_bytes, vec and vec_b are those of the kernel that runs, and so are the splits ti, tj, tc and tk
  * of MS_BODY_ROW_VECTORS and MS_BODY_STRIPS (their products may exceed the extents: the rest is masked; block_k of the
  * strips = threads, one per strip and channel); block_k of MS_BODY_IMAGE_ROWS = k values per filter plane.  All other
@@ -540,7 +542,7 @@ int32_t ms_variant_launch_static(ms_variant *v, const void *const *inputs, void 
 int32_t ms_variant_coverage(const ms_op *op, const ms_variant_params *params, int32_t *counts, int64_t out_elems);
 /*
  * The same for the reduction: walks the rfactor / k0 / k1 / k2 / k3 / intrinsic-k loops (depthwise: the filter taps)
- * that produce ONE output element and counts how often each position of the reduction is visited.  counts: host
+ * that produce ONE output element (MS_BODY_PHASES: one element of every phase) and counts how often each position of the reduction is visited.  counts: host
  * pointer to k_elems int32; *k_elems_needed (may be NULL) receives the length of the interpreted reduction (the
  * operator's K, rounded up where a convolution pads it to the intrinsic's k).  A correct split visits every position
  * exactly once, whatever the decisions.  Index arithmetic only.

@@ -104,22 +104,17 @@
 #endif
 #endif
 
-// Phase form of the transposed convolution (CV_PHASES 1).  An output pixel meets only the taps with
-// (oh + pad - kh) mod S = 0 (same for the columns), one in S^2 of them; the plain row order mixes the S^2 phases in
-// every tile, so each tile walks all KH*KW taps and multiplies zeros for the rest.  Here the rows are ordered so that
-// a tile lies in one phase, and the k loop covers that phase's (KH/S)*(KW/S) taps only: S^2 times fewer k steps and
-// activation loads, the same products.  Taken where every tile keeps to one phase and every k step to one tap;
-// elsewhere (filters that the stride does not divide, tiles wider than a phase) all taps are walked as before.
-// 16 x 16 x 256 -> 128, 4 x 4, stride 2, batch 64 in bf16: 77.8 -> 25.9 us.
-#if IS_CONV && CV_TRANSPOSED
-#define CV_BM_ (I1 * I2 * I3 * MI_M)
-#define CV_BK_ (K1 * K2 * K3 * MI_K)
-#define CV_PHASES (CV_STRIDE > 1 && DIM_B == 1 && CACHE_READ <= 4 && CV_KH % CV_STRIDE == 0 && CV_KW % CV_STRIDE == 0 && \
-                   CV_OH % CV_STRIDE == 0 && CV_OW % CV_STRIDE == 0 && (CV_N * (CV_OH / CV_STRIDE) * (CV_OW / CV_STRIDE)) % CV_BM_ == 0 && \
-                   CV_CIN % CV_BK_ == 0 && K0 * CV_BK_ == CV_KH * CV_KW * CV_CIN && K0 % (CV_STRIDE * CV_STRIDE * RFACTOR) == 0)
-#define K0_WALK (CV_PHASES ? K0 / (CV_STRIDE * CV_STRIDE) : K0) // k0 steps of a whole reduction
-#else
+// Phase form of the transposed convolution (CV_PHASES 1; the host's rule is conv_phases() in ms_interp.cpp).  An output pixel
+// meets only the taps with (oh + pad - kh) mod S = 0 (same for the columns), one in S^2 of them; the plain row order mixes
+// the S^2 phases in every tile, so each tile walks all KH*KW taps and multiplies zeros for the rest.  Here the rows are
+// ordered so that a tile lies in one phase, and the k loop covers that phase's (KH/S)*(KW/S) taps only: S^2 times fewer k
+// steps and activation loads, the same products.  16 x 16 x 256 -> 128, 4 x 4, stride 2, batch 64 in bf16: 77.8 -> 25.9 us.
+#ifndef CV_PHASES
 #define CV_PHASES 0
+#endif
+#if CV_PHASES
+#define K0_WALK (K0 / (CV_STRIDE * CV_STRIDE)) // k0 steps of a whole reduction
+#else
 #define K0_WALK K0
 #endif
 #define B_KMAJOR (!IS_CONV && SB_K == 1 && SB_J != 1)
@@ -319,6 +314,9 @@ static_assert((CV_D == 1 && CV_KD == 1) || (COMPUTE_AT == 0 && !CV_TRANSPOSED), 
 #if CV_PHASES
 // Phase form of the transposed convolution (see CV_PHASES above): row v of the launch's row order is output pixel
 // (n, a * S + ph, b * S + pw), where the workgroup's (ph, pw) = i0 mod S^2 and (n, a, b) counts inside the phase.
+static_assert(CV_TRANSPOSED && CV_KH % CV_STRIDE == 0 && CV_KW % CV_STRIDE == 0 && CV_OH % CV_STRIDE == 0 && CV_OW % CV_STRIDE == 0, "whole phases");
+static_assert((CV_N * (CV_OH / CV_STRIDE) * (CV_OW / CV_STRIDE)) % BM == 0 && CV_CIN % BK == 0 && K0 % (CV_STRIDE * CV_STRIDE) == 0,
+              "tiles of one phase, k steps of one tap");
 constexpr int PH_N = CV_STRIDE * CV_STRIDE;
 constexpr int PH_H = CV_OH / CV_STRIDE, PH_W = CV_OW / CV_STRIDE;      // pixels of one phase of one image
 constexpr int PH_TH = CV_KH / CV_STRIDE, PH_TW = CV_KW / CV_STRIDE;    // taps that meet a phase

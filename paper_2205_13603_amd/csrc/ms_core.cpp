@@ -1049,6 +1049,7 @@ extern "C" int32_t ms_trace_to_text(const ms_op *op, const ms_space *space, cons
             appendf(s, "# body=image-rows: %d pixels x %d channels per workgroup, %d k values per filter plane; the decisions do not act\n"
                        "tensorize(block=C, intrin=mfma_32x32x16)\ncache-read(buffers=[X, W], scope=lds, compute-at=filter plane, prefetch_distance=1)\n"
                        "cache-write(buffer=C, scope=lds, per wavefront)\n", p.block_m, p.block_n, p.block_k);
+        if (p.body == MS_BODY_PHASES) appendf(s, "# body=phases: i in the order of the %d output phases, k0 over the taps of a tile's phase only\n", p.body_tile);
         if (p.mfma && !image_rows) appendf(s, "tensorize(block=C, intrin=mfma_%dx%dx%d)\n", p.tile_unit[0], p.tile_unit[1], p.tile_unit[2]);
         const char *nm[4] = {"i", "j", "c", "k"};
         const int32_t *tl[4] = {p.ti, p.tj, p.tc, p.tk};
@@ -1081,7 +1082,7 @@ extern "C" int32_t ms_trace_to_text(const ms_op *op, const ms_space *space, cons
         if (p.family == MS_FAM_REDUCE) {
             // everything was said above
         } else {
-        if (p.body == MS_BODY_NEST) {
+        if (follows_decisions(&p)) {
         if (p.cache_read) {
             if (p.cache_read >= 8)
                 appendf(s, "cache-read(buffers=[A, B], scope=lds, at=k0, stages=%d, prefetch_distance=%d, direct_to_lds=1)\n"

@@ -197,6 +197,19 @@ int conv_rows(const ms_op *op, const ms_variant_params *p)
     return best;
 }
 
+// MS_BODY_PHASES: output phases (stride^2) of a transposed convolution whose rows can be ordered by phase, 0 = not taken.
+// Taken where every tile keeps to one phase and every k step to one tap: the k loop then covers that phase's taps only.
+// Elsewhere (filters that the stride does not divide, tiles wider than a phase) all taps are walked.
+int conv_phases(const ms_op *op, const ms_variant_params *p)
+{
+    const ms_op_desc &d = op->d;
+    const int64_t S = d.stride;
+    if (d.kind != MS_OP_CONV2D_TRANSPOSED_NHWC || p->family != MS_FAM_GEMM_MFMA || S < 2 || op->nb != 1 || p->cache_read > 4) return 0;
+    if (d.dims[5] % S || d.dims[6] % S || op->OH % S || op->OW % S) return 0;
+    if ((d.dims[0] * (op->OH / S) * (op->OW / S)) % p->block_m || d.dims[3] % p->block_k || op->K % p->block_k) return 0;
+    return p->tk[0] % (S * S * std::max(1, p->rfactor)) ? 0 : (int)(S * S);
+}
+
 void set4(int32_t *f, int64_t f0, int64_t f1, int64_t f2, int64_t f3)
 {
     f[0] = (int32_t)f0;
@@ -249,6 +262,7 @@ void resolve_body(const ms_op *op, ms_variant_params *p)
         p->acc_per_thread = c.tm * c.tn * 16;
         p->lds_bytes = (int32_t)c.lds;
     } else {
+        if ((p->body_tile = conv_phases(op, p))) p->body = MS_BODY_PHASES; // the launch is the nest's
         return;
     }
     p->waves = p->threads / 64;
@@ -278,7 +292,7 @@ uint64_t hash_params(const ms_op *op, const ms_variant_params *p)
         add((uint64_t)d.b_strides[i]);
     }
     add((uint64_t)p->family);
-    if (p->body) { // the operator and the body's own tile are all that such a kernel reads
+    if (!follows_decisions(p)) { // the operator and the body's own tile are all that such a kernel reads
         add(0xB0D7000000ull + (uint64_t)p->body);
         add((uint64_t)p->body_tile);
         return h;
@@ -772,7 +786,7 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
     auto &D = k.defines;
     D.push_back(def("IN_DT", dt_code(d.in_dtype)));
     D.push_back(def("OUT_DT", dt_code(d.out_dtype)));
-    if (p->body == MS_BODY_NEST) push_schedule(D, p);
+    if (follows_decisions(p)) push_schedule(D, p);
     if (p->family == MS_FAM_GEMM_ALU || p->family == MS_FAM_GEMM_MFMA) {
         D.push_back(def("DIM_B", op->nb));
         D.push_back(def("DIM_M", op->M));
@@ -801,7 +815,8 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             D.push_back(def("CV_OD", op->OD));
             D.push_back(def("CV_DIL", d.dilation));
             D.push_back(def("CV_TRANSPOSED", d.kind == MS_OP_CONV2D_TRANSPOSED_NHWC ? 1 : 0));
-            if (p->body == MS_BODY_NEST) {
+            if (follows_decisions(p)) {
+                if (d.kind == MS_OP_CONV2D_TRANSPOSED_NHWC) D.push_back(def("CV_PHASES", p->body == MS_BODY_PHASES ? 1 : 0));
                 D.push_back(def("CV_TAPROWS", p->tap_rows));
                 D.push_back(def("CV_KR", (d.dims[6] * d.dims[3] + p->tile_unit[2] - 1) / p->tile_unit[2] * p->tile_unit[2]));
             }
@@ -896,6 +911,14 @@ extern "C" int32_t ms_variant_kernel_text(const ms_op *op, const ms_variant_para
     return MS_OK;
 }
 
+// Phase form of the transposed convolution: output row of tile i0's row lr, filter taps that meet a phase.
+static int64_t phase_out_row(const ms_op *op, const ms_variant_params *p, int64_t i0, int64_t lr)
+{
+    const int64_t S = op->d.stride, ph_h = op->OH / S, ph_w = op->OW / S, cls = i0 % (S * S), u = i0 / (S * S) * p->block_m + lr;
+    return (u / (ph_h * ph_w) * op->OH + u / ph_w % ph_h * S + cls / S) * op->OW + u % ph_w * S + cls % S;
+}
+static int64_t phase_tap(int64_t ph, int64_t pad, int64_t S, int64_t t) { return (ph + pad) % S + S * t; }
+
 // Index of the four-level split: ((x0*f1 + x1)*f2 + x2)*f3 + x3.
 static inline int64_t split_index(const int32_t *f, int64_t x0, int64_t x1, int64_t x2, int64_t x3)
 {
@@ -958,6 +981,7 @@ extern "C" int32_t ms_variant_coverage(const ms_op *op, const ms_variant_params 
                                     for (int a = 0; a < um; ++a)
                                         for (int c = 0; c < un; ++c) {
                                             int64_t i = iu * um + a, j = ju * un + c;
+                                            if (p->body == MS_BODY_PHASES) i = phase_out_row(op, p, i0, i - i0 * p->block_m);
                                             if (i >= op->M || j >= op->N) return fail(MS_ERR_INVALID_TRACE, "coverage: index out of range");
                                             if (is_conv2d(op->d.kind)) ++counts[i * (op->N * op->nb) + b * op->N + j]; // groups interleave per pixel
                                             else ++counts[(b * op->M + i) * op->N + j];
@@ -1050,6 +1074,19 @@ extern "C" int32_t ms_variant_reduction_coverage(const ms_op *op, const ms_varia
     }
     const int rf = std::max(1, p->rfactor);
     if (p->tk[0] % rf) return fail(MS_ERR_INVALID_TRACE, "reduction coverage: rfactor does not divide k0");
+    if (p->body == MS_BODY_PHASES) {
+        // every output phase walks its own taps; together they are the filter
+        const ms_op_desc &d = op->d;
+        const int64_t S = d.stride, cin = d.dims[3], tw = d.dims[6] / S, steps = p->tk[0] / (S * S), bk = p->block_k;
+        for (int64_t cls = 0; cls < S * S; ++cls)
+            for (int64_t k = 0; k < steps * bk; ++k) {
+                const int64_t t = k / cin, kh = phase_tap(cls / S, op->pad_h, S, t / tw), kw = phase_tap(cls % S, d.pad, S, t % tw);
+                const int64_t at = (kh * d.dims[6] + kw) * cin + k % cin;
+                if (at < 0 || at >= len) return fail(MS_ERR_INVALID_TRACE, "reduction coverage: index out of range");
+                ++counts[at];
+            }
+        return MS_OK;
+    }
     const int64_t run = p->tk[0] / rf; // k0 steps of one workgroup
     for (int64_t s = 0; s < rf; ++s)
         for (int64_t q0 = s * run; q0 < (s + 1) * run; ++q0)

@@ -175,7 +175,7 @@ extern "C" int32_t ms_variant_features(const ms_op *op, const ms_variant_params 
 {
     if (!op || !p || !n_out) return fail(MS_ERR_BAD_ARG, "ms_variant_features: NULL argument");
     ms_variant_params of_body = *p;
-    if (p->body != MS_BODY_NEST) { // decisions that such a kernel does not read are no features of it
+    if (!follows_decisions(p)) { // decisions that such a kernel does not read are no features of it
         of_body.cache_read = of_body.cache_write = of_body.unroll = of_body.lds_pad = of_body.reorder = of_body.compute_at = 0;
         if (p->body == MS_BODY_IMAGE_ROWS) {
             memset(of_body.ti, 0, sizeof of_body.ti);

@@ -294,7 +294,8 @@ def test_transposed_conv_exact(stride, pad, k, H, W_):
                                                          (2, 2, 6, 2, 8, 4, 0x4FF), (3, 0, 3, 1, 8, 6, 0xFF)])
 def test_transposed_conv_phases_exact(stride, pad, k, N, H, W_, flags):
     """Traces whose tiles keep to one phase of the output grid and whose k steps keep to one tap: the kernel walks that
-    phase's taps only.  Integer-valued inputs, 2 instances: bit-equal fp32 outputs in every staging mode drawn."""
+    phase's taps only, and traces beside them that do not qualify walk all taps.  Integer-valued inputs, 2 instances:
+    bit-equal fp32 outputs in every staging mode drawn."""
     Cin, Cout = 64, 32
     g = I.rng(75)
     X = I.small_ints(g, (N, H, W_, Cin), -2, 2, "f16")
@@ -304,12 +305,19 @@ def test_transposed_conv_phases_exact(stride, pad, k, N, H, W_, flags):
     assert ref.shape[1:3] == (H * stride, W_ * stride)
     op = B.conv2d_transposed_op(N, H, W_, Cin, Cout, k, k, stride=stride, pad=pad, out_dtype="f32")
     space = op.space(flags)
-    modes = {}
+    modes, plain = {}, 0
     for idx in range(3000):
         t = B.trace_sample_valid(op, space, 76, idx)
         p = B.trace_validate(op, space, t)
         if (N * H * W_) % p.block_m or Cin % p.block_k or p.tk[0] % (stride * stride * p.rfactor) or p.block_m < 32:
+            if plain == 2 or p.block_m < 32:
+                continue
+            plain += 1
+            assert "-DCV_PHASES=0" in B.variant_kernel_text(op, p)
+            got = run_variant(op, space, t, [X, Wt, bias], "f32", ref.shape, instances=2)
+            assert got is None or (np.array_equal(got[0], ref) and np.array_equal(got[1], ref)), "trace %d" % idx
             continue
+        assert "-DCV_PHASES=1" in B.variant_kernel_text(op, p)
         mode = (p.cache_read, p.cache_write, p.rfactor > 1)
         if mode in modes:
             continue
@@ -319,7 +327,7 @@ def test_transposed_conv_phases_exact(stride, pad, k, N, H, W_, flags):
         if got is None:
             continue
         assert np.array_equal(got[0], ref) and np.array_equal(got[1], ref), "trace %d" % idx
-    assert len({m[0] for m in modes}) >= 3 and (flags == 0xFF or any(m[2] for m in modes)), modes
+    assert plain == 2 and len({m[0] for m in modes}) >= 3 and (flags == 0xFF or any(m[2] for m in modes)), modes
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])

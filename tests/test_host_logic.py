@@ -672,6 +672,27 @@ def test_image_rows_stage_the_columns_of_a_tile_not_whole_rows(mk, elements):
     assert p.lds_bytes <= max(weights + 2 * elements, p.waves * 32 * (p.block_n * 2 + 16))
 
 
+@pytest.mark.parametrize("N,H,W_,Cin,k,stride,pad", [(2, 8, 8, 64, 4, 2, 1), (2, 8, 4, 64, 4, 4, 0), (2, 8, 4, 64, 6, 2, 2), (1, 8, 6, 64, 3, 3, 0)])
+def test_phases_cover_the_output_and_the_filter_once(N, H, W_, Cin, k, stride, pad):
+    """Transposed convolution: the kernel text says which traces walk the taps of one output phase; the row order of those
+    is a permutation of the pixels and their taps of all phases together are the filter."""
+    op = B.conv2d_transposed_op(N, H, W_, Cin, 32, k, k, stride=stride, pad=pad)
+    sp = op.space(B.SPACE_DEFAULT | B.SPACE_RFACTOR)
+    seen = {}
+    for idx in range(300):
+        t = B.trace_sample_valid(op, sp, 37, idx)
+        p = B.trace_validate(op, sp, t)
+        qualifies = (N * H * W_) % p.block_m == 0 and Cin % p.block_k == 0 and p.tk[0] % (stride * stride * p.rfactor) == 0 and p.cache_read <= 4
+        assert (p.body == B.BODY_PHASES) == qualifies and p.body in (B.BODY_NEST, B.BODY_PHASES)
+        assert ("-DCV_PHASES=%d" % qualifies) in B.variant_kernel_text(op, p).splitlines()
+        seen[qualifies] = seen.get(qualifies, 0) + 1
+        if seen[qualifies] > 12:
+            continue
+        for cov in (B.variant_coverage(op, p, N * H * W_ * stride * stride * 32), B.variant_reduction_coverage(op, p)):
+            assert cov.min() == 1 and cov.max() == 1, t.decisions()
+    assert seen.get(True, 0) > 3 and seen.get(False, 0) > 3, seen
+
+
 def test_few_long_rows_keep_their_wide_lane_groups():
     """Softmax without staging: a few long rows keep a lane group of a wavefront or more per row; many rows, short rows and
     groups that walk a row or several rows in turn go to the row kernel, as do groups narrower than a line."""
