@@ -504,7 +504,8 @@ int32_t ms_jit_stats(int64_t *compiled, int64_t *from_disk, int64_t *from_memory
 
 /* Enqueue one execution over `instances` instances on `stream`.  inputs /
  * outputs: host arrays of device pointers (see ms_op_desc for the order; one
- * output).  workspace: device pointer, 16-byte aligned, of at least instances x
+ * output).  16-byte aligned pointers are always enough; the kernels of MS_BODY_ROW_VECTORS, MS_BODY_STRIPS and
+ * MS_BODY_IMAGE_ROWS need tensors aligned to their elements only (the bias to 16 bytes).  workspace: device pointer, 16-byte aligned, of at least instances x
  * workspace_bytes (ms_variant_info), owned by the caller and not shared with a
  * launch that may run at the same time; NULL if that is 0.  Its contents need no
  * initialisation and are undefined afterwards.  Asynchronous (a variant with

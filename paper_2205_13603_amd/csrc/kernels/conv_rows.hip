@@ -49,7 +49,7 @@ constexpr int LDS_B = PATCH_B + WT_B > STG_B ? PATCH_B + WT_B : STG_B;
 constexpr int cr_gcd(int a, int b) { return b ? cr_gcd(b, a % b) : a; }
 constexpr int AL = cr_gcd(16, cr_gcd(ORG, CV_STRIDE * CV_CIN * 2)); // alignment of a fragment in its row
 
-// inputs are aligned to their elements only: 16 bytes at any address
+// X, W and Y are aligned to their elements only: 16 bytes at any address
 struct __attribute__((packed, aligned(2))) raw16_t {
     u4_t v;
 };
@@ -232,7 +232,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
         for (int i = 0; i < 32 * OCB / 64; ++i) {
             const int idx = i * 64 + lane, r = idx / OCB, c = idx % OCB;
             const u4_t v = *reinterpret_cast<const u4_t *>(stg + r * SROW + c * 16);
-            if (pw + r < p_end) *reinterpret_cast<u4_t *>(Y + (long)(pw + r) * DIM_N + c * OV) = v;
+            if (pw + r < p_end) reinterpret_cast<raw16_t *>(Y + (long)(pw + r) * DIM_N + c * OV)->v = v;
         }
         __builtin_amdgcn_wave_barrier();
     }

@@ -35,6 +35,11 @@ constexpr int RQ = (RNV + RL - 1) / RL;                         // vectors per l
 constexpr int RWG = ROW_WAVES * (64 / RL);                      // rows per workgroup
 static_assert(RD_LEN % RV == 0 && 64 % RL == 0, "rows of whole vectors on whole lane groups");
 
+// tensors are aligned to their elements only: the nests that this kernel stands in for may read single elements
+template <typename T> struct __attribute__((packed, aligned(sizeof(T)))) row_vec_t {
+    T v[RV];
+};
+
 template <bool IS_MAX> __device__ __forceinline__ float row_combine(float v)
 {
 #pragma unroll
@@ -50,8 +55,8 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ unused1_, const 
 {
     (void)unused1_;
     (void)unused2_;
-    typedef vec_t<in_t, RV> rin_t;
-    typedef vec_t<out_t, RV> rout_t;
+    typedef row_vec_t<in_t> rin_t;
+    typedef row_vec_t<out_t> rout_t;
     const int z = blockIdx.z * gridDim.y + blockIdx.y; // instance
     const long row = (long)blockIdx.x * RWG + threadIdx.x / RL;
     if (z >= instances || row >= RD_ROWS) return; // the lanes of a row leave together

@@ -63,3 +63,24 @@ def run_variant_distinct(op, space, trace, per_instance_inputs, out_dtype, out_s
     R = len(per_instance_inputs)
     dev = [devmem.to_device(np.stack([per_instance_inputs[r][k] for r in range(R)])) for k in range(len(per_instance_inputs[0]))]
     return _launch_checked(v, dev, out_shape, out_dtype, R)
+
+
+def run_variant_offset(op, space, trace, inputs, out_dtype, out_shape, offsets):
+    """Like run_variant for one instance, with every tensor offsets[i] elements behind a 16-byte boundary (the last entry is
+    the output's); elements around the output must stay as they were."""
+    v = B.Variant(op, space, trace)
+    if not devmem.gpu_available():
+        return _precompiled()
+    dev = []
+    for a, off in zip(inputs, offsets):
+        flat = np.ascontiguousarray(a).reshape(-1)
+        dev.append(devmem.to_device(np.concatenate([np.zeros(off, flat.dtype), flat])))
+    n, off = int(np.prod(out_shape)), offsets[-1]
+    out = devmem.empty_output((n + off + 16,), out_dtype, poison=True)
+    before = devmem.to_host(out, out_dtype)
+    v.launch([d.data_ptr() + o * a.dtype.itemsize for d, o, a in zip(dev, offsets, inputs)], out.data_ptr() + off * out.element_size(),
+             stream=devmem.current_stream())
+    got = devmem.to_host(out, out_dtype).reshape(-1)
+    before = before.reshape(-1)
+    assert np.array_equal(got[:off], before[:off], equal_nan=True) and np.array_equal(got[off + n:], before[off + n:], equal_nan=True)
+    return got[off:off + n].reshape(out_shape)

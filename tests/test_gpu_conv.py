@@ -4,7 +4,7 @@ import pytest
 
 from oracle import compare, oracle as O
 from paper_2205_13603_amd import binding as B, inputs as I
-from gpu_util import run_variant, run_variant_distinct
+from gpu_util import run_variant, run_variant_distinct, run_variant_offset
 from test_gpu_gemm_mfma import traces_covering_intrinsics, F16_INTRINS
 
 pytestmark = pytest.mark.gpu
@@ -561,6 +561,20 @@ def test_first_layer_image_rows_exact(D, H, W_, Cin, Cout, k, stride, pad, dtype
     if got is not None:
         for r in range(2):
             assert np.array_equal(got[r], refs[r]), "instance %d" % r
+
+
+def test_first_layer_tensors_aligned_to_their_elements():
+    """Images, weights and outputs that start one element behind a 16-byte boundary: the im2col nest of such a layer reads
+    single elements and writes four at a time."""
+    g = I.rng(103)
+    X, Wt = I.small_ints(g, (1, 16, 24, 3), -2, 2, "f16"), I.small_ints(g, (3, 3, 3, 32), -2, 2, "f16")
+    bias = g.integers(-3, 4, size=32).astype(np.float32)
+    op = B.conv2d_op(1, 16, 24, 3, 32, 3, 3, stride=2, pad=1)
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 104, n) for n in range(50)) if B.trace_validate(op, space, t).body == B.BODY_IMAGE_ROWS)
+    got = run_variant_offset(op, space, t, [X, Wt, bias], "f16", (1, 8, 12, 32), [1, 1, 0, 1])
+    if got is not None:
+        assert np.array_equal(got, O.conv2d_nhwc(X, Wt, bias=bias, relu=True, stride=2, pad=1))
 
 
 @pytest.mark.parametrize("L_,Cin,Cout,k,stride,pad", [(1056, 4, 64, 7, 1, 3), (4096, 1, 32, 7, 2, 3), (2080, 2, 64, 3, 1, 1)])

@@ -6,7 +6,7 @@ import pytest
 
 from oracle import compare, oracle as O
 from paper_2205_13603_amd import binding as B, inputs as I
-from gpu_util import run_variant
+from gpu_util import run_variant, run_variant_offset
 
 pytestmark = pytest.mark.gpu
 
@@ -107,6 +107,20 @@ def test_softmax_whole_vector_rows(cols, dtype, out):
             continue
         compare.assert_float_close(got[0], ref, compare.RTOL_F32 if out == dtype == "f32" else compare.RTOL_HALF if out != "f32" else 1e-5, "softmax %d" % cols)
         assert np.array_equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_softmax_rows_aligned_to_their_elements(dtype):
+    """Whole-vector rows of tensors that start one element behind a 16-byte boundary: the nests that this kernel stands in
+    for read single elements."""
+    X = I.normal(I.rng(56), (1, 24, 136), 2.0, dtype)
+    op = B.softmax_op(1, 24, 136, dtype)
+    space = op.space()
+    t = B.make_trace(space, [[3, 1, 8, 1], [17, 1, 8, 1], [0]])
+    assert B.trace_validate(op, space, t).body == B.BODY_ROW_VECTORS
+    got = run_variant_offset(op, space, t, [X], dtype, X.shape, [1, 1])
+    if got is not None:
+        compare.assert_float_close(got, O.softmax(X), compare.RTOL_F32 if dtype == "f32" else compare.RTOL_HALF, "softmax %s" % dtype)
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
