@@ -563,6 +563,50 @@ def test_first_layer_image_rows_exact(D, H, W_, Cin, Cout, k, stride, pad, dtype
             assert np.array_equal(got[r], refs[r]), "instance %d" % r
 
 
+@pytest.mark.parametrize("k,stride,pad,D,H,W_,Cout", [(7, 2, 3, 6, 16, 20, 32), (3, 1, 1, 4, 8, 16, 32), (5, 2, 2, 4, 16, 16, 48)])
+def test_conv3d_padded_reduction_beside_the_image_rows(k, stride, pad, D, H, W_, Cout):
+    """3-channel 3-D layers that the image-row kernel does not take (rows of broken vectors, odd pixel steps, columns of 48):
+    the im2col loop with a reduction that is padded to the intrinsic's k.  Batch 2, integer-valued inputs -> exact."""
+    g = I.rng(105)
+    X = I.small_ints(g, (2, D, H, W_, 3), -2, 2, "f16")
+    Wt = I.small_ints(g, (k, k, k, 3, Cout), -2, 2, "f16")
+    bias = g.integers(-3, 4, size=Cout).astype(np.float32)
+    ref = O.conv3d_ndhwc(X, Wt, bias=bias, relu=True, stride=stride, pad=pad)
+    op = B.conv3d_op(2, D, H, W_, 3, Cout, k, stride=stride, pad=pad, out_dtype="f32")
+    space = op.space()
+    for n in range(4):
+        t = B.trace_sample_valid(op, space, 106, n)
+        p = B.trace_validate(op, space, t)
+        assert p.body == B.BODY_NEST and (k ** 3 * 3) % p.tile_unit[2]
+        got = run_variant(op, space, t, [X, Wt, bias], "f32", ref.shape, instances=2)
+        assert got is None or (np.array_equal(got[0], ref) and np.array_equal(got[1], ref)), "trace %d" % n
+
+
+@pytest.mark.parametrize("Cin,k,stride,pad,H,W_,Cout", [(3, 7, 2, 3, 32, 32, 48), (2, 5, 2, 2, 32, 18, 32), (4, 7, 2, 3, 32, 33, 32)])
+def test_filter_rows_beside_the_image_rows(Cin, k, stride, pad, H, W_, Cout):
+    """Filter-row layers of 2 to 4 channels that the image-row kernel does not take: im2col staging and the resident patch
+    whose weights are staged per step.  Batch 2, integer-valued inputs -> exact."""
+    g = I.rng(107)
+    X = I.small_ints(g, (2, H, W_, Cin), -2, 2, "f16")
+    Wt = I.small_ints(g, (k, k, Cin, Cout), -2, 2, "f16")
+    bias = g.integers(-3, 4, size=Cout).astype(np.float32)
+    ref = O.conv2d_nhwc(X, Wt, bias=bias, relu=True, stride=stride, pad=pad)
+    op = B.conv2d_op(2, H, W_, Cin, Cout, k, k, stride=stride, pad=pad, out_dtype="f32")
+    space = op.space(B.SPACE_DEFAULT | B.SPACE_TAP_ROWS)
+    want, idx = {0: 2, 1: 3}, 0
+    while any(want.values()) and idx < 800:
+        t = B.trace_sample_valid(op, space, 108, idx)
+        idx += 1
+        p = B.trace_validate(op, space, t)
+        if not want.get(p.compute_at):
+            continue
+        want[p.compute_at] -= 1
+        assert p.body == B.BODY_NEST and p.tap_rows == 1
+        got = run_variant(op, space, t, [X, Wt, bias], "f32", ref.shape, instances=2)
+        assert got is None or (np.array_equal(got[0], ref) and np.array_equal(got[1], ref)), "trace %d" % idx
+    assert not any(want.values()), want
+
+
 def test_first_layer_tensors_aligned_to_their_elements():
     """Images, weights and outputs that start one element behind a 16-byte boundary: the im2col nest of such a layer reads
     single elements and writes four at a time."""

@@ -91,7 +91,7 @@ def test_groups_wider_than_a_wavefront_and_exact_cases():
 @pytest.mark.parametrize("cols", [8, 24, 136, 1000, 1896, 4096])
 def test_softmax_whole_vector_rows(cols, dtype, out):
     """Rows of whole 16-byte vectors under narrow lane groups: one lane group of a wavefront holds the row, the last
-    vectors masked.  Row counts that no workgroup's rows divide, elements at -inf, a maximum in the last element."""
+    vectors masked.  Elements at -inf, a maximum in the last element."""
     g = I.rng(53)
     X = I.normal(g, (1, 24, cols), 2.0, dtype)
     X[0, 3, ::2] = -np.inf if dtype != "bf16" else X[0, 3, 1]
@@ -102,11 +102,60 @@ def test_softmax_whole_vector_rows(cols, dtype, out):
     for vals in ([[3, 1, 8, 1], [cols // 8, 1, 8, 1], [0]], [[1, 3, 8, 1], [1, cols // 8, 8, 1], [1]]):
         if vals[2] == [1] and cols > 8 * 64:
             continue
-        got = run_variant(op, space, B.make_trace(space, vals), [X], out, ref.shape, instances=2)
+        t = B.make_trace(space, vals)
+        assert "-DROW_VEC=" in B.variant_kernel_text(op, B.trace_validate(op, space, t))
+        got = run_variant(op, space, t, [X], out, ref.shape, instances=2)
         if got is None:
             continue
         compare.assert_float_close(got[0], ref, compare.RTOL_F32 if out == dtype == "f32" else compare.RTOL_HALF if out != "f32" else 1e-5, "softmax %d" % cols)
         assert np.array_equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("rows,i,cols,k", [(27, [27, 1, 1, 1], 1088, [17, 1, 64, 1]), (72, [9, 1, 8, 1], 24, [3, 1, 8, 1])])
+def test_softmax_whole_vector_rows_that_no_workgroup_divides(rows, i, cols, k):
+    """The last workgroup masks rows (4 rows of 64 lanes, 32 of 8 lanes).  A row of -inf, one with +inf and one with NaN are
+    NaN throughout and touch no other row, as in the oracle."""
+    X = I.normal(I.rng(57), (1, rows, cols), 2.0, "f32")
+    X[0, 1] = -np.inf
+    X[0, rows - 2, 3] = np.inf
+    X[0, rows - 4, cols - 1] = np.nan
+    op = B.softmax_op(1, rows, cols)
+    space = op.space()
+    t = B.make_trace(space, [i, k, [0]])
+    p = B.trace_validate(op, space, t)
+    assert p.body == B.BODY_ROW_VECTORS and rows % p.block_m
+    got = run_variant(op, space, t, [X], "f32", X.shape, instances=2)
+    if got is None:
+        return
+    bad = [1, rows - 2, rows - 4]
+    for r in range(2):
+        assert np.all(np.isnan(got[r][0, bad]))
+        compare.assert_float_close(np.delete(got[r], bad, 1), O.softmax(np.delete(X, bad, 1)), compare.RTOL_F32, "softmax masked rows")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("rows,cols,i,k,cache_read", [
+    (64, 250, [2, 1, 32, 1], [25, 5, 2, 1], 0), (64, 250, [1, 2, 32, 1], [5, 25, 2, 1], 0),       # not whole vectors
+    (16, 6144, [4, 2, 2, 1], [3, 4, 128, 4], 0), (16, 6144, [8, 1, 1, 2], [3, 8, 256, 1], 0),    # rows beyond 4096
+    (16, 6144, [4, 1, 4, 1], [6, 4, 64, 4], 0), (8, 6144, [1, 1, 8, 1], [96, 4, 8, 2], 0),
+    (16, 4096, [16, 1, 1, 1], [1, 2, 512, 4], 0), (16, 2048, [4, 1, 4, 1], [1, 8, 64, 4], 0),    # few long rows
+    (16, 768, [8, 2, 1, 1], [2, 3, 64, 2], 1), (16, 768, [2, 2, 2, 2], [1, 3, 256, 1], 1)])      # staged in registers
+def test_softmax_lane_groups_of_the_trace(rows, cols, i, k, cache_read, dtype):
+    """Traces that keep their own lane groups: rows read once per pass that are no whole vectors, beyond 4096 elements or
+    few and long, rows staged in registers by full lines; groups of 2 to 512 lanes."""
+    X = I.normal(I.rng(58), (1, rows, cols), 2.0, dtype)
+    X[0, 2, 1::2] = -np.inf
+    X[0, 3, cols - 1] = 9.0
+    op = B.softmax_op(1, rows, cols, dtype)
+    space = op.space()
+    t = B.make_trace(space, [i, k, [cache_read]])
+    p = B.trace_validate(op, space, t)
+    assert p.body == B.BODY_NEST and "-DCACHE_READ=%d" % cache_read in B.variant_kernel_text(op, p)
+    got = run_variant(op, space, t, [X], dtype, X.shape, instances=2)
+    if got is None:
+        return
+    compare.assert_float_close(got[0], O.softmax(X), compare.RTOL_F32 if dtype == "f32" else compare.RTOL_HALF, "softmax %d x %d" % (rows, cols))
+    assert np.array_equal(got[0], got[1])
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
