@@ -436,7 +436,8 @@ typedef struct ms_variant_params {
     int32_t rfactor;        /* workgroups that share the reduction of one output tile (1 = no workspace) */
     int32_t body;           /* ms_body */
     int32_t body_tile;      /* as ms_body says, 0 for the nest */
-    int32_t reserved;
+    int32_t body_tile_many; /* MS_BODY_IMAGE_ROWS: tile of launches whose instances fill the chip (ms_variant_launch_shape says
+                               which), 0 = body_tile; the launch fields above are those of one instance */
     uint64_t key;           /* hash of everything that selects the kernel */
 } ms_variant_params;
 
@@ -474,6 +475,10 @@ void ms_variant_destroy(ms_variant *v);
 /* params and workspace_bytes may be NULL.  *workspace_bytes = bytes of workspace ONE instance needs (0 unless
  * rfactor > 1: rfactor x batch x M x N accumulator values); a launch over R instances needs R times as much. */
 int32_t ms_variant_info(const ms_variant *v, ms_variant_params *params, size_t *workspace_bytes);
+/* What a launch over `instances` instances runs: the body's tile, workgroups per instance, bytes of LDS of a workgroup.  They
+ * are the fields of ms_variant_params unless the variant has a kernel of its own for many instances (body_tile_many).  Any
+ * pointer may be NULL.  BAD_ARG if instances < 1. */
+int32_t ms_variant_launch_shape(const ms_variant *v, int32_t instances, int32_t *body_tile, int32_t *workgroups, int32_t *lds_bytes);
 /* What materialising a variant compiles (Section 4, building a candidate): the kernel template's file name, then the
  * -D options that specialise it, one per line.  Two parameter sets that give the same text are the same kernel and
  * have the same params.key.  Writes at most cap bytes including the NUL; *needed (may be NULL) = size needed. */

@@ -90,7 +90,7 @@ class ms_variant_params(C.Structure):
                 ("waves", C.c_int32), ("acc_per_thread", C.c_int32), ("lds_bytes", C.c_int32),
                 ("cache_read", C.c_int32), ("vec", C.c_int32), ("unroll", C.c_int32), ("unroll_k1", C.c_int32),
                 ("unroll_k2", C.c_int32), ("lds_pad", C.c_int32), ("reorder", C.c_int32), ("vec_b", C.c_int32), ("cache_write", C.c_int32), ("compute_at", C.c_int32), ("tap_rows", C.c_int32), ("rfactor", C.c_int32),
-                ("body", C.c_int32), ("body_tile", C.c_int32), ("reserved", C.c_int32), ("key", C.c_uint64)]
+                ("body", C.c_int32), ("body_tile", C.c_int32), ("body_tile_many", C.c_int32), ("key", C.c_uint64)]
 
     def as_dict(self):
         out = {}
@@ -180,6 +180,7 @@ SYMBOLS = {
     "ms_variant_build": (C.c_int32, [C.c_void_p, _P(ms_space), _P(ms_trace), _P(C.c_void_p)]),
     "ms_variant_destroy": (None, [C.c_void_p]),
     "ms_variant_info": (C.c_int32, [C.c_void_p, _P(ms_variant_params), _P(C.c_size_t)]),
+    "ms_variant_launch_shape": (C.c_int32, [C.c_void_p, C.c_int32, _P(C.c_int32), _P(C.c_int32), _P(C.c_int32)]),
     "ms_variant_kernel_text": (C.c_int32, [C.c_void_p, _P(ms_variant_params), C.c_char_p, C.c_size_t, _P(C.c_size_t)]),
     "ms_variant_resources_get": (C.c_int32, [C.c_void_p, _P(ms_variant_resources)]),
     "ms_prebuild": (C.c_int32, [C.c_void_p, _P(ms_space), _P(ms_trace), C.c_int32, C.c_int32, _P(C.c_int32)]),
@@ -538,6 +539,12 @@ class Variant:
         ws = C.c_size_t()
         _check(lib().ms_variant_info(self.handle, C.byref(p), C.byref(ws)))
         return p
+
+    def launch_shape(self, instances):
+        """(body_tile, workgroups per instance, LDS bytes) of a launch over `instances` instances."""
+        out = [C.c_int32() for _ in range(3)]
+        _check(lib().ms_variant_launch_shape(self.handle, instances, *[C.byref(x) for x in out]))
+        return tuple(x.value for x in out)
 
     def resources(self):
         """Registers, scratch and LDS of the compiled kernel, from its code object's metadata."""

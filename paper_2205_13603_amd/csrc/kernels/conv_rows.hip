@@ -8,13 +8,15 @@
 // consecutive chunks of the whole plane, which need not belong to the same filter row, so that only runs are padded
 // (7 x 3 channels: 22 of 24) and not k steps.
 //
-// A workgroup makes CR_WAVES x CR_TM x 32 consecutive pixels of one output plane for CR_TN x 32 output channels.  Per
-// filter plane it stages the image rows that its pixels meet (where a row is several tiles long, CR_SPAN, only the columns
+// A workgroup makes CR_WAVES x TM x 32 consecutive pixels of one output plane for CR_TN x 32 output channels.  Per
+// filter plane it stages the image rows that its pixels meet (where a row is several tiles long, SPAN, only the columns
 // of those rows) and the plane's weights in LDS, and while it multiplies
 // them the next plane's rows and weights are on their way into registers.  Filter planes outside the input are skipped.
-// A wavefront holds CR_TM x CR_TN accumulator tiles: LDS reads 8 * (TM + TN) clocks per k step on each of four SIMDs
-// against 32 * TM * TN of the matrix cores.  8 x 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2 in fp16: 572 -> 144 us
-// (735 TFLOP/s); 128 x 224 x 224 x 3 -> 64, 7 x 7: 117 -> 75 us (3.3 TB/s).
+// A wavefront holds TM x CR_TN accumulator tiles: LDS reads 8 * (TM + TN) clocks per k step on each of four SIMDs
+// against 32 * TM * TN of the matrix cores.  The code object may hold two kernels: TM for one instance, chosen to spread it over
+// the chip, and a larger one for launches whose instances fill it.
+// Inputs changing from launch to launch, before (im2col loader) and now: 8 x 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2 in
+// fp16: 573 -> 127 us (835 TFLOP/s); 128 x 224 x 224 x 3 -> 64, 7 x 7: 117 -> 72.5 us (3.4 TB/s).
 #include "common.h"
 
 typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
@@ -23,11 +25,9 @@ typedef short tr4_t __attribute__((ext_vector_type(4)));
 typedef float accv_t __attribute__((ext_vector_type(16)));
 typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 
-constexpr int TM = CR_TM, TN = CR_TN, NT = CR_WAVES * 64;
-constexpr int PX = CR_WAVES * TM * 32;                    // output pixels of a workgroup
+constexpr int TN = CR_TN, NT = CR_WAVES * 64;
 constexpr int BN = TN * 32, JB = DIM_N / BN;              // output channels of a workgroup, column blocks
-// CR_SPAN: a workgroup keeps to one output row and stages the columns that its pixels meet, not whole image rows
-constexpr int OHW = CV_OH * CV_OW, TPR = (CV_OW + PX - 1) / PX, TILES = CR_SPAN ? CV_OH * TPR : (OHW + PX - 1) / PX;
+constexpr int OHW = CV_OH * CV_OW;
 constexpr int LEAD = CV_PAD * CV_CIN % 2;                 // runs start at even elements: 4-byte LDS reads
 constexpr int RUN = CV_KW * CV_CIN, CPR = (LEAD + RUN + 7) / 8; // elements of a filter row, its chunks
 constexpr int NCH = CV_KH * CPR, STEPS = (NCH + 1) / 2;   // chunks of a filter plane, matrix-core steps of two chunks
@@ -37,29 +37,37 @@ static_assert(ROW_E % 8 == 0 && CV_STRIDE * CV_CIN % 2 == 0 && DIM_N % BN == 0, 
 // LDS: image rows with their zero columns, then the weights row-major, rows padded by 32 bytes for the transposing reads
 constexpr int LHALO = ((CV_PAD * CV_CIN + LEAD) * 2 + 15) / 16 * 16;
 constexpr int ORG = LHALO - (CV_PAD * CV_CIN + LEAD) * 2; // byte of pixel 0's run in its row
-constexpr int READ_END = ORG + ((CR_SPAN ? PX : CV_OW) - 1) * CV_STRIDE * CV_CIN * 2 + CPR * 16, IMG_END = CR_SPAN ? 0 : LHALO + ROW_E * 2;
-constexpr int PRS = ((READ_END > IMG_END ? READ_END : IMG_END) + 15) / 16 * 16;
-constexpr int P_OUT_ = PX % CV_OW == 0 ? PX / CV_OW : (CV_OW + PX - 2) / CV_OW + 1;
-constexpr int P_OUT = CR_SPAN ? 1 : P_OUT_ < CV_OH ? P_OUT_ : CV_OH; // output rows that a workgroup can touch
-constexpr int PR = (P_OUT - 1) * CV_STRIDE + CV_KH;       // input rows
 constexpr int RMB = BN * 2 + 32;                          // bytes of a weight row
-constexpr int PATCH_B = PR * PRS, WT_B = STEPS * 16 * RMB;
+constexpr int WT_B = STEPS * 16 * RMB;
 constexpr int SROW = BN * (int)sizeof(out_t) + 16, STG_B = CR_WAVES * 32 * SROW; // staged output rows, 32 per wavefront
-constexpr int LDS_B = PATCH_B + WT_B > STG_B ? PATCH_B + WT_B : STG_B;
 constexpr int cr_gcd(int a, int b) { return b ? cr_gcd(b, a % b) : a; }
 constexpr int AL = cr_gcd(16, cr_gcd(ORG, CV_STRIDE * CV_CIN * 2)); // alignment of a fragment in its row
+
+// What depends on the tile: TM 32-pixel tiles per wavefront; SPAN: a workgroup keeps to one output row and stages the columns
+// that its pixels meet, not whole image rows.
+template <int TM, bool SPAN> struct tile_t {
+    static constexpr int PX = CR_WAVES * TM * 32;         // output pixels of a workgroup
+    static constexpr int TPR = (CV_OW + PX - 1) / PX, TILES = SPAN ? CV_OH * TPR : (OHW + PX - 1) / PX;
+    static constexpr int READ_END = ORG + ((SPAN ? PX : CV_OW) - 1) * CV_STRIDE * CV_CIN * 2 + CPR * 16, IMG_END = SPAN ? 0 : LHALO + ROW_E * 2;
+    static constexpr int PRS = ((READ_END > IMG_END ? READ_END : IMG_END) + 15) / 16 * 16;
+    static constexpr int P_OUT_ = PX % CV_OW == 0 ? PX / CV_OW : (CV_OW + PX - 2) / CV_OW + 1;
+    static constexpr int P_OUT = SPAN ? 1 : P_OUT_ < CV_OH ? P_OUT_ : CV_OH; // output rows that a workgroup can touch
+    static constexpr int PR = (P_OUT - 1) * CV_STRIDE + CV_KH; // input rows
+    static constexpr int PATCH_B = PR * PRS;
+    static constexpr int LDS_B = PATCH_B + WT_B > STG_B ? PATCH_B + WT_B : STG_B;
+    static constexpr int SV = SPAN ? PRS / 16 : CPW;      // staged vectors of an image row
+    static constexpr int XI = (PR * SV + NT - 1) / NT;    // staged vectors of the image rows per thread
+};
 
 // X, W and Y are aligned to their elements only: 16 bytes at any address
 struct __attribute__((packed, aligned(2))) raw16_t {
     u4_t v;
 };
-constexpr int SV = CR_SPAN ? PRS / 16 : CPW;              // staged vectors of an image row
-constexpr int XI = (PR * SV + NT - 1) / NT;               // staged vectors of the image rows per thread
 constexpr int WROWS = CV_KH * RUN, WCB = BN / 8;          // weight rows of a filter plane, 16-byte vectors of one
 constexpr int WI = (WROWS * WCB + NT - 1) / NT;
 
 // byte of chunk c relative to a pixel's run; the chunk behind the last one (odd counts) meets zero weights and is masked
-constexpr int koff(int c) { return c < NCH ? c / CPR * PRS + c % CPR * 16 : koff(c - 1); }
+constexpr int koff(int c, int prs) { return c < NCH ? c / CPR * prs + c % CPR * 16 : koff(c - 1, prs); }
 // bits of dword d of chunk c that belong to the run: the others are neighbours, which may be infinite or NaN
 constexpr unsigned kmask(int c, int d)
 {
@@ -80,16 +88,17 @@ __device__ __forceinline__ accv_t mfma(const u4_t &a, const u4_t &b, accv_t c)
 #endif
 }
 
-struct stage_t {
-    u4_t x[XI], w[WI];
+template <class T> struct stage_t {
+    u4_t x[T::XI], w[WI];
 };
 
-__device__ __forceinline__ void stage_fetch(stage_t &st, const in_t *__restrict__ plane, const in_t *__restrict__ wt, int ih_lo, int v_lo, int tid)
+template <int TM, bool SPAN, class T = tile_t<TM, SPAN>>
+__device__ __forceinline__ void stage_fetch(stage_t<T> &st, const in_t *__restrict__ plane, const in_t *__restrict__ wt, int ih_lo, int v_lo, int tid)
 {
 #pragma unroll
-    for (int i = 0; i < XI; ++i) {
-        const int idx = i * NT + tid, row = idx / SV, ih = ih_lo + row, col = (CR_SPAN ? v_lo : 0) + idx % SV;
-        const bool ok = (unsigned)ih < (unsigned)CV_H && row < PR && (!CR_SPAN || (unsigned)col < (unsigned)CPW);
+    for (int i = 0; i < T::XI; ++i) {
+        const int idx = i * NT + tid, row = idx / T::SV, ih = ih_lo + row, col = (SPAN ? v_lo : 0) + idx % T::SV;
+        const bool ok = (unsigned)ih < (unsigned)CV_H && row < T::PR && (!SPAN || (unsigned)col < (unsigned)CPW);
         // vectors outside the image read the plane's first one (always there) and become zero
         const u4_t v = reinterpret_cast<const raw16_t *>(plane + (ok ? ih * ROW_E + col * 8 : 0))->v;
         st.x[i] = ok ? v : u4_t{0, 0, 0, 0};
@@ -101,12 +110,14 @@ __device__ __forceinline__ void stage_fetch(stage_t &st, const in_t *__restrict_
     }
 }
 
-__device__ __forceinline__ void stage_commit(const stage_t &st, char *__restrict__ patch, char *__restrict__ wts, int tid)
+template <int TM, bool SPAN, class T = tile_t<TM, SPAN>>
+__device__ __forceinline__ void stage_commit(const stage_t<T> &st, char *__restrict__ patch, char *__restrict__ wts, int tid)
 {
 #pragma unroll
-    for (int i = 0; i < XI; ++i) {
+    for (int i = 0; i < T::XI; ++i) {
         const int idx = i * NT + tid;
-        if (PR * SV % NT == 0 || idx < PR * SV) *reinterpret_cast<u4_t *>(patch + idx / SV * PRS + (CR_SPAN ? 0 : LHALO) + idx % SV * 16) = st.x[i];
+        if (T::PR * T::SV % NT == 0 || idx < T::PR * T::SV)
+            *reinterpret_cast<u4_t *>(patch + idx / T::SV * T::PRS + (SPAN ? 0 : LHALO) + idx % T::SV * 16) = st.x[i];
     }
 #pragma unroll
     for (int i = 0; i < WI; ++i) {
@@ -116,10 +127,12 @@ __device__ __forceinline__ void stage_commit(const stage_t &st, char *__restrict
     }
 }
 
-extern "C" __global__ void __launch_bounds__(NT, 2)
-ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *__restrict__ bias_, void *__restrict__ y_, int instances)
+template <int TM, bool SPAN>
+__device__ __forceinline__ void image_rows(const void *__restrict__ x_, const void *__restrict__ w_, const void *__restrict__ bias_, void *__restrict__ y_, int instances)
 {
-    __shared__ __attribute__((aligned(16))) char smem[LDS_B];
+    typedef tile_t<TM, SPAN> T;
+    constexpr int PX = T::PX, TPR = T::TPR, TILES = T::TILES, PRS = T::PRS, PATCH_B = T::PATCH_B;
+    __shared__ __attribute__((aligned(16))) char smem[T::LDS_B];
     int wg = blockIdx.x, z = blockIdx.z * gridDim.y + blockIdx.y; // z = instance
     const long total = (long)gridDim.x * gridDim.y * gridDim.z;
     if (total % 8 == 0) { // workgroup order grouped per XCD: tiles that share input rows and planes meet in one L2
@@ -130,9 +143,9 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
     if (z >= instances) return;
     const int jb = wg % JB, od = wg / JB % CV_OD, tile = wg / (JB * CV_OD) % TILES, n = wg / (JB * CV_OD * TILES);
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, lrow = lane % 32, lgrp = lane / 32;
-    const int p0 = CR_SPAN ? tile / TPR * CV_OW + tile % TPR * PX : tile * PX, oh_lo = p0 / CV_OW, ih_lo = oh_lo * CV_STRIDE - CV_PAD_H;
-    const int p_end = CR_SPAN ? (oh_lo + 1) * CV_OW : OHW;        // end of the pixels that a workgroup stores
-    const int v_lo = tile % TPR * (PX * CV_STRIDE * CV_CIN / 8) - LHALO / 16; // CR_SPAN: first staged vector of an image row
+    const int p0 = SPAN ? tile / TPR * CV_OW + tile % TPR * PX : tile * PX, oh_lo = p0 / CV_OW, ih_lo = oh_lo * CV_STRIDE - CV_PAD_H;
+    const int p_end = SPAN ? (oh_lo + 1) * CV_OW : OHW;        // end of the pixels that a workgroup stores
+    const int v_lo = tile % TPR * (PX * CV_STRIDE * CV_CIN / 8) - LHALO / 16; // SPAN: first staged vector of an image row
     const in_t *X = (const in_t *)x_ + (long)z * A_INST + (long)n * CV_D * CV_H * ROW_E;
     const in_t *Wt = (const in_t *)w_ + (long)z * B_INST + jb * BN;
     char *patch = smem, *wts = smem + PATCH_B;
@@ -141,8 +154,8 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
     const int id0 = CV_D > 1 || CV_KD > 1 ? od * CV_STRIDE - CV_PAD : 0;
     const int kd_lo = id0 < 0 ? -id0 : 0, kd_hi = CV_D - id0 < CV_KD ? CV_D - id0 : CV_KD;
 
-    stage_t st;
-    if (kd_lo < kd_hi) stage_fetch(st, X + (long)(id0 + kd_lo) * CV_H * ROW_E, Wt + (long)kd_lo * WROWS * DIM_N, ih_lo, v_lo, tid);
+    stage_t<T> st;
+    if (kd_lo < kd_hi) stage_fetch<TM, SPAN>(st, X + (long)(id0 + kd_lo) * CV_H * ROW_E, Wt + (long)kd_lo * WROWS * DIM_N, ih_lo, v_lo, tid);
     // zero columns of the image rows and padding rows of the weights: written once, no plane overwrites them
     for (int i = tid; i < (PATCH_B + WT_B) / 16; i += NT) *reinterpret_cast<u4_t *>(smem + i * 16) = u4_t{0, 0, 0, 0};
 
@@ -154,7 +167,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
         for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = accv_t{};
         int p = p0 + (wave * TM + tm) * 32 + lrow;
         p = p < p_end ? p : p_end - 1; // pixels behind the last one repeat it and are not stored
-        pix[tm] = CR_SPAN ? ORG + (p - p0) * (CV_STRIDE * CV_CIN * 2)
+        pix[tm] = SPAN ? ORG + (p - p0) * (CV_STRIDE * CV_CIN * 2)
                           : (p / CV_OW - oh_lo) * CV_STRIDE * PRS + ORG + p % CV_OW * (CV_STRIDE * CV_CIN * 2);
     }
     const int li = lane % 16;
@@ -163,9 +176,9 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
 #pragma unroll 1
     for (int kd = kd_lo; kd < kd_hi; ++kd) {
         __syncthreads();
-        stage_commit(st, patch, wts, tid);
+        stage_commit<TM, SPAN>(st, patch, wts, tid);
         __syncthreads();
-        if (kd + 1 < kd_hi) stage_fetch(st, X + (long)(id0 + kd + 1) * CV_H * ROW_E, Wt + (long)(kd + 1) * WROWS * DIM_N, ih_lo, v_lo, tid);
+        if (kd + 1 < kd_hi) stage_fetch<TM, SPAN>(st, X + (long)(id0 + kd + 1) * CV_H * ROW_E, Wt + (long)(kd + 1) * WROWS * DIM_N, ih_lo, v_lo, tid);
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
             u4_t fa[TM], fb[TN];
@@ -183,7 +196,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm) {
                 const unsigned *src = reinterpret_cast<const unsigned *>(
-                    __builtin_assume_aligned(patch + (pix[tm] + lgrp * (koff(2 * s + 1) - koff(2 * s)) + koff(2 * s)), AL));
+                    __builtin_assume_aligned(patch + (pix[tm] + lgrp * (koff(2 * s + 1, PRS) - koff(2 * s, PRS)) + koff(2 * s, PRS)), AL));
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
                     const unsigned m0 = kmask(2 * s, d), m1 = kmask(2 * s + 1, d);
@@ -238,3 +251,18 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
     }
     (void)bias_;
 }
+
+extern "C" __global__ void __launch_bounds__(NT, 2)
+ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *__restrict__ bias_, void *__restrict__ y_, int instances)
+{
+    image_rows<CR_TM, CR_SPAN>(x_, w_, bias_, y_, instances);
+}
+
+#if CR_MANY_TM
+// the larger tile of launches over many instances; which launches take it says image_rows_many() in ms_interp.cpp
+extern "C" __global__ void __launch_bounds__(NT, 2)
+ms_kernel_many(const void *__restrict__ x_, const void *__restrict__ w_, const void *__restrict__ bias_, void *__restrict__ y_, int instances)
+{
+    image_rows<CR_MANY_TM, CR_MANY_SPAN>(x_, w_, bias_, y_, instances);
+}
+#endif

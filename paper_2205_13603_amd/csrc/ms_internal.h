@@ -72,7 +72,10 @@ struct KernelSpec {
     unsigned block[3];
     unsigned grid[3];          // per instance; instances multiply grid[2]
     unsigned lds_dynamic;
+    unsigned many_grid;        // grid[0] of the code object's second kernel, "<entry>_many"; 0 = it has none
 };
+// whether a launch over so many instances takes the second kernel (MS_BODY_IMAGE_ROWS, body_tile_many); its bytes of LDS
+bool image_rows_many(const ms_op *op, const ms_variant_params *p, int64_t instances, int64_t *lds);
 int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec *out);
 
 // JIT (ms_jit.cpp)

@@ -136,6 +136,11 @@ struct ConvRows {
     int64_t lead, cpr, steps; // unused elements before a run, 8-element chunks of a run, k steps of a filter plane
     int64_t groups;      // workgroups of one instance
     int64_t lds;         // bytes of a workgroup
+    int64_t regs;        // registers of a lane: accumulators, fragments, the next filter plane on its way, about 60 others
+    // estimate of a launch: rounds of the workgroups that the chip holds (two per compute unit, one where the LDS is too
+    // large), each a staging round trip of about three tiles' time and the tiles of a wavefront
+    int64_t cost(int64_t instances) const { return (groups * instances + slots() - 1) / slots() * (3 + tm * tn); }
+    int64_t slots() const { return 2 * lds > 160 * 1024 ? 256 : 512; }
 };
 ConvRows conv_rows_tiles(const ms_op *op, int tm)
 {
@@ -161,7 +166,32 @@ ConvRows conv_rows_tiles(const ms_op *op, int tm)
     const int64_t rows = c.tpr ? KH : (std::min(c.px % op->OW ? (op->OW + c.px - 2) / op->OW + 1 : c.px / op->OW, op->OH) - 1) * S + KH;
     c.lds = std::max(rows * ((row + 15) / 16 * 16) + c.steps * 16 * (bn * 2 + 32), waves * 32 * (bn * op->out_size + 16));
     c.groups = c.tiles * (Cout / bn) * op->OD * d.dims[0];
+    const int64_t vectors = (rows * (c.tpr ? (row + 15) / 16 : W * Cin / 8) + c.threads - 1) / c.threads + (KH * KW * Cin * bn / 8 + c.threads - 1) / c.threads;
+    c.regs = tm * c.tn * 16 + (tm + c.tn) * 4 + (op->kd > 1 ? vectors * 4 : 0) + 60;
     return c;
+}
+
+bool conv_rows_fits(const ConvRows &t)
+{
+    return t.tm * t.tn <= 8 && t.groups <= 0x7fffffff && t.lds <= g_limits.max_lds_bytes && t.threads <= g_limits.max_threads &&
+           t.threads / 64 <= g_limits.max_waves && t.tm * t.tn * 16 <= g_limits.max_acc_per_thread &&
+           t.regs <= 256; // two workgroups per compute unit; 16 x 224 x 224 x 4, 7 x 7 x 7 with tm = 4 spills 56 registers: 346 us, with 2 170
+}
+
+// tm of the image-row kernel for launches over many instances, 0 = the one for one instance.  That one is chosen to spread one
+// instance over the chip; where many instances fill it, larger tiles stage less per pixel.  224 x 224 x 3 -> 64, 7 x 7, stride 2
+// x 256: 182, 148, 139 us with tm = 1, 2, 4 (4.2, 5.2, 7.3 for one instance); 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2 x 8:
+// 156, 137, 125 (29.2, 23.7, 27.0).  Of 32 columns tm = 4 gains
+// at most 5 % over 2 and loses up to 14 % on small images.
+int conv_rows_many(const ms_op *op, int tm)
+{
+    int best = tm;
+    auto per_pixel = [](const ConvRows &t) { return (double)(3 + t.tm * t.tn) / (double)(t.tm * t.slots()); };
+    for (int t : {4, 2}) {
+        const ConvRows c = conv_rows_tiles(op, t);
+        if (t > tm && conv_rows_fits(c) && (c.tn > 1 || t <= 2) && per_pixel(c) < per_pixel(conv_rows_tiles(op, best))) best = t;
+    }
+    return best > tm ? best : 0;
 }
 
 // MS_BODY_IMAGE_ROWS: tm of the image-row kernel, 0 = not taken.  Taken for 1 to 4 channels per pixel where the cache-read
@@ -182,12 +212,7 @@ int conv_rows(const ms_op *op, const ms_variant_params *p)
     double cost = 0;
     for (int tm : {4, 2, 1}) {
         const ConvRows t = conv_rows_tiles(op, tm);
-        if (tm * t.tn > 8 || t.groups > 0x7fffffff) continue;
-        if (t.lds > g_limits.max_lds_bytes || t.threads > g_limits.max_threads || t.threads / 64 > g_limits.max_waves ||
-            tm * t.tn * 16 > g_limits.max_acc_per_thread)
-            continue;
-        // a staging round trip costs a wavefront about three tiles' time; two workgroups per compute unit.  One instance of the
-        // 3-D layer above takes 29.6, 23.5, 26.7 us with tm = 1, 2, 4, eight 165, 144, 133: instances are not known here
+        if (!conv_rows_fits(t)) continue;
         const double c = (double)((t.groups + 511) / 512) * (3 + tm * t.tn);
         if (!best || c < cost) {
             best = tm;
@@ -252,6 +277,7 @@ void resolve_body(const ms_op *op, ms_variant_params *p)
     } else if ((p->body_tile = conv_rows(op, p))) {
         const ConvRows c = conv_rows_tiles(op, p->body_tile);
         p->body = MS_BODY_IMAGE_ROWS;
+        p->body_tile_many = conv_rows_many(op, p->body_tile);
         p->grid[0] = (int32_t)c.groups;
         p->grid[1] = p->grid[2] = 1;
         p->block_m = (int32_t)c.px;
@@ -295,6 +321,7 @@ uint64_t hash_params(const ms_op *op, const ms_variant_params *p)
     if (!follows_decisions(p)) { // the operator and the body's own tile are all that such a kernel reads
         add(0xB0D7000000ull + (uint64_t)p->body);
         add((uint64_t)p->body_tile);
+        if (p->body_tile_many) add((uint64_t)p->body_tile_many);
         return h;
     }
     add((uint64_t)p->mfma);
@@ -783,6 +810,7 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
     k.grid[1] = (unsigned)p->grid[1];
     k.grid[2] = (unsigned)p->grid[2];
     k.lds_dynamic = 0;
+    k.many_grid = 0;
     auto &D = k.defines;
     D.push_back(def("IN_DT", dt_code(d.in_dtype)));
     D.push_back(def("OUT_DT", dt_code(d.out_dtype)));
@@ -853,6 +881,12 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             D.push_back(def("CR_TN", cr.tn));
             D.push_back(def("CR_SPAN", cr.tpr ? 1 : 0));
             D.push_back(def("CR_WAVES", p->waves));
+            if (p->body_tile_many) {
+                const ConvRows many = conv_rows_tiles(op, p->body_tile_many);
+                D.push_back(def("CR_MANY_TM", many.tm));
+                D.push_back(def("CR_MANY_SPAN", many.tpr ? 1 : 0));
+                k.many_grid = (unsigned)many.groups;
+            }
         } else if (p->family == MS_FAM_GEMM_MFMA) {
             k.template_name = "gemm_mfma.hip";
             D.push_back(def("MI_M", p->tile_unit[0]));
@@ -893,6 +927,18 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
 }
 
 } // namespace ms
+
+bool ms::image_rows_many(const ms_op *op, const ms_variant_params *p, int64_t instances, int64_t *lds)
+{
+    if (p->body != MS_BODY_IMAGE_ROWS || !p->body_tile_many || instances < 2) return false;
+    const ConvRows few = conv_rows_tiles(op, p->body_tile), many = conv_rows_tiles(op, p->body_tile_many);
+    if (lds) *lds = many.lds;
+    // short reductions (filters below 7 x 7 x 3) are bound by the launch's first loads and last stores: four full rounds, or the
+    // larger tile gains nothing (112 x 112 x 3 -> 64, 3 x 3, stride 2 x 64: 8.3 us with tm = 1, 9.9 with 4; 224 x 224 x 4 -> 64,
+    // 3 x 3 x 64: 118 and 96)
+    if (many.steps * op->kd < 11 && many.groups * instances < 4 * many.slots()) return false;
+    return many.cost(instances) < few.cost(instances);
+}
 
 extern "C" int32_t ms_variant_kernel_text(const ms_op *op, const ms_variant_params *p, char *buf, size_t cap, size_t *needed)
 {
@@ -935,8 +981,8 @@ extern "C" int32_t ms_variant_coverage(const ms_op *op, const ms_variant_params 
     const ms_op_desc &d = op->d;
     if (p->body == MS_BODY_IMAGE_ROWS) {
         const ConvRows c = conv_rows_tiles(op, p->body_tile);
-        const int64_t bn = p->block_n, jbs = op->N / bn, ohw = op->OH * op->OW;
-        for (int64_t wg = 0; wg < p->grid[0]; ++wg) {
+        const int64_t bn = c.tn * 32, jbs = op->N / bn, ohw = op->OH * op->OW;
+        for (int64_t wg = 0; wg < c.groups; ++wg) {
             const int64_t jb = wg % jbs, od = wg / jbs % op->OD, tile = wg / (jbs * op->OD) % c.tiles, n = wg / (jbs * op->OD * c.tiles);
             const int64_t oh = c.tpr ? tile / c.tpr : 0, first = c.tpr ? oh * op->OW + tile % c.tpr * c.px : tile * c.px;
             const int64_t end = c.tpr ? (oh + 1) * op->OW : ohw;

@@ -23,6 +23,7 @@ struct ms_variant {
     hipModule_t mod;
     hipFunction_t fn;
     hipFunction_t fn_reduce; // second kernel of an rfactor launch, else null
+    hipFunction_t fn_many;   // kernel of launches over many instances, else null
     int device;              // device the module is loaded on, -1 = not loaded
     int compute_units;       // of that device
 };
@@ -47,6 +48,7 @@ extern "C" int32_t ms_variant_build(const ms_op *op, const ms_space *space, cons
     v->mod = nullptr;
     v->fn = nullptr;
     v->fn_reduce = nullptr;
+    v->fn_many = nullptr;
     v->device = -1;
     rc = make_kernel_spec(op, &p, &v->spec);
     if (rc == MS_OK) rc = jit_get_code(v->spec, p.key, &v->code);
@@ -77,6 +79,18 @@ extern "C" int32_t ms_variant_info(const ms_variant *v, ms_variant_params *param
     if (!v) return fail(MS_ERR_BAD_ARG, "ms_variant_info: NULL variant");
     if (params) *params = v->p;
     if (workspace_bytes) *workspace_bytes = workspace_per_instance(v);
+    return MS_OK;
+}
+
+extern "C" int32_t ms_variant_launch_shape(const ms_variant *v, int32_t instances, int32_t *body_tile, int32_t *workgroups, int32_t *lds_bytes)
+{
+    if (!v) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_shape: NULL variant");
+    if (instances < 1) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_shape: instances = %d", instances);
+    int64_t lds = v->p.lds_bytes;
+    const bool many = image_rows_many(&v->op, &v->p, instances, &lds);
+    if (body_tile) *body_tile = many ? v->p.body_tile_many : v->p.body_tile;
+    if (workgroups) *workgroups = many ? (int32_t)v->spec.many_grid : v->p.grid[0] * v->p.grid[1] * v->p.grid[2];
+    if (lds_bytes) *lds_bytes = many ? (int32_t)lds : v->p.lds_bytes;
     return MS_OK;
 }
 
@@ -171,12 +185,17 @@ static int32_t ensure_loaded(ms_variant *v)
     HIP_TRY(hipGetDeviceProperties(&prop, dev));
     if (strncmp(prop.gcnArchName, "gfx950", 6) != 0)
         return fail(MS_ERR_UNSUPPORTED, "device %d is %s; kernels are built for gfx950 only", dev, prop.gcnArchName);
-    if ((size_t)v->p.lds_bytes > prop.sharedMemPerBlock)
-        return fail(MS_ERR_HIP, "variant needs %d bytes of LDS, the device offers %zu per workgroup", v->p.lds_bytes, (size_t)prop.sharedMemPerBlock);
+    int64_t lds = v->p.lds_bytes, lds_many = 0;
+    (void)image_rows_many(&v->op, &v->p, 2, &lds_many);
+    lds = std::max(lds, lds_many);
+    if ((size_t)lds > prop.sharedMemPerBlock)
+        return fail(MS_ERR_HIP, "variant needs %lld bytes of LDS, the device offers %zu per workgroup", (long long)lds, (size_t)prop.sharedMemPerBlock);
     HIP_TRY(hipModuleLoadData(&v->mod, v->code->data()));
     HIP_TRY(hipModuleGetFunction(&v->fn, v->mod, v->spec.entry.c_str()));
     v->fn_reduce = nullptr;
     if (v->p.rfactor > 1) HIP_TRY(hipModuleGetFunction(&v->fn_reduce, v->mod, "ms_rfactor_reduce"));
+    v->fn_many = nullptr;
+    if (v->spec.many_grid) HIP_TRY(hipModuleGetFunction(&v->fn_many, v->mod, (v->spec.entry + "_many").c_str()));
     v->device = dev;
     v->compute_units = prop.multiProcessorCount;
     return MS_OK;
@@ -294,7 +313,12 @@ extern "C" int32_t ms_variant_launch(ms_variant *v, const void *const *inputs, v
         gy = 1;
         gzz = 1;
     }
-    HIP_TRY(hipModuleLaunchKernel(v->fn, gx, gy, gzz, v->spec.block[0], 1, 1, v->spec.lds_dynamic, (hipStream_t)stream, args, nullptr));
+    hipFunction_t fn = v->fn;
+    if (v->fn_many && image_rows_many(&v->op, &v->p, instances, nullptr)) {
+        fn = v->fn_many;
+        gx = v->spec.many_grid;
+    }
+    HIP_TRY(hipModuleLaunchKernel(fn, gx, gy, gzz, v->spec.block[0], 1, 1, v->spec.lds_dynamic, (hipStream_t)stream, args, nullptr));
     if (v->p.rfactor > 1) {
         // stream order makes the partial sums visible to the kernel that adds them: 4 outputs per thread
         const uint64_t quads = (uint64_t)instances * (uint64_t)v->op.nb * (uint64_t)v->op.M * (uint64_t)(v->op.N / 4);

@@ -607,6 +607,28 @@ def test_filter_rows_beside_the_image_rows(Cin, k, stride, pad, H, W_, Cout):
     assert not any(want.values()), want
 
 
+@pytest.mark.parametrize("H,W_,Cin,Cout,k,stride,R", [(56, 64, 3, 64, 7, 2, 200), (20, 32, 4, 32, 3, 1, 700), (16, 528, 2, 96, 5, 2, 240)])
+def test_image_rows_over_many_instances_exact(H, W_, Cin, Cout, k, stride, R):
+    """Launches of one instance and of so many that the kernel of the larger tile takes them, three data sets in rotation;
+    integer-valued inputs -> exact."""
+    g = I.rng(109)
+    op = B.conv2d_op(1, H, W_, Cin, Cout, k, k, stride=stride, pad=k // 2, out_dtype="f32")
+    sets = [[I.small_ints(g, (1, H, W_, Cin), -2, 2, "f16"), I.small_ints(g, (k, k, Cin, Cout), -2, 2, "f16"),
+             g.integers(-3, 4, size=Cout).astype(np.float32)] for _ in range(3)]
+    refs = [O.conv2d_nhwc(x, w, bias=b, relu=True, stride=stride, pad=k // 2) for x, w, b in sets]
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 110, n) for n in range(100)) if B.trace_validate(op, space, t).body == B.BODY_IMAGE_ROWS)
+    v = B.Variant(op, space, t)
+    assert v.launch_shape(1)[0] < v.launch_shape(R)[0] == v.params().body_tile_many
+    for n in (1, R):
+        got = run_variant_distinct(op, space, t, [sets[r % 3] for r in range(n)], "f32", refs[0].shape)
+        if got is None:
+            continue
+        got = got.reshape((n,) + refs[0].shape)
+        for r in range(n):
+            assert np.array_equal(got[r], refs[r % 3]), "instance %d of %d" % (r, n)
+
+
 def test_first_layer_tensors_aligned_to_their_elements():
     """Images, weights and outputs that start one element behind a 16-byte boundary: the im2col nest of such a layer reads
     single elements and writes four at a time."""

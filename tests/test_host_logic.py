@@ -729,6 +729,37 @@ def test_small_depthwise_launches_keep_a_compact_nest():
     assert body(1, c=(9, 1, 16, 1)) == B.BODY_STRIPS  # 16 of 64 lanes
 
 
+@pytest.mark.parametrize("mk,flags,one,many", [
+    (lambda: B.conv2d_op(1, 224, 224, 3, 64, 7, 7, stride=2, pad=3), B.SPACE_DEFAULT | B.SPACE_TAP_ROWS, 1, 4),
+    (lambda: B.conv3d_op(1, 16, 224, 224, 3, 64, 7, stride=2, pad=3), B.SPACE_DEFAULT, 2, 4),
+    (lambda: B.conv3d_op(1, 16, 224, 224, 4, 64, 7, stride=2, pad=3), B.SPACE_DEFAULT, 2, 0),   # the next plane beside 4 x 2 tiles spills
+    (lambda: B.conv3d_op(8, 16, 224, 224, 4, 64, 7, stride=2, pad=3), B.SPACE_DEFAULT, 2, 0),
+    (lambda: B.conv2d_op(1, 64, 64, 3, 32, 3, 3, stride=2, pad=1), B.SPACE_DEFAULT, 1, 2),
+    (lambda: B.conv2d_op(1, 96, 96, 3, 96, 7, 7, stride=2, pad=3), B.SPACE_DEFAULT, 1, 2),      # 4 x 3 tiles are too many
+    (lambda: B.conv2d_op(128, 224, 224, 3, 64, 7, 7, stride=2, pad=3), B.SPACE_DEFAULT, 4, 0)])
+def test_image_rows_take_a_larger_tile_where_instances_fill_the_chip(mk, flags, one, many):
+    """The tile is chosen for one instance; a second kernel of the same code object serves launches over many.  Coverage of
+    both."""
+    op = mk()
+    sp = op.space(flags)
+    t = next(t for t in (B.trace_sample_valid(op, sp, 38, n) for n in range(100)) if B.trace_validate(op, sp, t).body == B.BODY_IMAGE_ROWS)
+    v = B.Variant(op, sp, t)
+    p = v.params()
+    assert (p.body_tile, p.body_tile_many) == (one, many) and v.resources().scratch_bytes == 0
+    assert v.launch_shape(1) == (one, p.grid[0], p.lds_bytes)
+    tiles = [v.launch_shape(n)[0] for n in (1, 2, 3, 4, 8, 16, 64, 256, 4096)]
+    assert set(tiles) <= {one, many or one} and tiles[-1] == (many or one)
+    text = B.variant_kernel_text(op, p)
+    assert ("-DCR_MANY_TM=%d" % many in text) == bool(many)
+    if op.tensor_bytes(-1) < 1 << 24:
+        for tile in {one, many or one}:
+            p.body_tile = tile
+            cov = B.variant_coverage(op, p, op.tensor_bytes(-1) // 2)
+            assert cov.min() == 1 and cov.max() == 1
+    with pytest.raises(B.MsError):
+        v.launch_shape(0)
+
+
 def test_a_search_measures_a_body_once():
     """Every trace of this operator resolves to the strip kernel: one measurement, the rest are duplicates."""
     op = B.dwconv2d_op(32, 57, 57, 48, stride=2)
