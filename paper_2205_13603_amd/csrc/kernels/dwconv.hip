@@ -23,7 +23,8 @@
 // What bounds the general kernel there is the L1: a 1 x 29 patch of one thread reads 6 values per output, lane groups of 16
 // channels read half lines, and its 188 registers leave one workgroup per compute unit.  The halo costs no branch: a
 // buffer load beyond the image's bytes returns zero, and pixels outside the image ask for such an offset.
-// 57 x 57 x 144, stride 2, batch 128: 75.1 -> 50.4 us (6.0 TB/s); of one channel 4 x 4 was the fastest (2 x 4: 53.1,
+// 57 x 57 x 144, stride 2, batch 128: 83.2 -> 60.7 us with inputs that change from launch to launch, 75.1 -> 50.4 with inputs
+// that stay; with those, of one channel 4 x 4 was the fastest (2 x 4: 53.1,
 // 6 x 6: 51.4, 8 x 8: 64.3), 2 and 4 channels per thread read more lines per output (2 x 4 of 2: 55.6, of 4: 49.8 but
 // 327 against 300 us on 112 x 112 x 32, stride 1).
 constexpr int SP_H = (STRIP - 1) * CV_STRIDE + CV_KH, SP_W = (STRIP - 1) * CV_STRIDE + CV_KW; // input patch of a strip

@@ -108,7 +108,7 @@
 // meets only the taps with (oh + pad - kh) mod S = 0 (same for the columns), one in S^2 of them; the plain row order mixes
 // the S^2 phases in every tile, so each tile walks all KH*KW taps and multiplies zeros for the rest.  Here the rows are
 // ordered so that a tile lies in one phase, and the k loop covers that phase's (KH/S)*(KW/S) taps only: S^2 times fewer k
-// steps and activation loads, the same products.  16 x 16 x 256 -> 128, 4 x 4, stride 2, batch 64 in bf16: 77.8 -> 25.9 us.
+// steps and activation loads, the same products.  16 x 16 x 256 -> 128, 4 x 4, stride 2, batch 64 in bf16: 77.5 -> 25.8 us.
 #ifndef CV_PHASES
 #define CV_PHASES 0
 #endif

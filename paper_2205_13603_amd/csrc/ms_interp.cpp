@@ -181,8 +181,7 @@ bool conv_rows_fits(const ConvRows &t)
 // tm of the image-row kernel for launches over many instances, 0 = the one for one instance.  That one is chosen to spread one
 // instance over the chip; where many instances fill it, larger tiles stage less per pixel.  224 x 224 x 3 -> 64, 7 x 7, stride 2
 // x 256: 182, 148, 139 us with tm = 1, 2, 4 (4.2, 5.2, 7.3 for one instance); 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2 x 8:
-// 156, 137, 125 (29.2, 23.7, 27.0).  Of 32 columns tm = 4 gains
-// at most 5 % over 2 and loses up to 14 % on small images.
+// 156, 137, 125 (29.2, 23.7, 27.0).  Of 32 columns tm = 4 gains at most 5 % over 2 and loses up to 14 % on small images.
 int conv_rows_many(const ms_op *op, int tm)
 {
     int best = tm;
@@ -196,8 +195,8 @@ int conv_rows_many(const ms_op *op, int tm)
 
 // MS_BODY_IMAGE_ROWS: tm of the image-row kernel, 0 = not taken.  Taken for 1 to 4 channels per pixel where the cache-read
 // of X is not shared by several tiles (compute_at 0, 1), where the im2col loader and the patch of single elements read
-// 2-byte elements (3-D: 572 -> 144 us for 8 x 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2, and 9.6 -> 7.7 us for one
-// 8 x 64 x 64 x 1, 5 x 5 x 5; 2-D in filter rows: 117 -> 75 us for 128 x 224 x 224 x 3 -> 64, 7 x 7, and 7.8 us on both
+// 2-byte elements (3-D: 573 -> 127 us for 8 x 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2, and 9.6 -> 7.7 us for one
+// 8 x 64 x 64 x 1, 5 x 5 x 5; 2-D in filter rows: 117 -> 72.5 us for 128 x 224 x 224 x 3 -> 64, 7 x 7, and 7.8 us on both
 // sides, which is a launch, for one 64 x 64 x 3).
 int conv_rows(const ms_op *op, const ms_variant_params *p)
 {
