@@ -690,15 +690,21 @@ struct conv_ctx {
 
 // ---- j-contiguous B kept row-major in LDS (direct-to-LDS rings and LDS_PAD 3): k-rows of BN elements, the
 // 16-column granules (what one transposing LDS load covers: 32 bytes of 2-byte, 16 bytes of 1-byte elements) of a row
-// XOR-swizzled with the row number; needs a power-of-two granule count
+// XOR-swizzled with the row number
 constexpr int CE = 16 / ES;                               // elements per 16-byte chunk
 #if !B_KMAJOR
 constexpr int CB = BN / CE;                               // 16-byte chunks per k-row of the j-contiguous B tile
 constexpr int BROW_BYTES = BN * ES;
 constexpr int NGRAN = BN / 16;
-constexpr int GRAN_MASK = (NGRAN & (NGRAN - 1)) ? 0 : (NGRAN > 16 ? 15 : NGRAN - 1);
+// LDS has 64 banks (256 bytes) and serves a transposing load 32 lanes at a time: GPB / 2 consecutive k-rows of two
+// neighbouring granules (32 x 32 intrinsics) or, KP rows apart, of one granule (16 x 16).  Rows that start at the same bank
+// differ by two granules each, rows KP apart by one: every such set covers all banks.  (512-byte rows, 8 wavefronts: 2.65
+// clocks per load and compute unit; 4.06 with the row number itself, 8.0 unswizzled.)
+constexpr int GPB = 256 / (16 * ES);                      // granules per 256 bytes
+constexpr int gran_block(int n) { return n % GPB == 0 ? GPB : n & -n; } // aligned granules that may trade places
+constexpr int GBLK = gran_block(NGRAN);
 // chunk-index XOR for k-row `k`: moves whole 16-column granules (ES chunks each)
-__device__ __forceinline__ int dl_swz_b(int k) { return (k & GRAN_MASK) * ES; }
+__device__ __forceinline__ int dl_swz_b(int k) { return GBLK < 2 ? 0 : ((k / (GPB / GBLK)) % (GBLK > 1 ? GBLK / 2 : 1) * 2 + k / KP % 2) * ES; }
 #endif
 typedef short tr4_t __attribute__((ext_vector_type(4)));
 typedef int tr2_t __attribute__((ext_vector_type(2)));
@@ -1024,7 +1030,10 @@ constexpr int NS = K1 * K2;
 constexpr int DL_STAGES = CACHE_READ >= 8 ? CACHE_READ - 6 : CACHE_READ - 3; // 5, 6, 7 and 8, 9, 10: rings of 2, 3, 4 stages
 constexpr int CPR = BK / CE;                              // 16-byte chunks per k-contiguous row
 constexpr int ROW_BYTES = BK * ES;
-constexpr int SWZ_DIV = CPR >= 8 ? 1 : 8 / CPR;           // rows that share one 128-byte line
+// rows that share one value of the swizzle: LDS serves 16 lanes of a 16-byte read at once, 16 rows of a 32 x 32 or 8 rows x 2
+// chunks of a 16 x 16 intrinsic, and they have to cover its 64 banks (64-byte rows, 32 x 32: 4.06 clocks per read and compute
+// unit; 8.0 with the 16 x 16 divisor)
+constexpr int SWZ_DIV = CPR >= 16 ? 1 : (MI_M == 32 ? 16 : 8) / CPR;
 constexpr int RPI = 64 / CPR;                             // rows per load instruction
 constexpr int DL_A_BYTES = BM * ROW_BYTES;
 #if B_KMAJOR
@@ -1044,8 +1053,15 @@ constexpr int DL_LPW_MIN = DL_INSTR / NWAVES;             // loads every wavefro
 static_assert((ES == 2 && KP == 8) || (ES == 1 && KP == 16), "direct-to-LDS path: 16-byte fragments of 2-byte or 1-byte inputs");
 static_assert(CPR == 4 || CPR == 8 || CPR == 16, "direct-to-LDS path: k tile of 64, 128 or 256 bytes");
 
-#define AS1(p) ((const __attribute__((address_space(1))) void *)(p))
-#define AS3(p) ((__attribute__((address_space(3))) void *)(p))
+// 16 bytes per lane from `base` (wave-uniform) + `voff` to `dst` (wave-uniform) + 16 * lane.  Written as assembly so that the
+// compiler does not see a write to LDS: before every LDS read behind the builtin it waits until all such loads have landed
+// (one s_waitcnt vmcnt(0) per k step, which drains the ring).  No register is written; the landing of a load is waited for by
+// count (DL_WAIT_VM) and published by a barrier.  M0 holds the LDS address.
+__device__ __forceinline__ void load_lds16(const char *base, unsigned voff, const char *dst)
+{
+    const unsigned at = (unsigned)(size_t)(const __attribute__((address_space(3))) char *)dst;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(at), "v"(voff), "s"(base) : "memory", "m0");
+}
 
 __device__ __forceinline__ int dl_swz(int row) { return (row / SWZ_DIV) % CPR; }
 
@@ -1063,7 +1079,7 @@ __device__ __forceinline__ void dl_issue(const in_t *__restrict__ A, const in_t 
             const int c = (lane % CPR) ^ dl_swz(row);
             const char *ub = (const char *)(A + ((long)i0 * BM + inst * RPI) * SA_I + k0e);
             const unsigned voff = (unsigned)(((lane / CPR) * SA_I + c * CE) * ES);
-            __builtin_amdgcn_global_load_lds(AS1(ub + voff), AS3(stage + inst * 1024), 16, 0, 0);
+            load_lds16(ub, voff, stage + inst * 1024);
         } else if (inst < DL_INSTR) {
             const int ib = inst - DL_IA;
 #if B_KMAJOR
@@ -1079,7 +1095,7 @@ __device__ __forceinline__ void dl_issue(const in_t *__restrict__ A, const in_t 
             const char *ub = (const char *)(B + k0e * SB_K + (long)j0 * BN);
             const unsigned voff = (unsigned)((k * SB_K + c * CE) * ES);
 #endif
-            __builtin_amdgcn_global_load_lds(AS1(ub + voff), AS3(stage + DL_A_BYTES + ib * 1024), 16, 0, 0);
+            load_lds16(ub, voff, stage + DL_A_BYTES + ib * 1024);
         }
     }
 }
@@ -1095,7 +1111,7 @@ __device__ __forceinline__ void dl_issue_one(const in_t *__restrict__ A, const i
         const int c = (lane % CPR) ^ dl_swz(row);
         const char *ub = (const char *)(A + ((long)i0 * BM + inst * RPI) * SA_I + k0e);
         const unsigned voff = (unsigned)(((lane / CPR) * SA_I + c * CE) * ES);
-        __builtin_amdgcn_global_load_lds(AS1(ub + voff), AS3(stage + inst * 1024), 16, 0, 0);
+        load_lds16(ub, voff, stage + inst * 1024);
     } else if (DL_INSTR % NWAVES == 0 || inst < DL_INSTR) {
         const int ib = inst - DL_IA;
 #if B_KMAJOR
@@ -1110,7 +1126,7 @@ __device__ __forceinline__ void dl_issue_one(const in_t *__restrict__ A, const i
         const char *ub = (const char *)(B + k0e * SB_K + (long)j0 * BN);
         const unsigned voff = (unsigned)((k * SB_K + c * CE) * ES);
 #endif
-        __builtin_amdgcn_global_load_lds(AS1(ub + voff), AS3(stage + DL_A_BYTES + ib * 1024), 16, 0, 0);
+        load_lds16(ub, voff, stage + DL_A_BYTES + ib * 1024);
     }
 }
 
@@ -1557,8 +1573,7 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
                 for (int e = 0; e < ACC_N; ++e) acc[tm][tn][e] = 0;
 #pragma unroll 1
         for (int k0 = 0; k0 < K0; ++k0) {
-            // right after an epilogue the counter also holds that tile's stores, which need not retire in
-            // order with the loads: drain it once, then count loads again
+            // right after an epilogue the counter also holds that tile's stores: drain it once, then count loads again
             if (k0 == 0 && ti > 0) DL_WAIT_VM(0);
             else DL_WAIT_VM((DL_STAGES - 2) * DL_LPW_MIN);
             __builtin_amdgcn_s_barrier();
