@@ -403,8 +403,12 @@ typedef enum ms_body {
                                 body_tile = pixels per side */
     MS_BODY_IMAGE_ROWS = 3,  /* conv with 1 to 4 channels per pixel: image rows and one filter plane's weights in LDS;
                                 body_tile = 32-pixel tiles of a wavefront */
-    MS_BODY_PHASES = 4       /* transposed conv: the nest, all decisions included, with its rows ordered by output phase and
+    MS_BODY_PHASES = 4,      /* transposed conv: the nest, all decisions included, with its rows ordered by output phase and
                                 the k0 loop over the taps that meet a tile's phase; body_tile = phases = stride^2 */
+    MS_BODY_DOUBLE_STEPS = 5 /* matrix products under ping-pong wave groups on the direct-to-LDS ring (cache_read 8, 9, 10): the
+                                nest with the decisions' workgroup and wavefront tiles in 16-row intrinsics, two 64-byte k0
+                                steps per LDS stage; body_tile = stages.  ti, tj, tk, tile_unit, mfma, block_k, cache_read,
+                                vec, vec_b, the unroll fields and lds_bytes are those of that nest */
 } ms_body;
 
 /* What the trace interpreter derives.  Unused fields are zero.  With bodies 1 to 3, block_*, grid, threads,

@@ -97,3 +97,11 @@ __device__ __forceinline__ void block_to_tile(int &z, int &i0, int &j0, int &ks)
 #endif
 }
 #endif
+
+// 16 bytes to global memory past the caches' replacement order: results that nothing on this compute unit reads again.  A launch
+// whose stores stay in the L2s writes them back at its end, when nothing else runs any more.
+__device__ __forceinline__ void store_stream(void *dst, const vec_t<unsigned, 4> &v)
+{
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store(__builtin_bit_cast(u4, v), reinterpret_cast<u4 *>(dst));
+}

@@ -1269,6 +1269,9 @@ __device__ __forceinline__ void write_tile(accv_t (&acc)[TM][TN], out_t *__restr
     (void)tid;
 }
 
+#ifndef PP_STAGES
+#define PP_STAGES 0
+#endif
 #if REORDER == 3
 // --------------------------------------------------------------------------------------
 // Persistent workgroups (REORDER 3, direct-to-LDS staging only): the launch has about one workgroup
@@ -1360,12 +1363,336 @@ __device__ __forceinline__ void write_tile_wave(accv_t (&acc)[TM][TN], out_t *__
                     const int row = idx / WS_CH, ch = idx % WS_CH;
                     const chunk_t v = *reinterpret_cast<const chunk_t *>(wstage + row * WS_ROW + ((ch ^ (row & WS_SWZ)) * 16));
                     char *dst = (char *)(C + ((long)i0 * BM + trow * MI_M + row) * LDC + (long)j0 * BN + tcol0 * MI_N) + ch * 16;
-                    *reinterpret_cast<chunk_t *>(dst) = v;
+                    store_stream(dst, v);
                 }
 #endif
             }
 }
 
+#if PP_STAGES
+// --------------------------------------------------------------------------------------
+// Double k steps (PP_STAGES > 0, the number of LDS stages; the host's rule is ring_pairs() in ms_interp.cpp).
+//
+// Two k0 steps of the ring are one stage of 128-byte rows, so that every load of a k-contiguous operand covers whole
+// cache lines.  A double step is PP_SLOTS slots; slot 0 reads all B fragments of the step and those of the first A tiles,
+// slot 1 the A fragments of the rest, so that B and the first part of A are free for refilling after slot 0.  The
+// wavefronts form two groups as above, group 1 one phase behind; every wavefront requests a share of the loads in every
+// phase, reading or multiplying, in the order  A part 0, first half of B, second half of B, A part 1  of a step.
+// Every wait leaves the loads behind the one it needs in flight, the stores of an epilogue among them (the counter of
+// vector-memory operations runs down in issue order).
+// What bounds it (256 x 256 tiles, 2 x 4 wavefronts): bf16 4096^3 takes 167 k clocks, 131 k of them matrix-core work, at the
+// 1.9 GHz that the power budget leaves (1.41 PFLOP/s; without the loads 1.73, the loads alone 53 us).  The loads behind the LDS
+// reads of a phase: 95.3 us; ahead of them 97.2, all between the products 100.9.  fp16 1024^3 x 64: 127 us, of which the loads
+// alone take 82 from HBM.  Before (single steps): 123 and 154 us.
+constexpr int P_KS = 2 * K2 * K3;                          // MFMA k steps of a double step
+// two phases of at least 256 matrix-core clocks each, or one: a barrier per phase costs about 60
+constexpr int P_SLOTS = (TM * TN * P_KS * (MI_M == 16 ? 16 : 32) > 512 || PP_STAGES < 3) && TM > 1 ? 2 : 1;
+constexpr int P_TM0 = P_SLOTS == 2 ? (TM + 1) / 2 : TM;    // row tiles of slot 0
+constexpr int P_ROW = 2 * BK * ES;
+static_assert(P_ROW == 128 && K1 == 1 && K0 % 2 == 0, "double steps: rows of one cache line");
+static_assert(P_SLOTS == 2 || PP_STAGES >= 3, "one slot per step needs three stages");
+constexpr int P_A = BM * P_ROW, P_B = BN * P_ROW;          // bytes of a stage
+constexpr int P_NA0 = I2 * P_TM0 * MI_M / 8, P_NA1 = BM / 8 - P_NA0, P_NB = BN / 8; // load instructions: 8 rows of A, 1 KiB of B
+constexpr int up(int n, int d) { return (n + d - 1) / d; }
+constexpr int P_LA0 = up(P_NA0, NWAVES), P_LA1 = up(P_NA1, NWAVES), P_LB = up(P_NB, NWAVES);       // of a wavefront, at most
+constexpr int P_MA0 = P_NA0 / NWAVES, P_MA1 = P_NA1 / NWAVES;                                      // and at least
+constexpr int P_LB0 = P_SLOTS == 2 ? P_LB / 2 : P_LB;      // B loads of the first half
+constexpr int P_MB = P_NB / NWAVES, P_MB0 = P_MB < P_LB0 ? P_MB : P_LB0;
+constexpr int P_MSTEP = P_MA0 + P_MA1 + P_MB;
+constexpr int P_STORES = CACHE_WRITE ? TM * J1 * (MI_M * WS_CH / 64) : TM * TN * (ACC_N / 4); // store instructions of an epilogue, at least
+constexpr int vm_cap(int n) { return n > 63 ? 63 : n; }
+
+extern "C" __global__ void __launch_bounds__(NTHREADS)
+ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *__restrict__ bias_, void *__restrict__ c_, int instances)
+{
+    (void)bias_;
+    const int tid = threadIdx.x;
+    const int lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int wi = wave / J2, wj = wave % J2;
+    const int lrow = lane % MI_M, lgrp = lane / MI_M;
+    const bool late = wave >= NWAVES / 2; // group 1: one phase behind
+
+    typedef __attribute__((address_space(3))) char lds_char;
+    constexpr int B_AT = PP_STAGES * P_A, W_AT = B_AT + PP_STAGES * P_B;
+    __shared__ __attribute__((aligned(1024))) char lds[W_AT + NWAVES * WS_BYTES];
+    char *const wstage = lds + W_AT + wave * WS_BYTES;
+
+    const long total = (long)I0 * J0 * DIM_B * instances;
+    const long first = blockIdx.x, stride = gridDim.x;
+    if (first >= total) return;
+    const long my_tiles = (total - first + stride - 1) / stride;
+    const long my_steps = my_tiles * (K0 / 2);
+
+    // ---- requests: the cursor is double step lk of tile lt, going into stage wr; past the end the last step is requested
+    // again (never read), so that every wavefront keeps issuing the same number of loads
+    long ls = 0, lf = first;
+    int lk = 0, wr = 0;
+    const char *cA, *cB;
+    auto locate = [&]() {
+        const tile_id t = decode_tile(lf, total);
+        cA = (const char *)((const in_t *)a_ + (long)t.inst * A_INST + (long)t.bb * SA_B + (long)t.i0 * BM * SA_I);
+        cB = (const char *)((const in_t *)b_ + (long)t.inst * B_INST + (long)t.bb * SB_B + (long)t.j0 * BN * SB_J);
+    };
+    locate();
+    // byte offsets of this lane's loads from the step's first row / k-row
+    unsigned va0[P_LA0], va1[P_LA1 ? P_LA1 : 1], vb[P_LB];
+    auto a_row = [&](int tm0, int pt, int inst) { // first of the 8 rows of load instruction `inst` of row tiles [tm0, tm0 + pt)
+        const int w = inst / (pt * (MI_M / 8)), r = inst % (pt * (MI_M / 8)), tm = tm0 + r / (MI_M / 8);
+        return ((tm / I3 * I2 + w) * I3 + tm % I3) * MI_M + r % (MI_M / 8) * 8;
+    };
+    auto p_swz = [](int row) { return (MI_M == 32 ? row / 2 : row) % 8; };
+    auto a_off = [&](int row0) { return (unsigned)((row0 + lane / 8) * SA_I * ES + ((lane % 8) ^ p_swz(row0 + lane / 8)) * 16); };
+#pragma unroll
+    for (int t = 0; t < P_LA0; ++t) va0[t] = a_off(a_row(0, P_TM0, t * NWAVES + wave));
+#pragma unroll
+    for (int t = 0; t < P_LA1; ++t) va1[t] = a_off(a_row(P_TM0, TM - P_TM0, t * NWAVES + wave));
+#pragma unroll
+    for (int t = 0; t < P_LB; ++t) {
+#if B_KMAJOR
+        const int row = (t * NWAVES + wave) * 8 + lane / 8;
+        vb[t] = (unsigned)(row * SB_J * ES + ((lane % 8) ^ p_swz(row)) * 16);
+#else
+        const int idx = (t * NWAVES + wave) * 64 + lane, k = idx / CB, c = (idx % CB) ^ dl_swz_b(k);
+        vb[t] = (unsigned)((k * SB_K + c * CE) * ES);
+#endif
+    }
+    auto load_a0 = [&](int t) {
+        const int inst = t * NWAVES + wave;
+        if (P_NA0 % NWAVES == 0 || inst < P_NA0)
+            load_lds16(cA, va0[t], lds + wr * P_A + a_row(0, P_TM0, inst) * P_ROW);
+    };
+    auto load_a1 = [&](int t) {
+        const int inst = t * NWAVES + wave;
+        if (P_NA1 % NWAVES == 0 || inst < P_NA1)
+            load_lds16(cA, va1[t], lds + wr * P_A + a_row(P_TM0, TM - P_TM0, inst) * P_ROW);
+    };
+    auto load_b = [&](int t) {
+        const int inst = t * NWAVES + wave;
+        if (P_NB % NWAVES == 0 || inst < P_NB)
+            load_lds16(cB, vb[t], lds + B_AT + wr * P_B + inst * 1024);
+    };
+    auto advance = [&]() {
+        wr = wr + 1 == PP_STAGES ? 0 : wr + 1;
+        if (ls + 1 < my_steps) {
+            ++ls;
+            cA += P_ROW;
+#if B_KMAJOR
+            cB += P_ROW;
+#else
+            cB += (long)2 * BK * SB_K * ES;
+#endif
+            if (++lk == K0 / 2) {
+                lk = 0;
+                lf += stride;
+                locate();
+            }
+        }
+    };
+    // part p of the loads of the step at the cursor: 0 A part 0, 1 first half of B, 2 second half of B, 3 A part 1; l counts inside it
+    auto part_loads = [](int p) { return p == 0 ? P_LA0 : p == 1 ? P_LB0 : p == 2 ? P_LB - P_LB0 : P_LA1; };
+    auto load = [&](int p, int l) {
+        if (p == 0) load_a0(l);
+        else if (p == 1) load_b(l);
+        else if (p == 2) load_b(P_LB0 + l);
+        else load_a1(l);
+    };
+    auto load_part = [&](int p) {
+#pragma unroll
+        for (int l = 0; l < 8; ++l)
+            if (l < part_loads(p)) load(p, l);
+        if (p == 3) advance();
+    };
+
+    // ---- fragments: LDS addresses without the stage and without compile-time offsets
+    const lds_char *const lds3 = (const lds_char *)lds;
+    int ra[P_KS], rb[TN];
+#pragma unroll
+    for (int q = 0; q < P_KS; ++q) ra[q] = (wi * I3 * MI_M + lrow) * P_ROW + ((q * LANE_GROUPS + lgrp) ^ p_swz(lrow)) * 16;
+#if !B_KMAJOR
+    const int li = lane % 16, tr_row = lgrp * KP + li / (ES == 2 ? 4 : 2); // k-row that this lane hands in
+#endif
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn) {
+        const int tcol = (tn / J3 * J2 + wj) * J3 + tn % J3;
+#if B_KMAJOR
+        rb[tn] = B_AT + (tcol * MI_N + lrow) * P_ROW;
+#else
+        rb[tn] = B_AT + tr_row * BROW_BYTES + ((((tcol * MI_N + lrow) / 16 * ES) ^ dl_swz_b(tr_row)) * 16) + (ES == 2 ? li % 4 : li % 2) * 8;
+#endif
+    }
+    accv_t acc[TM][TN];
+    frag_t fa[P_KS][P_TM0], fb[P_KS][TN];
+    auto read_a = [&](int stage, int tm0, int tm1) {
+#pragma unroll
+        for (int q = 0; q < P_KS; ++q) {
+            const lds_char *p = lds3 + (ra[q] + stage * P_A);
+#pragma unroll
+            for (int tm = tm0; tm < tm1; ++tm)
+                fa[q][tm - tm0] = *(const __attribute__((address_space(3))) frag_t *)(p + (tm / I3 * I2 * I3 + tm % I3) * MI_M * P_ROW);
+        }
+    };
+    auto read_b = [&](int stage) {
+#pragma unroll
+        for (int q = 0; q < P_KS; ++q)
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) {
+#if B_KMAJOR
+                fb[q][tn] = *(const __attribute__((address_space(3))) frag_t *)(lds3 + (rb[tn] + stage * P_B + ((q * LANE_GROUPS + lgrp) ^ p_swz(lrow)) * 16));
+#else
+                const lds_char *p = lds3 + (rb[tn] + stage * P_B);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#if IN_DT != DT_I8
+                    *reinterpret_cast<tr4_t *>(&fb[q][tn].v[4 * h]) =
+                        __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) tr4_t *)(p + (q * MI_K + h * 4) * BROW_BYTES));
+#else
+                    *reinterpret_cast<tr2_t *>(&fb[q][tn].v[8 * h]) =
+                        __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) tr2_t *)(p + (q * MI_K + h * 8) * BROW_BYTES));
+#endif
+                }
+#endif
+            }
+    };
+    // phase R of a slot, then phase M; both request the given part of the loads
+    auto phase_m = [&](int tm0, int tm1, int part) {
+        __builtin_amdgcn_s_setprio(1);
+        const int nm = P_KS * (tm1 - tm0) * TN, nl = part_loads(part);
+        int m = 0;
+#pragma unroll
+        for (int q = 0; q < P_KS; ++q)
+#pragma unroll
+            for (int tm = tm0; tm < tm1; ++tm)
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn) {
+                    acc[tm][tn] = mfma(fb[q][tn], fa[q][tm - tm0], acc[tm][tn]);
+                    ++m;
+                    const int due = m * (nl + 1) / nm, was = (m - 1) * (nl + 1) / nm;
+#pragma unroll
+                    for (int l = was; l < due; ++l)
+                        if (l < nl) load(part, l);
+                }
+        if (part == 3) advance();
+        __builtin_amdgcn_s_setprio(0);
+    };
+    auto zero_acc = [&]() {
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+                for (int e = 0; e < ACC_N; ++e) acc[tm][tn][e] = 0;
+    };
+    zero_acc();
+
+    // what has to have landed at the end of a phase: of the loads behind it so many may still be in flight
+    constexpr int KEEP_STEP = P_SLOTS == 2 ? P_MA1 + (PP_STAGES - 2) * P_MSTEP + P_MA0 + P_MB0 : (PP_STAGES - 2) * P_MSTEP; // A part 0 and B of the next step
+    constexpr int KEEP_A1 = (PP_STAGES - 1) * P_MSTEP;     // A part 1 of this step
+#pragma unroll
+    for (int t = 0; t < PP_STAGES - 1; ++t) {
+        load_part(0);
+        load_part(1);
+        load_part(2);
+        load_part(3);
+    }
+    if (P_SLOTS == 2) {
+        load_part(0);
+        load_part(1);
+    }
+    DL_WAIT_VM(vm_cap(KEEP_STEP));
+    PHASE_END();
+    if (late) {
+        // the phase in which group 0 reads slot 0 of step 0
+        if (P_SLOTS == 2) load_part(2);
+        else load_part(0);
+        PHASE_END();
+    }
+    int rd = 0;
+    bool stores = false; // an epilogue's stores lie between the loads that the next waits count
+#pragma unroll 1
+    for (long ti = 0; ti < my_tiles; ++ti) {
+        const tile_id ct = decode_tile(first + ti * stride, total);
+        if (late) {
+            // -- group 1
+#pragma unroll 1
+            for (int k0 = 0; k0 < K0 / 2; ++k0) {
+                read_b(rd);
+                read_a(rd, 0, P_TM0);
+                if (P_SLOTS == 2) {
+                    load_part(3);
+                    WAIT_LGKM0();
+                    if (stores) DL_WAIT_VM(vm_cap(KEEP_A1 + P_STORES));
+                    else DL_WAIT_VM(vm_cap(KEEP_A1));
+                    PHASE_END();
+                    phase_m(0, P_TM0, 0);
+                    PHASE_END();
+                    read_a(rd, P_TM0, TM);
+                    load_part(1);
+                    WAIT_LGKM0();
+                    if (stores) DL_WAIT_VM(vm_cap(KEEP_STEP + P_STORES));
+                    else DL_WAIT_VM(vm_cap(KEEP_STEP));
+                    PHASE_END();
+                    phase_m(P_TM0, TM, 2);
+                    PHASE_END();
+                } else {
+                    load_part(1);
+                    load_part(2);
+                    load_part(3);
+                    WAIT_LGKM0();
+                    if (stores) DL_WAIT_VM(vm_cap(KEEP_STEP + P_STORES));
+                    else DL_WAIT_VM(vm_cap(KEEP_STEP));
+                    PHASE_END();
+                    phase_m(0, TM, 0);
+                    PHASE_END();
+                }
+                stores = false;
+                rd = rd + 1 == PP_STAGES ? 0 : rd + 1;
+            }
+        } else {
+            // -- group 0
+#pragma unroll 1
+            for (int k0 = 0; k0 < K0 / 2; ++k0) {
+                read_b(rd);
+                read_a(rd, 0, P_TM0);
+                if (P_SLOTS == 2) {
+                    load_part(2);
+                    WAIT_LGKM0();
+                    PHASE_END();
+                    phase_m(0, P_TM0, 3);
+                    if (stores) DL_WAIT_VM(vm_cap(KEEP_A1 + P_STORES));
+                    else DL_WAIT_VM(vm_cap(KEEP_A1));
+                    PHASE_END();
+                    read_a(rd, P_TM0, TM);
+                    load_part(0);
+                    WAIT_LGKM0();
+                    PHASE_END();
+                    phase_m(P_TM0, TM, 1);
+                    DL_WAIT_VM(vm_cap(KEEP_STEP));
+                    PHASE_END();
+                } else {
+                    load_part(0);
+                    WAIT_LGKM0();
+                    PHASE_END();
+                    phase_m(0, TM, 1);
+                    load_part(2);
+                    load_part(3);
+                    DL_WAIT_VM(vm_cap(KEEP_STEP));
+                    PHASE_END();
+                }
+                stores = false;
+                rd = rd + 1 == PP_STAGES ? 0 : rd + 1;
+            }
+        }
+        // ---- phase E: results of the tile (the other group multiplies its last slot, or reads its first)
+        out_t *C = (out_t *)c_ + ((long)ct.inst * DIM_B + ct.bb) * ((long)DIM_M * DIM_N);
+        write_tile_wave(acc, C, ct.i0, ct.j0, wstage, lane, wi, wj, lrow, lgrp);
+        zero_acc();
+        stores = true;
+        PHASE_END();
+    }
+    if (!late) PHASE_END(); // group 1's last phase
+    DL_WAIT_VM(0);          // the re-loads past the end must land before the workgroup's LDS is released
+}
+#else
 // The loads of a step are cut into PP_PARTS parts, one per M phase that may carry them, and inside an M phase they
 // are spread evenly between the MFMAs.  A load instruction holds the wavefront that issues it until the memory
 // pipeline accepts it (about 30 cycles of the compute unit's time per KiB when the unit streams its tiles): issued
@@ -1516,6 +1843,7 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
     if (!late) PHASE_END(); // group 1's last phase
     DL_WAIT_VM(0);          // the re-loads past the end must land before the workgroup's LDS is released
 }
+#endif // PP_STAGES
 #else
 extern "C" __global__ void __launch_bounds__(NTHREADS)
 ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *__restrict__ bias_, void *__restrict__ c_, int instances)

@@ -26,7 +26,10 @@ int32_t fail(int32_t code, const char *fmt, ...) __attribute__((format(printf, 2
 // the two operators that share the conv2d kernels (the transposed one differs in the im2col index map only)
 inline bool is_conv2d(int32_t kind) { return kind == MS_OP_CONV2D_NHWC || kind == MS_OP_CONV2D_TRANSPOSED_NHWC; }
 // bodies whose kernel is built from the trace's decisions
-inline bool follows_decisions(const ms_variant_params *p) { return p->body == MS_BODY_NEST || p->body == MS_BODY_PHASES; }
+inline bool follows_decisions(const ms_variant_params *p)
+{
+    return p->body == MS_BODY_NEST || p->body == MS_BODY_PHASES || p->body == MS_BODY_DOUBLE_STEPS;
+}
 inline bool is_3d(const ms_op *op) { return op->depth > 1 || op->kd > 1; }
 
 // (m, n, k) of an MS_MFMA_CODE

@@ -430,6 +430,56 @@ def test_ping_pong_on_the_ring_exact():
     run(op8, sp8, tr_8, lambda r: list(pool8[r % 5]), lambda x: O.gemm(x[0], x[1]), "i32", "int8")
 
 
+@pytest.mark.parametrize("what,dt,nt,M,N,K,mfma,i,j,k,cache,cw,stages", [
+    ("one 128-byte row per tile, 4 stages", "f16", False, 96, 192, 64, 161632, [3, 1, 2, 1], [3, 1, 2, 2], [2, 1, 1, 1], 10, 1, 4),
+    ("3 odd row tiles, loads that the wavefronts do not share evenly", "bf16", False, 96, 128, 192, 161632, [2, 1, 1, 3], [2, 1, 4, 1], [3, 1, 1, 2], 8, 0, 4),
+    ("two slots of 3 and 2 row tiles, 6 wavefronts", "f16", False, 240, 256, 320, 161632, [1, 1, 3, 5], [2, 1, 2, 4], [10, 1, 1, 1], 9, 1, 2),
+    ("two slots, 2 stages, 12-granule rows of B", "f16", False, 256, 384, 256, 323216, [1, 1, 4, 2], [2, 1, 2, 3], [8, 1, 1, 2], 10, 0, 2),
+    ("strided tiles, B along k", "f16", True, 256, 256, 192, 323216, [1, 2, 2, 2], [1, 2, 4, 1], [6, 1, 1, 2], 10, 1, 2),
+    ("B along k, one slot, 3 stages", "bf16", True, 256, 128, 448, 323216, [1, 1, 2, 4], [1, 1, 4, 1], [7, 1, 2, 2], 8, 1, 3),
+    ("int8, 32-row intrinsic", "i8", False, 128, 256, 384, 323232, [1, 1, 2, 2], [1, 1, 4, 2], [3, 1, 2, 2], 8, 1, 2),
+    ("int8, rows of B of 3 granules", "i8", False, 96, 96, 256, 161664, [3, 1, 2, 1], [2, 1, 1, 3], [4, 1, 1, 1], 10, 0, 4),
+])
+def test_double_steps_exact(what, dt, nt, M, N, K, mfma, i, j, k, cache, cw, stages):
+    """The double-step form of the ping-pong ring, integer-valued inputs with exact sums: slots, stages, operand layouts and
+    tile counts at their edges, fewer tiles than compute units and several tiles per workgroup (with their own inputs)."""
+    g = I.rng(78)
+    op = B.bmm_op(1, M, N, K, True, dt) if nt else B.gemm_op(M, N, K, dt, "i32" if dt == "i8" else "f32")
+    sp = op.space()
+    t = B.make_trace(sp, [[mfma], i, j, k, [0], [cache], [16 if dt == "i8" else 8], [16 if dt == "i8" else 8], [0], [3], [cw]])
+    p = B.trace_validate(op, sp, t)
+    assert p.body == B.BODY_DOUBLE_STEPS and p.body_tile == stages, (p.body, p.body_tile)
+    lead = (1,) if nt else ()
+    draw = (lambda s: I.int8_uniform(g, s)) if dt == "i8" else (lambda s: I.small_ints(g, lead + s, -1, 1, dt))
+    pool = [(draw((M, K)), draw((N, K) if nt else (K, N))) for _ in range(3)]
+    refs = [O.bmm(a, b, trans_b=True, bf16=dt == "bf16")[0] if nt else O.gemm(a, b, bf16=dt == "bf16") for a, b in pool]
+    per_tile = M // p.block_m * (N // p.block_n)
+    for R in (2, 256 * 3 // per_tile + 1): # at most three tiles per workgroup, some with two
+        print(what, "R", R, "stages", p.body_tile, "lds", p.lds_bytes, flush=True)
+        got = run_variant_distinct(op, sp, t, [list(pool[r % 3]) for r in range(R)], dt if nt else "i32" if dt == "i8" else "f32", (M, N))
+        if got is None:
+            continue
+        for r in range(R):
+            assert np.array_equal(got[r], refs[r % 3]), "%s: instance %d of %d" % (what, r, R)
+
+
+def test_ping_pong_on_the_ring_without_double_steps_exact():
+    """Reductions of an odd number of 64-byte k tiles, and k tiles of 256 bytes, keep the single-step ring."""
+    g = I.rng(79)
+    for dt, K, mfma, k, cache in (("f16", 160, 323216, [5, 1, 1, 2], 10), ("bf16", 96, 161632, [3, 1, 1, 1], 9), ("f16", 384, 161632, [3, 1, 2, 2], 8)):
+        op = B.gemm_op(128, 192, K, dt, "f32")
+        sp = op.space()
+        half = mfma // 10000 // 16
+        t = B.make_trace(sp, [[mfma], [2, 1, 2, 2 // half], [3, 1, 2, 2 // half], k, [0], [cache], [8], [8], [0], [3], [1]])
+        assert B.trace_validate(op, sp, t).body == B.BODY_NEST
+        pool = [(I.small_ints(g, (128, K), -1, 1, dt), I.small_ints(g, (K, 192), -1, 1, dt)) for _ in range(3)]
+        got = run_variant_distinct(op, sp, t, [list(pool[r % 3]) for r in range(100)], "f32", (128, 192))
+        if got is None:
+            continue
+        for r in (0, 1, 2, 50, 99):
+            assert np.array_equal(got[r], O.gemm(*pool[r % 3], bf16=dt == "bf16")), (dt, K, r)
+
+
 def test_ping_pong_on_the_ring_c2_shape():
     """Config 2's shape in the launch configuration bench.py times (64 instances): sampled instances against the oracle."""
     op = B.gemm_op(1024, 1024, 1024, "f16")

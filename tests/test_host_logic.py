@@ -693,6 +693,44 @@ def test_phases_cover_the_output_and_the_filter_once(N, H, W_, Cin, k, stride, p
     assert seen.get(True, 0) > 3 and seen.get(False, 0) > 3, seen
 
 
+def test_double_steps_are_one_kernel_per_wave_tile():
+    """Ping-pong rings of whole 128-byte k rows: every ring, k split and unroll budget of one wave tile, in 32-row or 16-row
+    intrinsics, is one kernel; its parameters are those of the code object and cover the output and the reduction once.
+    Odd reductions and k tiles of 256 bytes keep the nest, and so do stages that a tightened LDS limit does not take."""
+    op = B.gemm_op(512, 512, 1024, "f16")
+    sp = op.space()
+
+    def params(mfma, i, j, k, cache, cw=1, op=op, sp=sp, unroll=0):
+        return B.trace_validate(op, sp, B.make_trace(sp, [[mfma], i, j, k, [unroll], [cache], [8], [8], [0], [3], [cw]]))
+
+    same = [params(323216, [2, 1, 2, 4], [2, 1, 4, 2], [32, 1, 1, 2], 10), params(323216, [2, 1, 2, 4], [2, 1, 4, 2], [32, 1, 2, 1], 9, unroll=16),
+            params(161632, [2, 1, 2, 8], [2, 1, 4, 4], [32, 1, 1, 1], 8)]
+    assert all(p.body == B.BODY_DOUBLE_STEPS and p.body_tile == 2 for p in same)
+    assert len({(p.key, B.variant_kernel_text(op, p)) for p in same}) == 1
+    p = params(323216, [4, 1, 2, 2], [4, 1, 4, 1], [16, 1, 2, 2], 8)
+    assert p.body_tile == 4 and p.key != same[0].key
+    for p in (same[0], p):
+        assert p.mfma == 161632 and p.block_k == 32 and p.lds_bytes == p.body_tile * (p.block_m + p.block_n) * 128 + p.waves * 16 * p.tj[3] * 16 * 2
+        for cov in (B.variant_coverage(op, p, 512 * 512), B.variant_reduction_coverage(op, p)):
+            assert cov.min() == 1 and cov.max() == 1
+    t = B.make_trace(sp, [[323216], [4, 1, 2, 2], [4, 1, 4, 1], [16, 1, 2, 2], [0], [8], [8], [8], [0], [3], [1]])
+    v = B.Variant(op, sp, t)
+    assert v.resources().lds_bytes == v.params().lds_bytes and v.resources().scratch_bytes == 0 and "body=double-steps" in B.trace_to_text(op, sp, t)
+    assert params(161632, [4, 1, 2, 4], [4, 1, 4, 2], [8, 1, 2, 2], 8).body == B.BODY_NEST       # 256-byte k tiles
+    odd = B.gemm_op(512, 512, 96, "f16")
+    assert params(161632, [4, 1, 2, 4], [4, 1, 4, 2], [3, 1, 1, 1], 10, op=odd, sp=odd.space()).body == B.BODY_NEST
+    lim = B.get_limits()
+    try:
+        for lds, stages in ((80 * 1024, 2), (60 * 1024, 0)):
+            tight = B.get_limits()
+            tight.max_lds_bytes = lds
+            B.set_limits(tight)
+            p = params(161632, [4, 1, 2, 4], [4, 1, 4, 2], [32, 1, 1, 1], 8)
+            assert (p.body_tile, p.body) == (stages, B.BODY_DOUBLE_STEPS if stages else B.BODY_NEST) and p.lds_bytes <= lds
+    finally:
+        B.set_limits(lim)
+
+
 def test_few_long_rows_keep_their_wide_lane_groups():
     """Softmax without staging: a few long rows keep a lane group of a wavefront or more per row; many rows, short rows and
     groups that walk a row or several rows in turn go to the row kernel, as do groups narrower than a line."""
