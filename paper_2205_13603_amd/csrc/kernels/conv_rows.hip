@@ -16,7 +16,8 @@
 // against 32 * TM * TN of the matrix cores.  The code object may hold two kernels: TM for one instance, chosen to spread it over
 // the chip, and a larger one for launches whose instances fill it.
 // Inputs changing from launch to launch, before (im2col loader) and now: 8 x 16 x 224 x 224 x 3 -> 64, 7 x 7 x 7, stride 2 in
-// fp16: 573 -> 127 us (835 TFLOP/s); 128 x 224 x 224 x 3 -> 64, 7 x 7: 117 -> 72.5 us (3.4 TB/s).
+// fp16: 573 -> 127 us (835 TFLOP/s); 128 x 224 x 224 x 3 -> 64, 7 x 7: 117 -> 72.5 us (3.4 TB/s),
+// 62 with results streamed past the caches (4.0 TB/s).
 #include "common.h"
 
 typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
@@ -245,7 +246,7 @@ __device__ __forceinline__ void image_rows(const void *__restrict__ x_, const vo
         for (int i = 0; i < 32 * OCB / 64; ++i) {
             const int idx = i * 64 + lane, r = idx / OCB, c = idx % OCB;
             const u4_t v = *reinterpret_cast<const u4_t *>(stg + r * SROW + c * 16);
-            if (pw + r < p_end) reinterpret_cast<raw16_t *>(Y + (long)(pw + r) * DIM_N + c * OV)->v = v;
+            if (pw + r < p_end) store_stream(Y + (long)(pw + r) * DIM_N + c * OV, v);
         }
         __builtin_amdgcn_wave_barrier();
     }

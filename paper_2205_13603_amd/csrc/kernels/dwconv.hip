@@ -23,7 +23,7 @@
 // What bounds the general kernel there is the L1: a 1 x 29 patch of one thread reads 6 values per output, lane groups of 16
 // channels read half lines, and its 188 registers leave one workgroup per compute unit.  The halo costs no branch: a
 // buffer load beyond the image's bytes returns zero, and pixels outside the image ask for such an offset.
-// 57 x 57 x 144, stride 2, batch 128: 83.2 -> 60.7 us with inputs that change from launch to launch, 75.1 -> 50.4 with inputs
+// 57 x 57 x 144, stride 2, batch 128: 83.2 -> 60.7 us with inputs that change from launch to launch (57.1 with results streamed), 75.1 -> 50.4 with inputs
 // that stay; with those, of one channel 4 x 4 was the fastest (2 x 4: 53.1,
 // 6 x 6: 51.4, 8 x 8: 64.3), 2 and 4 channels per thread read more lines per output (2 x 4 of 2: 55.6, of 4: 49.8 but
 // 327 against 300 us on 112 x 112 x 32, stride 1).
@@ -53,6 +53,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
     float *__restrict__ Y = (float *)y_ + (long)z * CV_OH * CV_OW * CV_C + c;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(X), 0, IMG_BYTES, 0x00020000);
 
+    constexpr bool STREAM = stream_from((long)CV_N * CV_OH * CV_OW * CV_C * 4) <= 1;
     float x[SP_H][SP_W], w[CV_KH][CV_KW];
 #pragma unroll
     for (int ph = 0; ph < SP_H; ++ph)
@@ -75,7 +76,11 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
             for (int kh = 0; kh < CV_KH; ++kh)
 #pragma unroll
                 for (int kw = 0; kw < CV_KW; ++kw) acc += x[a * CV_STRIDE + kh][b * CV_STRIDE + kw] * w[kh][kw];
-            if (oh + a < CV_OH && ow + b < CV_OW) Y[((oh + a) * CV_OW + ow + b) * CV_C] = acc;
+            if (oh + a < CV_OH && ow + b < CV_OW) {
+                float *y = Y + ((oh + a) * CV_OW + ow + b) * CV_C;
+                if constexpr (STREAM) store_stream(y, acc);
+                else *y = acc;
+            }
         }
 }
 #else

@@ -1196,9 +1196,17 @@ __device__ __forceinline__ long out_row(int i0, int lr) { return (long)i0 * BM +
 
 constexpr int CROW = BN * (int)sizeof(out_t) + 16; // bytes of one staged output row (cache-write)
 
+// Whole output rows, or pieces of whole lines, are streamed past the caches (conv 28 x 28 x 64, 1 x 1, batch 512: 24.6 -> 19.0 us;
+// 16 x 512 x 512 scores x 2: 10.5 -> 9.3).  Pieces that share lines with the next tile's are not (12 x 288 x 288 in 144 columns
+// x 273: 193 us, 212 streamed), nor pieces of a single line (12 x 240 x 128 in 64 columns x 117: 122, 126).
+constexpr int PIECE_BYTES = BN * (int)sizeof(out_t);
+constexpr bool STREAM_ROWS = BN == LDC || (PIECE_BYTES % 128 == 0 && PIECE_BYTES >= 256 && LDC * (int)sizeof(out_t) % 128 == 0);
+// instances from which on a launch streams
+constexpr int STREAM_FROM = stream_from((long)DIM_B * DIM_M * DIM_N * sizeof(out_t));
+
 // second half of the CACHE_WRITE epilogue: NT threads (t = 0 .. NT-1) write the staged tile as whole rows
-template <int NT>
-__device__ __forceinline__ void flush_cstage(out_t *__restrict__ C, int i0, int j0, const char *__restrict__ cstage, int t)
+template <int NT, bool STREAM>
+__device__ __forceinline__ void flush_rows(out_t *__restrict__ C, int i0, int j0, const char *__restrict__ cstage, int t)
 {
     constexpr int CHUNKS_PER_ROW = BN * (int)sizeof(out_t) / 16;
     constexpr int TOTAL = BM * CHUNKS_PER_ROW;
@@ -1208,14 +1216,24 @@ __device__ __forceinline__ void flush_cstage(out_t *__restrict__ C, int i0, int 
         const int row = idx / CHUNKS_PER_ROW, ch = idx % CHUNKS_PER_ROW;
         const chunk_t v = *reinterpret_cast<const chunk_t *>(cstage + row * CROW + ch * 16);
         char *dst = (char *)(C + out_row(i0, row) * LDC + (long)j0 * BN) + ch * 16;
-        *reinterpret_cast<chunk_t *>(dst) = v;
+        if constexpr (STREAM) store_stream(dst, v);
+        else *reinterpret_cast<chunk_t *>(dst) = v;
     }
+}
+
+template <int NT>
+__device__ __forceinline__ void flush_cstage(out_t *__restrict__ C, int i0, int j0, const char *__restrict__ cstage, int t, int instances)
+{
+    if constexpr (!STREAM_ROWS) flush_rows<NT, false>(C, i0, j0, cstage, t);
+    else if constexpr (STREAM_FROM <= 1) flush_rows<NT, true>(C, i0, j0, cstage, t);
+    else if (instances >= STREAM_FROM) flush_rows<NT, true>(C, i0, j0, cstage, t);
+    else flush_rows<NT, false>(C, i0, j0, cstage, t);
 }
 
 // Epilogue of one workgroup tile.  `cstage`: LDS region of BM * CROW bytes for CACHE_WRITE 1 (must not be
 // read or written by anything else between the caller's preceding barrier and the end of this call).
 __device__ __forceinline__ void write_tile(accv_t (&acc)[TM][TN], out_t *__restrict__ C, const void *__restrict__ bias_, int inst, int i0, int j0,
-                                           char *__restrict__ cstage, int tid, int wi, int wj, int lrow, int lgrp)
+                                           char *__restrict__ cstage, int tid, int wi, int wj, int lrow, int lgrp, int instances)
 {
     // epilogue: (+bias, ReLU,) one rounding to the output type.
     // With the operands swapped a lane holds row `lrow` of the tile and, per group g of 4 accumulator
@@ -1261,12 +1279,13 @@ __device__ __forceinline__ void write_tile(accv_t (&acc)[TM][TN], out_t *__restr
                 }
 #if CACHE_WRITE && !CONV_HELPERS
     __syncthreads();
-    flush_cstage<NTHREADS>(C, i0, j0, cstage, tid);
+    flush_cstage<NTHREADS>(C, i0, j0, cstage, tid, instances);
 #endif
     (void)bias_;
     (void)inst;
     (void)cstage;
     (void)tid;
+    (void)instances;
 }
 
 #ifndef PP_STAGES
@@ -1934,9 +1953,9 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
         out_t *C = (out_t *)c_ + ((long)ct.inst * DIM_B + ct.bb) * ((long)DIM_M * DIM_N);
 #if CACHE_WRITE
         // the staging area was last read by the previous tile's row stores, K0 barriers ago
-        write_tile(acc, C, bias_, ct.inst, ct.i0, ct.j0, lds + OPND_BYTES, tid, wi, wj, lrow, lgrp);
+        write_tile(acc, C, bias_, ct.inst, ct.i0, ct.j0, lds + OPND_BYTES, tid, wi, wj, lrow, lgrp, instances);
 #else
-        write_tile(acc, C, bias_, ct.inst, ct.i0, ct.j0, lds, tid, wi, wj, lrow, lgrp);
+        write_tile(acc, C, bias_, ct.inst, ct.i0, ct.j0, lds, tid, wi, wj, lrow, lgrp, instances);
 #endif
     }
     DL_WAIT_VM(0); // the re-loads past the end must land before the workgroup's LDS is released
@@ -2015,7 +2034,7 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
             if (f > first) {
                 const long g = f - 1;
                 out_t *Cp = c_of(g / (I0 * J0));
-                flush_cstage<P_NT>(Cp, (int)(g % I0), (int)((g / I0) % J0), cstage, htid);
+                flush_cstage<P_NT>(Cp, (int)(g % I0), (int)((g / I0) % J0), cstage, htid, instances);
             }
             __syncthreads(); // barrier B: the matrix-core wavefronts are done with patch f, the helpers with the staging area
             if (f + 1 < last) patch_commit(pr, pm, patch, htid);
@@ -2038,14 +2057,14 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
 #endif
             }
             __syncthreads(); // barrier B
-            write_tile(acc, nullptr, bias_of(z), (int)(z / DIM_B), i0, j0, cstage, tid, wi, wj, lrow, lgrp); // accumulators -> staging area only
+            write_tile(acc, nullptr, bias_of(z), (int)(z / DIM_B), i0, j0, cstage, tid, wi, wj, lrow, lgrp, instances); // accumulators -> staging area only
         }
     }
     __syncthreads();
     if (helper) {
         const long g = last - 1;
         out_t *Cp = c_of(g / (I0 * J0));
-        flush_cstage<P_NT>(Cp, (int)(g % I0), (int)((g / I0) % J0), cstage, htid);
+        flush_cstage<P_NT>(Cp, (int)(g % I0), (int)((g / I0) % J0), cstage, htid, instances);
     }
 }
 #else
@@ -2115,7 +2134,7 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
 #endif
             patch_commit(pr, pm, patch, tid);
         }
-        write_tile(acc, c_of(z), bias_of(z), (int)(z / DIM_B), i0, j0, cstage, tid, wi, wj, lrow, lgrp);
+        write_tile(acc, c_of(z), bias_of(z), (int)(z / DIM_B), i0, j0, cstage, tid, wi, wj, lrow, lgrp, instances);
     }
 }
 #endif // CONV_HELPERS
@@ -2431,7 +2450,7 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
     (void)C;
     (void)tid;
 #else
-    write_tile(acc, C, bias_, inst, i0, j0, lds, tid, wi, wj, lrow, lgrp);
+    write_tile(acc, C, bias_, inst, i0, j0, lds, tid, wi, wj, lrow, lgrp, instances);
 #endif
 }
 #endif // REORDER != 3

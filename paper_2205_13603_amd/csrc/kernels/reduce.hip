@@ -20,7 +20,7 @@
 // wastes it.  Rows are contiguous, so here a row belongs to ROW_LANES lanes of one wavefront that hold all of it in
 // registers as 16-byte vectors, the last ones masked; a workgroup takes its ROW_WAVES x (64 / ROW_LANES) rows once and
 // ends.  Sums are shorter per lane than in the narrow groups.
-// 65536 x 1000 in fp32: 174 -> 97 us (5.4 TB/s; 8 lanes per row, three passes before); 2944 x 776: 97 -> 9 us.
+// 65536 x 1000 in fp32: 174 -> 97 us, 92 with results streamed (5.7 TB/s; 8 lanes per row, three passes before); 2944 x 776: 97 -> 9 us.
 #include "common.h"
 
 #define RD_SOFTMAX 0
@@ -29,6 +29,8 @@
 #ifndef ROW_VEC
 #define ROW_VEC 0
 #endif
+// results of an instance large enough to stream (65536 x 1000 in fp32: 95 -> 90 us; 89408 x 160: 28.5 -> 22.2)
+constexpr bool STREAM = RD_OP == RD_SOFTMAX && stream_from((long)RD_ROWS * RD_LEN * sizeof(out_t)) <= 1;
 #if ROW_VEC
 constexpr int RV = ROW_VEC, RL = ROW_LANES, RNV = RD_LEN / RV; // elements per vector, lanes per row, vectors per row
 constexpr int RQ = (RNV + RL - 1) / RL;                         // vectors per lane, the last one masked
@@ -92,7 +94,8 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ unused1_, const 
             rout_t y;
 #pragma unroll
             for (int v = 0; v < RV; ++v) y.v[v] = from_acc(e[q][v] * inv);
-            *reinterpret_cast<rout_t *>(yr + (q * RL + t) * RV) = y;
+            if constexpr (STREAM) store_stream(yr + (q * RL + t) * RV, y);
+            else *reinterpret_cast<rout_t *>(yr + (q * RL + t) * RV) = y;
         }
 }
 #else
@@ -105,6 +108,13 @@ static_assert((long)I0 * I1 * I2 * I3 == RD_ROWS && (long)K0 * K1 * K2 * K3 == R
 
 typedef vec_t<in_t, K3> vin_t;
 typedef vec_t<out_t, K3> vout_t;
+
+// lane groups that write whole lines stream them past the caches
+__device__ __forceinline__ void store_row(out_t *dst, const vout_t &y)
+{
+    if constexpr (STREAM && K2 * K3 * sizeof(out_t) >= 128) store_stream(dst, y);
+    else *reinterpret_cast<vout_t *>(dst) = y;
+}
 
 template <bool IS_MAX> __device__ __forceinline__ float combine(float a, float b) { return IS_MAX ? fmaxf(a, b) : a + b; }
 
@@ -235,7 +245,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ unused1_, const 
                 vout_t y;
 #pragma unroll
                 for (int q3 = 0; q3 < K3; ++q3) y.v[q3] = from_acc(e[r][q][q3] * inv);
-                *reinterpret_cast<vout_t *>(yr + (long)r * RD_LEN + vec_off(q / K1, q % K1, t)) = y;
+                store_row(yr + (long)r * RD_LEN + vec_off(q / K1, q % K1, t), y);
             }
         }
 #else
@@ -291,7 +301,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ unused1_, const 
                     vout_t y;
 #pragma unroll
                     for (int q3 = 0; q3 < K3; ++q3) y.v[q3] = from_acc(expf(to_acc(x[r][q1].v[q3]) - m[r]) * inv[r]);
-                    *reinterpret_cast<vout_t *>(yr + (long)r * RD_LEN + vec_off(q0, q1, t)) = y;
+                    store_row(yr + (long)r * RD_LEN + vec_off(q0, q1, t), y);
                 }
         }
 #endif
