@@ -211,11 +211,12 @@ SYMBOLS = {
 }
 
 _lib = None
+_launch_native = None  # launch(variant address, inputs, output, instances, stream, workspace) -> status
 
 
 def lib():
     """Load libms.so (built by build_lib.py / __graft_entry__.build()).  Raises if it is missing."""
-    global _lib
+    global _lib, _launch_native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise OSError("%s is missing: run `python -m paper_2205_13603_amd.build_lib` (there is no fallback path)" % LIB_PATH)
@@ -230,6 +231,12 @@ def lib():
             fn = getattr(L, name)
             fn.restype = res
             fn.argtypes = args
+        try:
+            from . import _launch
+        except ImportError as e:
+            raise OSError("_launch.so is missing: run `python -m paper_2205_13603_amd.build_lib` (there is no fallback path): %s" % e)
+        _launch.bind(C.cast(L.ms_variant_launch, C.c_void_p).value)
+        _launch_native = _launch.launch
         _lib = L
     return _lib
 
@@ -528,6 +535,7 @@ class Variant:
         self.op = op
         self.handle = C.c_void_p()
         _check(lib().ms_variant_build(op.handle, C.byref(space), C.byref(trace), C.byref(self.handle)))
+        self._address = self.handle.value
 
     def __del__(self):
         if getattr(self, "handle", None) and _lib is not None:
@@ -561,9 +569,9 @@ class Variant:
 
     def launch(self, inputs, output, instances=1, stream=None, workspace=None):
         """inputs / output / workspace: device pointers (ints)."""
-        ins = (C.c_void_p * 4)(*[C.c_void_p(p) for p in inputs])
-        outs = (C.c_void_p * 1)(C.c_void_p(output))
-        _check(lib().ms_variant_launch(self.handle, ins, outs, workspace, instances, stream))
+        rc = _launch_native(self._address, inputs, output, instances, stream, workspace)
+        if rc:
+            _check(rc)
 
     def prepare(self):
         """Set-up for launch_static: loads the kernels on the current device, resolves the built-in workspace."""

@@ -854,6 +854,25 @@ def test_rfactor_is_an_opt_in_module_with_rules():
         v.launch([8, 8], 8, workspace=4)
 
 
+def test_launch_marshals_its_arguments():
+    """The binding's native entry hands ms_variant_launch what it was given: the checks that come before any device see it."""
+    import ctypes
+    op = B.gemm_op(64, 64, 64, "f16")
+    sp = op.space()
+    v = B.Variant(op, sp, B.trace_sample_valid(op, sp, 0, 0))
+    for inputs, output, instances, why in (([8], 8, 1, "NULL tensor"), ([8, None], 8, 1, "NULL tensor"), ([0, 8], 8, 1, "NULL tensor"), ((8, 8), None, 1, "NULL tensor"),
+                                           ((p for p in (8, 8)), 0, 1, "NULL tensor"), ([8, 8], 8, 0, "instances = 0"), ([8, 8], 8, -3, "instances = -3")):
+        with pytest.raises(B.MsError, match=why):
+            v.launch(inputs, output, instances=instances)
+    with pytest.raises(B.MsError, match="NULL tensor"):
+        v.launch([8], 8, stream=ctypes.c_void_p(None), workspace=ctypes.c_void_p(16))
+    for inputs, output in (([8, 8.0], 8), ([8, "8"], 8), ([8, 8], [8]), (8, 8)):
+        with pytest.raises(TypeError):
+            v.launch(inputs, output)
+    with pytest.raises(ValueError):
+        v.launch([8] * 5, 8)
+
+
 @pytest.mark.parametrize("mk", CONFIG_OPS + [lambda: B.softmax_op(1, 64, 256), lambda: B.norm_op(2, 32, 48),
                                              lambda: B.conv2d_op(1, 32, 32, 3, 32, 7, 7, stride=2, pad=3)])
 def test_interpreter_visits_every_reduction_position_once(mk):
