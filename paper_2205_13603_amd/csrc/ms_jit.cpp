@@ -19,7 +19,11 @@ namespace ms {
 
 static std::mutex g_mu;
 static std::map<uint64_t, std::unique_ptr<std::vector<char>>> g_codes;
-static std::map<std::string, std::string> g_sources;
+struct Source {
+    std::string text;
+    uint64_t hash; // of the text: 150 KB a byte at a time took 0.2 ms of every build
+};
+static std::map<std::string, Source> g_sources;
 static std::string g_cache_dir;
 static bool g_cache_dir_set = false;
 static int64_t g_n_compiled = 0, g_n_disk = 0, g_n_mem = 0;
@@ -86,13 +90,13 @@ static uint64_t hash_bytes(const std::string &s)
     return mix64(h);
 }
 
-static int32_t get_source(const std::string &name, std::string *src)
+static int32_t get_source(const std::string &name, const Source **src) // entries stay where they are until the process ends
 {
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_sources.find(name);
         if (it != g_sources.end()) {
-            *src = it->second;
+            *src = &it->second;
             return MS_OK;
         }
     }
@@ -104,17 +108,18 @@ static int32_t get_source(const std::string &name, std::string *src)
     std::string marker = "#include \"common.h\"";
     size_t at = body.find(marker);
     if (at != std::string::npos) body.replace(at, marker.size(), common);
+    const uint64_t hash = hash_bytes(body);
     std::lock_guard<std::mutex> lk(g_mu);
-    g_sources[name] = body;
-    *src = body;
+    *src = &g_sources.emplace(name, Source{body, hash}).first->second;
     return MS_OK;
 }
 
 int32_t jit_get_code(const KernelSpec &spec, uint64_t key, std::vector<char> **code_out)
 {
-    std::string src;
-    int32_t rc = get_source(spec.template_name, &src);
+    const Source *source = nullptr;
+    int32_t rc = get_source(spec.template_name, &source);
     if (rc != MS_OK) return rc;
+    const std::string &src = source->text;
     std::string opts_joined;
     for (auto &d : spec.defines) opts_joined += d + " ";
     // developer knob: extra -D options for experiments with a private copy of the templates
@@ -131,7 +136,7 @@ int32_t jit_get_code(const KernelSpec &spec, uint64_t key, std::vector<char> **c
         }
         for (auto &x : extra) opts_joined += x + " ";
     }
-    uint64_t k = mix64(key ^ hash_bytes(src) ^ mix64(hash_bytes(opts_joined)) ^ mix64(0xC0DE000000000000ull ^ compiler_id()));
+    uint64_t k = mix64(key ^ source->hash ^ mix64(hash_bytes(opts_joined)) ^ mix64(0xC0DE000000000000ull ^ compiler_id()));
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_codes.find(k);
