@@ -392,7 +392,7 @@ int32_t ms_trace_from_text(const ms_space *space, const char *text, ms_trace *ou
 /* ------------------------------------------------------------------ g(e0,tau) */
 
 /* The program that a trace resolves to.  MS_BODY_NEST: the loop nest that the decisions spell out.  Where no decisions can
- * spell out a good kernel the interpreter gives the trace another body.  Bodies 1 to 3 read the operator and their own tile
+ * spell out a good kernel the interpreter gives the trace another body.  Bodies 1 to 3 and 6 read the operator and their own tile
  * (and, of the decisions, nothing): all traces that a rule takes to one of them are one kernel and share one key.  The rules keep to
  * ms_limits; where a body would exceed them the trace stays with its nest. */
 typedef enum ms_body {
@@ -405,13 +405,16 @@ typedef enum ms_body {
                                 body_tile = 32-pixel tiles of a wavefront */
     MS_BODY_PHASES = 4,      /* transposed conv: the nest, all decisions included, with its rows ordered by output phase and
                                 the k0 loop over the taps that meet a tile's phase; body_tile = phases = stride^2 */
-    MS_BODY_DOUBLE_STEPS = 5 /* matrix products under ping-pong wave groups on the direct-to-LDS ring (cache_read 8, 9, 10): the
+    MS_BODY_DOUBLE_STEPS = 5, /* matrix products under ping-pong wave groups on the direct-to-LDS ring (cache_read 8, 9, 10): the
                                 nest with the decisions' workgroup and wavefront tiles in 16-row intrinsics, two 64-byte k0
                                 steps per LDS stage; body_tile = stages.  ti, tj, tk, tile_unit, mfma, block_k, cache_read,
                                 vec, vec_b, the unroll fields and lds_bytes are those of that nest */
+    MS_BODY_CONV_STEPS = 6   /* conv and transposed conv whose pixels are whole 16-byte groups of channels, cache-read under the k0
+                                loop (compute_at 0): persistent workgroups multiply pixels by weights in 128-byte k steps,
+                                taps gathered straight into LDS; body_tile = 1000 * pixels + channels of a workgroup */
 } ms_body;
 
-/* What the trace interpreter derives.  Unused fields are zero.  With bodies 1 to 3, block_*, grid, threads,
+/* What the trace interpreter derives.  Unused fields are zero.  With bodies 1 to 3 and 6, block_*, grid, threads,
  * waves, acc_per_thread, lds_bytes, vec and vec_b are those of the kernel that runs, and so are the splits ti, tj, tc and tk
  * of MS_BODY_ROW_VECTORS and MS_BODY_STRIPS (their products may exceed the extents: the rest is masked; block_k of the
  * strips = threads, one per strip and channel); block_k of MS_BODY_IMAGE_ROWS = k values per filter plane.  All other

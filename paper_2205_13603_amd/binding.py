@@ -26,7 +26,7 @@ SPACE_RFACTOR = 0x400  # opt-in: sample the split of the reduction across workgr
 SPACE_DEFAULT = 0xFF
 STATIC_WORKSPACE_BYTES = 32 << 20
 FAM_GEMM_ALU, FAM_GEMM_MFMA, FAM_DWCONV, FAM_REDUCE = range(4)
-BODY_NEST, BODY_ROW_VECTORS, BODY_STRIPS, BODY_IMAGE_ROWS, BODY_PHASES, BODY_DOUBLE_STEPS = range(6)
+BODY_NEST, BODY_ROW_VECTORS, BODY_STRIPS, BODY_IMAGE_ROWS, BODY_PHASES, BODY_DOUBLE_STEPS, BODY_CONV_STEPS = range(7)
 MAX_SLOTS, MAX_FACTORS, MAX_CANDS, MAX_LOOPS = 16, 4, 12, 8
 
 F8E4M3 = 5

@@ -112,6 +112,9 @@
 #ifndef CV_PHASES
 #define CV_PHASES 0
 #endif
+#ifndef CONV_STEPS
+#define CONV_STEPS 0
+#endif
 #if CV_PHASES
 #define K0_WALK (K0 / (CV_STRIDE * CV_STRIDE)) // k0 steps of a whole reduction
 #else
@@ -1063,6 +1066,18 @@ __device__ __forceinline__ void load_lds16(const char *base, unsigned voff, cons
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(at), "v"(voff), "s"(base) : "memory", "m0");
 }
 
+// The same from a buffer at `base`: `voff` per lane, `soff` wave-uniform.  Lanes that ask for OUTSIDE write zeros (a range-checked
+// load beyond the buffer returns zero, into LDS too).
+constexpr unsigned OUTSIDE = 0x80000000u;
+__device__ __forceinline__ void gather_lds16(const char *base, unsigned voff, unsigned soff, const char *dst)
+{
+    typedef unsigned rsrc_t __attribute__((ext_vector_type(4)));
+    const unsigned at = (unsigned)(size_t)(const __attribute__((address_space(3))) char *)dst;
+    const unsigned long b = (unsigned long)base;
+    const rsrc_t rs = {(unsigned)b, (unsigned)(b >> 32) & 0xffffu, 0x7ffffff0u, 0x00020000u};
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(at), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
+}
+
 __device__ __forceinline__ int dl_swz(int row) { return (row / SWZ_DIV) % CPR; }
 
 // issue this wavefront's share of the loads of tile `k0` into the stage at `stage`
@@ -1189,9 +1204,34 @@ __device__ __forceinline__ void dl_read_frags(frag_t (&fa)[K3][TM], frag_t (&fb)
 #endif // CACHE_READ >= 5
 
 
+#if CONV_STEPS
+// Convolutions as products on double steps (CONV_STEPS, see below): tiles of BM pixels of one output phase, CS_PN phases per side
+constexpr int CS_TILES = I0 / (CS_PN * CS_PN);             // tiles of a phase
+constexpr int CS_ROWS = CS_N * CS_PH_H * CS_PH_W;          // pixels of a phase, the last tile's rest is masked
+struct pixel_t {
+    int n, a, b;                                           // image, row and column inside the phase
+};
+__device__ __forceinline__ pixel_t tile_pixel(int i0, int lr)
+{
+    const int u = i0 / (CS_PN * CS_PN) * BM + lr;
+    return {u / (CS_PH_W * CS_PH_H), u / CS_PH_W % CS_PH_H, u % CS_PH_W};
+}
+__device__ __forceinline__ bool tile_row_ok(int i0, int lr) { return CS_ROWS % BM == 0 || i0 / (CS_PN * CS_PN) * BM + lr < CS_ROWS; }
+__device__ __forceinline__ long out_row(int i0, int lr)
+{
+    if constexpr (CS_PN == 1) return (long)i0 * BM + lr;
+    const int cls = i0 % (CS_PN * CS_PN);
+    const pixel_t p = tile_pixel(i0, lr);
+    return ((long)p.n * (CS_PH_H * CS_PN) + p.a * CS_PN + cls / CS_PN) * (CS_PH_W * CS_PN) + p.b * CS_PN + cls % CS_PN;
+}
+#define TILE_BIAS ((const float *)bias_ + (long)ct.inst * LDC)
+#else
 #if !CV_PHASES
 // row of the output that row `lr` of tile i0 is
 __device__ __forceinline__ long out_row(int i0, int lr) { return (long)i0 * BM + lr; }
+#endif
+__device__ __forceinline__ constexpr bool tile_row_ok(int, int) { return true; }
+#define TILE_BIAS nullptr
 #endif
 
 constexpr int CROW = BN * (int)sizeof(out_t) + 16; // bytes of one staged output row (cache-write)
@@ -1348,8 +1388,8 @@ constexpr int WS_SWZ = (WS_CH & (WS_CH - 1)) == 0 ? (WS_CH > 8 ? 7 : WS_CH - 1) 
 constexpr int WS_BYTES = CACHE_WRITE ? MI_M * WS_ROW : 0;
 static_assert(!CACHE_WRITE || WS_ROW % 16 == 0, "staged output rows are whole 16-byte chunks");
 
-__device__ __forceinline__ void write_tile_wave(accv_t (&acc)[TM][TN], out_t *__restrict__ C, int i0, int j0, char *__restrict__ wstage, int lane,
-                                                int wi, int wj, int lrow, int lgrp)
+__device__ __forceinline__ void write_tile_wave(accv_t (&acc)[TM][TN], out_t *__restrict__ C, const float *__restrict__ bias, int i0, int j0,
+                                                char *__restrict__ wstage, int lane, int wi, int wj, int lrow, int lgrp)
 {
 #pragma unroll
     for (int r1 = 0; r1 < I1; ++r1)
@@ -1365,13 +1405,26 @@ __device__ __forceinline__ void write_tile_wave(accv_t (&acc)[TM][TN], out_t *__
                     for (int g = 0; g < ACC_N / 4; ++g) {
                         const int lc = c3 * MI_N + (MI_M == 16 ? 4 * lgrp : 8 * g + 4 * lgrp); // column inside the staged rows
                         vec_t<out_t, 4> o;
+#if CONV_STEPS && HAS_BIAS
+                        const vec_t<float, 4> bv = *reinterpret_cast<const vec_t<float, 4> *>(bias + (long)j0 * BN + tcol0 * MI_N + lc);
+#endif
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) o.v[e] = from_acc(acc[r1 * I3 + r3][c1 * J3 + c3][4 * g + e]);
+                        for (int e = 0; e < 4; ++e) {
+                            acc_t x = acc[r1 * I3 + r3][c1 * J3 + c3][4 * g + e];
+#if CONV_STEPS && HAS_BIAS
+                            x += bv.v[e];
+#endif
+#if CONV_STEPS && RELU
+                            x = x > 0 ? x : 0;
+#endif
+                            o.v[e] = from_acc(x);
+                        }
 #if CACHE_WRITE
                         const int byte = lc * (int)sizeof(out_t);
                         *reinterpret_cast<vec_t<out_t, 4> *>(wstage + lrow * WS_ROW + (((byte / 16) ^ (lrow & WS_SWZ)) * 16) + byte % 16) = o;
 #else
-                        *reinterpret_cast<vec_t<out_t, 4> *>(C + ((long)i0 * BM + trow * MI_M + lrow) * LDC + (long)j0 * BN + tcol0 * MI_N + lc) = o;
+                        if (tile_row_ok(i0, trow * MI_M + lrow))
+                            *reinterpret_cast<vec_t<out_t, 4> *>(C + out_row(i0, trow * MI_M + lrow) * LDC + (long)j0 * BN + tcol0 * MI_N + lc) = o;
 #endif
                     }
 #if CACHE_WRITE
@@ -1381,11 +1434,12 @@ __device__ __forceinline__ void write_tile_wave(accv_t (&acc)[TM][TN], out_t *__
                 for (int idx = lane; idx < MI_M * WS_CH; idx += 64) {
                     const int row = idx / WS_CH, ch = idx % WS_CH;
                     const chunk_t v = *reinterpret_cast<const chunk_t *>(wstage + row * WS_ROW + ((ch ^ (row & WS_SWZ)) * 16));
-                    char *dst = (char *)(C + ((long)i0 * BM + trow * MI_M + row) * LDC + (long)j0 * BN + tcol0 * MI_N) + ch * 16;
-                    store_stream(dst, v);
+                    char *dst = (char *)(C + out_row(i0, trow * MI_M + row) * LDC + (long)j0 * BN + tcol0 * MI_N) + ch * 16;
+                    if (tile_row_ok(i0, trow * MI_M + row)) store_stream(dst, v);
                 }
 #endif
             }
+    (void)bias;
 }
 
 #if PP_STAGES
@@ -1421,6 +1475,16 @@ constexpr int P_MSTEP = P_MA0 + P_MA1 + P_MB;
 constexpr int P_STORES = CACHE_WRITE ? TM * J1 * (MI_M * WS_CH / 64) : TM * TN * (ACC_N / 4); // store instructions of an epilogue, at least
 constexpr int vm_cap(int n) { return n > 63 ? 63 : n; }
 
+#if CONV_STEPS
+// Convolutions (2-byte, whole 8-channel groups) as products: A's rows are pixels, k = (tap, channel), and a lane's 16 bytes are 8
+// channels of one pixel under one tap, gathered straight into LDS; taps outside the image, pixels behind the last and k behind
+// the reduction become zeros there.  A transposed convolution is one such product per output phase.
+// What bounds it: the gather's index arithmetic beside the products of narrow tiles (a 64-bit address per lane and load instead
+// of range-checked 32-bit offsets: 40.2 us against 35.7 for 16 x 16 x 64 -> 64, 5 x 5, batch 512), rounds of few tiles where images
+// are small, and HBM: 28 x 28 x 128 -> 128, dilation 2, batch 232 runs at 0.90 PFLOP/s (100 -> 59 us), 48 x 48 x 32 -> 128, batch 256 at
+// 2.8 TB/s (101 -> 67), 40 x 40 x 128 -> 256, 1 x 1, batch 88 at 4.7 TB/s (40 -> 23).
+#endif
+
 extern "C" __global__ void __launch_bounds__(NTHREADS)
 ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *__restrict__ bias_, void *__restrict__ c_, int instances)
 {
@@ -1442,23 +1506,79 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
     const long my_tiles = (total - first + stride - 1) / stride;
     const long my_steps = my_tiles * (K0 / 2);
 
+    auto a_row = [&](int tm0, int pt, int inst) { // first of the 8 rows of load instruction `inst` of row tiles [tm0, tm0 + pt)
+        const int w = inst / (pt * (MI_M / 8)), r = inst % (pt * (MI_M / 8)), tm = tm0 + r / (MI_M / 8);
+        return ((tm / I3 * I2 + w) * I3 + tm % I3) * MI_M + r % (MI_M / 8) * 8;
+    };
     // ---- requests: the cursor is double step lk of tile lt, going into stage wr; past the end the last step is requested
     // again (never read), so that every wavefront keeps issuing the same number of loads
     long ls = 0, lf = first;
     int lk = 0, wr = 0;
     const char *cA, *cB;
+#if CONV_STEPS
+    // A is gathered: per load the byte offset of a row's pixel under tap (0, 0) from the image stack and the taps that lie inside
+    // the image (rows in the low, columns in the high half); of the step at the cursor the tap, as such a pair of bits, and its
+    // offset, with the channels of this lane's 16-byte chunk, the same in every load, where a step is not of one tap
+    unsigned pix0[P_LA0], pix1[P_LA1 ? P_LA1 : 1];
+    unsigned in0[P_LA0], in1[P_LA1 ? P_LA1 : 1];
+    unsigned tap_in = 0, tap_off = 0;
+    // distances that keep pixel and tap offsets positive
+    constexpr int PIX_0 = CS_TR ? 0 : (CS_PAD_H * CS_W + CS_PAD_W) * CS_C * ES, TAP_0 = CS_TR ? ((CS_TH - 1) * CS_W + CS_TW - 1) * CS_C * ES : 0;
+    constexpr bool WHOLE_TAPS = CS_C % (2 * BK) == 0;
+    int cls = 0, lt_i0 = 0; // phase and number of the tile at the cursor, its weights
+    const char *tB = nullptr;
+    const int chunk_k = ((lane % 8) ^ (lane / 8)) * CE;
+    // first filter row (column) of a phase's taps and what they add to the pixel's row (column): kh = r + S * t meets row a + add - t
+    auto phase_r = [](int ph, int pad) { return (ph + pad) % CS_PN; };
+    auto phase_add = [](int ph, int pad) { return (ph + pad) / CS_PN; };
+    auto place = [&](int row, unsigned &pix, unsigned &in) {
+        const pixel_t p = tile_pixel(lt_i0, row);
+        const int h0 = CS_TR ? p.a + phase_add(cls / CS_PN, CS_PAD_H) : p.a * CS_S - CS_PAD_H;
+        const int w0 = CS_TR ? p.b + phase_add(cls % CS_PN, CS_PAD_W) : p.b * CS_S - CS_PAD_W;
+        constexpr int STEP_H = CS_TR ? -1 : CS_DIL;
+        pix = (unsigned)(((p.n * CS_H + h0) * CS_W + w0) * (CS_C * ES) + PIX_0 + (WHOLE_TAPS ? chunk_k * ES : 0));
+        in = 0;
+        if (tile_row_ok(lt_i0, row)) {
+#pragma unroll
+            for (int q = 0; q < CS_TH; ++q) in |= (unsigned)((unsigned)(h0 + q * STEP_H) < (unsigned)CS_H) << q;
+#pragma unroll
+            for (int q = 0; q < CS_TW; ++q) in |= (unsigned)((unsigned)(w0 + q * STEP_H) < (unsigned)CS_W) << (16 + q);
+        }
+    };
+    // the tap of double step lk; wave-uniform where channels come in whole steps
+    auto find_tap = [&]() {
+        constexpr int STEP_H = CS_TR ? -1 : CS_DIL;
+        const int k = WHOLE_TAPS ? lk * (2 * BK) : lk * (2 * BK) + chunk_k, tap = k / CS_C, th = tap / CS_TW, tw = tap % CS_TW;
+        tap_off = (unsigned)(((th * CS_W + tw) * STEP_H * CS_C + k % CS_C) * ES + TAP_0);
+        tap_in = 1u << th | 1u << (16 + tw);
+        if (!WHOLE_TAPS && th >= CS_TH) tap_in = 1u << 15; // behind the reduction: no such tap is inside
+#if CS_TR
+        // the filter's rows of a phase do not follow each other: one tap per step
+        const int ut = lk * (2 * BK) / CS_C, kh = phase_r(cls / CS_PN, CS_PAD_H) + CS_PN * (ut / CS_TW), kw = phase_r(cls % CS_PN, CS_PAD_W) + CS_PN * (ut % CS_TW);
+        cB = tB + ((long)(kh * CS_KW + kw) * CS_C + lk * (2 * BK) % CS_C) * SB_K * ES;
+#endif
+    };
+#else
+    const unsigned pix0[1] = {}, pix1[1] = {}, in0[1] = {}, in1[1] = {};
+#endif
     auto locate = [&]() {
         const tile_id t = decode_tile(lf, total);
         cA = (const char *)((const in_t *)a_ + (long)t.inst * A_INST + (long)t.bb * SA_B + (long)t.i0 * BM * SA_I);
         cB = (const char *)((const in_t *)b_ + (long)t.inst * B_INST + (long)t.bb * SB_B + (long)t.j0 * BN * SB_J);
+#if CONV_STEPS
+        tB = cB;
+        lt_i0 = t.i0;
+        cls = t.i0 % (CS_PN * CS_PN);
+#pragma unroll
+        for (int q = 0; q < P_LA0; ++q) place(a_row(0, P_TM0, q * NWAVES + wave) + lane / 8, pix0[q], in0[q]);
+#pragma unroll
+        for (int q = 0; q < P_LA1; ++q) place(a_row(P_TM0, TM - P_TM0, q * NWAVES + wave) + lane / 8, pix1[q], in1[q]);
+        find_tap();
+#endif
     };
     locate();
     // byte offsets of this lane's loads from the step's first row / k-row
     unsigned va0[P_LA0], va1[P_LA1 ? P_LA1 : 1], vb[P_LB];
-    auto a_row = [&](int tm0, int pt, int inst) { // first of the 8 rows of load instruction `inst` of row tiles [tm0, tm0 + pt)
-        const int w = inst / (pt * (MI_M / 8)), r = inst % (pt * (MI_M / 8)), tm = tm0 + r / (MI_M / 8);
-        return ((tm / I3 * I2 + w) * I3 + tm % I3) * MI_M + r % (MI_M / 8) * 8;
-    };
     auto p_swz = [](int row) { return (MI_M == 32 ? row / 2 : row) % 8; };
     auto a_off = [&](int row0) { return (unsigned)((row0 + lane / 8) * SA_I * ES + ((lane % 8) ^ p_swz(row0 + lane / 8)) * 16); };
 #pragma unroll
@@ -1475,26 +1595,49 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
         vb[t] = (unsigned)((k * SB_K + c * CE) * ES);
 #endif
     }
+    auto load_a = [&](const auto &pix, const auto &in, const auto &va, int t, const char *dst) {
+#if CONV_STEPS
+        const bool ok = (in[t] & tap_in) == tap_in;
+        const char *base = cA - (PIX_0 + TAP_0);
+        if constexpr (WHOLE_TAPS) gather_lds16(base, ok ? pix[t] : OUTSIDE, tap_off, dst);
+        else gather_lds16(base, ok ? pix[t] + tap_off : OUTSIDE, 0, dst);
+        (void)va;
+#else
+        load_lds16(cA, va[t], dst);
+        (void)pix;
+        (void)in;
+#endif
+    };
     auto load_a0 = [&](int t) {
         const int inst = t * NWAVES + wave;
         if (P_NA0 % NWAVES == 0 || inst < P_NA0)
-            load_lds16(cA, va0[t], lds + wr * P_A + a_row(0, P_TM0, inst) * P_ROW);
+            load_a(pix0, in0, va0, t, lds + wr * P_A + a_row(0, P_TM0, inst) * P_ROW);
     };
     auto load_a1 = [&](int t) {
         const int inst = t * NWAVES + wave;
         if (P_NA1 % NWAVES == 0 || inst < P_NA1)
-            load_lds16(cA, va1[t], lds + wr * P_A + a_row(P_TM0, TM - P_TM0, inst) * P_ROW);
+            load_a(pix1, in1, va1, t, lds + wr * P_A + a_row(P_TM0, TM - P_TM0, inst) * P_ROW);
     };
     auto load_b = [&](int t) {
         const int inst = t * NWAVES + wave;
         if (P_NB % NWAVES == 0 || inst < P_NB)
+        {
+#if CONV_STEPS
+            if constexpr (DIM_K % (2 * BK) != 0) { // k-rows behind the reduction
+                const int k = (inst * 64 + lane) / CB;
+                gather_lds16(cB, lk * (2 * BK) + k < DIM_K ? vb[t] : OUTSIDE, 0, lds + B_AT + wr * P_B + inst * 1024);
+            } else
+#endif
             load_lds16(cB, vb[t], lds + B_AT + wr * P_B + inst * 1024);
+        }
     };
     auto advance = [&]() {
         wr = wr + 1 == PP_STAGES ? 0 : wr + 1;
         if (ls + 1 < my_steps) {
             ++ls;
+#if !CONV_STEPS
             cA += P_ROW;
+#endif
 #if B_KMAJOR
             cB += P_ROW;
 #else
@@ -1505,6 +1648,9 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
                 lf += stride;
                 locate();
             }
+#if CONV_STEPS
+            else find_tap();
+#endif
         }
     };
     // part p of the loads of the step at the cursor: 0 A part 0, 1 first half of B, 2 second half of B, 3 A part 1; l counts inside it
@@ -1703,7 +1849,7 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
         }
         // ---- phase E: results of the tile (the other group multiplies its last slot, or reads its first)
         out_t *C = (out_t *)c_ + ((long)ct.inst * DIM_B + ct.bb) * ((long)DIM_M * DIM_N);
-        write_tile_wave(acc, C, ct.i0, ct.j0, wstage, lane, wi, wj, lrow, lgrp);
+        write_tile_wave(acc, C, TILE_BIAS, ct.i0, ct.j0, wstage, lane, wi, wj, lrow, lgrp);
         zero_acc();
         stores = true;
         PHASE_END();
@@ -1854,7 +2000,7 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
         }
         // ---- phase E: results of the tile (the other group multiplies its last slot, or reads its first)
         out_t *C = (out_t *)c_ + ((long)ct.inst * DIM_B + ct.bb) * ((long)DIM_M * DIM_N);
-        write_tile_wave(acc, C, ct.i0, ct.j0, wstage, lane, wi, wj, lrow, lgrp);
+        write_tile_wave(acc, C, TILE_BIAS, ct.i0, ct.j0, wstage, lane, wi, wj, lrow, lgrp);
         zero_acc();
         drain = true;
         PHASE_END();

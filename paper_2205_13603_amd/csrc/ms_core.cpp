@@ -1050,6 +1050,7 @@ extern "C" int32_t ms_trace_to_text(const ms_op *op, const ms_space *space, cons
                        "tensorize(block=C, intrin=mfma_32x32x16)\ncache-read(buffers=[X, W], scope=lds, compute-at=filter plane, prefetch_distance=1)\n"
                        "cache-write(buffer=C, scope=lds, per wavefront)\n", p.block_m, p.block_n, p.block_k);
         if (p.body == MS_BODY_PHASES) appendf(s, "# body=phases: i in the order of the %d output phases, k0 over the taps of a tile's phase only\n", p.body_tile);
+        if (p.body == MS_BODY_CONV_STEPS) appendf(s, "# body=conv-steps: %d pixels x %d channels per workgroup, this operator's own split\n", p.block_m, p.block_n);
         if (p.body == MS_BODY_DOUBLE_STEPS) appendf(s, "# body=double-steps: two k0 steps per LDS stage, %d stages\n", p.body_tile);
         if (p.mfma && !image_rows) appendf(s, "tensorize(block=C, intrin=mfma_%dx%dx%d)\n", p.tile_unit[0], p.tile_unit[1], p.tile_unit[2]);
         const char *nm[4] = {"i", "j", "c", "k"};

@@ -263,6 +263,80 @@ int double_steps(const ms_op *op, const ms_variant_params *p)
     return stages < 2 || (stages == 2 && double_step_rows(p) < 2) ? 0 : (int)stages;
 }
 
+// MS_BODY_CONV_STEPS: convolutions as matrix products on double steps (gemm_mfma.hip, CONV_STEPS).  Taken for 2-byte inputs whose
+// pixels are whole 16-byte groups of channels, where the cache-read of X sits under the k0 loop (compute_at 0): that nest stages
+// its im2col tile through registers with index arithmetic per load, its tiles have to divide the pixels, and a step of a
+// transposed convolution may mix phases.  48 x 48 x 32 -> 128, 3 x 3, batch 256: 101 -> 67 us; 16 x 16 x 256 -> 256, dilation 2, batch 88:
+// 51 -> 32; transposed 12 x 12 x 512 -> 64, 4 x 4, stride 2, batch 72: 123 -> 28; 16 x 16 x 256 -> 128, batch 64: 27.4 -> 22.2.
+struct ConvSteps {
+    int bm, bn, wi, wj, stages;      // workgroup tile, wavefronts, LDS stages of 128-byte rows
+    int64_t phases, th, tw;          // output phases (stride^2 of a transposed convolution), taps of one
+    int64_t tiles, steps;            // tiles and 128-byte k steps of one phase
+    int64_t lds, cost;
+};
+ConvSteps conv_steps_tile(const ms_op *op, int bm, int bn)
+{
+    const ms_op_desc &d = op->d;
+    ConvSteps c;
+    c.bm = bm;
+    c.bn = bn;
+    c.wj = bn == 32 ? 1 : bn == 256 || (bn == 128 && bm < 256) ? 4 : 2;
+    c.wi = 8 / c.wj;
+    const int64_t S = d.kind == MS_OP_CONV2D_TRANSPOSED_NHWC ? d.stride : 1;
+    c.phases = S * S;
+    c.th = d.dims[5] / S;
+    c.tw = d.dims[6] / S;
+    const int64_t rows = d.dims[0] * (op->OH / S) * (op->OW / S), staging = 8 * 16 * (bn / c.wj) * op->out_size, stage = (bm + bn) * 128;
+    c.tiles = (rows + bm - 1) / bm;
+    c.steps = (c.th * c.tw * d.dims[3] + 63) / 64;
+    c.stages = (int)std::min<int64_t>(4, (g_limits.max_lds_bytes - staging) / stage);
+    c.lds = c.stages * stage + staging;
+    // clocks of a launch: rounds of 256 workgroups; a step is bound by the matrix cores or by its bytes from the L2, a tile starts and
+    // ends with nothing beside it.  One image is launched over many instances (16 here) or is bound by the launch itself.
+    const int64_t launch = c.tiles * c.phases * (op->N / bn) * (d.dims[0] == 1 ? 16 : 1);
+    c.cost = (launch + 255) / 256 * (2500 + c.steps * std::max<int64_t>(bm * bn / 24, (bm + bn) * 3) + bm * bn / 16);
+    return c;
+}
+// tile of the body as bm * 1000 + bn, 0 = not taken
+int conv_steps(const ms_op *op, const ms_variant_params *p)
+{
+    const ms_op_desc &d = op->d;
+    if (!is_conv2d(d.kind) || p->family != MS_FAM_GEMM_MFMA || op->nb != 1 || is_3d(op) || op->in_size != 2 || p->compute_at || p->cache_read > 4 ||
+        p->rfactor > 1 || p->tap_rows)
+        return 0;
+    const bool transposed = d.kind == MS_OP_CONV2D_TRANSPOSED_NHWC;
+    const int64_t S = transposed ? d.stride : 1, Cin = d.dims[3];
+    if (Cin < 32 || Cin % (transposed ? 64 : 8) || op->N % (transposed ? 64 : 32)) return 0;
+    // nests of small tiles (pixels with few divisors) lose to it everywhere
+    const bool small_nest = p->block_m * p->block_n < 64 * 32;
+    // single images of few channels: the search has better locations for X (56 x 56 x 64 -> 64, 3 x 3, x 512: 143 us resident)
+    if (d.dims[0] == 1 && Cin <= 64 && op->N <= 64 && !small_nest) return 0;
+    // one k step per tile leaves nothing to overlap (20 x 20 x 64, 1 x 1, x 512: 20.2 and 20.4 us), and steps of several taps cost index
+    // arithmetic that narrow tiles do not hide (14 x 14 x 32 -> 64, 3 x 3, batch 512: 12.7 and 13.4; -> 256: 32.3 and 28.3)
+    if (op->K / (S * S) <= 64 || (Cin % 64 && op->N < 128 && !small_nest)) return 0;
+    // short reductions into 32 columns (14 x 14 x 256 -> 32, 1 x 1, batch 200: 6.5 and 7.3), and small batches of the several-tap kind
+    // (8 x 14 x 14 x 96 -> 32, 3 x 3: 7.7 and 9.7)
+    if ((op->N == 32 && op->K < 512) || (Cin % 64 && op->N < 128 && d.dims[0] > 1 && op->M < 4096)) return 0;
+    if (d.dims[5] % S || d.dims[6] % S || op->OH % S || op->OW % S || d.dims[5] / S > 15 || d.dims[6] / S > 15) return 0;
+    // 32-bit byte offsets from the image stack and inside the k-rows of a step
+    if (d.dims[0] * d.dims[1] * d.dims[2] * Cin > 0x3fffffff || (op->K + 64) * op->N > 0x3fffffff) return 0;
+    if (g_limits.max_threads < 512 || g_limits.max_waves < 8) return 0;
+    int best = 0;
+    int64_t cost = 0;
+    for (int bn : {256, 128, 96, 64, 32})
+        for (int bm : {256, 128, 64}) {
+            if (op->N % bn || (bn == 32 && bm < 128) || bm * bn > 256 * 128) continue; // 256 x 256 spills
+            const ConvSteps c = conv_steps_tile(op, bm, bn);
+            if (c.stages < 2 || bm * bn / 512 > g_limits.max_acc_per_thread || c.tiles * c.phases * (op->N / bn) > 0x7fffffff) continue;
+            if (c.stages < 3 && bm / c.wi < 32) continue; // one slot per step needs three stages
+            if (!best || c.cost < cost) {
+                best = bm * 1000 + bn;
+                cost = c.cost;
+            }
+        }
+    return best;
+}
+
 void set4(int32_t *f, int64_t f0, int64_t f1, int64_t f2, int64_t f3)
 {
     f[0] = (int32_t)f0;
@@ -315,6 +389,29 @@ void resolve_body(const ms_op *op, ms_variant_params *p)
         p->threads = c.threads;
         p->acc_per_thread = c.tm * c.tn * 16;
         p->lds_bytes = (int32_t)c.lds;
+    } else if ((p->body_tile = conv_steps(op, p))) {
+        const ConvSteps c = conv_steps_tile(op, p->body_tile / 1000, p->body_tile % 1000);
+        p->body = MS_BODY_CONV_STEPS;
+        set4(p->ti, c.tiles * c.phases, 1, c.wi, c.bm / 16 / c.wi);
+        set4(p->tj, op->N / c.bn, 1, c.wj, c.bn / 16 / c.wj);
+        set4(p->tk, 2 * c.steps, 1, 1, 1);
+        p->tile_unit[0] = p->tile_unit[1] = 16;
+        p->tile_unit[2] = 32;
+        p->mfma = MS_MFMA_CODE(16, 16, 32);
+        p->block_m = c.bm;
+        p->block_n = c.bn;
+        p->block_k = 32;
+        p->grid[0] = p->ti[0] * p->tj[0];
+        p->grid[1] = p->grid[2] = 1;
+        p->threads = 512;
+        p->acc_per_thread = c.bm * c.bn / 512;
+        p->lds_bytes = (int32_t)c.lds;
+        p->cache_read = 10;
+        p->cache_write = 1;
+        p->reorder = 3;
+        p->vec = p->vec_b = 8;
+        p->lds_pad = p->unroll = 0;
+        p->unroll_k1 = p->unroll_k2 = 1;
     } else if ((p->body_tile = double_steps(op, p))) {
         const int es = op->in_size, unit_k = 64 / es;
         p->body = MS_BODY_DOUBLE_STEPS;
@@ -414,6 +511,8 @@ void unroll_factors(ms_variant_params *p)
 }
 
 } // namespace
+
+static thread_local bool t_nests_only = false; // validate_as_nest
 
 extern "C" int32_t ms_trace_validate(const ms_op *op, const ms_space *space, const ms_trace *trace, ms_variant_params *out)
 {
@@ -802,10 +901,18 @@ extern "C" int32_t ms_trace_validate(const ms_op *op, const ms_space *space, con
     } else {
         return fail(MS_ERR_BAD_ARG, "ms_trace_validate: unknown family %d", space->family);
     }
-    resolve_body(op, &p);
+    if (!t_nests_only) resolve_body(op, &p);
     p.key = hash_params(op, &p);
     if (out) *out = p;
     return MS_OK;
+}
+
+int32_t ms::validate_as_nest(const ms_op *op, const ms_space *space, const ms_trace *trace, ms_variant_params *out)
+{
+    t_nests_only = true;
+    const int32_t rc = ms_trace_validate(op, space, trace, out);
+    t_nests_only = false;
+    return rc;
 }
 
 namespace ms {
@@ -859,13 +966,14 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
     auto &D = k.defines;
     D.push_back(def("IN_DT", dt_code(d.in_dtype)));
     D.push_back(def("OUT_DT", dt_code(d.out_dtype)));
-    if (follows_decisions(p)) push_schedule(D, p);
+    const bool conv_steps = p->body == MS_BODY_CONV_STEPS;
+    if (follows_decisions(p) || conv_steps) push_schedule(D, p);
     if (p->family == MS_FAM_GEMM_ALU || p->family == MS_FAM_GEMM_MFMA) {
         D.push_back(def("DIM_B", op->nb));
         D.push_back(def("DIM_M", op->M));
         D.push_back(def("DIM_N", op->N));
-        D.push_back(def("DIM_K", op->K));
-        bool conv = is_conv2d(d.kind);
+        D.push_back(def("DIM_K", conv_steps ? op->K / conv_steps_tile(op, p->block_m, p->block_n).phases : op->K));
+        bool conv = is_conv2d(d.kind) && !conv_steps;
         D.push_back(def("IS_CONV", conv ? 1 : 0));
         if (conv) {
             D.push_back(def("CV_N", d.dims[0]));
@@ -904,6 +1012,37 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             D.push_back(def("SB_J", 1));
             D.push_back(def("A_INST", d.dims[0] * op->depth * d.dims[1] * d.dims[2] * d.dims[3]));
             D.push_back(def("B_INST", op->K * op->N * op->nb));
+        } else if (conv_steps) {
+            const ConvSteps c = conv_steps_tile(op, p->block_m, p->block_n);
+            const bool transposed = d.kind == MS_OP_CONV2D_TRANSPOSED_NHWC;
+            const int64_t S = transposed ? d.stride : 1;
+            D.push_back(def("CONV_STEPS", 1));
+            D.push_back(def("PP_STAGES", c.stages));
+            D.push_back(def("HAS_BIAS", d.has_bias ? 1 : 0));
+            D.push_back(def("RELU", d.relu ? 1 : 0));
+            D.push_back(def("CS_TR", transposed ? 1 : 0));
+            D.push_back(def("CS_N", d.dims[0]));
+            D.push_back(def("CS_H", d.dims[1]));
+            D.push_back(def("CS_W", d.dims[2]));
+            D.push_back(def("CS_C", d.dims[3]));
+            D.push_back(def("CS_KW", d.dims[6]));
+            D.push_back(def("CS_TH", c.th));
+            D.push_back(def("CS_TW", c.tw));
+            D.push_back(def("CS_S", d.stride));
+            D.push_back(def("CS_DIL", std::max(1, (int)d.dilation)));
+            D.push_back(def("CS_PAD_H", op->pad_h));
+            D.push_back(def("CS_PAD_W", d.pad));
+            D.push_back(def("CS_PN", S));
+            D.push_back(def("CS_PH_H", op->OH / S));
+            D.push_back(def("CS_PH_W", op->OW / S));
+            D.push_back(def("SA_B", 0));
+            D.push_back(def("SA_I", 0));
+            D.push_back(def("SA_K", 1));
+            D.push_back(def("SB_B", 0));
+            D.push_back(def("SB_K", op->N));
+            D.push_back(def("SB_J", 1));
+            D.push_back(def("A_INST", d.dims[0] * d.dims[1] * d.dims[2] * d.dims[3]));
+            D.push_back(def("B_INST", op->K * op->N));
         } else {
             D.push_back(def("HAS_BIAS", 0));
             D.push_back(def("RELU", 0));
@@ -1040,6 +1179,21 @@ extern "C" int32_t ms_variant_coverage(const ms_op *op, const ms_variant_params 
                     ++counts[at];
                 }
         }
+    } else if (p->body == MS_BODY_CONV_STEPS) {
+        const ConvSteps c = conv_steps_tile(op, p->block_m, p->block_n);
+        const int64_t S = d.kind == MS_OP_CONV2D_TRANSPOSED_NHWC ? d.stride : 1, rows = op->M / c.phases;
+        for (int64_t wg = 0; wg < p->grid[0]; ++wg) {
+            const int64_t i0 = wg / p->tj[0], j0 = wg % p->tj[0];
+            for (int64_t lr = 0; lr < c.bm; ++lr) {
+                if (i0 / c.phases * c.bm + lr >= rows) continue; // pixels behind the last one are not stored
+                const int64_t i = S == 1 ? i0 * c.bm + lr : phase_out_row(op, p, i0, lr);
+                for (int64_t j = 0; j < c.bn; ++j) {
+                    const int64_t at = i * op->N + j0 * c.bn + j;
+                    if (at >= out_elems) return fail(MS_ERR_INVALID_TRACE, "coverage: index out of range");
+                    ++counts[at];
+                }
+            }
+        }
     } else if (p->body == MS_BODY_STRIPS) {
         const int64_t C = d.dims[3], strip = p->body_tile, sw = p->tj[0];
         for (int64_t n = 0; n < d.dims[0]; ++n)
@@ -1134,7 +1288,7 @@ extern "C" int32_t ms_variant_reduction_coverage(const ms_op *op, const ms_varia
     if (!op || !p) return fail(MS_ERR_BAD_ARG, "ms_variant_reduction_coverage: NULL argument");
     const bool dw = p->family == MS_FAM_DWCONV;
     const int unit = dw ? 1 : std::max(1, p->tile_unit[2]);
-    const bool masked = p->body == MS_BODY_ROW_VECTORS || p->body == MS_BODY_IMAGE_ROWS; // positions beyond K are left out
+    const bool masked = p->body == MS_BODY_ROW_VECTORS || p->body == MS_BODY_IMAGE_ROWS || p->body == MS_BODY_CONV_STEPS; // positions beyond K are left out
     const int64_t len = dw ? (int64_t)op->d.dims[4] * op->d.dims[5] : masked ? op->K : (int64_t)p->tk[0] * p->tk[1] * p->tk[2] * p->tk[3] * unit;
     if (needed) *needed = len;
     if (!counts) return needed ? MS_OK : fail(MS_ERR_BAD_ARG, "ms_variant_reduction_coverage: NULL argument");
@@ -1162,6 +1316,21 @@ extern "C" int32_t ms_variant_reduction_coverage(const ms_op *op, const ms_varia
                     const int64_t q = ch % c.cpr * 8 + e - c.lead;
                     if (ch < KH * c.cpr && q >= 0 && q < run) ++counts[(kd * KH + ch / c.cpr) * run + q];
                 }
+        return MS_OK;
+    }
+    if (p->body == MS_BODY_CONV_STEPS) {
+        // every output phase walks its own taps; together they are the filter
+        const ms_op_desc &d = op->d;
+        const ConvSteps c = conv_steps_tile(op, p->block_m, p->block_n);
+        const int64_t S = d.kind == MS_OP_CONV2D_TRANSPOSED_NHWC ? d.stride : 1, cin = d.dims[3];
+        for (int64_t cls = 0; cls < c.phases; ++cls)
+            for (int64_t k = 0; k < c.steps * 64; ++k) {
+                if (k >= c.th * c.tw * cin) continue;
+                const int64_t t = k / cin, kh = S == 1 ? t / c.tw : phase_tap(cls / S, op->pad_h, S, t / c.tw), kw = S == 1 ? t % c.tw : phase_tap(cls % S, d.pad, S, t % c.tw);
+                const int64_t at = (kh * d.dims[6] + kw) * cin + k % cin;
+                if (at < 0 || at >= len) return fail(MS_ERR_INVALID_TRACE, "reduction coverage: index out of range");
+                ++counts[at];
+            }
         return MS_OK;
     }
     const int rf = std::max(1, p->rfactor);

@@ -24,6 +24,10 @@ struct ms_variant {
     hipFunction_t fn;
     hipFunction_t fn_reduce; // second kernel of an rfactor launch, else null
     hipFunction_t fn_many;   // kernel of launches over many instances, else null
+    ms_variant *nest;        // MS_BODY_CONV_STEPS: the trace's nest, built when a launch brings operands off 16-byte boundaries
+    ms_space space;          // of the nest
+    ms_trace trace;
+    std::mutex nest_mu;
     int device;              // device the module is loaded on, -1 = not loaded
     int compute_units;       // of that device
 };
@@ -34,13 +38,8 @@ struct ms_variant {
         if (e_ != hipSuccess) return fail(MS_ERR_HIP, "%s: %s", #call, hipGetErrorString(e_));      \
     } while (0)
 
-extern "C" int32_t ms_variant_build(const ms_op *op, const ms_space *space, const ms_trace *trace, ms_variant **out)
+static int32_t build_variant(const ms_op *op, const ms_variant_params &p, ms_variant **out)
 {
-    if (!op || !space || !trace || !out) return fail(MS_ERR_BAD_ARG, "ms_variant_build: NULL argument");
-    *out = nullptr;
-    ms_variant_params p;
-    int32_t rc = ms_trace_validate(op, space, trace, &p);
-    if (rc != MS_OK) return rc;
     ms_variant *v = new (std::nothrow) ms_variant();
     if (!v) return fail(MS_ERR_NOMEM, "ms_variant_build: out of memory");
     v->op = *op;
@@ -49,8 +48,9 @@ extern "C" int32_t ms_variant_build(const ms_op *op, const ms_space *space, cons
     v->fn = nullptr;
     v->fn_reduce = nullptr;
     v->fn_many = nullptr;
+    v->nest = nullptr;
     v->device = -1;
-    rc = make_kernel_spec(op, &p, &v->spec);
+    int32_t rc = make_kernel_spec(op, &p, &v->spec);
     if (rc == MS_OK) rc = jit_get_code(v->spec, p.key, &v->code);
     if (rc != MS_OK) {
         delete v;
@@ -60,9 +60,25 @@ extern "C" int32_t ms_variant_build(const ms_op *op, const ms_space *space, cons
     return MS_OK;
 }
 
+extern "C" int32_t ms_variant_build(const ms_op *op, const ms_space *space, const ms_trace *trace, ms_variant **out)
+{
+    if (!op || !space || !trace || !out) return fail(MS_ERR_BAD_ARG, "ms_variant_build: NULL argument");
+    *out = nullptr;
+    ms_variant_params p;
+    int32_t rc = ms_trace_validate(op, space, trace, &p);
+    if (rc != MS_OK) return rc;
+    rc = build_variant(op, p, out);
+    if (rc == MS_OK && p.body == MS_BODY_CONV_STEPS) {
+        (*out)->space = *space;
+        (*out)->trace = *trace;
+    }
+    return rc;
+}
+
 extern "C" void ms_variant_destroy(ms_variant *v)
 {
     if (!v) return;
+    ms_variant_destroy(v->nest);
     if (v->mod) (void)hipModuleUnload(v->mod);
     delete v;
 }
@@ -276,6 +292,21 @@ extern "C" int32_t ms_variant_launch(ms_variant *v, const void *const *inputs, v
     uint64_t gz = (uint64_t)v->spec.grid[2] * (uint64_t)instances;
     if (gz > 65535ull * 32768ull || (uint64_t)v->spec.grid[0] * gz > 0x7fffffffull)
         return fail(MS_ERR_BAD_ARG, "ms_variant_launch: %d instances overflow the grid", instances);
+    if (v->p.body == MS_BODY_CONV_STEPS && (((uintptr_t)inputs[0] | (uintptr_t)inputs[1]) & 15u)) {
+        // loads straight into LDS move aligned 16-byte groups; the nest's loads go through registers and take any address
+        ms_variant *nest;
+        {
+            std::lock_guard<std::mutex> lk(v->nest_mu);
+            if (!v->nest) {
+                ms_variant_params p;
+                int32_t rc = validate_as_nest(&v->op, &v->space, &v->trace, &p);
+                if (rc == MS_OK) rc = build_variant(&v->op, p, &v->nest);
+                if (rc != MS_OK) return rc;
+            }
+            nest = v->nest;
+        }
+        return ms_variant_launch(nest, inputs, outputs, workspace, instances, stream);
+    }
     int32_t rc = ensure_loaded(v);
     if (rc != MS_OK) return rc;
     const void *in0 = inputs[0], *in1 = one_input ? nullptr : inputs[1];

@@ -740,3 +740,56 @@ def test_cbr_first_layer_filter_row_layout():
             continue
         compare.assert_float_close(got, ref, compare.RTOL_HALF, "CBR filter rows trace %d" % idx)
     assert want[0] == 0 and want[1] == 0 and want[2] == 0, want
+
+
+@pytest.mark.parametrize("N,H,W_,Cin,Cout,k,stride,pad,dil,transposed", [
+    (2, 8, 7, 64, 32, 3, 1, 1, 1, False),      # 112 pixels: one tile, its rest masked
+    (3, 16, 16, 32, 128, 3, 1, 1, 1, False),   # steps of two taps, the last one half empty
+    (2, 15, 11, 96, 256, 3, 2, 1, 1, False),   # steps that straddle taps, stride 2, odd extents
+    (4, 14, 14, 128, 96, 3, 1, 2, 2, False),   # dilation, 96 columns
+    (4, 7, 4, 72, 128, 1, 1, 0, 1, False),     # 72 channels: a step and an eighth
+    (2, 8, 8, 256, 64, 5, 1, 2, 1, False),
+    (1, 20, 20, 64, 128, 3, 1, 1, 1, False),
+    (2, 6, 4, 64, 64, 3, 1, 1, 1, True),       # one phase
+    (2, 4, 6, 128, 64, 4, 2, 1, 1, True),
+    (3, 3, 5, 128, 192, 4, 4, 0, 1, True),      # one tap per phase
+    (2, 4, 4, 64, 128, 6, 2, 2, 1, True),
+])
+def test_conv_steps_exact(N, H, W_, Cin, Cout, k, stride, pad, dil, transposed):
+    """Convolutions as products on double steps, integer-valued inputs with exact sums: partial tiles, padding, k behind the
+    reduction, phases, few and many instances with their own inputs (several tiles per persistent workgroup)."""
+    g = I.rng(105)
+    pool = [(I.small_ints(g, (N, H, W_, Cin), -2, 2, "f16"), I.small_ints(g, (k, k, Cin, Cout), -1, 1, "f16"),
+             g.integers(-3, 4, size=Cout).astype(np.float32)) for _ in range(2)]
+    if transposed:
+        refs = [O.conv2d_transposed_nhwc(x, w, bias=b, relu=True, stride=stride, pad=pad) for x, w, b in pool]
+        op = B.conv2d_transposed_op(N, H, W_, Cin, Cout, k, k, stride=stride, pad=pad, out_dtype="f32")
+    else:
+        refs = [O.conv2d_nhwc(x, w, bias=b, relu=True, stride=stride, pad=pad, dilation=dil) for x, w, b in pool]
+        op = B.conv2d_op(N, H, W_, Cin, Cout, k, k, stride=stride, pad=pad, out_dtype="f32", dilation=dil)
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 106, n) for n in range(400)) if B.trace_validate(op, space, t).body == B.BODY_CONV_STEPS)
+    p = B.trace_validate(op, space, t)
+    for R in (2, 300):
+        print("R", R, "tile", p.body_tile, "tiles", p.grid[0], flush=True)
+        got = run_variant_distinct(op, space, t, [list(pool[r % 2]) for r in range(R)], "f32", refs[0].shape)
+        if got is None:
+            continue
+        for r in range(R):
+            assert np.array_equal(got[r], refs[r % 2]), "instance %d of %d" % (r, R)
+
+
+def test_conv_steps_operands_off_16_byte_boundaries():
+    """Loads straight into LDS want aligned groups: operands that are aligned to their elements only run on the trace's nest."""
+    g = I.rng(107)
+    X = I.small_ints(g, (4, 8, 8, 64), -2, 2, "f16")
+    Wt = I.small_ints(g, (3, 3, 64, 64), -1, 1, "f16")
+    bias = g.integers(-3, 4, size=64).astype(np.float32)
+    ref = O.conv2d_nhwc(X, Wt, bias=bias, relu=True, stride=1, pad=1)
+    op = B.conv2d_op(4, 8, 8, 64, 64, 3, 3, stride=1, pad=1, out_dtype="f32")
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 108, n) for n in range(400)) if B.trace_validate(op, space, t).body == B.BODY_CONV_STEPS)
+    for offsets in ([0, 0, 0, 0], [3, 0, 0, 0], [0, 1, 0, 0]):
+        got = run_variant_offset(op, space, t, [X, Wt, bias], "f32", ref.shape, offsets)
+        if got is not None:
+            assert np.array_equal(got, ref), offsets

@@ -731,6 +731,31 @@ def test_double_steps_are_one_kernel_per_wave_tile():
         B.set_limits(lim)
 
 
+@pytest.mark.parametrize("mk,elems", [(lambda: B.conv2d_op(2, 15, 11, 96, 256, 3, 3, stride=2, pad=1), 2 * 8 * 6 * 256),
+                                      (lambda: B.conv2d_op(4, 14, 14, 128, 96, 3, 3, pad=2, stride=1, dilation=2), 4 * 196 * 96),
+                                      (lambda: B.conv2d_transposed_op(2, 4, 6, 128, 64, 4, 4, stride=2, pad=1), 2 * 96 * 64)])
+def test_conv_steps_cover_the_output_and_the_filter_once(mk, elems):
+    """Convolutions with their cache-read under the k0 loop are one kernel with one key whatever the decisions; its tiles cover
+    the output and its steps the filter once, and its resources are those of the code object."""
+    op = mk()
+    sp = op.space()
+    keys, K = set(), int(np.prod([e for n, e, red in op.loops() if red]))
+    for idx in range(200):
+        t = B.trace_sample_valid(op, sp, 39, idx)
+        p = B.trace_validate(op, sp, t)
+        assert (p.body == B.BODY_CONV_STEPS) == ("CONV_STEPS=1" in B.variant_kernel_text(op, p))
+        if p.body != B.BODY_CONV_STEPS:
+            continue
+        if not keys:
+            for cov in (B.variant_coverage(op, p, elems), B.variant_reduction_coverage(op, p)):
+                assert cov.min() == 1 and cov.max() == 1
+            assert len(cov) == K and p.body_tile == p.block_m * 1000 + p.block_n
+            r = B.Variant(op, sp, t).resources()
+            assert r.lds_bytes == p.lds_bytes and r.scratch_bytes == 0 and "body=conv-steps" in B.trace_to_text(op, sp, t)
+        keys.add((p.key, B.variant_kernel_text(op, p)))
+    assert len(keys) == 1
+
+
 def test_few_long_rows_keep_their_wide_lane_groups():
     """Softmax without staging: a few long rows keep a lane group of a wavefront or more per row; many rows, short rows and
     groups that walk a row or several rows in turn go to the row kernel, as do groups narrower than a line."""
