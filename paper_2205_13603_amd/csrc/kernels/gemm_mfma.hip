@@ -1060,10 +1060,18 @@ static_assert(CPR == 4 || CPR == 8 || CPR == 16, "direct-to-LDS path: k tile of 
 // compiler does not see a write to LDS: before every LDS read behind the builtin it waits until all such loads have landed
 // (one s_waitcnt vmcnt(0) per k step, which drains the ring).  No register is written; the landing of a load is waited for by
 // count (DL_WAIT_VM) and published by a barrier.  M0 holds the LDS address.
+// Operands of the two loads below that have to sit in scalar registers: equal in all lanes by construction, but the compiler keeps
+// some of them (a base chosen by a wave's number, an LDS address of a deep ring) in vector registers and then rejects the asm.
+__device__ __forceinline__ unsigned uniform(unsigned x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ unsigned long uniform(const char *p)
+{
+    const unsigned long a = (unsigned long)p;
+    return (unsigned long)uniform((unsigned)(a >> 32)) << 32 | uniform((unsigned)a);
+}
 __device__ __forceinline__ void load_lds16(const char *base, unsigned voff, const char *dst)
 {
     const unsigned at = (unsigned)(size_t)(const __attribute__((address_space(3))) char *)dst;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(at), "v"(voff), "s"(base) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(uniform(at)), "v"(voff), "s"(uniform(base)) : "memory", "m0");
 }
 
 // The same from a buffer at `base`: `voff` per lane, `soff` wave-uniform.  Lanes that ask for OUTSIDE write zeros (a range-checked
@@ -1073,9 +1081,10 @@ __device__ __forceinline__ void gather_lds16(const char *base, unsigned voff, un
 {
     typedef unsigned rsrc_t __attribute__((ext_vector_type(4)));
     const unsigned at = (unsigned)(size_t)(const __attribute__((address_space(3))) char *)dst;
-    const unsigned long b = (unsigned long)base;
+    const unsigned long b = uniform(base);
     const rsrc_t rs = {(unsigned)b, (unsigned)(b >> 32) & 0xffffu, 0x7ffffff0u, 0x00020000u};
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(at), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 : : "s"(uniform(at)), "v"(voff), "s"(rs), "s"(uniform(soff)) : "memory", "m0");
 }
 
 __device__ __forceinline__ int dl_swz(int row) { return (row / SWZ_DIV) % CPR; }

@@ -169,6 +169,7 @@ int32_t jit_get_code(const KernelSpec &spec, uint64_t key, std::vector<char> **c
         opts.push_back(std::string("--offload-arch=") + (arch_env && *arch_env ? arch_env : "gfx950"));
         opts.push_back("-O3");
         opts.push_back("-std=c++17");
+        opts.push_back("-Wno-inline-asm"); // M0 is named as overwritten where a load into LDS sets it
         // no fast-math: results must not depend on reassociation
         // scalar fp32 code only: the packed fp32 forms are kept out of generated code
         opts.push_back("-Xclang");
