@@ -79,6 +79,10 @@ struct KernelSpec {
 };
 // whether a launch over so many instances takes the second kernel (MS_BODY_IMAGE_ROWS, body_tile_many); its bytes of LDS
 bool image_rows_many(const ms_op *op, const ms_variant_params *p, int64_t instances, int64_t *lds);
+// MS_BODY_DOUBLE_STEPS: the kernel of launches of few tiles, 64 x 64 instead of the decisions' tile; false = none is worth it.
+// And whether a launch over so many instances takes it.
+bool double_steps_few(const ms_op *op, const ms_variant_params *p, ms_variant_params *few);
+bool takes_few(const ms_op *op, const ms_variant_params *p, const ms_variant_params *few, int64_t instances);
 // ms_trace_validate with every rule that gives the trace another body left out
 int32_t validate_as_nest(const ms_op *op, const ms_space *space, const ms_trace *trace, ms_variant_params *out);
 int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec *out);

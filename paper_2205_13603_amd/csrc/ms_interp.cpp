@@ -241,8 +241,8 @@ int conv_phases(const ms_op *op, const ms_variant_params *p)
 // 1024 x 1024 x 1024 fp16 x 64: 168 -> 113 us, 4096^3 bf16: 121 -> 95.
 // The intrinsic is the 16-row one of the same wave tile: a launch that keeps the matrix cores busy is held by the power it
 // draws, and the 16-row forms run it at 1.84 GHz where the 32-row forms run at 1.62 (bf16 4096^3: 97.5 and 104 us).
-// One stage more than two as long as the LDS takes it, up to four: small tiles multiply a step in one phase (rows of one
-// slot) and need three.
+// As many stages as the LDS takes, up to eight: small tiles multiply a step in one phase (rows of one slot) and need three, and
+// a step of theirs takes less than a round trip to memory.
 int64_t double_step_rows(const ms_variant_params *p) { return (int64_t)p->ti[1] * p->ti[3] * (p->tile_unit[0] / 16); } // 16-row tiles of a wavefront
 int64_t double_step_staging(const ms_op *op, const ms_variant_params *p) // bytes of the staged output rows of all wavefronts
 {
@@ -259,7 +259,7 @@ int double_steps(const ms_op *op, const ms_variant_params *p)
     const int64_t b_span = d.b_strides[2] == 1 ? k_row * d.b_strides[1] : (int64_t)p->block_n * d.b_strides[2];
     if (std::max((int64_t)p->block_m * d.a_strides[1], b_span) > 0x7ffffff0 / es) return 0;
     const int64_t stage = (int64_t)(p->block_m + p->block_n) * 128;
-    const int64_t stages = std::min<int64_t>(4, (g_limits.max_lds_bytes - double_step_staging(op, p)) / stage);
+    const int64_t stages = std::min<int64_t>(8, (g_limits.max_lds_bytes - double_step_staging(op, p)) / stage);
     return stages < 2 || (stages == 2 && double_step_rows(p) < 2) ? 0 : (int)stages;
 }
 
@@ -289,7 +289,7 @@ ConvSteps conv_steps_tile(const ms_op *op, int bm, int bn)
     const int64_t rows = d.dims[0] * (op->OH / S) * (op->OW / S), staging = 8 * 16 * (bn / c.wj) * op->out_size, stage = (bm + bn) * 128;
     c.tiles = (rows + bm - 1) / bm;
     c.steps = (c.th * c.tw * d.dims[3] + 63) / 64;
-    c.stages = (int)std::min<int64_t>(4, (g_limits.max_lds_bytes - staging) / stage);
+    c.stages = (int)std::min<int64_t>(8, (g_limits.max_lds_bytes - staging) / stage);
     c.lds = c.stages * stage + staging;
     // clocks of a launch: rounds of 256 workgroups; a step is bound by the matrix cores or by its bytes from the L2, a tile starts and
     // ends with nothing beside it.  One image is launched over many instances (16 here) or is bound by the launch itself.
@@ -313,7 +313,12 @@ int conv_steps(const ms_op *op, const ms_variant_params *p)
     if (d.dims[0] == 1 && Cin <= 64 && op->N <= 64 && !small_nest) return 0;
     // one k step per tile leaves nothing to overlap (20 x 20 x 64, 1 x 1, x 512: 20.2 and 20.4 us), and steps of several taps cost index
     // arithmetic that narrow tiles do not hide (14 x 14 x 32 -> 64, 3 x 3, batch 512: 12.7 and 13.4; -> 256: 32.3 and 28.3)
-    if (op->K / (S * S) <= 64 || (Cin % 64 && op->N < 128 && !small_nest)) return 0;
+    // (transposed 8 x 8 x 128 -> 64, 2 x 2, batch 256, two steps: 6.05 and 6.24; 24 x 24 x 64 -> 256, batch 96, one step: 42.4 and 26.9;
+    // half a step, 16 x 16 x 32 -> 128, 1 x 1, batch 512: 9.4 and 10.1; 28 x 28 x 32 -> 256, batch 256: 32.9 and 23.3)
+    const int k_of_tap_set = op->K / (S * S);
+    if (op->N <= 64 && k_of_tap_set <= (transposed ? 128 : 64)) return 0;
+    if (op->N <= 128 && k_of_tap_set < 64) return 0;
+    if (Cin % 64 && op->N < 128 && !small_nest) return 0;
     // short reductions into 32 columns (14 x 14 x 256 -> 32, 1 x 1, batch 200: 6.5 and 7.3), and small batches of the several-tap kind
     // (8 x 14 x 14 x 96 -> 32, 3 x 3: 7.7 and 9.7)
     if ((op->N == 32 && op->K < 512) || (Cin % 64 && op->N < 128 && d.dims[0] > 1 && op->M < 4096)) return 0;
@@ -905,6 +910,40 @@ extern "C" int32_t ms_trace_validate(const ms_op *op, const ms_space *space, con
     p.key = hash_params(op, &p);
     if (out) *out = p;
     return MS_OK;
+}
+
+// Estimate of a double-step launch in clocks: rounds of 256 persistent workgroups; a step is bound by the matrix cores, by its bytes
+// from the L2 or by two barriers, and a tile starts and ends with nothing beside it.
+static int64_t double_step_cost(const ms_op *op, const ms_variant_params *p, int64_t instances)
+{
+    const int64_t tiles = (int64_t)p->grid[0] * op->nb * instances, steps = op->K * op->in_size / 128, bm = p->block_m, bn = p->block_n;
+    return (tiles + 255) / 256 * (2500 + steps * std::max<int64_t>({bm * bn / 24, (bm + bn) * 3, 600}) + bm * bn / 16);
+}
+
+bool ms::double_steps_few(const ms_op *op, const ms_variant_params *p, ms_variant_params *few)
+{
+    if (p->body != MS_BODY_DOUBLE_STEPS || op->M % 64 || op->N % 64 || g_limits.max_threads < 512 || g_limits.max_waves < 8) return false;
+    *few = *p;
+    set4(few->ti, op->M / 64, 1, 4, 1);
+    set4(few->tj, op->N / 64, 1, 2, 2);
+    few->block_m = few->block_n = 64;
+    few->threads = 512;
+    few->waves = 8;
+    few->acc_per_thread = 8;
+    if ((op->M / 64) * (op->N / 64) > 0x7fffffff / std::max<int64_t>(1, op->nb)) return false;
+    few->grid[0] = few->ti[0] * few->tj[0];
+    few->body_tile = double_steps(op, few);
+    if (few->body_tile < 3) return false;
+    few->lds_bytes = (int32_t)(few->body_tile * (int64_t)128 * 128 + double_step_staging(op, few));
+    few->key = hash_params(op, few);
+    return few->key != p->key && takes_few(op, p, few, 1);
+}
+
+bool ms::takes_few(const ms_op *op, const ms_variant_params *p, const ms_variant_params *few, int64_t instances)
+{
+    // not for what the estimate cannot tell.  768 x 576 x 2048 x 2 in bf16 (128 x 192 tiles on 24 compute units): 24.9 -> 12.8 us;
+    // 576 x 1024 x 3264: 31.3 -> 18.4; 1024^3: 11.3 -> 8.5, x 2 stays at 11.3; 576 x 2048 x 1280, two rounds of 64 x 64, 15.4 and 16.6
+    return double_step_cost(op, few, instances) * 10 < double_step_cost(op, p, instances) * 9;
 }
 
 int32_t ms::validate_as_nest(const ms_op *op, const ms_space *space, const ms_trace *trace, ms_variant_params *out)

@@ -25,6 +25,7 @@ struct ms_variant {
     hipFunction_t fn_reduce; // second kernel of an rfactor launch, else null
     hipFunction_t fn_many;   // kernel of launches over many instances, else null
     ms_variant *nest;        // MS_BODY_CONV_STEPS: the trace's nest, built when a launch brings operands off 16-byte boundaries
+    ms_variant *few;         // MS_BODY_DOUBLE_STEPS: the kernel of launches of few tiles, else null
     ms_space space;          // of the nest
     ms_trace trace;
     std::mutex nest_mu;
@@ -49,6 +50,7 @@ static int32_t build_variant(const ms_op *op, const ms_variant_params &p, ms_var
     v->fn_reduce = nullptr;
     v->fn_many = nullptr;
     v->nest = nullptr;
+    v->few = nullptr;
     v->device = -1;
     int32_t rc = make_kernel_spec(op, &p, &v->spec);
     if (rc == MS_OK) rc = jit_get_code(v->spec, p.key, &v->code);
@@ -60,6 +62,8 @@ static int32_t build_variant(const ms_op *op, const ms_variant_params &p, ms_var
     return MS_OK;
 }
 
+extern "C" void ms_variant_destroy(ms_variant *v);
+
 extern "C" int32_t ms_variant_build(const ms_op *op, const ms_space *space, const ms_trace *trace, ms_variant **out)
 {
     if (!op || !space || !trace || !out) return fail(MS_ERR_BAD_ARG, "ms_variant_build: NULL argument");
@@ -68,6 +72,15 @@ extern "C" int32_t ms_variant_build(const ms_op *op, const ms_space *space, cons
     int32_t rc = ms_trace_validate(op, space, trace, &p);
     if (rc != MS_OK) return rc;
     rc = build_variant(op, p, out);
+    ms_variant_params few;
+    if (rc == MS_OK && double_steps_few(op, &p, &few)) {
+        rc = build_variant(op, few, &(*out)->few);
+        if (rc != MS_OK) {
+            ms_variant_destroy(*out);
+            *out = nullptr;
+            return rc;
+        }
+    }
     if (rc == MS_OK && p.body == MS_BODY_CONV_STEPS) {
         (*out)->space = *space;
         (*out)->trace = *trace;
@@ -79,6 +92,7 @@ extern "C" void ms_variant_destroy(ms_variant *v)
 {
     if (!v) return;
     ms_variant_destroy(v->nest);
+    ms_variant_destroy(v->few);
     if (v->mod) (void)hipModuleUnload(v->mod);
     delete v;
 }
@@ -102,6 +116,7 @@ extern "C" int32_t ms_variant_launch_shape(const ms_variant *v, int32_t instance
 {
     if (!v) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_shape: NULL variant");
     if (instances < 1) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_shape: instances = %d", instances);
+    if (v->few && takes_few(&v->op, &v->p, &v->few->p, instances)) v = v->few;
     int64_t lds = v->p.lds_bytes;
     const bool many = image_rows_many(&v->op, &v->p, instances, &lds);
     if (body_tile) *body_tile = many ? v->p.body_tile_many : v->p.body_tile;
@@ -192,6 +207,10 @@ static int32_t ensure_loaded(ms_variant *v)
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     if (v->device == dev) return MS_OK;
+    if (v->few) {
+        const int32_t rc = ensure_loaded(v->few);
+        if (rc != MS_OK) return rc;
+    }
     if (v->mod) {
         (void)hipModuleUnload(v->mod);
         v->mod = nullptr;
@@ -292,6 +311,7 @@ extern "C" int32_t ms_variant_launch(ms_variant *v, const void *const *inputs, v
     uint64_t gz = (uint64_t)v->spec.grid[2] * (uint64_t)instances;
     if (gz > 65535ull * 32768ull || (uint64_t)v->spec.grid[0] * gz > 0x7fffffffull)
         return fail(MS_ERR_BAD_ARG, "ms_variant_launch: %d instances overflow the grid", instances);
+    if (v->few && takes_few(&v->op, &v->p, &v->few->p, instances)) return ms_variant_launch(v->few, inputs, outputs, workspace, instances, stream);
     if (v->p.body == MS_BODY_CONV_STEPS && (((uintptr_t)inputs[0] | (uintptr_t)inputs[1]) & 15u)) {
         // loads straight into LDS move aligned 16-byte groups; the nest's loads go through registers and take any address
         ms_variant *nest;

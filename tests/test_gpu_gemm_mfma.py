@@ -431,18 +431,19 @@ def test_ping_pong_on_the_ring_exact():
 
 
 @pytest.mark.parametrize("what,dt,nt,M,N,K,mfma,i,j,k,cache,cw,stages", [
-    ("one 128-byte row per tile, 4 stages", "f16", False, 96, 192, 64, 161632, [3, 1, 2, 1], [3, 1, 2, 2], [2, 1, 1, 1], 10, 1, 4),
-    ("3 odd row tiles, loads that the wavefronts do not share evenly", "bf16", False, 96, 128, 192, 161632, [2, 1, 1, 3], [2, 1, 4, 1], [3, 1, 1, 2], 8, 0, 4),
+    ("one 128-byte row per tile, 8 stages", "f16", False, 96, 192, 64, 161632, [3, 1, 2, 1], [3, 1, 2, 2], [2, 1, 1, 1], 10, 1, 8),
+    ("3 odd row tiles, loads that the wavefronts do not share evenly", "bf16", False, 96, 128, 192, 161632, [2, 1, 1, 3], [2, 1, 4, 1], [3, 1, 1, 2], 8, 0, 8),
     ("two slots of 3 and 2 row tiles, 6 wavefronts", "f16", False, 240, 256, 320, 161632, [1, 1, 3, 5], [2, 1, 2, 4], [10, 1, 1, 1], 9, 1, 2),
     ("two slots, 2 stages, 12-granule rows of B", "f16", False, 256, 384, 256, 323216, [1, 1, 4, 2], [2, 1, 2, 3], [8, 1, 1, 2], 10, 0, 2),
     ("strided tiles, B along k", "f16", True, 256, 256, 192, 323216, [1, 2, 2, 2], [1, 2, 4, 1], [6, 1, 1, 2], 10, 1, 2),
     ("B along k, one slot, 3 stages", "bf16", True, 256, 128, 448, 323216, [1, 1, 2, 4], [1, 1, 4, 1], [7, 1, 2, 2], 8, 1, 3),
     ("int8, 32-row intrinsic", "i8", False, 128, 256, 384, 323232, [1, 1, 2, 2], [1, 1, 4, 2], [3, 1, 2, 2], 8, 1, 2),
-    ("int8, rows of B of 3 granules", "i8", False, 96, 96, 256, 161664, [3, 1, 2, 1], [2, 1, 1, 3], [4, 1, 1, 1], 10, 0, 4),
+    ("int8, rows of B of 3 granules", "i8", False, 96, 96, 256, 161664, [3, 1, 2, 1], [2, 1, 1, 3], [4, 1, 1, 1], 10, 0, 8),
 ])
 def test_double_steps_exact(what, dt, nt, M, N, K, mfma, i, j, k, cache, cw, stages):
     """The double-step form of the ping-pong ring, integer-valued inputs with exact sums: slots, stages, operand layouts and
-    tile counts at their edges, fewer tiles than compute units and several tiles per workgroup (with their own inputs)."""
+    tile counts at their edges, fewer tiles than compute units (the 64 x 64 kernel of such launches, where it divides the
+    extents) and several tiles per workgroup (with their own inputs)."""
     g = I.rng(78)
     op = B.bmm_op(1, M, N, K, True, dt) if nt else B.gemm_op(M, N, K, dt, "i32" if dt == "i8" else "f32")
     sp = op.space()

@@ -716,6 +716,13 @@ def test_double_steps_are_one_kernel_per_wave_tile():
     t = B.make_trace(sp, [[323216], [4, 1, 2, 2], [4, 1, 4, 1], [16, 1, 2, 2], [0], [8], [8], [8], [0], [3], [1]])
     v = B.Variant(op, sp, t)
     assert v.resources().lds_bytes == v.params().lds_bytes and v.resources().scratch_bytes == 0 and "body=double-steps" in B.trace_to_text(op, sp, t)
+    # launches of few tiles take 64 x 64 tiles instead, launches that fill the chip do not, and products that always do have none
+    small = v.launch_shape(1)
+    assert small[1] == 64 and small[0] >= 3 and v.launch_shape(64) == (4, 16, v.params().lds_bytes)
+    big = B.gemm_op(4096, 4096, 1024, "f16")
+    bsp = big.space()
+    vb = B.Variant(big, bsp, B.make_trace(bsp, [[323216], [16, 1, 2, 4], [16, 1, 4, 2], [32, 1, 1, 2], [0], [10], [8], [8], [0], [3], [1]]))
+    assert vb.launch_shape(1) == (2, 256, vb.params().lds_bytes)
     assert params(161632, [4, 1, 2, 4], [4, 1, 4, 2], [8, 1, 2, 2], 8).body == B.BODY_NEST       # 256-byte k tiles
     odd = B.gemm_op(512, 512, 96, "f16")
     assert params(161632, [4, 1, 2, 4], [4, 1, 4, 2], [3, 1, 1, 1], 10, op=odd, sp=odd.space()).body == B.BODY_NEST
