@@ -24,10 +24,9 @@ struct ms_variant {
     hipFunction_t fn;
     hipFunction_t fn_reduce; // second kernel of an rfactor launch, else null
     hipFunction_t fn_many;   // kernel of launches over many instances, else null
-    ms_variant *nest;        // MS_BODY_CONV_STEPS: the trace's nest, built when a launch brings operands off 16-byte boundaries
+    ms_variant *nest;        // MS_BODY_CONV_STEPS: the trace's nest, for operands off 16-byte boundaries (nest_of), else null
     ms_variant *few;         // MS_BODY_DOUBLE_STEPS: the kernel of launches of few tiles, else null
-    ms_space space;          // of the nest
-    ms_trace trace;
+    ms_variant_params nest_p;
     std::mutex nest_mu;
     int device;              // device the module is loaded on, -1 = not loaded
     int compute_units;       // of that device
@@ -81,9 +80,9 @@ extern "C" int32_t ms_variant_build(const ms_op *op, const ms_space *space, cons
             return rc;
         }
     }
-    if (rc == MS_OK && p.body == MS_BODY_CONV_STEPS) {
-        (*out)->space = *space;
-        (*out)->trace = *trace;
+    if (rc == MS_OK && p.body == MS_BODY_CONV_STEPS && (rc = validate_as_nest(op, space, trace, &(*out)->nest_p)) != MS_OK) {
+        ms_variant_destroy(*out);
+        *out = nullptr;
     }
     return rc;
 }
@@ -192,6 +191,8 @@ extern "C" int32_t ms_prebuild(const ms_op *op, const ms_space *space, const ms_
             KernelSpec spec;
             std::vector<char> *code;
             if (make_kernel_spec(op, &p, &spec) == MS_OK && jit_get_code(spec, p.key, &code) == MS_OK) built.fetch_add(1);
+            ms_variant_params few;
+            if (double_steps_few(op, &p, &few) && make_kernel_spec(op, &few, &spec) == MS_OK) (void)jit_get_code(spec, few.key, &code);
         }
     };
     std::vector<std::thread> pool;
@@ -236,6 +237,19 @@ static int32_t ensure_loaded(ms_variant *v)
     return MS_OK;
 }
 
+// The nest that the trace of a variant on MS_BODY_CONV_STEPS spells out, for operands off 16-byte boundaries: built once, by
+// ms_variant_prepare or by the first such launch.
+static int32_t nest_of(ms_variant *v, ms_variant **nest)
+{
+    std::lock_guard<std::mutex> lk(v->nest_mu);
+    if (!v->nest) {
+        const int32_t rc = build_variant(&v->op, v->nest_p, &v->nest);
+        if (rc != MS_OK) return rc;
+    }
+    *nest = v->nest;
+    return MS_OK;
+}
+
 // ---------------------------------------------------------------- launch without allocation
 //
 // Workspace of ms_variant_launch_static: one array per GPU, in the library's own device image, held until the
@@ -273,6 +287,12 @@ extern "C" int32_t ms_variant_prepare(ms_variant *v)
     if (!v) return fail(MS_ERR_BAD_ARG, "ms_variant_prepare: NULL variant");
     int32_t rc = ensure_loaded(v);
     if (rc != MS_OK) return rc;
+    if (v->p.body == MS_BODY_CONV_STEPS) { // a launch may bring operands of any address, and must not build or load anything
+        ms_variant *nest;
+        rc = nest_of(v, &nest);
+        if (rc == MS_OK) rc = ensure_loaded(nest);
+        if (rc != MS_OK) return rc;
+    }
     void *ptr = nullptr;
     return scratch_on_current_device(true, &ptr);
 }
@@ -315,16 +335,8 @@ extern "C" int32_t ms_variant_launch(ms_variant *v, const void *const *inputs, v
     if (v->p.body == MS_BODY_CONV_STEPS && (((uintptr_t)inputs[0] | (uintptr_t)inputs[1]) & 15u)) {
         // loads straight into LDS move aligned 16-byte groups; the nest's loads go through registers and take any address
         ms_variant *nest;
-        {
-            std::lock_guard<std::mutex> lk(v->nest_mu);
-            if (!v->nest) {
-                ms_variant_params p;
-                int32_t rc = validate_as_nest(&v->op, &v->space, &v->trace, &p);
-                if (rc == MS_OK) rc = build_variant(&v->op, p, &v->nest);
-                if (rc != MS_OK) return rc;
-            }
-            nest = v->nest;
-        }
+        const int32_t rc = nest_of(v, &nest);
+        if (rc != MS_OK) return rc;
         return ms_variant_launch(nest, inputs, outputs, workspace, instances, stream);
     }
     int32_t rc = ensure_loaded(v);

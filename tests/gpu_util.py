@@ -65,9 +65,9 @@ def run_variant_distinct(op, space, trace, per_instance_inputs, out_dtype, out_s
     return _launch_checked(v, dev, out_shape, out_dtype, R)
 
 
-def run_variant_offset(op, space, trace, inputs, out_dtype, out_shape, offsets):
+def run_variant_offset(op, space, trace, inputs, out_dtype, out_shape, offsets, static=False):
     """Like run_variant for one instance, with every tensor offsets[i] elements behind a 16-byte boundary (the last entry is
-    the output's); elements around the output must stay as they were."""
+    the output's); elements around the output must stay as they were.  static: through the launch that allocates nothing."""
     v = B.Variant(op, space, trace)
     if not devmem.gpu_available():
         return _precompiled()
@@ -78,8 +78,12 @@ def run_variant_offset(op, space, trace, inputs, out_dtype, out_shape, offsets):
     n, off = int(np.prod(out_shape)), offsets[-1]
     out = devmem.empty_output((n + off + 16,), out_dtype, poison=True)
     before = devmem.to_host(out, out_dtype)
-    v.launch([d.data_ptr() + o * a.dtype.itemsize for d, o, a in zip(dev, offsets, inputs)], out.data_ptr() + off * out.element_size(),
-             stream=devmem.current_stream())
+    launch = v.launch
+    if static:
+        v.prepare()
+        launch = v.launch_static
+    launch([d.data_ptr() + o * a.dtype.itemsize for d, o, a in zip(dev, offsets, inputs)], out.data_ptr() + off * out.element_size(),
+           stream=devmem.current_stream())
     got = devmem.to_host(out, out_dtype).reshape(-1)
     before = before.reshape(-1)
     assert np.array_equal(got[:off], before[:off], equal_nan=True) and np.array_equal(got[off + n:], before[off + n:], equal_nan=True)

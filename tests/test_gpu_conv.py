@@ -779,8 +779,10 @@ def test_conv_steps_exact(N, H, W_, Cin, Cout, k, stride, pad, dil, transposed):
             assert np.array_equal(got[r], refs[r % 2]), "instance %d of %d" % (r, R)
 
 
-def test_conv_steps_operands_off_16_byte_boundaries():
-    """Loads straight into LDS want aligned groups: operands that are aligned to their elements only run on the trace's nest."""
+@pytest.mark.parametrize("static", [False, True])
+def test_conv_steps_operands_off_16_byte_boundaries(static):
+    """Loads straight into LDS want aligned groups: operands that are aligned to their elements only run on the trace's nest,
+    which the set-up call has ready for the launch that allocates nothing."""
     g = I.rng(107)
     X = I.small_ints(g, (4, 8, 8, 64), -2, 2, "f16")
     Wt = I.small_ints(g, (3, 3, 64, 64), -1, 1, "f16")
@@ -790,6 +792,6 @@ def test_conv_steps_operands_off_16_byte_boundaries():
     space = op.space()
     t = next(t for t in (B.trace_sample_valid(op, space, 108, n) for n in range(400)) if B.trace_validate(op, space, t).body == B.BODY_CONV_STEPS)
     for offsets in ([0, 0, 0, 0], [3, 0, 0, 0], [0, 1, 0, 0]):
-        got = run_variant_offset(op, space, t, [X, Wt, bias], "f32", ref.shape, offsets)
+        got = run_variant_offset(op, space, t, [X, Wt, bias], "f32", ref.shape, offsets, static=static)
         if got is not None:
             assert np.array_equal(got, ref), offsets
