@@ -112,7 +112,12 @@ bool keeps_small_launch(const ms_op *op, const ms_variant_params *p, int64_t str
 // MS_BODY_STRIPS: output pixels per side of a thread's strip in the strip kernel (dwconv.hip), 0 = not taken.
 // Taken where an output extent above 2 has no divisor from 3 to 8: perfect tiles then leave a thread a row, a column or a
 // single pixel, which reads its inputs several times over (57 x 57 x 144, stride 2, batch 128: 75 against 50 us; 73 x 73 x 32,
-// batch 22: 119 against 6).  Elsewhere the factors can say better what fits.
+// batch 22: 119 against 6).
+// And taken whatever the extents in launches of more than four strip wavefronts per compute unit, from 8 output pixels a side on
+// (fewer leave too much of a strip masked): strips read an input 2.25 times (3 x 3, stride 1) and keep many loads in flight,
+// where nests are bound by reading it more often or by few lanes and long chains.  274 nests of 23 operators: at least 1.11 times
+// the strips' time, 4.6 times in the mean (64 x 56 x 56 x 96: 35.1 against 22.0 us with 2 x 7 pixels per thread; 29 x 91 x 91 x 128
+// with single pixels: 121 against 51).  Smaller launches keep their nests: there the factors can say better what fits.
 int dw_strip(const ms_op *op, const ms_variant_params *p)
 {
     const ms_op_desc &d = op->d;
@@ -121,7 +126,8 @@ int dw_strip(const ms_op *op, const ms_variant_params *p)
             if (e % f == 0) return false;
         return e > 2;
     };
-    if (!stubborn(op->OH) && !stubborn(op->OW)) return 0;
+    const bool many = op->OH >= 8 && op->OW >= 8 && d.dims[0] * dw_strip_items(op, 4) > 4 * 256 * 64;
+    if (!stubborn(op->OH) && !stubborn(op->OW) && !many) return 0;
     const int64_t strip = 4, regs = ((strip - 1) * d.stride + d.dims[4]) * ((strip - 1) * d.stride + d.dims[5]) + d.dims[4] * d.dims[5];
     if (regs > g_limits.max_acc_per_thread || dw_strip_threads(op, strip) > g_limits.max_threads) return 0; // patch and taps stay in registers
     // 32-bit byte offsets inside an image, 32-bit counts of its strips

@@ -74,3 +74,18 @@ def test_depthwise_strips_exact(H, W_, Cc, stride, pad, k):
         return
     for r in range(2):
         assert np.array_equal(got[r], refs[r]), "instance %d" % r
+
+
+@pytest.mark.parametrize("N,H,W_,Cc,stride,pad,k", [(65, 8, 8, 256, 1, 1, 3), (58, 9, 10, 128, 1, 2, 5), (80, 30, 16, 104, 2, 1, 3)])
+def test_large_depthwise_launches_exact(N, H, W_, Cc, stride, pad, k):
+    """Extents with divisors from 3 to 8 in launches large enough for strips; integer-valued inputs -> exact."""
+    g = I.rng(6)
+    ins = [[I.small_ints(g, (N, H, W_, Cc), -3, 3, "f32"), I.small_ints(g, (k, k, Cc), -3, 3, "f32")]]
+    ref = O.dwconv2d_nhwc(*ins[0], stride=stride, pad=pad)
+    op = B.dwconv2d_op(N, H, W_, Cc, k, k, stride=stride, pad=pad)
+    space = op.space()
+    t = B.trace_sample_valid(op, space, 17, 0)
+    assert B.trace_validate(op, space, t).body == B.BODY_STRIPS
+    got = run_variant_distinct(op, space, t, ins, "f32", ref.shape)
+    if got is not None:
+        assert np.array_equal(got, ref)

@@ -799,6 +799,15 @@ def test_small_depthwise_launches_keep_a_compact_nest():
     assert body(1, c=(9, 1, 16, 1)) == B.BODY_STRIPS  # 16 of 64 lanes
 
 
+@pytest.mark.parametrize("batch,size,channels,strips", [(65, 8, 256, True), (64, 8, 256, False), (400, 7, 100, False), (29, 56, 12, True)])
+def test_large_depthwise_launches_run_on_strips(batch, size, channels, strips):
+    """More than four strip wavefronts per compute unit and at least 8 output pixels a side: strips whatever the decisions."""
+    op = B.dwconv2d_op(batch, size, size, channels)
+    sp = op.space()
+    for n in range(20):
+        assert B.trace_validate(op, sp, B.trace_sample_valid(op, sp, 16, n)).body == (B.BODY_STRIPS if strips else B.BODY_NEST)
+
+
 @pytest.mark.parametrize("mk,flags,one,many", [
     (lambda: B.conv2d_op(1, 224, 224, 3, 64, 7, 7, stride=2, pad=3), B.SPACE_DEFAULT | B.SPACE_TAP_ROWS, 1, 4),
     (lambda: B.conv3d_op(1, 16, 224, 224, 3, 64, 7, stride=2, pad=3), B.SPACE_DEFAULT, 2, 4),
