@@ -5,6 +5,7 @@ import collections
 import math
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -736,6 +737,53 @@ def test_double_steps_are_one_kernel_per_wave_tile():
             assert (p.body_tile, p.body) == (stages, B.BODY_DOUBLE_STEPS if stages else B.BODY_NEST) and p.lds_bytes <= lds
     finally:
         B.set_limits(lim)
+
+
+def _short_waits(code_object):
+    """Loads into LDS of a code object, and those that read a scalar register fewer than five wait states after a vector
+    instruction wrote it."""
+    text = subprocess.run(["/opt/rocm/llvm/bin/llvm-objdump", "-d", code_object], stdout=subprocess.PIPE, text=True, check=True).stdout
+    code = [line.split("//")[0].split(None, 1) for line in text.splitlines() if line.startswith("\t")]
+    code = [(c[0], re.split(r"[ ,]+", c[1].strip()) if len(c) > 1 else []) for c in code]
+
+    def scalars(token):
+        m = re.fullmatch(r"s(?:(\d+)|\[(\d+):(\d+)\])", token)
+        return set() if not m else {int(m[1])} if m[1] else set(range(int(m[2]), int(m[3]) + 1))
+
+    loads, short = 0, []
+    for at, (name, args) in enumerate(code):
+        if not (name.startswith("global_load_lds") or (name.startswith("buffer_load") and args[-1] == "lds")):
+            continue
+        loads += 1
+        operands, states = set().union(*map(scalars, args)), 0
+        for before, what in code[at - 1::-1]:
+            if states >= 5:
+                break
+            if before.startswith("s_mov") and what:
+                operands -= scalars(what[0])
+            if before.startswith("v_") and what and scalars(what[0]) & operands:
+                short.append((before, what, name, args, states))
+            states += int(what[0], 0) + 1 if before == "s_nop" else 1
+    return loads, short
+
+
+def test_loads_into_lds_wait_for_their_scalar_operands(tmp_path):
+    """The loads are written as assembly, where the compiler does not see the wait states that they need."""
+    gemm, conv = B.gemm_op(256, 256, 704, "f16"), B.conv2d_op(8, 12, 14, 64, 128, 3, 3, stride=1, pad=1)
+    sp, csp = gemm.space(), conv.space()
+    ring = [[323216], [1, 1, 2, 4], [1, 1, 4, 2], [22, 1, 1, 2], [0], [7], [8], [8], [0], [3], [0]]
+    gather = next(t for t in (B.trace_sample_valid(conv, csp, 106, n) for n in range(400)) if B.trace_validate(conv, csp, t).body == B.BODY_CONV_STEPS)
+    steps = [[161632], [1, 1, 2, 8], [1, 1, 4, 4], [22, 1, 1, 1], [0], [8], [8], [8], [0], [3], [1]]
+    try:
+        for n, (op, space, t) in enumerate(((gemm, sp, B.make_trace(sp, ring)), (gemm, sp, B.make_trace(sp, steps)), (conv, csp, gather))):
+            at = tmp_path / str(n)
+            at.mkdir()
+            B.set_cache_dir(str(at))
+            B.Variant(op, space, t)
+            found = [_short_waits(str(f)) for f in at.iterdir() if f.suffix == ".hsaco"]
+            assert found and all(loads > 0 and not short for loads, short in found), found
+    finally:
+        B.set_cache_dir(os.environ.get("MS_CACHE_DIR") or os.path.join(ROOT, "paper_2205_13603_amd", "kcache"))
 
 
 @pytest.mark.parametrize("mk,elems", [(lambda: B.conv2d_op(2, 15, 11, 96, 256, 3, 3, stride=2, pad=1), 2 * 8 * 6 * 256),
