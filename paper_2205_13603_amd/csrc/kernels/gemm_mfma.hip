@@ -1500,6 +1500,8 @@ constexpr int P_MB = P_NB / NWAVES, P_MB0 = P_MB < P_LB0 ? P_MB : P_LB0;
 constexpr int P_MSTEP = P_MA0 + P_MA1 + P_MB;
 constexpr int P_STORES = CACHE_WRITE ? TM * J1 * (MI_M * WS_CH / 64) : TM * TN * (ACC_N / 4); // store instructions of an epilogue, at least
 constexpr int vm_cap(int n) { return n > 63 ? 63 : n; }
+constexpr int larger(int a, int b) { return a > b ? a : b; }
+constexpr int P_MOST = larger(larger(P_LA0, P_LA1), larger(P_LB0, P_LB - P_LB0)); // loads of a part: 2 wavefronts and 256 columns have 16
 
 #if CONV_STEPS
 // Convolutions (2-byte, whole 8-channel groups) as products: A's rows are pixels, k = (tap, channel), and a lane's 16 bytes are 8
@@ -1688,7 +1690,7 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
     };
     auto load_part = [&](int p) {
 #pragma unroll
-        for (int l = 0; l < 8; ++l)
+        for (int l = 0; l < P_MOST; ++l)
             if (l < part_loads(p)) load(p, l);
         if (p == 3) advance();
     };

@@ -439,6 +439,11 @@ def test_ping_pong_on_the_ring_exact():
     ("B along k, one slot, 3 stages", "bf16", True, 256, 128, 448, 323216, [1, 1, 2, 4], [1, 1, 4, 1], [7, 1, 2, 2], 8, 1, 3),
     ("int8, 32-row intrinsic", "i8", False, 128, 256, 384, 323232, [1, 1, 2, 2], [1, 1, 4, 2], [3, 1, 2, 2], 8, 1, 2),
     ("int8, rows of B of 3 granules", "i8", False, 96, 96, 256, 161664, [3, 1, 2, 1], [2, 1, 1, 3], [4, 1, 1, 1], 10, 0, 8),
+    ("2 wavefronts, 16 loads of A each", "f16", False, 256, 96, 320, 161632, [1, 1, 2, 8], [3, 1, 1, 2], [10, 1, 1, 1], 10, 0, 4),
+    ("2 wavefronts, 16 loads of B each", "bf16", False, 96, 256, 320, 161632, [3, 1, 1, 2], [1, 1, 2, 8], [10, 1, 1, 1], 9, 1, 4),
+    ("2 wavefronts, B along k, 2 x 16 loads of B each", "f16", True, 32, 512, 256, 161632, [1, 1, 1, 2], [1, 1, 2, 16], [8, 1, 1, 1], 8, 0, 2),
+    ("4 wavefronts, 12 loads of B each", "f16", False, 96, 384, 256, 161632, [6, 1, 1, 1], [1, 1, 4, 6], [8, 1, 1, 1], 10, 0, 3),
+    ("4 wavefronts, 12 loads of A each", "bf16", False, 384, 96, 256, 161632, [1, 1, 4, 6], [3, 1, 1, 2], [8, 1, 1, 1], 10, 0, 3),
 ])
 def test_double_steps_exact(what, dt, nt, M, N, K, mfma, i, j, k, cache, cw, stages):
     """The double-step form of the ping-pong ring, integer-valued inputs with exact sums: slots, stages, operand layouts and

@@ -786,6 +786,26 @@ def test_loads_into_lds_wait_for_their_scalar_operands(tmp_path):
         B.set_cache_dir(os.environ.get("MS_CACHE_DIR") or os.path.join(ROOT, "paper_2205_13603_amd", "kcache"))
 
 
+@pytest.mark.parametrize("M,N,i,j,stages,step", [
+    (256, 96, [1, 1, 2, 8], [3, 1, 1, 2], 4, 18), (96, 256, [3, 1, 1, 2], [1, 1, 2, 8], 4, 18), (32, 512, [1, 1, 1, 2], [1, 1, 2, 16], 2, 34),
+    (96, 384, [6, 1, 1, 1], [1, 1, 4, 6], 3, 12), (384, 96, [1, 1, 4, 6], [3, 1, 1, 2], 3, 13)])
+def test_double_steps_request_every_row_of_a_stage(M, N, i, j, stages, step, tmp_path):
+    """Few wavefronts on a long tile: a wavefront's share of a double step, 1 KiB per load, is in the code once per stage filled
+    ahead and once in each group's loop, however many loads one part of it holds."""
+    op = B.bmm_op(1, M, N, 704, True, "f16")
+    sp = op.space()
+    t = B.make_trace(sp, [[161632], i, j, [22, 1, 1, 1], [0], [10], [8], [8], [0], [3], [0]])
+    p = B.trace_validate(op, sp, t)
+    assert (p.body, p.body_tile) == (B.BODY_DOUBLE_STEPS, stages) and (p.block_m + p.block_n) // (8 * p.waves) == step
+    try:
+        B.set_cache_dir(str(tmp_path))
+        B.Variant(op, sp, t)
+    finally:
+        B.set_cache_dir(os.environ.get("MS_CACHE_DIR") or os.path.join(ROOT, "paper_2205_13603_amd", "kcache"))
+    loads, short = max(_short_waits(str(f)) for f in tmp_path.iterdir() if f.suffix == ".hsaco")
+    assert loads >= (stages + 1) * step and not short
+
+
 @pytest.mark.parametrize("mk,elems", [(lambda: B.conv2d_op(2, 15, 11, 96, 256, 3, 3, stride=2, pad=1), 2 * 8 * 6 * 256),
                                       (lambda: B.conv2d_op(4, 14, 14, 128, 96, 3, 3, pad=2, stride=1, dilation=2), 4 * 196 * 96),
                                       (lambda: B.conv2d_transposed_op(2, 4, 6, 128, 64, 4, 4, stride=2, pad=1), 2 * 96 * 64)])
