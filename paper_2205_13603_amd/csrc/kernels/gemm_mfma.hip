@@ -1243,6 +1243,7 @@ __device__ __forceinline__ pixel_t tile_pixel(int i0, int lr)
     return {u / (CS_PH_W * CS_PH_H), u / CS_PH_W % CS_PH_H, u % CS_PH_W};
 }
 __device__ __forceinline__ bool tile_row_ok(int i0, int lr) { return CS_ROWS % BM == 0 || i0 / (CS_PN * CS_PN) * BM + lr < CS_ROWS; }
+__device__ __forceinline__ bool tile_whole(int i0) { return tile_row_ok(i0, BM - 1); }
 __device__ __forceinline__ long out_row(int i0, int lr)
 {
     if constexpr (CS_PN == 1) return (long)i0 * BM + lr;
@@ -1257,6 +1258,7 @@ __device__ __forceinline__ long out_row(int i0, int lr)
 __device__ __forceinline__ long out_row(int i0, int lr) { return (long)i0 * BM + lr; }
 #endif
 __device__ __forceinline__ constexpr bool tile_row_ok(int, int) { return true; }
+__device__ __forceinline__ constexpr bool tile_whole(int) { return true; }
 #define TILE_BIAS nullptr
 #endif
 
@@ -1498,7 +1500,7 @@ constexpr int P_MA0 = P_NA0 / NWAVES, P_MA1 = P_NA1 / NWAVES;                   
 constexpr int P_LB0 = P_SLOTS == 2 ? P_LB / 2 : P_LB;      // B loads of the first half
 constexpr int P_MB = P_NB / NWAVES, P_MB0 = P_MB < P_LB0 ? P_MB : P_LB0;
 constexpr int P_MSTEP = P_MA0 + P_MA1 + P_MB;
-constexpr int P_STORES = CACHE_WRITE ? TM * J1 * (MI_M * WS_CH / 64) : TM * TN * (ACC_N / 4); // store instructions of an epilogue, at least
+constexpr int P_STORES = CACHE_WRITE ? TM * J1 * (MI_M * WS_CH / 64) : TM * TN * (ACC_N / 4); // store instructions of a whole tile's epilogue, at least
 constexpr int vm_cap(int n) { return n > 63 ? 63 : n; }
 constexpr int larger(int a, int b) { return a > b ? a : b; }
 constexpr int P_MOST = larger(larger(P_LA0, P_LA1), larger(P_LB0, P_LB - P_LB0)); // loads of a part: 2 wavefronts and 256 columns have 16
@@ -1799,7 +1801,9 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
         PHASE_END();
     }
     int rd = 0;
-    bool stores = false; // an epilogue's stores lie between the loads that the next waits count
+    // an epilogue's stores lie between the loads that the next waits count; a partial tile's are not counted: a wavefront with no
+    // pixel left branches around them
+    bool stores = false;
 #pragma unroll 1
     for (long ti = 0; ti < my_tiles; ++ti) {
         const tile_id ct = decode_tile(first + ti * stride, total);
@@ -1878,7 +1882,7 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
         out_t *C = (out_t *)c_ + ((long)ct.inst * DIM_B + ct.bb) * ((long)DIM_M * DIM_N);
         write_tile_wave(acc, C, TILE_BIAS, ct.i0, ct.j0, wstage, lane, wi, wj, lrow, lgrp);
         zero_acc();
-        stores = true;
+        stores = tile_whole(ct.i0);
         PHASE_END();
     }
     if (!late) PHASE_END(); // group 1's last phase

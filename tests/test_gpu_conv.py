@@ -779,6 +779,32 @@ def test_conv_steps_exact(N, H, W_, Cin, Cout, k, stride, pad, dil, transposed):
             assert np.array_equal(got[r], refs[r % 2]), "instance %d of %d" % (r, R)
 
 
+@pytest.mark.parametrize("N,H,W_,Cin,Cout,k,stride,pad,transposed,many", [
+    (2, 8, 7, 64, 32, 3, 1, 1, False, 700),      # one slot, seven stages, the last of eight wavefronts without a pixel
+    (3, 8, 18, 64, 128, 3, 1, 1, False, 120),    # one slot, eight stages of 64 x 64
+    (33, 28, 28, 64, 256, 1, 1, 0, False, 6),    # two slots, two stages, one step per tile, 16 pixels in the last tile
+    (2, 5, 4, 128, 128, 4, 2, 1, True, 150),     # phases of 40 pixels
+])
+def test_conv_steps_partial_tiles_without_bias_exact(N, H, W_, Cin, Cout, k, stride, pad, transposed, many):
+    """Workgroups that go on after a tile whose last wavefronts have nothing to store: the next tile's operands have to have
+    landed all the same.  No bias: nothing else in the epilogue waits for loads."""
+    g = I.rng(109)
+    pool = [(I.small_ints(g, (N, H, W_, Cin), -2, 2, "f16"), I.small_ints(g, (k, k, Cin, Cout), -1, 1, "f16")) for _ in range(2)]
+    ref, mk = (O.conv2d_transposed_nhwc, B.conv2d_transposed_op) if transposed else (O.conv2d_nhwc, B.conv2d_op)
+    refs = [ref(x, w, stride=stride, pad=pad) for x, w in pool]
+    op = mk(N, H, W_, Cin, Cout, k, k, stride=stride, pad=pad, has_bias=False, relu=False, out_dtype="f32")
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 106, n) for n in range(400)) if B.trace_validate(op, space, t).body == B.BODY_CONV_STEPS)
+    p = B.trace_validate(op, space, t)
+    phases = stride * stride if transposed else 1
+    assert N * H * W_ % p.block_m and p.grid[0] * many > 512
+    print("R", many, "tile", p.body_tile, "tiles", p.grid[0], "phases", phases, flush=True)
+    got = run_variant_distinct(op, space, t, [list(pool[r % 2]) for r in range(many)], "f32", refs[0].shape)
+    if got is not None:
+        for r in range(many):
+            assert np.array_equal(got[r], refs[r % 2]), "instance %d of %d" % (r, many)
+
+
 @pytest.mark.parametrize("static", [False, True])
 def test_conv_steps_operands_off_16_byte_boundaries(static):
     """Loads straight into LDS want aligned groups: operands that are aligned to their elements only run on the trace's nest,
