@@ -1566,7 +1566,8 @@ ms_kernel(const void *__restrict__ a_, const void *__restrict__ b_, const void *
         const int h0 = CS_TR ? p.a + phase_add(cls / CS_PN, CS_PAD_H) : p.a * CS_S - CS_PAD_H;
         const int w0 = CS_TR ? p.b + phase_add(cls % CS_PN, CS_PAD_W) : p.b * CS_S - CS_PAD_W;
         constexpr int STEP_H = CS_TR ? -1 : CS_DIL;
-        pix = (unsigned)(((p.n * CS_H + h0) * CS_W + w0) * (CS_C * ES) + PIX_0 + (WHOLE_TAPS ? chunk_k * ES : 0));
+        // unsigned: it may wrap for pixels behind the last, none of whose taps are inside
+        pix = (((unsigned)p.n * CS_H + (unsigned)h0) * CS_W + (unsigned)w0) * (unsigned)(CS_C * ES) + (unsigned)(PIX_0 + (WHOLE_TAPS ? chunk_k * ES : 0));
         in = 0;
         if (tile_row_ok(lt_i0, row)) {
 #pragma unroll

@@ -329,8 +329,11 @@ int conv_steps(const ms_op *op, const ms_variant_params *p)
     // (8 x 14 x 14 x 96 -> 32, 3 x 3: 7.7 and 9.7)
     if ((op->N == 32 && op->K < 512) || (Cin % 64 && op->N < 128 && d.dims[0] > 1 && op->M < 4096)) return 0;
     if (d.dims[5] % S || d.dims[6] % S || op->OH % S || op->OW % S || d.dims[5] / S > 15 || d.dims[6] / S > 15) return 0;
-    // 32-bit byte offsets from the image stack and inside the k-rows of a step
-    if (d.dims[0] * d.dims[1] * d.dims[2] * Cin > 0x3fffffff || (op->K + 64) * op->N > 0x3fffffff) return 0;
+    // 32-bit byte offsets from the image stack and inside the k-rows of a step.  The kernel's offsets start ahead of the stack, by
+    // the padding or by the taps of a phase (PIX_0, TAP_0 in gemm_mfma.hip), and end before the buffer does (0x7ffffff0)
+    const int64_t ahead = (transposed ? (d.dims[5] / S - 1) * d.dims[2] + d.dims[6] / S - 1 : op->pad_h * d.dims[2] + d.pad) * Cin * 2;
+    if (d.dims[0] * d.dims[1] * d.dims[2] * Cin * 2 + ahead > 0x7ffffff0 || (op->K + 64) * op->N > 0x3fffffff) return 0;
+    if (op->M > 0x7fffffff - 256) return 0; // 32-bit numbers of pixels, those of the last tile that are masked among them
     if (g_limits.max_threads < 512 || g_limits.max_waves < 8) return 0;
     int best = 0;
     int64_t cost = 0;

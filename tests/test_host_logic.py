@@ -831,6 +831,24 @@ def test_conv_steps_cover_the_output_and_the_filter_once(mk, elems):
     assert len(keys) == 1
 
 
+@pytest.mark.parametrize("mk,image,ahead,step", [
+    # bytes of one image, those that an offset starts ahead of the images (padding, or the taps of a phase), images per 16 pixels
+    (lambda n: B.conv2d_op(n, 20, 20, 96, 128, 3, 3, stride=1, pad=1), 400 * 96 * 2, 21 * 96 * 2, 1),
+    (lambda n: B.conv2d_op(n, 14, 14, 32, 128, 3, 3, stride=1, pad=2, dilation=2), 196 * 32 * 2, 30 * 32 * 2, 4),
+    (lambda n: B.conv2d_op(n, 16, 16, 256, 128, 1, 1), 256 * 256 * 2, 0, 1),
+    (lambda n: B.conv2d_transposed_op(n, 8, 8, 64, 64, 9, 9, stride=1, pad=4), 64 * 64 * 2, 72 * 64 * 2, 1),
+])
+def test_conv_steps_end_where_their_offsets_do(mk, image, ahead, step):
+    """The gather's 32-bit offsets count from ahead of the image stack: images beyond what they reach keep the nest."""
+    most = (0x7ffffff0 - ahead) // image // step * step
+    for n, taken in ((most, True), (most + step, False)):
+        op = mk(n)
+        sp = op.space()
+        M, N, K = (e for _, e, _ in op.loops())
+        p = B.trace_validate(op, sp, B.make_trace(sp, [[161632], [M // 16, 1, 1, 1], [N // 32, 1, 2, 1], [K // 32, 1, 1, 1], [0], [2], [8], [8], [0], [0], [0], [0]][:sp.n_slots]))
+        assert (p.body == B.BODY_CONV_STEPS) == taken, (n, taken, p.body)
+
+
 def test_few_long_rows_keep_their_wide_lane_groups():
     """Softmax without staging: a few long rows keep a lane group of a wavefront or more per row; many rows, short rows and
     groups that walk a row or several rows in turn go to the row kernel, as do groups narrower than a line."""
