@@ -522,7 +522,9 @@ int32_t ms_jit_stats(int64_t *compiled, int64_t *from_disk, int64_t *from_memory
  * workspace_bytes (ms_variant_info), owned by the caller and not shared with a
  * launch that may run at the same time; NULL if that is 0.  Its contents need no
  * initialisation and are undefined afterwards.  Asynchronous (a variant with
- * rfactor > 1 enqueues two kernels); returns launch errors only.  BAD_ARG if
+ * rfactor > 1 enqueues two kernels); returns launch errors only.  The first launch of a variant on a device loads its
+ * kernels there.  A variant of MS_BODY_CONV_STEPS whose operands are off 16-byte boundaries runs its nest, which the first such
+ * launch compiles unless ms_variant_prepare has: under graph capture or where a pause hurts, prepare first.  BAD_ARG if
  * instances < 1, the grid would exceed 2^31-1 workgroups, or a needed workspace is NULL. */
 int32_t ms_variant_launch(ms_variant *v, const void *const *inputs, void *const *outputs,
                           void *workspace, int32_t instances, void *stream);
@@ -532,11 +534,13 @@ int32_t ms_variant_launch(ms_variant *v, const void *const *inputs, void *const 
  * hipMalloc): ms_variant_launch with the workspace taken from an array inside the library's own device image
  * instead of from the caller.  MS_STATIC_WORKSPACE_BYTES of it exist on every GPU the library runs on, from the first
  * ms_variant_prepare on that GPU until the process ends.
- *   ms_variant_prepare        set-up, may allocate: loads the variant's kernels on the current device and resolves
- *                             that device's copy of the workspace.  Once per variant and device.
+ *   ms_variant_prepare        set-up, may allocate: builds and loads every kernel that a launch of the variant
+ *                             may run on the current device and resolves that device's copy of the workspace.  Once per
+ *                             variant and device.
  *   ms_variant_launch_static  allocates nothing and frees nothing.  Same inputs / outputs / instances / stream as
  *                             ms_variant_launch.  BAD_ARG if ms_variant_prepare has not run for this variant on the
- *                             current device, or if instances x workspace_bytes exceeds MS_STATIC_WORKSPACE_BYTES
+ *                             current device (or a launch on another device has taken the kernel there since), or if
+ *                             instances x workspace_bytes exceeds MS_STATIC_WORKSPACE_BYTES
  *                             (a variant with rfactor = 1 needs none and always fits).
  * All calls on one GPU share that GPU's array, which keeps the previous call's partial sums: every value a call
  * reads it has written itself, so nothing needs clearing, but two calls that overlap on one GPU (two streams, two

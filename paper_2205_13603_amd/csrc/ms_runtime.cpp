@@ -203,15 +203,15 @@ extern "C" int32_t ms_prebuild(const ms_op *op, const ms_space *space, const ms_
     return MS_OK;
 }
 
-static int32_t ensure_loaded(ms_variant *v)
+// Loads the kernels of a variant on device `dev`, the current one: also that of few tiles, whichever a launch takes, so that a
+// variant that has been launched once loads nothing more on that device.
+static int32_t ensure_loaded(ms_variant *v, int dev)
 {
-    int dev = 0;
-    HIP_TRY(hipGetDevice(&dev));
-    if (v->device == dev) return MS_OK;
     if (v->few) {
-        const int32_t rc = ensure_loaded(v->few);
+        const int32_t rc = ensure_loaded(v->few, dev);
         if (rc != MS_OK) return rc;
     }
+    if (v->device == dev) return MS_OK;
     if (v->mod) {
         (void)hipModuleUnload(v->mod);
         v->mod = nullptr;
@@ -250,6 +250,22 @@ static int32_t nest_of(ms_variant *v, ms_variant **nest)
     return MS_OK;
 }
 
+// The variant whose kernel a launch runs: the one for few tiles, the nest, else `v` itself.  Null where that is a nest nobody has
+// built yet and `build` is false.
+static int32_t runs(ms_variant *v, const void *const *inputs, int32_t instances, bool build, ms_variant **out)
+{
+    *out = v;
+    if (v->few && takes_few(&v->op, &v->p, &v->few->p, instances)) {
+        *out = v->few;
+    } else if (v->p.body == MS_BODY_CONV_STEPS && (((uintptr_t)inputs[0] | (uintptr_t)inputs[1]) & 15u)) {
+        // loads straight into LDS move aligned 16-byte groups; the nest's loads go through registers and take any address
+        if (build) return nest_of(v, out);
+        std::lock_guard<std::mutex> lk(v->nest_mu);
+        *out = v->nest;
+    }
+    return MS_OK;
+}
+
 // ---------------------------------------------------------------- launch without allocation
 //
 // Workspace of ms_variant_launch_static: one array per GPU, in the library's own device image, held until the
@@ -285,12 +301,14 @@ int32_t scratch_on_current_device(bool resolve, void **out)
 extern "C" int32_t ms_variant_prepare(ms_variant *v)
 {
     if (!v) return fail(MS_ERR_BAD_ARG, "ms_variant_prepare: NULL variant");
-    int32_t rc = ensure_loaded(v);
+    int dev = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    int32_t rc = ensure_loaded(v, dev);
     if (rc != MS_OK) return rc;
     if (v->p.body == MS_BODY_CONV_STEPS) { // a launch may bring operands of any address, and must not build or load anything
         ms_variant *nest;
         rc = nest_of(v, &nest);
-        if (rc == MS_OK) rc = ensure_loaded(nest);
+        if (rc == MS_OK) rc = ensure_loaded(nest, dev);
         if (rc != MS_OK) return rc;
     }
     void *ptr = nullptr;
@@ -303,7 +321,10 @@ extern "C" int32_t ms_variant_launch_static(ms_variant *v, const void *const *in
     if (instances < 1) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_static: instances = %d", instances);
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
-    if (v->device != dev || !v->fn) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_static: call ms_variant_prepare on device %d first (loading a kernel allocates)", dev);
+    ms_variant *run = v;
+    if (inputs[0] && (v->p.family == MS_FAM_REDUCE || inputs[1])) (void)runs(v, inputs, instances, false, &run);
+    if (v->device != dev || !v->fn || !run || run->device != dev || !run->fn)
+        return fail(MS_ERR_BAD_ARG, "ms_variant_launch_static: call ms_variant_prepare on device %d first (loading a kernel allocates)", dev);
     const size_t need = workspace_per_instance(v) * (size_t)instances;
     if (need > (size_t)MS_STATIC_WORKSPACE_BYTES)
         return fail(MS_ERR_BAD_ARG, "ms_variant_launch_static: %d instances need a workspace of %zu bytes, the built-in one holds %zu",
@@ -331,16 +352,13 @@ extern "C" int32_t ms_variant_launch(ms_variant *v, const void *const *inputs, v
     uint64_t gz = (uint64_t)v->spec.grid[2] * (uint64_t)instances;
     if (gz > 65535ull * 32768ull || (uint64_t)v->spec.grid[0] * gz > 0x7fffffffull)
         return fail(MS_ERR_BAD_ARG, "ms_variant_launch: %d instances overflow the grid", instances);
-    if (v->few && takes_few(&v->op, &v->p, &v->few->p, instances)) return ms_variant_launch(v->few, inputs, outputs, workspace, instances, stream);
-    if (v->p.body == MS_BODY_CONV_STEPS && (((uintptr_t)inputs[0] | (uintptr_t)inputs[1]) & 15u)) {
-        // loads straight into LDS move aligned 16-byte groups; the nest's loads go through registers and take any address
-        ms_variant *nest;
-        const int32_t rc = nest_of(v, &nest);
-        if (rc != MS_OK) return rc;
-        return ms_variant_launch(nest, inputs, outputs, workspace, instances, stream);
-    }
-    int32_t rc = ensure_loaded(v);
+    int dev = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    ms_variant *run = v;
+    int32_t rc = runs(v, inputs, instances, true, &run);
+    if (rc == MS_OK) rc = ensure_loaded(run == v->few ? v : run, dev);
     if (rc != MS_OK) return rc;
+    if (run != v) return ms_variant_launch(run, inputs, outputs, workspace, instances, stream);
     const void *in0 = inputs[0], *in1 = one_input ? nullptr : inputs[1];
     const void *in2 = nullptr;
     if (is_conv2d(v->op.d.kind) && v->op.d.has_bias) {

@@ -29,3 +29,18 @@ def test_host_logic_and_oracle_under_asan_ubsan(tmp_path):
     sys.stdout.write(r.stdout[-2000:])
     assert r.returncode == 0, r.stdout[-6000:]
     assert "sanitized host checks ok" in r.stdout
+
+
+def test_launches_build_and_load_what_their_contract_says(tmp_path):
+    """Variant handles on a stand-in for HIP that keeps book of modules and devices: a static launch loads nothing, whatever ran
+    on another device in between, and set-up readies every kernel that a launch may take."""
+    exe = str(tmp_path / "ms_launches")
+    srcs = [os.path.join(CSRC, f) for f in ("ms_core.cpp", "ms_interp.cpp", "ms_model.cpp", "ms_search.cpp", "ms_runtime.cpp")]
+    r = subprocess.run(["g++", "-std=c++17", "-g", "-O1", "-fno-omit-frame-pointer", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                        "-D__HIP_PLATFORM_AMD__", "-D__align__(n)=", "-DHIP_SYMBOL(x)=(&x)", "-I", "/opt/rocm/include", "-o", exe] + srcs +
+                       [os.path.join(ROOT, "tests", "sanitize", "launch_driver.cpp"), "-lm", "-lpthread"], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-4000:]
+    env = dict(os.environ)
+    env.pop("LD_PRELOAD", None)
+    r = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, env=env, timeout=600)
+    assert r.returncode == 0 and "launch checks ok" in r.stdout, r.stdout[-6000:]
