@@ -1270,7 +1270,15 @@ constexpr int CROW = BN * (int)sizeof(out_t) + 16; // bytes of one staged output
 constexpr int PIECE_BYTES = BN * (int)sizeof(out_t);
 constexpr bool STREAM_ROWS = BN == LDC || (PIECE_BYTES % 128 == 0 && PIECE_BYTES >= 256 && LDC * (int)sizeof(out_t) % 128 == 0);
 // instances from which on a launch streams
-constexpr int STREAM_FROM = stream_from((long)DIM_B * DIM_M * DIM_N * sizeof(out_t));
+constexpr long OUT_BYTES = (long)DIM_B * DIM_M * DIM_N * sizeof(out_t), ALL_BYTES = ((long)A_INST + B_INST) * ES + OUT_BYTES;
+constexpr int STREAM_FROM = stream_from(OUT_BYTES);
+// and up to which.  Workgroups of at most 8 wavefronts gain at every size.  Of larger ones one or two fit a compute unit and nothing
+// runs beside their stores: launches that move more than the 256 MB of the last-level cache turn over lose, and the earlier the less
+// of the bytes are results (12 heads, 64 values each; scores of 144 x 144, 9 wavefronts: x 100 21.3 us against 24.8 plain, x 320 60 and
+// 64, x 512 105 and 97; of 208 x 208, 13 wavefronts: x 200 55 and 71, x 400 127 and 128, x 512 158 and 156; of 208 x 208 in 32 values
+// x 512: 116 and 121; probabilities of 160 x 160 by values, 10 wavefronts: x 64 18.5 and 19.0, x 256 63 and 61, x 512 118 and 113).
+constexpr long STREAM_MOST = OUT_BYTES * 5 >= ALL_BYTES * 3 ? 700000000l : OUT_BYTES * 5 >= ALL_BYTES * 2 ? 350000000l : 200000000l;
+constexpr int STREAM_TO = NWAVES > 8 ? (int)(STREAM_MOST / ALL_BYTES) : 0x7fffffff;
 
 // second half of the CACHE_WRITE epilogue: NT threads (t = 0 .. NT-1) write the staged tile as whole rows
 template <int NT, bool STREAM>
@@ -1293,8 +1301,8 @@ template <int NT>
 __device__ __forceinline__ void flush_cstage(out_t *__restrict__ C, int i0, int j0, const char *__restrict__ cstage, int t, int instances)
 {
     if constexpr (!STREAM_ROWS) flush_rows<NT, false>(C, i0, j0, cstage, t);
-    else if constexpr (STREAM_FROM <= 1) flush_rows<NT, true>(C, i0, j0, cstage, t);
-    else if (instances >= STREAM_FROM) flush_rows<NT, true>(C, i0, j0, cstage, t);
+    else if constexpr (STREAM_FROM <= 1 && NWAVES <= 8) flush_rows<NT, true>(C, i0, j0, cstage, t);
+    else if (instances >= STREAM_FROM && instances <= STREAM_TO) flush_rows<NT, true>(C, i0, j0, cstage, t);
     else flush_rows<NT, false>(C, i0, j0, cstage, t);
 }
 
@@ -1416,6 +1424,10 @@ constexpr int WS_SWZ = (WS_CH & (WS_CH - 1)) == 0 ? (WS_CH > 8 ? 7 : WS_CH - 1) 
 constexpr int WS_BYTES = CACHE_WRITE ? MI_M * WS_ROW : 0;
 static_assert(!CACHE_WRITE || WS_ROW % 16 == 0, "staged output rows are whole 16-byte chunks");
 
+// Staged rows of a wavefront's own columns are streamed whatever their size: half lines (64 columns of a wavefront and less) and small
+// launches take the same time either way (512 x 512 x 512: 5.50 us both; 14 x 14 x 128 -> 128, batch 16: 10.26 both), large ones gain
+// (1024 x 1024 x 256 x 64: 41.7 us, 53.5 plain; int8 256 x 256 x 256 x 512: 33 and 48; 40 x 40 x 128 -> 256, 1 x 1, batch 88: 22 and 31)
+// or lose 1 % at most (1024 x 1024 x 1024 x 64: 127.9 and 126.6).
 __device__ __forceinline__ void write_tile_wave(accv_t (&acc)[TM][TN], out_t *__restrict__ C, const float *__restrict__ bias, int i0, int j0,
                                                 char *__restrict__ wstage, int lane, int wi, int wj, int lrow, int lgrp)
 {
@@ -1472,7 +1484,7 @@ __device__ __forceinline__ void write_tile_wave(accv_t (&acc)[TM][TN], out_t *__
 
 #if PP_STAGES
 // --------------------------------------------------------------------------------------
-// Double k steps (PP_STAGES > 0, the number of LDS stages; the host's rule is ring_pairs() in ms_interp.cpp).
+// Double k steps (PP_STAGES > 0, the number of LDS stages; the host's rule is double_steps() in ms_interp.cpp).
 //
 // Two k0 steps of the ring are one stage of 128-byte rows, so that every load of a k-contiguous operand covers whole
 // cache lines.  A double step is PP_SLOTS slots; slot 0 reads all B fragments of the step and those of the first A tiles,

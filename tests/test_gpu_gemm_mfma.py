@@ -222,6 +222,23 @@ def test_bmm_instances_with_distinct_inputs():
             compare.assert_float_close(got[r], refs[r], compare.RTOL_HALF, "instance %d trace %d" % (r, n))
 
 
+@pytest.mark.parametrize("many", [8, 9, 372, 373])
+def test_whole_rows_of_large_workgroups_exact(many):
+    """Nine wavefronts that write whole rows: from 9 instances (4 MiB of results) to 372 (350 MB in all) the stores are streamed,
+    below and beyond they are not."""
+    g = I.rng(111)
+    pool = [(I.small_ints(g, (12, 144, 64), -2, 2, "f16"), I.small_ints(g, (12, 144, 64), -2, 2, "f16")) for _ in range(2)]
+    refs = [O.bmm(a, b, trans_b=True) for a, b in pool]
+    op = B.bmm_op(12, 144, 144, 64, True, "f16")
+    space = op.space()
+    t = B.make_trace(space, [[161632], [1, 1, 9, 1], [1, 9, 1, 1], [1, 1, 2, 1], [16], [1], [8], [8], [0], [0], [1]])
+    assert B.trace_validate(op, space, t).waves == 9
+    got = run_variant_distinct(op, space, t, [list(pool[r % 2]) for r in range(many)], "f16", refs[0].shape)
+    if got is not None:
+        for r in range(many):
+            assert np.array_equal(got[r], refs[r % 2]), "instance %d of %d" % (r, many)
+
+
 def test_persistent_workgroups_many_tiles_per_workgroup():
     """reorder = 3: 3 instances x 256 tiles = 768 tiles for at most 256 workgroups, so every workgroup walks
     through several tiles, crossing instance boundaries; distinct inputs per instance; fp32 output."""
