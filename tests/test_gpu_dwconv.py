@@ -76,9 +76,11 @@ def test_depthwise_strips_exact(H, W_, Cc, stride, pad, k):
         assert np.array_equal(got[r], refs[r]), "instance %d" % r
 
 
-@pytest.mark.parametrize("N,H,W_,Cc,stride,pad,k", [(65, 8, 8, 256, 1, 1, 3), (58, 9, 10, 128, 1, 2, 5), (80, 30, 16, 104, 2, 1, 3)])
+@pytest.mark.parametrize("N,H,W_,Cc,stride,pad,k", [(65, 8, 8, 256, 1, 1, 3), (58, 9, 10, 128, 1, 2, 5), (80, 30, 16, 104, 2, 1, 3),
+                                                    (50, 37, 37, 72, 1, 1, 3), (51, 37, 37, 72, 1, 1, 3), (32, 57, 57, 40, 2, 1, 3)])
 def test_large_depthwise_launches_exact(N, H, W_, Cc, stride, pad, k):
-    """Extents with divisors from 3 to 8 in launches large enough for strips; integer-valued inputs -> exact."""
+    """Extents with divisors from 3 to 8 in launches large enough for strips; results below and above the 20 MB from which pixels that
+    share lines are streamed, and with stride 2 above 4 MiB; integer-valued inputs -> exact."""
     g = I.rng(6)
     ins = [[I.small_ints(g, (N, H, W_, Cc), -3, 3, "f32"), I.small_ints(g, (k, k, Cc), -3, 3, "f32")]]
     ref = O.dwconv2d_nhwc(*ins[0], stride=stride, pad=pad)
