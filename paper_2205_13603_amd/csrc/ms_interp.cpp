@@ -244,11 +244,14 @@ int conv_phases(const ms_op *op, const ms_variant_params *p)
 // 0 = not taken.  Taken for every ring of 64- or 128-byte k tiles under the ping-pong order (cache_read 8, 9, 10) whose reduction is
 // whole 128-byte rows: a load of a k-contiguous operand then covers whole cache lines (46.6 bytes per clock and compute unit
 // from the L2 to LDS, 34 to 39 with rows of 64 bytes), and a stage is refilled part by part, up to four times as early.
-// 1024 x 1024 x 1024 fp16 x 64: 168 -> 113 us, 4096^3 bf16: 121 -> 95.
+// 1024 x 1024 x 1024 fp16 x 64: 154 -> 130 us, 4096^3 bf16: 123 -> 97.
 // The intrinsic is the 16-row one of the same wave tile: a launch that keeps the matrix cores busy is held by the power it
 // draws, and the 16-row forms run it at 1.84 GHz where the 32-row forms run at 1.62 (bf16 4096^3: 97.5 and 104 us).
 // As many stages as the LDS takes, up to eight: small tiles multiply a step in one phase (rows of one slot) and need three, and
 // a step of theirs takes less than a round trip to memory.
+// Wave tiles that fill the register file spill here, as they do in the nest; of 22 such tiles timed on both, 20 are faster here (256 x 256
+// of 4 x 8 tiles per wavefront, fp16 1024^3 x 64: 142 us, 150 in the nest; four wavefronts of 9 x 6: 145 and 229), two of int8 slower
+// (ten wavefronts of 3 x 5: 230 and 206; 10 x 3: 219 and 214).
 int64_t double_step_rows(const ms_variant_params *p) { return (int64_t)p->ti[1] * p->ti[3] * (p->tile_unit[0] / 16); } // 16-row tiles of a wavefront
 int64_t double_step_staging(const ms_op *op, const ms_variant_params *p) // bytes of the staged output rows of all wavefronts
 {
