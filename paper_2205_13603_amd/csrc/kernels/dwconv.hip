@@ -31,13 +31,15 @@ constexpr int SP_H = (STRIP - 1) * CV_STRIDE + CV_KH, SP_W = (STRIP - 1) * CV_ST
 constexpr int S_OH = (CV_OH + STRIP - 1) / STRIP, S_OW = (CV_OW + STRIP - 1) / STRIP;           // strips of an image
 constexpr int IMG_BYTES = CV_H * CV_W * CV_C * 4;
 
-// Results of 4 MiB and more are streamed where a pixel's channels are whole 128-byte lines (200 launches measured, 3 x 3 on 57 x 57 x 128,
-// batch 145: 89.2 us, plain 90.7) or the stride leaves a quarter of the stores (1 to 11 % faster).  At stride 1 the pixels of other
-// channel counts share lines; wavefronts that stream them write such a line in pieces (57 x 57 x 24, batch 49: 9.85 us, 8.67 plain; 57 x 57
-// x 72, batch 257: 129 and 120), which pays only for results about the size of the eight L2s, 32 MiB: kept there they are written back
-// when nothing else runs any more (57 x 57 x 72, batch 33, 31 MB: 13.1 us, 19.2 plain).
+// Results of 4 MiB and more are streamed (200 launches measured on both sides; 57 x 57 x 144, stride 2, batch 128: 56.8 us, plain 60.2).
+// Not where small filters of stride 1 leave a pixel less than three lines and part of one: neighbouring pixels share lines, which
+// streaming wavefronts write in pieces, with few loads to hide it (3 x 3, 57 x 57 x 24, batch 49: 9.85 us, 8.67 plain; 57 x 57 x 72, batch 257:
+// 129 and 120; 104 channels and more, or 5 x 5: within 5 % either way, 1 and 2 % faster in the mean).  Around the size of the eight L2s,
+// 32 MiB, streaming pays all the same: kept there, results are written back when nothing else runs any more (57 x 57 x 72, batch 33, 31 MB:
+// 13.1 us, 19.2 plain; at 60 MB either side wins by up to 9 %).
 constexpr long OUT_BYTES = (long)CV_N * CV_OH * CV_OW * CV_C * 4;
-constexpr bool STREAM = stream_from(OUT_BYTES) <= 1 && (CV_C % 32 == 0 || CV_STRIDE > 1 || (OUT_BYTES >= 20000000 && OUT_BYTES <= 50000000));
+constexpr bool SHARED_LINES = CV_STRIDE == 1 && CV_KH * CV_KW < 25 && CV_C % 32 != 0 && CV_C < 96;
+constexpr bool STREAM = stream_from(OUT_BYTES) <= 1 && (!SHARED_LINES || (OUT_BYTES >= 20000000 && OUT_BYTES <= 100000000));
 
 extern "C" __global__ void __launch_bounds__(STRIP_THREADS)
 ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *__restrict__ unused_, void *__restrict__ y_, int instances)
