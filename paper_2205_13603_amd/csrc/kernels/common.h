@@ -116,3 +116,60 @@ template <class T> __device__ __forceinline__ void store_stream(void *dst, const
 // nothing and the caches join the pieces of a line (softmax 896 x 1456 in bf16: 3.40 us, 3.48 streamed; 16 x 64 x 64 scores x 3:
 // 2.25, 2.45).
 constexpr int stream_from(long bytes_per_instance) { return (int)(((4l << 20) + bytes_per_instance - 1) / bytes_per_instance); }
+
+// ---- loads straight into LDS
+//
+// 16 bytes per lane from `base` (wave-uniform) + `voff` to `dst` (wave-uniform) + 16 * lane.  Written as assembly so that the
+// compiler does not see a write to LDS: before every LDS read behind the builtin it waits until all such loads have landed
+// (one s_waitcnt vmcnt(0) per k step, which drains the ring).  No register is written; the landing of a load is waited for by
+// count (DL_WAIT_VM) and published by a barrier.  M0 holds the LDS address.
+// A scalar register that a vector instruction has written (v_readfirstlane, or v_readlane where the compiler spilled it) takes
+// five wait states before a vector-memory instruction may read it.  The compiler keeps this rule for its own loads but does not
+// see one inside the asm, so the asm keeps it: a plain load reads a copy made by the scalar unit, which no rule delays, and a
+// gather spends the wait on its own index arithmetic (bf16 4096^3: 97.1 us, 98.6 with s_nop 3 instead, 96.4 without any wait;
+// transposed 16 x 16 x 256 -> 128, 4 x 4, batch 64: 20.6, 21.0, 20.5).  M0 takes one wait state before the load.
+// Operands of the loads below that have to sit in scalar registers: equal in all lanes by construction, but the compiler keeps
+// some of them (a base chosen by a wave's number, an LDS address of a deep ring) in vector registers and then rejects the asm.
+__device__ __forceinline__ unsigned uniform(unsigned x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ unsigned long uniform(const char *p)
+{
+    const unsigned long a = (unsigned long)p;
+    return (unsigned long)uniform((unsigned)(a >> 32)) << 32 | uniform((unsigned)a);
+}
+__device__ __forceinline__ unsigned lds_address(const char *p) { return uniform((unsigned)(size_t)(const __attribute__((address_space(3))) char *)p); }
+__device__ __forceinline__ void load_lds16(const char *base, unsigned voff, const char *dst)
+{
+    unsigned long copy;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+                 : "=&s"(copy) : "s"(lds_address(dst)), "v"(voff), "s"(uniform(base)) : "memory", "m0");
+}
+
+// The same from a buffer at `base`: `voff` per lane, `soff` wave-uniform.  Lanes that ask for OUTSIDE write zeros (a range-checked
+// load beyond the buffer returns zero, into LDS too).
+constexpr unsigned OUTSIDE = 0x80000000u;
+typedef unsigned rsrc_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ rsrc_t buffer_at(const char *base, unsigned bytes = 0x7ffffff0u)
+{
+    const unsigned long b = uniform(base);
+    return {(unsigned)b, (unsigned)(b >> 32) & 0xffffu, uniform(bytes), 0x00020000u};
+}
+__device__ __forceinline__ void gather_lds16(const rsrc_t &buffer, unsigned voff, const char *dst)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 : : "s"(lds_address(dst)), "v"(voff), "s"(buffer) : "memory", "m0");
+}
+__device__ __forceinline__ void gather_lds16(const char *base, unsigned voff, unsigned soff, const char *dst)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 : : "s"(lds_address(dst)), "v"(voff), "s"(buffer_at(base)), "s"(uniform(soff)) : "memory", "m0");
+}
+// voff where all bits of `want` are set in `have`, else OUTSIDE.  A mask in VCC takes two wait states before it is read.
+__device__ __forceinline__ void gather_lds16(const char *base, unsigned voff, unsigned have, unsigned want, unsigned soff, const char *dst)
+{
+    unsigned at;
+    asm volatile("s_mov_b32 m0, %1\n\tv_and_b32 %0, %3, %4\n\tv_cmp_eq_u32 vcc, %0, %4\n\tv_mov_b32 %0, 0x80000000\n\t"
+                 "s_nop 0\n\tv_cndmask_b32 %0, %0, %2, vcc\n\tbuffer_load_dwordx4 %0, %5, %6 offen lds"
+                 : "=&v"(at) : "s"(lds_address(dst)), "v"(voff), "v"(have), "v"(want), "s"(buffer_at(base)), "s"(uniform(soff)) : "memory", "m0", "vcc");
+}
+// wait until at most `n` of this wavefront's vector-memory operations are outstanding
+#define DL_WAIT_VM(n) __builtin_amdgcn_s_waitcnt((((n) & 15) | (((n) >> 4) << 14) | (7 << 4) | (15 << 8)))

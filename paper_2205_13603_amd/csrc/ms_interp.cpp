@@ -354,6 +354,103 @@ int conv_steps(const ms_op *op, const ms_variant_params *p)
     return best;
 }
 
+// MS_BODY_CONV_PATCH: convolutions of stride 1 from input patches in LDS (conv_patch.hip), the second kernel of a convolution's
+// variant (conv_patch_many, takes_patch).  Not for filters of one column, which read every input once, nor for strides: of nine layers
+// at stride 2 four were slower than their nests and gathers (48 x 48 x 64 -> 64, batch 512: 46.6 us and 52.9; 20 x 20 x 256 -> 256, batch
+// 176: 34.5 and 44.9), and transposed ones by phases share too few taps (16 x 16 x 256 -> 128, 4 x 4, batch 64: 22.0 and 27.3).
+constexpr int CONV_PATCH_MANY = 1 << 25; // in a tile's code: chosen for launches over many instances too
+struct ConvPatch {
+    int cw, r, tn;                   // a wavefront's tile: a strip of cw columns (of 16 / cw bands of rows), rows, 16-channel tiles
+    int ws, wr, wj;                  // wavefronts over strips, rows and channels
+    bool whole;                      // a tile is whole images
+    int rows, imgs;                  // rows of an image, images of a tile
+    int64_t tiles;                   // of one instance
+    int64_t patch, weights, lds;     // bytes of a patch, of a step's weights, of a workgroup
+    int loads;                       // load instructions of a patch and of a step's weights
+    int waves, per_cu;               // that multiply, of a workgroup; workgroups on a compute unit
+    int64_t clocks;                  // estimate for a tile
+    int code() const { return cw | r << 5 | tn << 13 | wr << 16 | wj << 20 | whole << 24; }
+};
+ConvPatch conv_patch_tile(const ms_op *op, int code)
+{
+    const ms_op_desc &d = op->d;
+    ConvPatch c;
+    c.cw = code & 31;
+    c.r = code >> 5 & 31;
+    c.tn = code >> 13 & 7;
+    c.wr = code >> 16 & 15;
+    c.wj = code >> 20 & 7;
+    c.whole = code >> 24 & 1;
+    const int64_t dil = std::max(1, (int)d.dilation), th = d.dims[5], tw = d.dims[6], oh = op->OH, ow = op->OW;
+    const int bands = 16 / c.cw;
+    c.rows = c.whole ? (int)oh : bands * c.wr * c.r;
+    c.imgs = c.whole ? bands * c.wr : 1;
+    c.ws = (int)((ow + c.cw - 1) / c.cw);
+    c.waves = c.ws * c.wr * c.wj;
+    const int64_t bn = c.wj * c.tn * 16, pw = ow + (tw - 1) * dil, slots = c.imgs * (c.rows + (th - 1) * dil) * (c.cw == 4 ? pw | 1 : pw);
+    c.patch = (slots + 15) / 16 * 1024;
+    c.weights = th * 32 * bn * 2;
+    c.loads = (int)((c.patch + c.weights) / 1024);
+    c.lds = 2 * c.patch + 3 * c.weights + (d.has_bias ? 2048 : 0) + 128;
+    c.per_cu = 2 * c.lds <= 160 * 1024 && c.waves <= 5 ? 2 : 1;
+    c.tiles = (c.whole ? (d.dims[0] + c.imgs - 1) / c.imgs : d.dims[0] * ((oh + c.rows - 1) / c.rows)) * (op->N / bn);
+    // a step: products of the wavefronts of a SIMD, their LDS reads at 128 bytes per clock, loads into LDS at 36
+    const int64_t per_simd = (c.waves * c.per_cu + 3) / 4, rows_read = c.r + (th - 1) * dil;
+    const int64_t chunks = d.dims[3] / 32, mfma = th * c.r * c.tn * 16, step = per_simd * mfma * 11 / 8 + 400;
+    const int64_t lds = (rows_read + th * c.tn) * 8 * c.waves * c.per_cu, fill = (c.patch / tw + c.weights) / 34 * c.per_cu;
+    c.clocks = chunks * tw * std::max({step, lds, fill, (int64_t)1200}) * (c.per_cu == 2 ? 27 : 20) / 20 + per_simd * c.r * c.tn * 88 + 500;
+    return c;
+}
+int conv_patch(const ms_op *op)
+{
+    const ms_op_desc &d = op->d;
+    if (!is_conv2d(d.kind) || op->nb != 1 || is_3d(op) || op->in_size != 2 || op->out_size != 2 || d.dims[3] % 32) return 0;
+    if (d.stride > 1 || d.dims[6] < 2 || d.dims[6] > 15 || d.dims[5] > 15) return 0;
+    // 32-bit byte offsets inside a filter; images of a tile, with what lies ahead of and behind them, below half of that
+    if (op->K * op->N > 0x3fffffff) return 0;
+    const int64_t oh = op->OH, images = std::max(d.dims[1] * d.dims[2] * d.dims[3], oh * op->OW * op->N) * 2;
+    const int64_t ahead = (d.dims[5] * std::max(1, (int)d.dilation) + oh) * d.dims[2] * d.dims[3] * 2;
+    int best = 0, best_many = 0; // for one instance, for many
+    double cost = 0, cost_many = 0;
+    for (int tn : {4, 2})
+        for (int wj = 1; wj <= 4; ++wj) {
+            if (op->N % (wj * tn * 16) || (tn == 2 && op->N % 64 == 0 && wj % 2)) continue; // 32 channels of a line of 64: both halves here
+            for (int cw : {16, 8, 4})
+                for (int64_t r = 1; r <= std::min<int64_t>(16, oh); ++r)
+                    for (int wr = 1; wr <= 8; ++wr)
+                        for (int whole = 0; whole <= (r == oh); ++whole) {
+                            const int bands = 16 / cw;
+                            if (whole ? bands * wr > d.dims[0] : (bands * wr - 1) * r >= oh) continue; // wavefronts with nothing to do
+                            ConvPatch t{};
+                            t.cw = cw;
+                            t.r = (int)r;
+                            t.tn = tn;
+                            t.wr = wr;
+                            t.wj = wj;
+                            t.whole = whole;
+                            const ConvPatch c = conv_patch_tile(op, t.code());
+                            const int per_simd = (c.per_cu * (c.waves + 1) + 3) / 4;
+                            if (c.waves > 15 || c.waves < 2 || c.waves >= g_limits.max_waves || (c.waves + 1) * 64 > g_limits.max_threads) continue;
+                            if (c.lds > g_limits.max_lds_bytes || c.loads > 150) continue; // a register of the loads' wavefront for each
+                            // sums, a step's weights and about 60 others
+                            if (r * tn * 4 + d.dims[5] * tn * 4 + 60 > 512 / per_simd / 8 * 8 || r * tn * 4 > g_limits.max_acc_per_thread) continue;
+                            if (c.imgs * images + ahead > 0x3fffffff || c.tiles > 0x7fffffff) continue;
+                            const int64_t slots = 256 * c.per_cu;
+                            const double clocks = (double)((c.tiles + slots - 1) / slots) * c.clocks, many = (double)c.tiles / slots * c.clocks;
+                            if (!best || clocks < cost) {
+                                best = c.code();
+                                cost = clocks;
+                            }
+                            if (!best_many || many < cost_many) {
+                                best_many = c.code();
+                                cost_many = many;
+                            }
+                        }
+        }
+    // single images come in many instances; a batch as one
+    return d.dims[0] == 1 || best == best_many ? best_many | CONV_PATCH_MANY : best;
+}
+
 void set4(int32_t *f, int64_t f0, int64_t f1, int64_t f2, int64_t f3)
 {
     f[0] = (int32_t)f0;
@@ -958,6 +1055,54 @@ bool ms::takes_few(const ms_op *op, const ms_variant_params *p, const ms_variant
     return double_step_cost(op, few, instances) * 10 < double_step_cost(op, p, instances) * 9;
 }
 
+bool ms::conv_patch_many(const ms_op *op, const ms_variant_params *p, ms_variant_params *patch)
+{
+    if (p->family != MS_FAM_GEMM_MFMA || p->body == MS_BODY_IMAGE_ROWS) return false;
+    const int tile = conv_patch(op);
+    if (!tile) return false;
+    const ConvPatch c = conv_patch_tile(op, tile);
+    *patch = *p;
+    patch->body = MS_BODY_CONV_PATCH;
+    patch->body_tile = tile;
+    patch->block_m = c.ws * c.wr * c.r * 16;
+    patch->block_n = c.wj * c.tn * 16;
+    patch->block_k = (int32_t)op->d.dims[5] * 32;
+    patch->grid[0] = (int32_t)c.tiles;
+    patch->grid[1] = patch->grid[2] = 1;
+    patch->waves = c.waves + 1;
+    patch->threads = patch->waves * 64;
+    patch->acc_per_thread = c.r * c.tn * 4;
+    patch->lds_bytes = (int32_t)c.lds;
+    patch->compute_at = patch->rfactor = 0;
+    patch->reorder = 3;
+    patch->key = hash_params(op, patch);
+    return true;
+}
+
+bool ms::takes_patch(const ms_op *op, const ms_variant_params *p, const ms_variant_params *patch, int64_t instances)
+{
+    // its wavefronts count steps in 32 bits
+    const int64_t tiles = (int64_t)patch->grid[0] * instances;
+    if (tiles * op->K > 0x7fffffffll * 256 || (instances > 1 && !(patch->body_tile & CONV_PATCH_MANY))) return false;
+    // The tiles of a batch that would run on gathers are as large as these and lose to them at any size (28 x 28 x 128 -> 128,
+    // batch 4: 10.3 us and 9.2, batch 64: 21.4 and 17.3).  Elsewhere the last round must not leave too much of the chip idle: 35 % of
+    // the rounds' workgroups have to be there where single images would run on gathers (28 x 28 x 128 -> 128 x 32, 64 tiles: 22 and
+    // 26; x 128: 69 and 27), 60 % for nests of small tiles (16 x 16 x 64 -> 64, batch 330: 23.3 and 14.7; 40 x 40 x 96 -> 32 x 80: 33
+    // and 17), 80 % for those whose weights and patches stay in LDS too (56 x 56 x 64 -> 64, four tiles: x 1 7.8 and 15.5, x 32 15.7 and
+    // 17.7, x 64 22.7 and 20.0, x 80 27.1 and 29.4, x 200 57.6 and 59.4).
+    const int64_t slots = 256 * conv_patch_per_cu(op, patch), busy = (tiles + slots - 1) / slots * slots;
+    const bool gathers = p->body == MS_BODY_CONV_STEPS, single = op->d.dims[0] == 1;
+    return (gathers && !single) || tiles * 100 >= busy * (gathers ? 35 : p->compute_at >= 2 && single ? 80 : 60);
+}
+
+uint64_t ms::launch_key(const ms_op *op, const ms_variant_params *p, int64_t instances)
+{
+    ms_variant_params patch;
+    return conv_patch_many(op, p, &patch) && takes_patch(op, p, &patch, instances) ? patch.key : p->key;
+}
+
+int ms::conv_patch_per_cu(const ms_op *op, const ms_variant_params *p) { return conv_patch_tile(op, p->body_tile).per_cu; }
+
 int32_t ms::validate_as_nest(const ms_op *op, const ms_space *space, const ms_trace *trace, ms_variant_params *out)
 {
     t_nests_only = true;
@@ -1017,14 +1162,14 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
     auto &D = k.defines;
     D.push_back(def("IN_DT", dt_code(d.in_dtype)));
     D.push_back(def("OUT_DT", dt_code(d.out_dtype)));
-    const bool conv_steps = p->body == MS_BODY_CONV_STEPS;
+    const bool conv_patch = p->body == MS_BODY_CONV_PATCH, conv_steps = p->body == MS_BODY_CONV_STEPS;
     if (follows_decisions(p) || conv_steps) push_schedule(D, p);
     if (p->family == MS_FAM_GEMM_ALU || p->family == MS_FAM_GEMM_MFMA) {
         D.push_back(def("DIM_B", op->nb));
         D.push_back(def("DIM_M", op->M));
         D.push_back(def("DIM_N", op->N));
         D.push_back(def("DIM_K", conv_steps ? op->K / conv_steps_tile(op, p->block_m, p->block_n).phases : op->K));
-        bool conv = is_conv2d(d.kind) && !conv_steps;
+        bool conv = is_conv2d(d.kind) && !conv_steps && !conv_patch;
         D.push_back(def("IS_CONV", conv ? 1 : 0));
         if (conv) {
             D.push_back(def("CV_N", d.dims[0]));
@@ -1063,12 +1208,13 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             D.push_back(def("SB_J", 1));
             D.push_back(def("A_INST", d.dims[0] * op->depth * d.dims[1] * d.dims[2] * d.dims[3]));
             D.push_back(def("B_INST", op->K * op->N * op->nb));
-        } else if (conv_steps) {
-            const ConvSteps c = conv_steps_tile(op, p->block_m, p->block_n);
+        } else if (conv_steps || conv_patch) {
             const bool transposed = d.kind == MS_OP_CONV2D_TRANSPOSED_NHWC;
             const int64_t S = transposed ? d.stride : 1;
-            D.push_back(def("CONV_STEPS", 1));
-            D.push_back(def("PP_STAGES", c.stages));
+            if (conv_steps) {
+                D.push_back(def("CONV_STEPS", 1));
+                D.push_back(def("PP_STAGES", conv_steps_tile(op, p->block_m, p->block_n).stages));
+            }
             D.push_back(def("HAS_BIAS", d.has_bias ? 1 : 0));
             D.push_back(def("RELU", d.relu ? 1 : 0));
             D.push_back(def("CS_TR", transposed ? 1 : 0));
@@ -1077,8 +1223,8 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             D.push_back(def("CS_W", d.dims[2]));
             D.push_back(def("CS_C", d.dims[3]));
             D.push_back(def("CS_KW", d.dims[6]));
-            D.push_back(def("CS_TH", c.th));
-            D.push_back(def("CS_TW", c.tw));
+            D.push_back(def("CS_TH", d.dims[5] / S));
+            D.push_back(def("CS_TW", d.dims[6] / S));
             D.push_back(def("CS_S", d.stride));
             D.push_back(def("CS_DIL", std::max(1, (int)d.dilation)));
             D.push_back(def("CS_PAD_H", op->pad_h));
@@ -1109,7 +1255,19 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             D.push_back(def("A_INST", ab / op->in_size));
             D.push_back(def("B_INST", bb / op->in_size));
         }
-        if (p->body == MS_BODY_IMAGE_ROWS) {
+        if (conv_patch) {
+            const ConvPatch c = conv_patch_tile(op, p->body_tile);
+            k.template_name = "conv_patch.hip";
+            D.push_back(def("CP_CW", c.cw));
+            D.push_back(def("CP_R", c.r));
+            D.push_back(def("CP_TN", c.tn));
+            D.push_back(def("CP_WR", c.wr));
+            D.push_back(def("CP_WJ", c.wj));
+            D.push_back(def("CP_WHOLE", c.whole));
+            D.push_back(def("CP_THREADS", (c.waves + 1) * 64));
+            D.push_back(def("CP_PER_CU", c.per_cu));
+            D.push_back(def("CP_LDS", c.lds));
+        } else if (p->body == MS_BODY_IMAGE_ROWS) {
             const ConvRows cr = conv_rows_tiles(op, p->body_tile);
             k.template_name = "conv_rows.hip";
             D.push_back(def("CR_TM", cr.tm));

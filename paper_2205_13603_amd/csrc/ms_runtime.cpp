@@ -26,6 +26,7 @@ struct ms_variant {
     hipFunction_t fn_many;   // kernel of launches over many instances, else null
     ms_variant *nest;        // MS_BODY_CONV_STEPS: the trace's nest, for operands off 16-byte boundaries (nest_of), else null
     ms_variant *few;         // MS_BODY_DOUBLE_STEPS: the kernel of launches of few tiles, else null
+    ms_variant *patch;       // convolutions: the kernel of launches that fill the chip (MS_BODY_CONV_PATCH), else null
     ms_variant_params nest_p;
     std::mutex nest_mu;
     int device;              // device the module is loaded on, -1 = not loaded
@@ -50,6 +51,7 @@ static int32_t build_variant(const ms_op *op, const ms_variant_params &p, ms_var
     v->fn_many = nullptr;
     v->nest = nullptr;
     v->few = nullptr;
+    v->patch = nullptr;
     v->device = -1;
     int32_t rc = make_kernel_spec(op, &p, &v->spec);
     if (rc == MS_OK) rc = jit_get_code(v->spec, p.key, &v->code);
@@ -71,14 +73,13 @@ extern "C" int32_t ms_variant_build(const ms_op *op, const ms_space *space, cons
     int32_t rc = ms_trace_validate(op, space, trace, &p);
     if (rc != MS_OK) return rc;
     rc = build_variant(op, p, out);
-    ms_variant_params few;
-    if (rc == MS_OK && double_steps_few(op, &p, &few)) {
-        rc = build_variant(op, few, &(*out)->few);
-        if (rc != MS_OK) {
-            ms_variant_destroy(*out);
-            *out = nullptr;
-            return rc;
-        }
+    ms_variant_params second;
+    if (rc == MS_OK && double_steps_few(op, &p, &second)) rc = build_variant(op, second, &(*out)->few);
+    if (rc == MS_OK && conv_patch_many(op, &p, &second)) rc = build_variant(op, second, &(*out)->patch);
+    if (rc != MS_OK) {
+        ms_variant_destroy(*out);
+        *out = nullptr;
+        return rc;
     }
     if (rc == MS_OK && p.body == MS_BODY_CONV_STEPS && (rc = validate_as_nest(op, space, trace, &(*out)->nest_p)) != MS_OK) {
         ms_variant_destroy(*out);
@@ -92,6 +93,7 @@ extern "C" void ms_variant_destroy(ms_variant *v)
     if (!v) return;
     ms_variant_destroy(v->nest);
     ms_variant_destroy(v->few);
+    ms_variant_destroy(v->patch);
     if (v->mod) (void)hipModuleUnload(v->mod);
     delete v;
 }
@@ -116,6 +118,7 @@ extern "C" int32_t ms_variant_launch_shape(const ms_variant *v, int32_t instance
     if (!v) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_shape: NULL variant");
     if (instances < 1) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_shape: instances = %d", instances);
     if (v->few && takes_few(&v->op, &v->p, &v->few->p, instances)) v = v->few;
+    if (v->patch && takes_patch(&v->op, &v->p, &v->patch->p, instances)) v = v->patch;
     int64_t lds = v->p.lds_bytes;
     const bool many = image_rows_many(&v->op, &v->p, instances, &lds);
     if (body_tile) *body_tile = many ? v->p.body_tile_many : v->p.body_tile;
@@ -191,8 +194,9 @@ extern "C" int32_t ms_prebuild(const ms_op *op, const ms_space *space, const ms_
             KernelSpec spec;
             std::vector<char> *code;
             if (make_kernel_spec(op, &p, &spec) == MS_OK && jit_get_code(spec, p.key, &code) == MS_OK) built.fetch_add(1);
-            ms_variant_params few;
-            if (double_steps_few(op, &p, &few) && make_kernel_spec(op, &few, &spec) == MS_OK) (void)jit_get_code(spec, few.key, &code);
+            ms_variant_params second;
+            if (double_steps_few(op, &p, &second) && make_kernel_spec(op, &second, &spec) == MS_OK) (void)jit_get_code(spec, second.key, &code);
+            if (conv_patch_many(op, &p, &second) && make_kernel_spec(op, &second, &spec) == MS_OK) (void)jit_get_code(spec, second.key, &code);
         }
     };
     std::vector<std::thread> pool;
@@ -207,8 +211,8 @@ extern "C" int32_t ms_prebuild(const ms_op *op, const ms_space *space, const ms_
 // variant that has been launched once loads nothing more on that device.
 static int32_t ensure_loaded(ms_variant *v, int dev)
 {
-    if (v->few) {
-        const int32_t rc = ensure_loaded(v->few, dev);
+    for (ms_variant *second : {v->few, v->patch}) {
+        const int32_t rc = second ? ensure_loaded(second, dev) : MS_OK;
         if (rc != MS_OK) return rc;
     }
     if (v->device == dev) return MS_OK;
@@ -257,6 +261,8 @@ static int32_t runs(ms_variant *v, const void *const *inputs, int32_t instances,
     *out = v;
     if (v->few && takes_few(&v->op, &v->p, &v->few->p, instances)) {
         *out = v->few;
+    } else if (v->patch && !(((uintptr_t)inputs[0] | (uintptr_t)inputs[1] | (v->op.d.has_bias ? (uintptr_t)inputs[2] : 0)) & 15u) && takes_patch(&v->op, &v->p, &v->patch->p, instances)) {
+        *out = v->patch;
     } else if (v->p.body == MS_BODY_CONV_STEPS && (((uintptr_t)inputs[0] | (uintptr_t)inputs[1]) & 15u)) {
         // loads straight into LDS move aligned 16-byte groups; the nest's loads go through registers and take any address
         if (build) return nest_of(v, out);
@@ -356,7 +362,7 @@ extern "C" int32_t ms_variant_launch(ms_variant *v, const void *const *inputs, v
     HIP_TRY(hipGetDevice(&dev));
     ms_variant *run = v;
     int32_t rc = runs(v, inputs, instances, true, &run);
-    if (rc == MS_OK) rc = ensure_loaded(run == v->few ? v : run, dev);
+    if (rc == MS_OK) rc = ensure_loaded(run == v->few || run == v->patch ? v : run, dev);
     if (rc != MS_OK) return rc;
     if (run != v) return ms_variant_launch(run, inputs, outputs, workspace, instances, stream);
     const void *in0 = inputs[0], *in1 = one_input ? nullptr : inputs[1];
@@ -382,7 +388,8 @@ extern "C" int32_t ms_variant_launch(ms_variant *v, const void *const *inputs, v
     if (v->p.family == MS_FAM_GEMM_MFMA && v->p.reorder == 3) {
         // persistent workgroups: one per compute unit (fewer if there are fewer tiles), each loops over its tiles
         uint64_t total = (uint64_t)v->spec.grid[0] * gz;
-        gx = (unsigned)std::min<uint64_t>(total, (uint64_t)std::max(1, v->compute_units));
+        const int per_cu = v->p.body == MS_BODY_CONV_PATCH ? conv_patch_per_cu(&v->op, &v->p) : 1;
+        gx = (unsigned)std::min<uint64_t>(total, (uint64_t)std::max(1, v->compute_units) * per_cu);
         gy = 1;
         gzz = 1;
     }

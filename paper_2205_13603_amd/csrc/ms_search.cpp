@@ -69,6 +69,8 @@ struct Search {
     int32_t n_feat = 0;
     bool stop = false;
 
+    // key of the kernel that a measurement of the variant runs
+    uint64_t kernel(const ms_variant_params &p) const { return fake ? p.key : launch_key(op, &p, cfg->measure.instances); }
     // returns latency in us, or < 0 when the candidate produced no measurement
     double evaluate(const ms_trace &t, uint64_t *key_out)
     {
@@ -78,7 +80,8 @@ struct Search {
             return -1;
         }
         *key_out = p.key;
-        if (seen.count(p.key)) {
+        const uint64_t runs = kernel(p);
+        if (seen.count(runs)) {
             ++res->n_duplicate;
             return -2;
         }
@@ -97,7 +100,7 @@ struct Search {
             }
             ms_variant_destroy(v);
         }
-        seen[p.key] = us;
+        seen[runs] = us;
         ms_trial tr;
         memset(&tr, 0, sizeof tr);
         tr.trace = t;
@@ -235,7 +238,7 @@ extern "C" int32_t ms_search(const ms_op *op, const ms_space *space, const ms_se
                 ++out->n_invalid;
                 continue;
             }
-            if (have.count(p.key)) {
+            if (have.count(S.kernel(p))) {
                 ++out->n_duplicate;
                 continue;
             }
@@ -244,7 +247,7 @@ extern "C" int32_t ms_search(const ms_op *op, const ms_space *space, const ms_se
             if (ms_variant_features(op, &p, fv, 128, &nf) != MS_OK) continue;
             if (nf != S.n_feat) return fail(MS_ERR_BAD_ARG, "ms_search: pre-training rows have %d features, this operator's variants %d", S.n_feat, nf);
             if (ms_cost_model_predict(model, fv, 1, nf, &d.pred) != MS_OK) continue;
-            have[p.key] = true;
+            have[S.kernel(p)] = true;
             drawn.push_back(d);
         }
         std::vector<size_t> by_pred(drawn.size());
@@ -365,7 +368,7 @@ extern "C" int32_t ms_search(const ms_op *op, const ms_space *space, const ms_se
                         ++out->n_invalid;
                         continue;
                     }
-                    if (S.seen.count(p.key) || in_batch.count(p.key)) {
+                    if (S.seen.count(S.kernel(p)) || in_batch.count(S.kernel(p))) {
                         ++out->n_duplicate;
                         continue;
                     }
@@ -380,7 +383,7 @@ extern "C" int32_t ms_search(const ms_op *op, const ms_space *space, const ms_se
                         if (fc > parent_cost && !(unit_uniform(rng) < exp(-(fc - parent_cost) / (T * fbest)))) continue;
                     }
                     sc.key = p.key;
-                    in_batch[p.key] = true;
+                    in_batch[S.kernel(p)] = true;
                     cand.push_back(sc);
                 }
             }

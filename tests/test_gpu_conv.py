@@ -821,3 +821,85 @@ def test_conv_steps_operands_off_16_byte_boundaries(static):
         got = run_variant_offset(op, space, t, [X, Wt, bias], "f32", ref.shape, offsets, static=static)
         if got is not None:
             assert np.array_equal(got, ref), offsets
+
+
+@pytest.mark.parametrize("N,H,W_,Cin,Cout,k,pad,dil,transposed,R,dtype", [
+    (1, 56, 56, 64, 64, 3, 1, 1, False, 64, "f16"),     # strips of 8 columns, two bands of 7 rows
+    (1, 16, 11, 32, 32, 3, 1, 1, False, 400, "f16"),    # one chunk per tile, masked columns, 32 channels per wavefront
+    (1, 12, 16, 64, 64, 3, 3, 1, False, 300, "bf16"),   # 4 x 4 blocks, padding wider than the filter's half
+    (1, 16, 20, 32, 128, 3, 3, 3, False, 200, "f16"),   # dilation 3, odd row pitch, two column blocks
+    (1, 28, 28, 32, 64, 5, 2, 1, False, 200, "bf16"),   # five filter columns
+    (1, 40, 40, 96, 32, 3, 2, 2, False, 130, "f16"),    # dilation 2, three chunks
+    (40, 12, 28, 64, 256, 3, 2, 2, False, 1, "f16"),    # a batch, wavefronts side by side over channels
+    (50, 20, 20, 64, 96, 3, 1, 1, False, 1, "f16"),     # three of 32 channels, rows behind the image
+    (237, 8, 8, 64, 64, 3, 1, 1, False, 1, "f16"),
+    (96, 5, 10, 32, 64, 2, 0, 1, False, 1, "f16"),      # two filter columns, no padding, rows that no tile fills
+    (1602, 2, 7, 32, 64, 2, 1, 1, False, 1, "f16"),    # eight whole images per tile, the last one of two
+    (30, 24, 24, 64, 64, 3, 1, 1, True, 1, "f16"),      # transposed: the filter turned round
+    (40, 6, 10, 64, 128, 3, 0, 1, True, 1, "bf16"),
+])
+@pytest.mark.parametrize("epilogue", [True, False])
+def test_conv_patch_exact(N, H, W_, Cin, Cout, k, pad, dil, transposed, R, dtype, epilogue):
+    """Launches of convolutions that fill the chip run on input patches.  Inputs of two instances in turn, integers whose sums the
+    output type holds: equal results."""
+    g = I.rng(111)
+    kw = {"bf16": True} if dtype == "bf16" else {}
+    if transposed:
+        ref_of, op = O.conv2d_transposed_nhwc, B.conv2d_transposed_op(N, H, W_, Cin, Cout, k, k, stride=1, pad=pad, in_dtype=dtype, has_bias=epilogue, relu=epilogue)
+    else:
+        ref_of, op = O.conv2d_nhwc, B.conv2d_op(N, H, W_, Cin, Cout, k, k, stride=1, pad=pad, in_dtype=dtype, dilation=dil, has_bias=epilogue, relu=epilogue)
+        kw["dilation"] = dil
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 112, n) for n in range(400)) if B.trace_validate(op, space, t).family == B.FAM_GEMM_MFMA)
+    v = B.Variant(op, space, t)
+    own = v.params().body_tile
+    R = R if R == 1 else next(r for r in range(R, 2 * R) if v.launch_shape(r)[0] != own) # instances that make whole rounds of tiles
+    tile, groups, _ = v.launch_shape(R)
+    assert tile != own
+    # one weight in `keep` counts, so that sums of bf16 stay below 256
+    keep = 16 if dtype == "bf16" else 2
+    pool = []
+    for _ in range(min(R, 2)):
+        x, w = I.small_ints(g, (N, H, W_, Cin), -2, 2, dtype), I.small_ints(g, (k, k, Cin, Cout), -1, 1, dtype)
+        w[g.integers(0, keep, size=w.shape) != 0] = 0
+        pool.append([x, w] + ([g.integers(-3, 4, size=Cout).astype(np.float32)] if epilogue else []))
+    refs = [ref_of(p[0], p[1], bias=p[2] if epilogue else None, relu=epilogue, stride=1, pad=pad, **kw) for p in pool]
+    assert max(np.abs(r).max() for r in refs) <= (256 if dtype == "bf16" else 2048)
+    print("tile", tile, "tiles", groups * R, flush=True)
+    got = run_variant_distinct(op, space, t, [pool[r % len(pool)] for r in range(R)], dtype, refs[0].shape)
+    if got is not None:
+        for r in range(R):
+            assert np.array_equal(got[r] if R > 1 else got.reshape(refs[0].shape), refs[r % len(pool)]), "instance %d of %d" % (r, R)
+
+
+@pytest.mark.parametrize("kh,kw", [(1, 3), (3, 2), (2, 5)])
+def test_conv_patch_oblong_filters_exact(kh, kw):
+    """Filters of one row, and of more columns than rows and fewer, over a batch."""
+    g = I.rng(115)
+    X, Wt = I.small_ints(g, (112, 16, 17, 64), -2, 2, "f16"), I.small_ints(g, (kh, kw, 64, 64), -1, 1, "f16")
+    bias = g.integers(-3, 4, size=64).astype(np.float32)
+    ref = O.conv2d_nhwc(X, Wt, bias=bias, relu=True, stride=1, pad=0)
+    op = B.conv2d_op(112, 16, 17, 64, 64, kh, kw, stride=1, pad=0)
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 116, n) for n in range(400)) if B.trace_validate(op, space, t).family == B.FAM_GEMM_MFMA)
+    v = B.Variant(op, space, t)
+    assert v.launch_shape(1)[0] != v.params().body_tile
+    got = run_variant(op, space, t, [X, Wt, bias], "f16", ref.shape)
+    assert got is None or np.array_equal(got.reshape(ref.shape), ref)
+
+
+def test_conv_patch_operands_off_16_byte_boundaries():
+    """Operands that are aligned to their elements only run on the trace's nest also where the launch would fill the chip."""
+    g = I.rng(113)
+    X, Wt = I.small_ints(g, (64, 16, 16, 32), -2, 2, "f16"), I.small_ints(g, (3, 3, 32, 32), -1, 1, "f16")
+    bias = g.integers(-3, 4, size=32).astype(np.float32)
+    ref = O.conv2d_nhwc(X, Wt, bias=bias, relu=True, stride=1, pad=1)
+    op = B.conv2d_op(64, 16, 16, 32, 32, 3, 3, stride=1, pad=1)
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 114, n) for n in range(400)) if B.trace_validate(op, space, t).family == B.FAM_GEMM_MFMA)
+    v = B.Variant(op, space, t)
+    assert v.launch_shape(1)[0] != v.params().body_tile
+    for offsets in ([0, 0, 0, 3], [3, 0, 0, 0], [0, 1, 0, 0]):
+        got = run_variant_offset(op, space, t, [X, Wt, bias], "f16", ref.shape, offsets)
+        if got is not None:
+            assert np.array_equal(got, ref), offsets
