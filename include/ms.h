@@ -413,8 +413,10 @@ typedef enum ms_body {
     MS_BODY_CONV_STEPS = 6,  /* conv and transposed conv whose pixels are whole 16-byte groups of channels, cache-read under the k0
                                 loop (compute_at 0): persistent workgroups multiply pixels by weights in 128-byte k steps,
                                 taps gathered straight into LDS; body_tile = 1000 * pixels + channels of a workgroup */
-    MS_BODY_CONV_PATCH = 7   /* a convolution's second kernel, of launches that fill the chip (ms_variant_launch_shape): input patches
+    MS_BODY_CONV_PATCH = 7,  /* a convolution's second kernel, of launches that fill the chip (ms_variant_launch_shape): input patches
                                 of 32 channels in LDS, read under every tap; body_tile packs the tile */
+    MS_BODY_CONV_PLANES = 8  /* the same of MS_BODY_IMAGE_ROWS: persistent workgroups, a filter plane's rows and weights loaded straight
+                                into LDS; body_tile = 32-pixel tiles of a wavefront */
 } ms_body;
 
 /* What the trace interpreter derives.  Unused fields are zero.  With bodies 1 to 3 and 6, block_*, grid, threads,
@@ -487,7 +489,7 @@ void ms_variant_destroy(ms_variant *v);
 int32_t ms_variant_info(const ms_variant *v, ms_variant_params *params, size_t *workspace_bytes);
 /* What a launch over `instances` instances runs: the body's tile, workgroups per instance, bytes of LDS of a workgroup.  They
  * are the fields of ms_variant_params unless the variant has a kernel of its own for many instances (body_tile_many), for
- * few tiles (MS_BODY_DOUBLE_STEPS) or for launches that fill the chip (MS_BODY_CONV_PATCH; tensors aligned to 16 bytes, others run
+ * few tiles (MS_BODY_DOUBLE_STEPS) or for launches that fill the chip (MS_BODY_CONV_PATCH, _PLANES; tensors aligned to 16 bytes, others run
  * what the parameters say).  Any pointer may be NULL.  BAD_ARG if instances < 1. */
 int32_t ms_variant_launch_shape(const ms_variant *v, int32_t instances, int32_t *body_tile, int32_t *workgroups, int32_t *lds_bytes);
 /* What materialising a variant compiles (Section 4, building a candidate): the kernel template's file name, then the

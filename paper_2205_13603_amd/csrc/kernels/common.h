@@ -59,6 +59,31 @@ __device__ __forceinline__ out_t from_acc(acc_t x)
 #endif
 }
 
+#if defined(RELU) && (OUT_DT == DT_F16 || OUT_DT == DT_BF16)
+// ReLU and the one rounding of two sums
+__device__ __forceinline__ unsigned finish(float x, float y)
+{
+#if OUT_DT == DT_F16
+    // the rounding keeps signs: ReLU on the rounded pair is ReLU ahead of the rounding (NaN becomes 0 either way)
+    typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+    typedef float f2_t __attribute__((ext_vector_type(2)));
+    h2_t v = __builtin_convertvector((f2_t{x, y}), h2_t);
+#if RELU
+    v = __builtin_elementwise_max(v, h2_t{0, 0});
+#endif
+    return __builtin_bit_cast(unsigned, v);
+#else
+#if RELU
+    // the middle of (v, 0, infinity), one instruction (NaN becomes 0); a maximum would first quiet v
+    x = __builtin_amdgcn_fmed3f(x, 0.f, __builtin_inff());
+    y = __builtin_amdgcn_fmed3f(y, 0.f, __builtin_inff());
+#endif
+    typedef __bf16 b2_t __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, (b2_t{(__bf16)x, (__bf16)y}));
+#endif
+}
+#endif
+
 #ifdef I0 // kernels built from the factors of a trace
 // Workgroup -> (z, i0, j0): z = instance * batch + batch index, (i0, j0) = the two outer spatial loops.
 // REORDER 0: i outer.  1: j outer.  2: i outer, after a permutation of the launch-wide workgroup
@@ -137,12 +162,13 @@ __device__ __forceinline__ unsigned long uniform(const char *p)
     return (unsigned long)uniform((unsigned)(a >> 32)) << 32 | uniform((unsigned)a);
 }
 __device__ __forceinline__ unsigned lds_address(const char *p) { return uniform((unsigned)(size_t)(const __attribute__((address_space(3))) char *)p); }
-__device__ __forceinline__ void load_lds16(const char *base, unsigned voff, const char *dst)
+__device__ __forceinline__ void load_lds16_to(const char *base, unsigned voff, unsigned dst)
 {
     unsigned long copy;
     asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
-                 : "=&s"(copy) : "s"(lds_address(dst)), "v"(voff), "s"(uniform(base)) : "memory", "m0");
+                 : "=&s"(copy) : "s"(dst), "v"(voff), "s"(uniform(base)) : "memory", "m0");
 }
+__device__ __forceinline__ void load_lds16(const char *base, unsigned voff, const char *dst) { load_lds16_to(base, voff, lds_address(dst)); }
 
 // The same from a buffer at `base`: `voff` per lane, `soff` wave-uniform.  Lanes that ask for OUTSIDE write zeros (a range-checked
 // load beyond the buffer returns zero, into LDS too).
@@ -153,10 +179,11 @@ __device__ __forceinline__ rsrc_t buffer_at(const char *base, unsigned bytes = 0
     const unsigned long b = uniform(base);
     return {(unsigned)b, (unsigned)(b >> 32) & 0xffffu, uniform(bytes), 0x00020000u};
 }
-__device__ __forceinline__ void gather_lds16(const rsrc_t &buffer, unsigned voff, const char *dst)
+typedef __attribute__((address_space(3))) char lds_char;
+__device__ __forceinline__ void gather_lds16(const rsrc_t &buffer, unsigned voff, const lds_char *dst)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 : : "s"(lds_address(dst)), "v"(voff), "s"(buffer) : "memory", "m0");
+                 : : "s"(uniform((unsigned)(size_t)dst)), "v"(voff), "s"(buffer) : "memory", "m0");
 }
 __device__ __forceinline__ void gather_lds16(const char *base, unsigned voff, unsigned soff, const char *dst)
 {

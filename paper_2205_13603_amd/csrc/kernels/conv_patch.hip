@@ -1,5 +1,5 @@
 // Convolution of stride 1 (conv2d or transposed, + bias + ReLU; whole 32-channel groups) on the CDNA4 matrix cores from input
-// patches in LDS; which launches run here says takes_patch() in ms_interp.cpp.
+// patches in LDS; which launches run here says takes_fill() in ms_interp.cpp.
 //
 // A tile is rows of one image (or whole images) by BN output channels.  Its reduction runs over chunks of 32 input channels: the
 // chunk's patch, zero border included, is loaded straight into LDS once and read under every tap, while the next chunk's is on
@@ -21,7 +21,6 @@ typedef short tr4_t __attribute__((ext_vector_type(4)));
 typedef float accv_t __attribute__((ext_vector_type(4)));
 typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u2_t __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) char lds_char;
 
 constexpr int TH = CS_TH, TW = CS_TW, DIL = CS_DIL;
 constexpr int OH = CS_PH_H, OW = CS_PH_W, CHUNKS = CS_C / 32, PIXEL_B = CS_C * 2;
@@ -64,29 +63,6 @@ __device__ __forceinline__ accv_t mfma(const u4_t &a, const u4_t &b, accv_t c)
 #endif
 }
 
-// ReLU and the one rounding of two sums
-__device__ __forceinline__ unsigned finish(float x, float y)
-{
-#if OUT_DT == DT_F16
-    // the rounding keeps signs: ReLU on the rounded pair is ReLU ahead of the rounding (NaN becomes 0 either way)
-    typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
-    typedef float f2_t __attribute__((ext_vector_type(2)));
-    h2_t v = __builtin_convertvector((f2_t{x, y}), h2_t);
-#if RELU
-    v = __builtin_elementwise_max(v, h2_t{0, 0});
-#endif
-    return __builtin_bit_cast(unsigned, v);
-#else
-#if RELU
-    // the middle of (v, 0, infinity), one instruction (NaN becomes 0); a maximum would first quiet v
-    x = __builtin_amdgcn_fmed3f(x, 0.f, __builtin_inff());
-    y = __builtin_amdgcn_fmed3f(y, 0.f, __builtin_inff());
-#endif
-    typedef __bf16 b2_t __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(unsigned, (b2_t{(__bf16)x, (__bf16)y}));
-#endif
-}
-
 struct tile_id {
     int inst, n0, row0, jb;                               // instance, first image, first output row, column block
 };
@@ -116,7 +92,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
 {
     const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
     __shared__ __attribute__((aligned(1024))) char lds[LDS_B];
-    const lds_char *const lds3 = (const lds_char *)lds;
+    lds_char *const lds3 = (lds_char *)lds;
 
     const long total = (long)JB * TPI * GROUPS * instances, first = blockIdx.x, stride = gridDim.x;
     if (first >= total) return;
@@ -187,7 +163,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
         };
         auto load_weights = [&]() INLINE {
 #pragma unroll
-            for (int i = 0; i < NWI; ++i) load_lds16(wbase, woff[i], lds + W_AT + ws * W_B + i * 1024);
+            for (int i = 0; i < NWI; ++i) load_lds16_to(wbase, woff[i], uniform((unsigned)(size_t)(lds3 + W_AT + ws * W_B + i * 1024)));
             ws = ws + 1 == WST ? 0 : ws + 1;
             if (++wtw < TW) return weights_at();
             if (wc + 1 < CHUNKS) {
@@ -208,7 +184,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
 #if HAS_BIAS
             const tile_id t = decode(first + bt * stride, total);
             const char *b = (const char *)bias_ + ((long)t.inst * DIM_N + t.jb * BN) * 4;
-            gather_lds16(buffer_at(b, BN * 4), (unsigned)lane * 16, lds + BIAS_AT + bh * 1024);
+            gather_lds16(buffer_at(b, BN * 4), (unsigned)lane * 16, lds3 + BIAS_AT + bh * 1024);
             if (bt + 1 < my_tiles) ++bt;
             bh ^= 1;
 #endif
@@ -217,7 +193,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
         weights_tile();
         load_bias();
 #pragma unroll
-        for (int i = 0; i < NPI; ++i) gather_lds16(prs, poff[i] + ptoff, lds + pb * PATCH_B + i * 1024);
+        for (int i = 0; i < NPI; ++i) gather_lds16(prs, poff[i] + ptoff, lds3 + pb * PATCH_B + i * 1024);
         next_patch();
 #pragma unroll
         for (int s = 0; s < WST - 1; ++s) load_weights();
@@ -234,7 +210,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
             if (kw == 0 && first_chunk) load_bias();
             load_weights();
 #pragma unroll
-            for (int i = lo; i < hi; ++i) gather_lds16(prs, poff[i] + ptoff, lds + pb * PATCH_B + i * 1024);
+            for (int i = lo; i < hi; ++i) gather_lds16(prs, poff[i] + ptoff, lds3 + pb * PATCH_B + i * 1024);
             if (kw == TW - 2) next_patch();
             // Landed by now: the weights of step s + 1 and, behind the last step of a chunk, the next patch.  Loads land in order, and
             // behind the weights of step s + 1 there are the patch's share of the last slot and all of this one

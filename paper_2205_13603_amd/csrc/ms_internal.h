@@ -83,12 +83,12 @@ bool image_rows_many(const ms_op *op, const ms_variant_params *p, int64_t instan
 // And whether a launch over so many instances takes it.
 bool double_steps_few(const ms_op *op, const ms_variant_params *p, ms_variant_params *few);
 bool takes_few(const ms_op *op, const ms_variant_params *p, const ms_variant_params *few, int64_t instances);
-// MS_BODY_CONV_PATCH: the kernel of convolution launches that fill the chip; false = the operator has none.  Whether a launch over so
-// many instances takes it, and its workgroups per compute unit.
-bool conv_patch_many(const ms_op *op, const ms_variant_params *p, ms_variant_params *patch);
-bool takes_patch(const ms_op *op, const ms_variant_params *p, const ms_variant_params *patch, int64_t instances);
+// The kernel of convolution launches that fill the chip (MS_BODY_CONV_PATCH, MS_BODY_CONV_PLANES); false = the operator has none.
+// Whether a launch over so many instances takes it, and its workgroups per compute unit.
+bool fill_kernel(const ms_op *op, const ms_variant_params *p, ms_variant_params *fill);
+bool takes_fill(const ms_op *op, const ms_variant_params *p, const ms_variant_params *fill, int64_t instances);
+int fill_per_cu(const ms_op *op, const ms_variant_params *p);
 uint64_t launch_key(const ms_op *op, const ms_variant_params *p, int64_t instances); // key of the kernel that such a launch runs
-int conv_patch_per_cu(const ms_op *op, const ms_variant_params *p);
 // ms_trace_validate with every rule that gives the trace another body left out
 int32_t validate_as_nest(const ms_op *op, const ms_space *space, const ms_trace *trace, ms_variant_params *out);
 int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec *out);

@@ -354,8 +354,58 @@ int conv_steps(const ms_op *op, const ms_variant_params *p)
     return best;
 }
 
+// MS_BODY_CONV_PLANES: first layers on persistent workgroups over filter planes (conv_planes.hip), the second kernel of a variant on
+// MS_BODY_IMAGE_ROWS (fill_kernel, takes_fill).
+struct ConvPlanes {
+    int tm, tn;
+    int64_t steps;                   // k steps of a filter plane
+    int64_t tiles, lds, clocks;      // tiles of an instance, bytes of a workgroup, estimate for a tile
+    int waves() const { return 4; }
+    int per_cu() const { return 2 * lds <= 160 * 1024 ? 2 : 1; }
+};
+ConvPlanes conv_planes_tile(const ms_op *op, int tm)
+{
+    const ms_op_desc &d = op->d;
+    const int64_t W = d.dims[2], Cin = d.dims[3], Cout = d.dims[4], KH = d.dims[5], KW = d.dims[6], S = d.stride, ohw = op->OH * op->OW;
+    ConvPlanes c;
+    c.tm = tm;
+    c.tn = Cout / 32 % 2 == 0 ? 2 : 1;
+    const int64_t px = c.waves() * tm * 32, lead = d.pad * Cin % 2, cpr = (lead + KW * Cin + 7) / 8, steps = c.steps = (KH * cpr + 1) / 2, bn = c.tn * 32;
+    const int64_t halo = ((d.pad * Cin + lead) * 2 + 15) / 16 * 16, last = halo - (d.pad * Cin + lead) * 2 + (op->OW - 1) * S * Cin * 2 + cpr * 16;
+    const int64_t units = (std::max(halo + W * Cin * 2, last) + 15) / 16;
+    const int64_t rows = (std::min(px % op->OW ? (op->OW + px - 2) / op->OW + 1 : px / op->OW, op->OH) - 1) * S + KH;
+    const int64_t stage = ((rows * units + 63) / 64 + (steps * 16 * bn / 8 + 63) / 64) * 1024;
+    c.lds = stage + (d.has_bias ? 2048 : 0);
+    c.tiles = (ohw + px - 1) / px * (Cout / bn) * op->OD * d.dims[0];
+    // a plane: products of the two wavefronts of a SIMD, their LDS reads at 128 bytes per clock; what a load's latency leaves; results
+    const int64_t n = c.per_cu();
+    c.clocks = op->kd * (std::max(n * steps * tm * c.tn * 32, n * steps * (tm + c.tn) * 32) + 1500) + n * tm * c.tn * 500;
+    return c;
+}
+int conv_planes(const ms_op *op)
+{
+    const ms_op_desc &d = op->d;
+    // columns of 96 channels would leave as parts of lines (128 x 128 x 3 -> 96, 3 x 3, batch 115: 20.4 us and 26.2)
+    if (op->out_size != 2 || op->in_size != 2 || op->N / 32 % 3 == 0) return 0;
+    if (d.dims[1] * d.dims[2] * d.dims[3] > 0x0fffffff || op->K * op->N > 0x3fffffff) return 0; // 32-bit byte offsets, ahead of a plane and behind it too
+    int best = 0;
+    double cost = 0;
+    for (int tm : {4, 3, 2, 1}) {
+        const ConvPlanes c = conv_planes_tile(op, tm);
+        if (tm * c.tn > 8 || c.lds > g_limits.max_lds_bytes || c.tiles > 0x7fffffff || c.waves() > g_limits.max_waves || c.waves() * 64 > g_limits.max_threads) continue;
+        if (tm * c.tn * 16 > g_limits.max_acc_per_thread) continue;
+        const int64_t slots = 256 * c.per_cu();
+        const double clocks = d.dims[0] == 1 ? (double)c.tiles / slots * c.clocks : (double)((c.tiles + slots - 1) / slots) * c.clocks;
+        if (!best || clocks < cost) {
+            best = tm;
+            cost = clocks;
+        }
+    }
+    return best;
+}
+
 // MS_BODY_CONV_PATCH: convolutions of stride 1 from input patches in LDS (conv_patch.hip), the second kernel of a convolution's
-// variant (conv_patch_many, takes_patch).  Not for filters of one column, which read every input once, nor for strides: of nine layers
+// variant (fill_kernel, takes_fill).  Not for filters of one column, which read every input once, nor for strides: of nine layers
 // at stride 2 four were slower than their nests and gathers (48 x 48 x 64 -> 64, batch 512: 46.6 us and 52.9; 20 x 20 x 256 -> 256, batch
 // 176: 34.5 and 44.9), and transposed ones by phases share too few taps (16 x 16 x 256 -> 128, 4 x 4, batch 64: 22.0 and 27.3).
 constexpr int CONV_PATCH_MANY = 1 << 25; // in a tile's code: chosen for launches over many instances too
@@ -1055,9 +1105,29 @@ bool ms::takes_few(const ms_op *op, const ms_variant_params *p, const ms_variant
     return double_step_cost(op, few, instances) * 10 < double_step_cost(op, p, instances) * 9;
 }
 
-bool ms::conv_patch_many(const ms_op *op, const ms_variant_params *p, ms_variant_params *patch)
+bool ms::fill_kernel(const ms_op *op, const ms_variant_params *p, ms_variant_params *patch)
 {
-    if (p->family != MS_FAM_GEMM_MFMA || p->body == MS_BODY_IMAGE_ROWS) return false;
+    if (p->family != MS_FAM_GEMM_MFMA) return false;
+    if (p->body == MS_BODY_IMAGE_ROWS) {
+        const int tile = conv_planes(op);
+        if (!tile) return false;
+        const ConvPlanes c = conv_planes_tile(op, tile);
+        *patch = *p;
+        patch->body = MS_BODY_CONV_PLANES;
+        patch->body_tile = tile;
+        patch->body_tile_many = 0;
+        patch->block_m = c.waves() * c.tm * 32;
+        patch->grid[0] = (int32_t)c.tiles;
+        patch->grid[1] = patch->grid[2] = 1;
+        patch->waves = c.waves();
+        patch->threads = c.waves() * 64;
+        patch->acc_per_thread = c.tm * c.tn * 16;
+        patch->lds_bytes = (int32_t)c.lds;
+        patch->compute_at = 0;
+        patch->reorder = 3;
+        patch->key = hash_params(op, patch);
+        return true;
+    }
     const int tile = conv_patch(op);
     if (!tile) return false;
     const ConvPatch c = conv_patch_tile(op, tile);
@@ -1079,8 +1149,17 @@ bool ms::conv_patch_many(const ms_op *op, const ms_variant_params *p, ms_variant
     return true;
 }
 
-bool ms::takes_patch(const ms_op *op, const ms_variant_params *p, const ms_variant_params *patch, int64_t instances)
+bool ms::takes_fill(const ms_op *op, const ms_variant_params *p, const ms_variant_params *patch, int64_t instances)
 {
+    if (patch->body == MS_BODY_CONV_PLANES) {
+        // Launches whose rounds leave more than a quarter of the chip idle spread better in the smaller tiles of image rows (3 x 16 x
+        // 64 x 64 -> 64, 7 x 7 x 7, x 4: 11.5 us and 18.7), and a single round of small tiles (64 x 64 x 4 -> 64, 7 x 7, batch 114: 7.4
+        // and 8.1) or planes of few steps (3-D, 192 x 192 x 3 -> 32, 3 x 3 x 3, x 11: 15.2 and 17.0) hide no loads.
+        const ConvPlanes c = conv_planes_tile(op, patch->body_tile);
+        const int64_t tiles = (int64_t)patch->grid[0] * instances, slots = 256 * c.per_cu(), busy = (tiles + slots - 1) / slots * slots;
+        if (op->kd > 1 && c.steps < 4) return false;
+        return tiles * 100 >= busy * 75 && (c.tn == 1 || c.tm >= 3 || tiles > slots);
+    }
     // its wavefronts count steps in 32 bits
     const int64_t tiles = (int64_t)patch->grid[0] * instances;
     if (tiles * op->K > 0x7fffffffll * 256 || (instances > 1 && !(patch->body_tile & CONV_PATCH_MANY))) return false;
@@ -1090,7 +1169,7 @@ bool ms::takes_patch(const ms_op *op, const ms_variant_params *p, const ms_varia
     // 26; x 128: 69 and 27), 60 % for nests of small tiles (16 x 16 x 64 -> 64, batch 330: 23.3 and 14.7; 40 x 40 x 96 -> 32 x 80: 33
     // and 17), 80 % for those whose weights and patches stay in LDS too (56 x 56 x 64 -> 64, four tiles: x 1 7.8 and 15.5, x 32 15.7 and
     // 17.7, x 64 22.7 and 20.0, x 80 27.1 and 29.4, x 200 57.6 and 59.4).
-    const int64_t slots = 256 * conv_patch_per_cu(op, patch), busy = (tiles + slots - 1) / slots * slots;
+    const int64_t slots = 256 * fill_per_cu(op, patch), busy = (tiles + slots - 1) / slots * slots;
     const bool gathers = p->body == MS_BODY_CONV_STEPS, single = op->d.dims[0] == 1;
     return (gathers && !single) || tiles * 100 >= busy * (gathers ? 35 : p->compute_at >= 2 && single ? 80 : 60);
 }
@@ -1098,10 +1177,13 @@ bool ms::takes_patch(const ms_op *op, const ms_variant_params *p, const ms_varia
 uint64_t ms::launch_key(const ms_op *op, const ms_variant_params *p, int64_t instances)
 {
     ms_variant_params patch;
-    return conv_patch_many(op, p, &patch) && takes_patch(op, p, &patch, instances) ? patch.key : p->key;
+    return fill_kernel(op, p, &patch) && takes_fill(op, p, &patch, instances) ? patch.key : p->key;
 }
 
-int ms::conv_patch_per_cu(const ms_op *op, const ms_variant_params *p) { return conv_patch_tile(op, p->body_tile).per_cu; }
+int ms::fill_per_cu(const ms_op *op, const ms_variant_params *p)
+{
+    return p->body == MS_BODY_CONV_PLANES ? conv_planes_tile(op, p->body_tile).per_cu() : conv_patch_tile(op, p->body_tile).per_cu;
+}
 
 int32_t ms::validate_as_nest(const ms_op *op, const ms_space *space, const ms_trace *trace, ms_variant_params *out)
 {
@@ -1267,6 +1349,13 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             D.push_back(def("CP_THREADS", (c.waves + 1) * 64));
             D.push_back(def("CP_PER_CU", c.per_cu));
             D.push_back(def("CP_LDS", c.lds));
+        } else if (p->body == MS_BODY_CONV_PLANES) {
+            const ConvPlanes c = conv_planes_tile(op, p->body_tile);
+            k.template_name = "conv_planes.hip";
+            D.push_back(def("CR_TM", c.tm));
+            D.push_back(def("CR_TN", c.tn));
+            D.push_back(def("CR_WAVES", c.waves()));
+            D.push_back(def("CR_LDS", c.lds));
         } else if (p->body == MS_BODY_IMAGE_ROWS) {
             const ConvRows cr = conv_rows_tiles(op, p->body_tile);
             k.template_name = "conv_rows.hip";

@@ -26,7 +26,7 @@ struct ms_variant {
     hipFunction_t fn_many;   // kernel of launches over many instances, else null
     ms_variant *nest;        // MS_BODY_CONV_STEPS: the trace's nest, for operands off 16-byte boundaries (nest_of), else null
     ms_variant *few;         // MS_BODY_DOUBLE_STEPS: the kernel of launches of few tiles, else null
-    ms_variant *patch;       // convolutions: the kernel of launches that fill the chip (MS_BODY_CONV_PATCH), else null
+    ms_variant *fill;        // convolutions: the kernel of launches that fill the chip, else null
     ms_variant_params nest_p;
     std::mutex nest_mu;
     int device;              // device the module is loaded on, -1 = not loaded
@@ -51,7 +51,7 @@ static int32_t build_variant(const ms_op *op, const ms_variant_params &p, ms_var
     v->fn_many = nullptr;
     v->nest = nullptr;
     v->few = nullptr;
-    v->patch = nullptr;
+    v->fill = nullptr;
     v->device = -1;
     int32_t rc = make_kernel_spec(op, &p, &v->spec);
     if (rc == MS_OK) rc = jit_get_code(v->spec, p.key, &v->code);
@@ -75,7 +75,7 @@ extern "C" int32_t ms_variant_build(const ms_op *op, const ms_space *space, cons
     rc = build_variant(op, p, out);
     ms_variant_params second;
     if (rc == MS_OK && double_steps_few(op, &p, &second)) rc = build_variant(op, second, &(*out)->few);
-    if (rc == MS_OK && conv_patch_many(op, &p, &second)) rc = build_variant(op, second, &(*out)->patch);
+    if (rc == MS_OK && fill_kernel(op, &p, &second)) rc = build_variant(op, second, &(*out)->fill);
     if (rc != MS_OK) {
         ms_variant_destroy(*out);
         *out = nullptr;
@@ -93,7 +93,7 @@ extern "C" void ms_variant_destroy(ms_variant *v)
     if (!v) return;
     ms_variant_destroy(v->nest);
     ms_variant_destroy(v->few);
-    ms_variant_destroy(v->patch);
+    ms_variant_destroy(v->fill);
     if (v->mod) (void)hipModuleUnload(v->mod);
     delete v;
 }
@@ -118,7 +118,7 @@ extern "C" int32_t ms_variant_launch_shape(const ms_variant *v, int32_t instance
     if (!v) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_shape: NULL variant");
     if (instances < 1) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_shape: instances = %d", instances);
     if (v->few && takes_few(&v->op, &v->p, &v->few->p, instances)) v = v->few;
-    if (v->patch && takes_patch(&v->op, &v->p, &v->patch->p, instances)) v = v->patch;
+    if (v->fill && takes_fill(&v->op, &v->p, &v->fill->p, instances)) v = v->fill;
     int64_t lds = v->p.lds_bytes;
     const bool many = image_rows_many(&v->op, &v->p, instances, &lds);
     if (body_tile) *body_tile = many ? v->p.body_tile_many : v->p.body_tile;
@@ -196,7 +196,7 @@ extern "C" int32_t ms_prebuild(const ms_op *op, const ms_space *space, const ms_
             if (make_kernel_spec(op, &p, &spec) == MS_OK && jit_get_code(spec, p.key, &code) == MS_OK) built.fetch_add(1);
             ms_variant_params second;
             if (double_steps_few(op, &p, &second) && make_kernel_spec(op, &second, &spec) == MS_OK) (void)jit_get_code(spec, second.key, &code);
-            if (conv_patch_many(op, &p, &second) && make_kernel_spec(op, &second, &spec) == MS_OK) (void)jit_get_code(spec, second.key, &code);
+            if (fill_kernel(op, &p, &second) && make_kernel_spec(op, &second, &spec) == MS_OK) (void)jit_get_code(spec, second.key, &code);
         }
     };
     std::vector<std::thread> pool;
@@ -211,7 +211,7 @@ extern "C" int32_t ms_prebuild(const ms_op *op, const ms_space *space, const ms_
 // variant that has been launched once loads nothing more on that device.
 static int32_t ensure_loaded(ms_variant *v, int dev)
 {
-    for (ms_variant *second : {v->few, v->patch}) {
+    for (ms_variant *second : {v->few, v->fill}) {
         const int32_t rc = second ? ensure_loaded(second, dev) : MS_OK;
         if (rc != MS_OK) return rc;
     }
@@ -261,8 +261,8 @@ static int32_t runs(ms_variant *v, const void *const *inputs, int32_t instances,
     *out = v;
     if (v->few && takes_few(&v->op, &v->p, &v->few->p, instances)) {
         *out = v->few;
-    } else if (v->patch && !(((uintptr_t)inputs[0] | (uintptr_t)inputs[1] | (v->op.d.has_bias ? (uintptr_t)inputs[2] : 0)) & 15u) && takes_patch(&v->op, &v->p, &v->patch->p, instances)) {
-        *out = v->patch;
+    } else if (v->fill && !(((uintptr_t)inputs[0] | (uintptr_t)inputs[1] | (v->op.d.has_bias ? (uintptr_t)inputs[2] : 0)) & 15u) && takes_fill(&v->op, &v->p, &v->fill->p, instances)) {
+        *out = v->fill;
     } else if (v->p.body == MS_BODY_CONV_STEPS && (((uintptr_t)inputs[0] | (uintptr_t)inputs[1]) & 15u)) {
         // loads straight into LDS move aligned 16-byte groups; the nest's loads go through registers and take any address
         if (build) return nest_of(v, out);
@@ -362,7 +362,7 @@ extern "C" int32_t ms_variant_launch(ms_variant *v, const void *const *inputs, v
     HIP_TRY(hipGetDevice(&dev));
     ms_variant *run = v;
     int32_t rc = runs(v, inputs, instances, true, &run);
-    if (rc == MS_OK) rc = ensure_loaded(run == v->few || run == v->patch ? v : run, dev);
+    if (rc == MS_OK) rc = ensure_loaded(run == v->few || run == v->fill ? v : run, dev);
     if (rc != MS_OK) return rc;
     if (run != v) return ms_variant_launch(run, inputs, outputs, workspace, instances, stream);
     const void *in0 = inputs[0], *in1 = one_input ? nullptr : inputs[1];
@@ -388,7 +388,7 @@ extern "C" int32_t ms_variant_launch(ms_variant *v, const void *const *inputs, v
     if (v->p.family == MS_FAM_GEMM_MFMA && v->p.reorder == 3) {
         // persistent workgroups: one per compute unit (fewer if there are fewer tiles), each loops over its tiles
         uint64_t total = (uint64_t)v->spec.grid[0] * gz;
-        const int per_cu = v->p.body == MS_BODY_CONV_PATCH ? conv_patch_per_cu(&v->op, &v->p) : 1;
+        const int per_cu = v->p.body == MS_BODY_CONV_PATCH || v->p.body == MS_BODY_CONV_PLANES ? fill_per_cu(&v->op, &v->p) : 1;
         gx = (unsigned)std::min<uint64_t>(total, (uint64_t)std::max(1, v->compute_units) * per_cu);
         gy = 1;
         gzz = 1;

@@ -903,3 +903,44 @@ def test_conv_patch_operands_off_16_byte_boundaries():
         got = run_variant_offset(op, space, t, [X, Wt, bias], "f16", ref.shape, offsets)
         if got is not None:
             assert np.array_equal(got, ref), offsets
+
+
+@pytest.mark.parametrize("N,D,H,W_,Cin,Cout,k,stride,pad,dtype,R", [
+    (1, 6, 64, 64, 3, 64, 7, 2, 3, "f16", 30),          # planes at the ends of the depth meet fewer filter planes
+    (1, 7, 41, 72, 1, 32, 7, 2, 3, "bf16", 60),         # 32 channels, the last tile of a plane in part
+    (2, 6, 33, 40, 4, 128, 5, 1, 0, "f16", 20),         # two column blocks, no padding
+    (1, 2, 28, 48, 3, 64, 5, 2, 4, "f16", 80),          # output planes that no filter plane meets
+    (130, 1, 60, 104, 3, 64, 7, 2, 3, "f16", 1),        # 2-D: one plane per tile, a batch
+    (90, 1, 67, 64, 2, 32, 3, 1, 1, "bf16", 1),
+    (1, 1, 80, 96, 4, 64, 5, 2, 2, "f16", 200),         # instances with their own weights
+])
+@pytest.mark.parametrize("epilogue", [True, False])
+def test_first_layer_planes_exact(N, D, H, W_, Cin, Cout, k, stride, pad, dtype, R, epilogue):
+    """First layers whose launches fill the chip, on persistent workgroups over filter planes.  Inputs of two instances in turn,
+    integers whose sums the output type holds; an infinite pixel reaches the outputs whose windows hold it and no others."""
+    g = I.rng(117)
+    kw = {"bf16": True} if dtype == "bf16" else {}
+    shape, wshape = ((N, D, H, W_, Cin), (k, k, k, Cin, Cout)) if D > 1 else ((N, H, W_, Cin), (k, k, Cin, Cout))
+    ref_of = O.conv3d_ndhwc if D > 1 else O.conv2d_nhwc
+    args = dict(stride=stride, pad=pad, in_dtype=dtype, has_bias=epilogue, relu=epilogue)
+    op = B.conv3d_op(N, D, H, W_, Cin, Cout, k, **args) if D > 1 else B.conv2d_op(N, H, W_, Cin, Cout, k, k, **args)
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 118, n) for n in range(200))
+             if B.trace_validate(op, space, t).compute_at == 0 and B.trace_validate(op, space, t).family == B.FAM_GEMM_MFMA)
+    v = B.Variant(op, space, t)
+    p = v.params()
+    own = (p.grid[0], p.body_tile, p.body_tile_many)
+    R = R if R == 1 else next(r for r in range(R, 3 * R) if v.launch_shape(r)[2] % 1024 == 0 and v.launch_shape(r)[0] <= 4 and v.launch_shape(r)[2] != p.lds_bytes)
+    print("tile", v.launch_shape(R), "own", own, "R", R, flush=True)
+    pool = []
+    for _ in range(min(R, 2)):
+        x, w = I.small_ints(g, shape, -1, 1, dtype), I.small_ints(g, wshape, -1, 1, dtype)
+        w[w == 0] = 1 if dtype == "f16" else 0x3F80
+        x[tuple(e // 2 for e in x.shape)] = np.inf if dtype == "f16" else 0x7F80
+        pool.append([x, w] + ([g.integers(-3, 4, size=Cout).astype(np.float32)] if epilogue else []))
+    refs = [ref_of(q[0], q[1], bias=q[2] if epilogue else None, relu=epilogue, stride=stride, pad=pad, **kw) for q in pool]
+    assert max(np.abs(r[np.isfinite(r)]).max() for r in refs) <= (256 if dtype == "bf16" else 2048)
+    got = run_variant_distinct(op, space, t, [pool[r % len(pool)] for r in range(R)], dtype, refs[0].shape)
+    if got is not None:
+        for r in range(R):
+            assert np.array_equal(got[r] if R > 1 else got.reshape(refs[0].shape), refs[r % len(pool)], equal_nan=True), "instance %d of %d" % (r, R)
