@@ -489,8 +489,9 @@ void ms_variant_destroy(ms_variant *v);
 int32_t ms_variant_info(const ms_variant *v, ms_variant_params *params, size_t *workspace_bytes);
 /* What a launch over `instances` instances runs: the body's tile, workgroups per instance, bytes of LDS of a workgroup.  They
  * are the fields of ms_variant_params unless the variant has a kernel of its own for many instances (body_tile_many), for
- * few tiles (MS_BODY_DOUBLE_STEPS) or for launches that fill the chip (MS_BODY_CONV_PATCH, _PLANES; tensors aligned to 16 bytes, others run
- * what the parameters say).  Any pointer may be NULL.  BAD_ARG if instances < 1. */
+ * few tiles (MS_BODY_DOUBLE_STEPS) or for launches that fill the chip (MS_BODY_CONV_PATCH; tensors aligned to 16 bytes, others run
+ * what the parameters say).  Of MS_BODY_IMAGE_ROWS they are those of that body, whether or not MS_BODY_CONV_PLANES takes its place.
+ * Any pointer may be NULL.  BAD_ARG if instances < 1. */
 int32_t ms_variant_launch_shape(const ms_variant *v, int32_t instances, int32_t *body_tile, int32_t *workgroups, int32_t *lds_bytes);
 /* What materialising a variant compiles (Section 4, building a candidate): the kernel template's file name, then the
  * -D options that specialise it, one per line.  Two parameter sets that give the same text are the same kernel and
