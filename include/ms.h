@@ -415,8 +415,10 @@ typedef enum ms_body {
                                 taps gathered straight into LDS; body_tile = 1000 * pixels + channels of a workgroup */
     MS_BODY_CONV_PATCH = 7,  /* a convolution's second kernel, of launches that fill the chip (ms_variant_launch_shape): input patches
                                 of 32 channels in LDS, read under every tap; body_tile packs the tile */
-    MS_BODY_CONV_PLANES = 8  /* the same of MS_BODY_IMAGE_ROWS: persistent workgroups, a filter plane's rows and weights loaded straight
+    MS_BODY_CONV_PLANES = 8, /* the same of MS_BODY_IMAGE_ROWS: persistent workgroups, a filter plane's rows and weights loaded straight
                                 into LDS; body_tile = 32-pixel tiles of a wavefront */
+    MS_BODY_FEW_ROWS = 9     /* the same of a nest over up to 128 rows times a row-major matrix (fp16, bf16), of launches of up to 64 x 64
+                                outputs per compute unit: wavefronts of a workgroup share its reduction; body_tile packs the tile */
 } ms_body;
 
 /* What the trace interpreter derives.  Unused fields are zero.  With bodies 1 to 3 and 6, block_*, grid, threads,
@@ -489,9 +491,9 @@ void ms_variant_destroy(ms_variant *v);
 int32_t ms_variant_info(const ms_variant *v, ms_variant_params *params, size_t *workspace_bytes);
 /* What a launch over `instances` instances runs: the body's tile, workgroups per instance, bytes of LDS of a workgroup.  They
  * are the fields of ms_variant_params unless the variant has a kernel of its own for many instances (body_tile_many), for
- * few tiles (MS_BODY_DOUBLE_STEPS) or for launches that fill the chip (MS_BODY_CONV_PATCH; tensors aligned to 16 bytes, others run
- * what the parameters say).  Of MS_BODY_IMAGE_ROWS they are those of that body, whether or not MS_BODY_CONV_PLANES takes its place.
- * Any pointer may be NULL.  BAD_ARG if instances < 1. */
+ * few tiles (MS_BODY_DOUBLE_STEPS), for launches that fill the chip (MS_BODY_CONV_PATCH) or for few rows (MS_BODY_FEW_ROWS); the last
+ * two need tensors aligned to 16 bytes, others run what the parameters say.  Of MS_BODY_IMAGE_ROWS they are those of that body,
+ * whether or not MS_BODY_CONV_PLANES takes its place.  Any pointer may be NULL.  BAD_ARG if instances < 1. */
 int32_t ms_variant_launch_shape(const ms_variant *v, int32_t instances, int32_t *body_tile, int32_t *workgroups, int32_t *lds_bytes);
 /* What materialising a variant compiles (Section 4, building a candidate): the kernel template's file name, then the
  * -D options that specialise it, one per line.  Two parameter sets that give the same text are the same kernel and

@@ -83,7 +83,8 @@ bool image_rows_many(const ms_op *op, const ms_variant_params *p, int64_t instan
 // And whether a launch over so many instances takes it.
 bool double_steps_few(const ms_op *op, const ms_variant_params *p, ms_variant_params *few);
 bool takes_few(const ms_op *op, const ms_variant_params *p, const ms_variant_params *few, int64_t instances);
-// The kernel of convolution launches that fill the chip (MS_BODY_CONV_PATCH, MS_BODY_CONV_PLANES); false = the operator has none.
+// The kernel of convolution launches that fill the chip (MS_BODY_CONV_PATCH, MS_BODY_CONV_PLANES) or of products of few rows that
+// do not (MS_BODY_FEW_ROWS); false = the operator has none.
 // Whether a launch over so many instances takes it, and its workgroups per compute unit.
 bool fill_kernel(const ms_op *op, const ms_variant_params *p, ms_variant_params *fill);
 bool takes_fill(const ms_op *op, const ms_variant_params *p, const ms_variant_params *fill, int64_t instances);

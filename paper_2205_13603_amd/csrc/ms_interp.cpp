@@ -354,6 +354,58 @@ int conv_steps(const ms_op *op, const ms_variant_params *p)
     return best;
 }
 
+// MS_BODY_FEW_ROWS: products of few rows with a row-major matrix (gemm_rows.hip), the second kernel of a nest's variant
+// (fill_kernel, takes_fill).
+struct FewRows {
+    int mt, nc;                 // 16-row tiles and 16-column tiles of a workgroup
+    int waves, depth, lds;      // wavefronts that share its reduction, their blocks of 64 k values in flight
+    int64_t tiles;
+};
+FewRows few_rows_tile(const ms_op *op, int tile)
+{
+    FewRows c;
+    c.mt = tile & 15;
+    c.nc = tile >> 4 & 15;
+    c.waves = tile >> 8 & 31;
+    c.depth = tile >> 16;
+    c.tiles = op->M / (c.mt * 16) * (op->N / (c.nc * 16));
+    int g = c.mt;
+    while (c.mt % g || (g > 1 && c.waves * g * c.nc * 1024 > 64 * 1024)) --g;
+    c.lds = c.waves * std::max(g * c.nc * 1024, c.mt * 2048);
+    return c;
+}
+// its tile, 0 = not taken
+int few_rows(const ms_op *op)
+{
+    const ms_op_desc &d = op->d;
+    if (d.kind != MS_OP_GEMM || op->in_size != 2 || op->M > 128 || op->M % 16 || op->N % 32 || op->K % 64) return 0;
+    // rows of B that lanes read side by side, 16-byte groups of k values of A, 32-bit offsets of elements
+    if (d.a_strides[2] != 1 || d.b_strides[2] != 1 || d.a_strides[1] % 8 || d.b_strides[1] % 8) return 0;
+    if (op->K * d.b_strides[1] > 0x7fffffff || op->M * d.a_strides[1] > 0x7fffffff) return 0;
+    // below 1 MiB of weights launches take the 3.5 us that any launch takes
+    if (op->K * op->N < 512 * 1024) return 0;
+    int best = 0;
+    int64_t cost = 0;
+    for (int nc : {2, 4})
+        for (int mt = 1; mt <= 8; ++mt) {
+            if (op->M / 16 % mt || op->N % (nc * 16)) continue;
+            // eight wavefronts hide latency better than four (48 x 4096 x 2048, mt = 1: 6.9 us and 7.3) until their sums are many
+            // (48 x 8000 x 1536, mt = 3: 7.5 and 7.2)
+            const int tile = mt | nc << 4 | (mt <= 2 ? 8 : 4) << 8 | (mt <= 2 ? 2 : 3) << 16;
+            const FewRows c = few_rows_tile(op, tile);
+            if (c.lds > g_limits.max_lds_bytes || c.waves > g_limits.max_waves || c.waves * 64 > g_limits.max_threads) continue;
+            if (mt * nc * 4 > g_limits.max_acc_per_thread || c.tiles > 1024) continue;
+            // a k value costs address lookups: mt for A and 4 for B, whatever its columns; a second round overlaps the first in part
+            // (112 x 2048 x 2048, mt = 1: 224 tiles 6.5 us, 448 of half the columns 8.2)
+            const int64_t rounds = (c.tiles + 255) / 256, clocks = op->K * (mt + 4) * (rounds == 1 ? 5 : rounds * 4);
+            if (!best || clocks < cost) {
+                best = tile;
+                cost = clocks;
+            }
+        }
+    return best;
+}
+
 // MS_BODY_CONV_PLANES: first layers on persistent workgroups over filter planes (conv_planes.hip), the second kernel of a variant on
 // MS_BODY_IMAGE_ROWS (fill_kernel, takes_fill).
 struct ConvPlanes {
@@ -1108,6 +1160,28 @@ bool ms::takes_few(const ms_op *op, const ms_variant_params *p, const ms_variant
 bool ms::fill_kernel(const ms_op *op, const ms_variant_params *p, ms_variant_params *patch)
 {
     if (p->family != MS_FAM_GEMM_MFMA) return false;
+    if (op->d.kind == MS_OP_GEMM) {
+        // not for what one instance does not take either; a split reduction is replaced too (128 x 1024 x 1024 in 8 parts, a second
+        // kernel: 8.8 us and 3.3)
+        const int tile = p->body == MS_BODY_NEST && op->M * op->N <= 1024 * 1024 ? few_rows(op) : 0;
+        if (!tile) return false;
+        const FewRows c = few_rows_tile(op, tile);
+        *patch = *p;
+        patch->body = MS_BODY_FEW_ROWS;
+        patch->body_tile = tile;
+        patch->block_m = c.mt * 16;
+        patch->block_n = c.nc * 16;
+        patch->block_k = c.waves * 32;
+        patch->grid[0] = (int32_t)c.tiles;
+        patch->grid[1] = patch->grid[2] = 1;
+        patch->waves = c.waves;
+        patch->threads = c.waves * 64;
+        patch->acc_per_thread = c.mt * c.nc * 4;
+        patch->lds_bytes = c.lds;
+        patch->compute_at = patch->rfactor = patch->reorder = 0;
+        patch->key = hash_params(op, patch);
+        return true;
+    }
     if (p->body == MS_BODY_IMAGE_ROWS) {
         const int tile = conv_planes(op);
         if (!tile) return false;
@@ -1151,6 +1225,13 @@ bool ms::fill_kernel(const ms_op *op, const ms_variant_params *p, ms_variant_par
 
 bool ms::takes_fill(const ms_op *op, const ms_variant_params *p, const ms_variant_params *patch, int64_t instances)
 {
+    if (patch->body == MS_BODY_FEW_ROWS) {
+        // Up to 64 x 64 outputs per compute unit and four workgroups on each: there it is faster than the best of 60 to 120 sampled
+        // nests (48 x 4096 x 2048: 7.0 us and 11.2; x 2: 10.5 and 12.2; 128 x 1024 x 1024: x 4 8.8 and 12.5; 128 x 8192 x 4096:
+        // 23 and 33; 16 x 16384 x 4096: 23.1 and 23.5).  Beyond, nests fill the chip and load each operand fewer times (48 x 4096 x
+        // 2048 x 8: 31 and 25; 16 x 1024 x 1024 x 64: 30 and 22; 128 x 16384 x 1024: 13.1 and 10.4).
+        return patch->grid[0] * instances <= 1024 && op->M * op->N * instances <= 1024 * 1024;
+    }
     if (patch->body == MS_BODY_CONV_PLANES) {
         // Launches whose rounds leave more than a quarter of the chip idle spread better in the smaller tiles of image rows (3 x 16 x
         // 64 x 64 -> 64, 7 x 7 x 7, x 4: 11.5 us and 18.7), and a single round of small tiles (64 x 64 x 4 -> 64, 7 x 7, batch 114: 7.4
@@ -1337,7 +1418,15 @@ int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec
             D.push_back(def("A_INST", ab / op->in_size));
             D.push_back(def("B_INST", bb / op->in_size));
         }
-        if (conv_patch) {
+        if (p->body == MS_BODY_FEW_ROWS) {
+            const FewRows c = few_rows_tile(op, p->body_tile);
+            k.template_name = "gemm_rows.hip";
+            D.push_back(def("FR_MT", c.mt));
+            D.push_back(def("FR_NC", c.nc));
+            D.push_back(def("FR_WAVES", c.waves));
+            D.push_back(def("FR_DEPTH", c.depth));
+            D.push_back(def("FR_LDS", c.lds));
+        } else if (conv_patch) {
             const ConvPatch c = conv_patch_tile(op, p->body_tile);
             k.template_name = "conv_patch.hip";
             D.push_back(def("CP_CW", c.cw));

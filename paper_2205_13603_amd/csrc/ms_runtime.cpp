@@ -26,7 +26,7 @@ struct ms_variant {
     hipFunction_t fn_many;   // kernel of launches over many instances, else null
     ms_variant *nest;        // MS_BODY_CONV_STEPS: the trace's nest, for operands off 16-byte boundaries (nest_of), else null
     ms_variant *few;         // MS_BODY_DOUBLE_STEPS: the kernel of launches of few tiles, else null
-    ms_variant *fill;        // convolutions: the kernel of launches that fill the chip, else null
+    ms_variant *fill;        // the kernel of convolutions that fill the chip or of products of few rows, else null
     ms_variant_params nest_p;
     std::mutex nest_mu;
     int device;              // device the module is loaded on, -1 = not loaded
@@ -118,7 +118,7 @@ extern "C" int32_t ms_variant_launch_shape(const ms_variant *v, int32_t instance
     if (!v) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_shape: NULL variant");
     if (instances < 1) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_shape: instances = %d", instances);
     if (v->few && takes_few(&v->op, &v->p, &v->few->p, instances)) v = v->few;
-    if (v->fill && v->fill->p.body == MS_BODY_CONV_PATCH && takes_fill(&v->op, &v->p, &v->fill->p, instances)) v = v->fill;
+    if (v->fill && v->fill->p.body != MS_BODY_CONV_PLANES && takes_fill(&v->op, &v->p, &v->fill->p, instances)) v = v->fill;
     int64_t lds = v->p.lds_bytes;
     const bool many = image_rows_many(&v->op, &v->p, instances, &lds);
     if (body_tile) *body_tile = many ? v->p.body_tile_many : v->p.body_tile;

@@ -4,7 +4,7 @@ import pytest
 
 from oracle import compare, oracle as O
 from paper_2205_13603_amd import binding as B, inputs as I
-from gpu_util import run_variant, run_variant_distinct
+from gpu_util import run_variant, run_variant_distinct, run_variant_offset
 
 pytestmark = pytest.mark.gpu
 
@@ -705,3 +705,41 @@ def test_one_wavefront_per_simd_tiles_exact():
             continue
         compare.assert_int_equal(got[0], ref8, "128 x 128 wave tiles, int8 trace %d" % n)
         compare.assert_int_equal(got[1], ref8, "128 x 128 wave tiles, int8 trace %d, instance 1" % n)
+
+
+@pytest.mark.parametrize("M,N,K,dtype,out,R,a_row,b_row", [
+    (16, 8192, 64, "f16", "f32", 1, 64, 8192),        # one block of k values: seven wavefronts add nothing
+    (48, 2080, 320, "f16", "f16", 1, 320, 2080),      # odd number of 32-column tiles; five blocks for four wavefronts
+    (80, 4544, 192, "bf16", "f32", 1, 200, 4552),     # strides between rows, fewer blocks than wavefronts
+    (112, 1088, 1152, "bf16", "bf16", 2, 1152, 1088), # instances, a tile count that 8 does not divide
+    (128, 8192, 1088, "f16", "f32", 1, 1088, 8192),   # the largest
+    (96, 1024, 4096, "f16", "f16", 3, 4104, 1024),
+    (64, 7296, 832, "bf16", "f32", 1, 832, 7296),
+])
+def test_few_rows_exact(M, N, K, dtype, out, R, a_row, b_row):
+    """Products of few rows whose wavefronts split the reduction: integer inputs, every partial sum exact in fp32, against the oracle.
+    An infinite weight reaches its column only.  Operands off 16-byte boundaries run the nest."""
+    g = I.rng(121)
+    op = B.gemm_op(M, N, K, dtype, out, a_strides=[0, a_row, 1], b_strides=[0, b_row, 1])
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 122, n) for n in range(400)) if B.trace_validate(op, space, t).body == B.BODY_NEST)
+    v = B.Variant(op, space, t)
+    assert v.launch_shape(R)[0] != v.params().body_tile
+    pool = []
+    for _ in range(min(R, 2)):
+        a, b = I.small_ints(g, (M, a_row), -1, 1, dtype), I.small_ints(g, (K, b_row), -1, 1, dtype)
+        b[K // 2, N // 3] = np.inf if dtype == "f16" else 0x7F80
+        a[:, K // 2] = 1 if dtype == "f16" else 0x3F80
+        pool.append([a, b])
+    refs = [O.gemm(np.ascontiguousarray(a[:, :K]), np.ascontiguousarray(b[:, :N]), bf16=(dtype == "bf16")) for a, b in pool]
+    assert max(np.abs(r[np.isfinite(r)]).max() for r in refs) <= (256 if out == "bf16" else 2048)
+    # the last rows end with their last elements
+    ins = [[np.ravel(a)[: (M - 1) * a_row + K], np.ravel(b)[: (K - 1) * b_row + N]] for a, b in pool]
+    got = run_variant_distinct(op, space, t, [ins[r % len(ins)] for r in range(R)], out, (M, N))
+    if got is not None:
+        for r in range(R):
+            assert np.array_equal(got[r] if R > 1 else got.reshape(M, N), refs[r % len(refs)], equal_nan=True), "instance %d of %d" % (r, R)
+    if R == 1:
+        got = run_variant_offset(op, space, t, ins[0], out, (M, N), [1, 0, 0])
+        if got is not None:
+            assert np.array_equal(got.reshape(M, N), refs[0], equal_nan=True), "offset"
