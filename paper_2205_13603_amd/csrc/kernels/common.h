@@ -91,6 +91,10 @@ __device__ __forceinline__ unsigned finish(float x, float y)
 // (x fastest, then y, z) to XCD f mod 8, so id (f mod 8) * (total / 8) + f / 8 makes the workgroups
 // one XCD receives consecutive in (z, i0, j0) order; tiles that share operand panels, and whole
 // instances, then sit behind one L2.
+// Batched products of several tiles do so under REORDER 0 and 1 too where the launch writes more than the L2s hold: tiles whose rows
+// are no whole lines then join them in one L2, and tiles of one product find its operands there (12 x 416 x 416 x 128 x 71 in fp16:
+// 139 -> 124 us; 16 x 432 x 432 x 32 x 42 in bf16: 81 -> 65; 8 x 448 x 128 x 448 x 75: 118 -> 100).  Launches below lose a little to
+// the arithmetic (12 x 384 x 384 x 32 x 2: 4.1 and 4.4).
 // RFACTOR > 1 (matrix-core kernels): RFACTOR consecutive workgroups share one output tile, workgroup ks
 // of them reduces over the ks-th run of k0 steps.
 #ifndef RFACTOR
@@ -101,16 +105,25 @@ __device__ __forceinline__ void block_to_tile(int &z, int &i0, int &j0, int &ks)
     constexpr int G = I0 * J0 * RFACTOR;
     int wg = blockIdx.x;
     z = blockIdx.z * gridDim.y + blockIdx.y;
-#if REORDER >= 2
-    const int nz = gridDim.y * gridDim.z;
-    const long total = (long)G * nz;
-    if (total % 8 == 0) {
-        const long f = wg + (long)G * z;
-        const long g = (f % 8) * (total / 8) + f / 8;
-        wg = (int)(g % G);
-        z = (int)(g / G);
-    }
+#if defined(DIM_B) && !IS_CONV
+    constexpr bool JOIN = REORDER < 2 && DIM_B > 1 && G > 1;
+#else
+    constexpr bool JOIN = false;
 #endif
+    if constexpr (REORDER >= 2 || JOIN) {
+        const int nz = gridDim.y * gridDim.z;
+        const long total = (long)G * nz;
+        bool permute = total % 8 == 0;
+#if defined(DIM_B) && !IS_CONV
+        if (JOIN) permute = permute && nz >= (32l << 20) / ((long)DIM_M * DIM_N * (int)sizeof(out_t));
+#endif
+        if (permute) {
+            const long f = wg + (long)G * z;
+            const long g = (f % 8) * (total / 8) + f / 8;
+            wg = (int)(g % G);
+            z = (int)(g / G);
+        }
+    }
     ks = wg % RFACTOR;
     wg /= RFACTOR;
 #if REORDER == 1

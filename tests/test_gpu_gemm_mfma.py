@@ -743,3 +743,28 @@ def test_few_rows_exact(M, N, K, dtype, out, R, a_row, b_row):
         got = run_variant_offset(op, space, t, ins[0], out, (M, N), [1, 0, 0])
         if got is not None:
             assert np.array_equal(got.reshape(M, N), refs[0], equal_nan=True), "offset"
+
+
+@pytest.mark.parametrize("trans_b", [True, False])
+@pytest.mark.parametrize("reorder", [0, 1])
+@pytest.mark.parametrize("many", [48, 49, 50])
+def test_batched_tiles_of_large_launches_exact(trans_b, reorder, many):
+    """Products of several tiles on either side of the 32 MiB of results (388 products) from which an XCD's tiles follow each other,
+    also where the workgroups are no multiple of 8.  Two inputs in turn, exact integers."""
+    Bn, S, D = 8 if many != 50 else 9, 208, 32
+    M, N, K = (S, S, D) if trans_b else (S, S, 2 * D)
+    g = I.rng(131)
+    op = B.bmm_op(Bn, M, N, K, trans_b, "f16")
+    space = op.space()
+
+    def fits(t):
+        p = B.trace_validate(op, space, t)
+        return p.body == B.BODY_NEST and p.reorder == reorder and p.rfactor <= 1 and p.grid[0] > 1 and (many != 50 or p.grid[0] * Bn * many % 8)
+
+    t = next(t for t in (B.trace_sample_valid(op, space, 132, n) for n in range(600)) if fits(t))
+    pool = [[I.small_ints(g, (Bn, M, K), -3, 3, "f16"), I.small_ints(g, (Bn, N, K) if trans_b else (Bn, K, N), -3, 3, "f16")] for _ in range(2)]
+    refs = [O.bmm(a, b, trans_b) for a, b in pool]
+    got = run_variant_distinct(op, space, t, [pool[r % 2] for r in range(many)], "f16", (Bn, M, N))
+    if got is not None:
+        for r in range(many):
+            assert np.array_equal(got[r], refs[r % 2]), "instance %d of %d" % (r, many)
