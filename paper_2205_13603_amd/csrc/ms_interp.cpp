@@ -60,7 +60,20 @@ RowVectors row_vectors_split(const ms_op *op, int v)
 {
     RowVectors r = {1, 0, 0, 256};
     while (r.lanes < 64 && r.lanes * v < op->K) r.lanes *= 2;
-    r.vectors = (int)((op->K / v + r.lanes - 1) / r.lanes);
+    auto vectors = [&](int lanes) { return (int)((op->K / v + lanes - 1) / lanes); };
+    // Rows of 2-byte values are bound by the exponentials, masked lanes included: narrower groups with fewer masked vectors, as long as
+    // they read 128 bytes and more at a time.  206464 x 304 in fp16: 64 lanes 61 us, 16 lanes 44; 25024 x 672: 15.2, 32 lanes 12.7;
+    // 200000 x 136: 32 lanes 29.8, 8 lanes 22.1.  Where fewer than four wavefronts per compute unit would be left, a launch waits for one
+    // row's chain instead (1024 x 1064: 64 lanes 3.45, 32 lanes 4.0; 4096 x 304, 16 lanes: 3.45 and 3.3).
+    // Not for a seventh fewer (30016 x 1320, 32 lanes: 13.8 and 13.6; 50048 x 552: 32 lanes 20.9, 16 lanes 21.3); fp32 rows are bound
+    // by memory, where wide groups write whole lines (55104 x 336: 64 lanes 21.9, 32 lanes 22.9).
+    if (v == 8)
+        for (int lanes : {32, 16, 8}) {
+            if (lanes >= r.lanes || op->M * lanes < 4 * 256 * 64 || vectors(lanes) > 8 || vectors(lanes) * v > g_limits.max_acc_per_thread) continue;
+            const int now = r.lanes * vectors(r.lanes), then = lanes * vectors(lanes);
+            if (lanes == 32 ? then * 6 <= now * 5 : then * 5 <= now * 4) r.lanes = lanes;
+        }
+    r.vectors = vectors(r.lanes);
     r.rows = r.threads / r.lanes;
     return r;
 }

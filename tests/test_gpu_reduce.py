@@ -173,6 +173,28 @@ def test_softmax_rows_aligned_to_their_elements(dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("rows,cols,lanes", [(4104, 304, 16), (8208, 136, 8), (2056, 552, 32), (2040, 552, 64), (2056, 1064, 32), (2056, 2016, 64)])
+def test_softmax_narrow_lane_groups(rows, cols, lanes, dtype):
+    """2-byte rows whose lane groups are narrower, with fewer masked vectors, from 4 wavefronts per compute unit on; the last workgroup in
+    part.  Lowest values and -infinity take no weight, a row of -infinity is NaN and leaves its neighbours alone."""
+    X = I.normal(I.rng(59), (1, rows, cols), 2.0, dtype)
+    low, inf = (np.finfo(np.float16).min, -np.inf) if dtype == "f16" else (0xFF7F, 0xFF80)
+    X[0, 2, 1::2], X[0, 3, : cols - 1], X[0, rows - 1, 8:] = low, inf, inf
+    X[0, 5] = inf
+    op = B.softmax_op(1, rows, cols, dtype)
+    space = op.space()
+    t = B.make_trace(space, [[rows // 8, 1, 8, 1], [cols // 8, 1, 8, 1], [0]])
+    p = B.trace_validate(op, space, t)
+    assert (p.body, p.tk[2]) == (B.BODY_ROW_VECTORS, lanes)
+    got = run_variant(op, space, t, [X], dtype, X.shape)
+    if got is not None:
+        got = got.reshape(X.shape)
+        assert np.all(np.isnan(got[0, 5]))
+        ref = O.softmax(np.delete(X, 5, 1), bf16=dtype == "bf16")
+        compare.assert_float_close(np.delete(got, 5, 1), ref, compare.RTOL_HALF, "softmax %d x %d" % (rows, cols))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_softmax_and_norm_half_inputs_odd_shapes(dtype):
     """Extents with factors 3 and 5; the softmax output is rounded once to the input type."""
     g = I.rng(53)
