@@ -6,7 +6,8 @@
 // What bounds it: the address lookups of a compute unit's loads, one per clock for four lanes, whatever they load; next the
 // misses that its L1 keeps in flight, from HBM.  So every lane loads 16 bytes and four lanes 64 bytes that follow each other: lines of
 // B as they lie, their columns dealt out by trades between lanes; lines of A by way of LDS (loaded as fragments, from 16 rows at
-// once, they took four times the lookups: 48 x 6720 x 4096 23.8 us, 19.0 so; 96 x 1728 x 3072 10.0 and 7.4).
+// once, they took four times the lookups: 48 x 6720 x 4096 23.8 us, 19.0 so; 96 x 1728 x 3072 10.0 and 7.4; tiles of 32 columns with 8-byte loads: 32 x 2048 x 2816
+// 7.65, 7.13 so).
 // Against nests whose workgroups stage 256 k values under barriers: 48 x 4096 x 2048 in fp16 8.25 -> 6.9 us (2.8 at the rate of a copy, 3.5
 // any launch), 128 x 6720 x 2048 in bf16 43.6 -> 9.7, 16 x 5440 x 2304 9.7 -> 7.1, 128 x 8192 x 4096 57 -> 26 (2.9 TB/s).
 #include "common.h"
@@ -30,12 +31,12 @@ constexpr int G = rows_per_pass();
 static_assert(DIM_M % R == 0 && DIM_N % C == 0 && DIM_K % 64 == 0 && sizeof(in_t) == 2, "see few_rows()");
 static_assert(NW * G * NC * 1024 <= FR_LDS && NW * MT * 2048 <= FR_LDS, "the host's count of LDS");
 
-template <int N> struct __attribute__((aligned(4 * N))) dwords {
-    unsigned v[N];
-};
+// Lane 16 q + UL t + u: load r of B brings columns 8 u ... of k value 16 q + 2 NC t + r; after the trades the lane holds columns 8 u + NC t ... of all
+// 16 k values of q
+constexpr int UL = NC * 2;
 struct block {
     u4_t a[MT][2];    // row 8 h + lane / 8 of a tile, 16-byte chunk lane % 8 of its line (swizzled by the row)
-    dwords<NC> b[8];  // k value 16 q + 8 t + r, columns 2 NC u ...: lane = 16 q + 8 t + u
+    u4_t b[2 * NC];
 };
 
 __device__ __forceinline__ f4_t mfma(const u4_t &a, const u4_t &b, f4_t c)
@@ -50,11 +51,17 @@ __device__ __forceinline__ f4_t mfma(const u4_t &a, const u4_t &b, f4_t c)
 __device__ __forceinline__ void request(block &x, const in_t *a, const in_t *b, int kb)
 {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) x.b[r] = *(const dwords<NC> *)(b + (unsigned)(kb * 64 + r) * (unsigned)SB_K);
+    for (int r = 0; r < 2 * NC; ++r) x.b[r] = *(const u4_t *)(b + (unsigned)(kb * 64 + r) * (unsigned)SB_K);
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int h = 0; h < 2; ++h) x.a[m][h] = *(const u4_t *)(a + (unsigned)((m * 16 + h * 8) * SA_I + kb * 64));
+}
+
+// `keep`, in the banks of four lanes of `BANKS` the value of `from` that a rotation of 16 lanes brings
+template <int ROTATE, int BANKS> __device__ __forceinline__ unsigned trade(unsigned keep, unsigned from)
+{
+    return __builtin_amdgcn_update_dpp(keep, from, ROTATE, 0xf, BANKS, false);
 }
 
 __device__ __forceinline__ void multiply(const block &x, char *own, int lane, f4_t (&acc)[MT][NC])
@@ -64,16 +71,26 @@ __device__ __forceinline__ void multiply(const block &x, char *own, int lane, f4
     for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int h = 0; h < 2; ++h) *(u4_t *)(own + (m * 2 + h) * 1024 + lane * 16) = x.a[m][h];
-    // trades between lanes 8 apart: each keeps NC of the 2 NC columns, for 16 k values
+    // trades between lanes 8 and 4 apart: each keeps NC of the 8 columns, for 16 k values
     unsigned v[16][NC / 2];
 #pragma unroll
-    for (int r = 0; r < 8; ++r)
+    for (int r = 0; r < 2 * NC; ++r) {
+        unsigned own_half[2], other[2];
 #pragma unroll
-        for (int d = 0; d < NC / 2; ++d) {
-            const unsigned lo = x.b[r].v[d], hi = x.b[r].v[d + NC / 2];
-            v[r][d] = __builtin_amdgcn_update_dpp(lo, hi, 0x128, 0xf, 0xc, false);
-            v[r + 8][d] = __builtin_amdgcn_update_dpp(hi, lo, 0x128, 0xf, 0x3, false);
+        for (int d = 0; d < 2; ++d) {
+            own_half[d] = trade<0x128, 0xc>(x.b[r][d], x.b[r][d + 2]);
+            other[d] = trade<0x128, 0x3>(x.b[r][d + 2], x.b[r][d]);
         }
+        if constexpr (NC == 4) {
+#pragma unroll
+            for (int d = 0; d < 2; ++d) v[r][d] = own_half[d], v[r + 8][d] = other[d];
+        } else {
+            v[r][0] = trade<0x124, 0xa>(own_half[0], own_half[1]);
+            v[r + 4][0] = trade<0x12c, 0x5>(own_half[1], own_half[0]);
+            v[r + 8][0] = trade<0x124, 0xa>(other[0], other[1]);
+            v[r + 12][0] = trade<0x12c, 0x5>(other[1], other[0]);
+        }
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         u4_t f[NC];
@@ -102,8 +119,8 @@ extern "C" __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void ms_kernel(co
     A += (size_t)inst * A_INST + (unsigned)(rt * R * SA_I);
     B += (size_t)inst * B_INST + (unsigned)(ct * C);
     Y += (size_t)inst * DIM_M * DIM_N;
-    const int row = lane / 8, chunk = lane % 8 ^ row, t = l / 8, u = l % 8;
-    const in_t *a = A + (unsigned)(row * SA_I + chunk * 8), *b = B + ((unsigned)(q * 16 + t * 8) * (unsigned)SB_K + u * 2 * NC);
+    const int row = lane / 8, chunk = lane % 8 ^ row, t = l / UL, u = l % UL;
+    const in_t *a = A + (unsigned)(row * SA_I + chunk * 8), *b = B + ((unsigned)(q * 16 + t * 2 * NC) * (unsigned)SB_K + u * 8);
     char *own = lds + wave * MT * 2048;
     const int lo = wave * KB / NW, n = (wave + 1) * KB / NW - lo;
     const int turn = n ? ct % n : 0; // columns start at different blocks of A: 48 x 4096 x 2048 7.7 us without, 6.9
@@ -161,7 +178,7 @@ extern "C" __global__ __launch_bounds__(NW * 64, (NW + 3) / 4) void ms_kernel(co
 #pragma unroll
             for (int c = 0; c < NC; ++c) o.v[c] = from_acc(y.v[c]);
             const int row = rt * R + (p * G + s / 4) * 16 + q * 4 + s % 4;
-            *(vec_t<out_t, NC> *)(Y + (size_t)row * DIM_N + ct * C + l % 8 * 2 * NC + l / 8 * NC) = o;
+            *(vec_t<out_t, NC> *)(Y + (size_t)row * DIM_N + ct * C + u * 8 + t * NC) = o;
         }
     }
 }

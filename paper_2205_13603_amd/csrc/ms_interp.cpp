@@ -408,8 +408,9 @@ int few_rows(const ms_op *op)
             const FewRows c = few_rows_tile(op, tile);
             if (c.lds > g_limits.max_lds_bytes || c.waves > g_limits.max_waves || c.waves * 64 > g_limits.max_threads) continue;
             if (mt * nc * 4 > g_limits.max_acc_per_thread || c.tiles > 1024) continue;
-            // a k value costs address lookups: mt for A and 4 for B, whatever its columns; a second round overlaps the first in part
-            // (112 x 2048 x 2048, mt = 1: 224 tiles 6.5 us, 448 of half the columns 8.2)
+            // a k value costs lookups of mt + 4 groups of four lanes (columns by 32: of mt + 2, at half the bytes for a line of the L2,
+            // which comes to the same); a second round overlaps the first in part (112 x 2176 x 1280, mt = 1: 238 tiles of 64 columns
+            // 5.3 us, 476 of 32 6.2)
             const int64_t rounds = (c.tiles + 255) / 256, clocks = op->K * (mt + 4) * (rounds == 1 ? 5 : rounds * 4);
             if (!best || clocks < cost) {
                 best = tile;
