@@ -47,10 +47,11 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
     (void)unused_;
     int z = blockIdx.z * gridDim.y + blockIdx.y; // instance * N + n
     int wg = blockIdx.x;
-    const long total = (long)gridDim.x * gridDim.y * gridDim.z;
-    if (total % 8 == 0) { // workgroup order grouped per XCD: strips that share input rows meet in one L2
-        const long f = wg + (long)gridDim.x * z;
-        const long g = (f % 8) * (total / 8) + f / 8;
+    {
+        // workgroup order grouped per XCD, in runs that differ by one at most: strips that share input rows meet in one L2 (18 x 66 x 66 x 328,
+        // stride 1, 6678 workgroups: 52 us in the order of launch)
+        const unsigned total = gridDim.x * gridDim.y * gridDim.z, f = wg + gridDim.x * z, xcd = f % 8, left = total % 8;
+        const unsigned g = xcd * (total / 8) + (xcd < left ? xcd : left) + f / 8;
         wg = (int)(g % gridDim.x);
         z = (int)(g / gridDim.x);
     }

@@ -91,3 +91,18 @@ def test_large_depthwise_launches_exact(N, H, W_, Cc, stride, pad, k):
     got = run_variant_distinct(op, space, t, ins, "f32", ref.shape)
     if got is not None:
         assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("N,H,W_,Cc,stride,pad,k", [(1, 23, 23, 24, 1, 1, 3), (3, 23, 23, 24, 1, 1, 3), (101, 18, 22, 40, 1, 1, 3), (29, 19, 37, 104, 2, 2, 5)])
+def test_depthwise_strip_workgroups_no_multiple_of_8_exact(N, H, W_, Cc, stride, pad, k):
+    """Workgroups dealt to the XCDs in runs of unequal length, fewer than 8 among them; integer-valued inputs -> exact."""
+    g = I.rng(8)
+    ins = [[I.small_ints(g, (N, H, W_, Cc), -3, 3, "f32"), I.small_ints(g, (k, k, Cc), -3, 3, "f32")]]
+    ref = O.dwconv2d_nhwc(*ins[0], stride=stride, pad=pad)
+    op = B.dwconv2d_op(N, H, W_, Cc, k, k, stride=stride, pad=pad)
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 19, n) for n in range(200)) if B.trace_validate(op, space, t).body == B.BODY_STRIPS)
+    assert B.trace_validate(op, space, t).grid[0] * N % 8
+    got = run_variant_distinct(op, space, t, ins, "f32", ref.shape)
+    if got is not None:
+        assert np.array_equal(got, ref)
