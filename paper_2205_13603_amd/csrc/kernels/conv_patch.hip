@@ -68,7 +68,7 @@ struct tile_id {
 };
 __device__ __forceinline__ tile_id decode(long f, long total)
 {
-    if (total % 8 == 0) f = (f % 8) * (total / 8) + f / 8; // tiles of one XCD follow each other: they share patch rows
+    f = f % 8 * (total / 8) + (f % 8 < total % 8 ? f % 8 : total % 8) + f / 8; // tiles of one XCD follow each other: they share patch rows
     constexpr int G = JB * TPI * GROUPS;
     const int g = (int)(f % G), t = g / JB;
     return {(int)uniform((unsigned)(f / G)), (int)uniform(t / TPI * IMGS), (int)uniform(t % TPI * ROWS), (int)uniform(g % JB)};

@@ -75,7 +75,7 @@ struct tile_id {
 };
 __device__ __forceinline__ tile_id decode(long f, long total)
 {
-    if (total % 8 == 0) f = (f % 8) * (total / 8) + f / 8; // tiles of one XCD follow each other: they share input rows and planes
+    f = f % 8 * (total / 8) + (f % 8 < total % 8 ? f % 8 : total % 8) + f / 8; // tiles of one XCD follow each other: they share input rows and planes
     constexpr int G = JB * CV_OD * TILES * CV_N;
     const int g = (int)(f % G);
     tile_id t;

@@ -135,9 +135,11 @@ __device__ __forceinline__ void image_rows(const void *__restrict__ x_, const vo
     constexpr int PX = T::PX, TPR = T::TPR, TILES = T::TILES, PRS = T::PRS, PATCH_B = T::PATCH_B;
     __shared__ __attribute__((aligned(16))) char smem[T::LDS_B];
     int wg = blockIdx.x, z = blockIdx.z * gridDim.y + blockIdx.y; // z = instance
-    const long total = (long)gridDim.x * gridDim.y * gridDim.z;
-    if (total % 8 == 0) { // workgroup order grouped per XCD: tiles that share input rows and planes meet in one L2
-        const long f = wg + (long)gridDim.x * z, g = (f % 8) * (total / 8) + f / 8;
+    {
+        // workgroup order grouped per XCD, in runs that differ by one at most: tiles that share input rows and planes meet in one L2
+        // (5 x 8 x 160 x 160 x 4 -> 32, 7 x 7 x 7: 24.6 us in the order of launch, 22.1)
+        const unsigned total = gridDim.x * gridDim.y * gridDim.z, f = wg + gridDim.x * z, left = total % 8;
+        const unsigned g = f % 8 * (total / 8) + (f % 8 < left ? f % 8 : left) + f / 8;
         wg = (int)(g % gridDim.x);
         z = (int)(g / gridDim.x);
     }

@@ -939,3 +939,20 @@ def test_first_layer_planes_exact(N, D, H, W_, Cin, Cout, k, stride, pad, dtype,
     if got is not None:
         for r in range(R):
             assert np.array_equal(got[r] if R > 1 else got.reshape(refs[0].shape), refs[r % len(pool)], equal_nan=True), "instance %d of %d" % (r, R)
+
+
+@pytest.mark.parametrize("N,H,W_,Cin,Cout,k,R", [(3, 40, 24, 3, 32, 7, 1), (1, 96, 64, 3, 96, 3, 9), (5, 64, 48, 4, 64, 5, 1)])
+def test_first_layer_workgroups_no_multiple_of_8_exact(N, H, W_, Cin, Cout, k, R):
+    """Image rows whose workgroups are dealt to the XCDs in runs of unequal length, fewer than 8 among them: integers, two inputs in turn."""
+    g = I.rng(141)
+    op = B.conv2d_op(N, H, W_, Cin, Cout, k, k, stride=2, pad=k // 2)
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 142, n) for n in range(200)) if B.trace_validate(op, space, t).body == B.BODY_IMAGE_ROWS)
+    assert B.trace_validate(op, space, t).grid[0] * R % 8
+    pool = [[I.small_ints(g, (N, H, W_, Cin), -1, 1, "f16"), I.small_ints(g, (k, k, Cin, Cout), -1, 1, "f16"), g.integers(-3, 4, size=Cout).astype(np.float32)]
+            for _ in range(2)]
+    refs = [O.conv2d_nhwc(q[0], q[1], bias=q[2], relu=True, stride=2, pad=k // 2) for q in pool]
+    got = run_variant_distinct(op, space, t, [pool[r % 2] for r in range(R)], "f16", refs[0].shape)
+    if got is not None:
+        for r in range(R):
+            assert np.array_equal(got[r] if R > 1 else got.reshape(refs[0].shape), refs[r % 2]), "instance %d of %d" % (r, R)
