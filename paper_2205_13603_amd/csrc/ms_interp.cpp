@@ -563,6 +563,7 @@ int conv_patch(const ms_op *op)
                             }
                         }
         }
+    if (!best) return 0; // no tile fits: channels that are no whole columns of 32, rows wider than 15 wavefronts
     // single images come in many instances; a batch as one
     return d.dims[0] == 1 || best == best_many ? best_many | CONV_PATCH_MANY : best;
 }

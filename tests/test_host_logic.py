@@ -849,6 +849,24 @@ def test_conv_steps_end_where_their_offsets_do(mk, image, ahead, step):
         assert (p.body == B.BODY_CONV_STEPS) == taken, (n, taken, p.body)
 
 
+@pytest.mark.parametrize("mk", [
+    lambda: B.conv2d_op(8, 56, 56, 64, 48, 3, 3, pad=1),                 # 48 output channels: no whole columns of 32
+    lambda: B.conv2d_op(1, 20, 20, 32, 16, 3, 3, pad=1, in_dtype="bf16"),
+    lambda: B.conv2d_op(1, 256, 256, 64, 64, 3, 3, pad=1),               # a row is 16 strips of 16 columns
+    lambda: B.conv1d_op(1, 256, 64, 128, 3, pad=1),
+    lambda: B.conv2d_transposed_op(1, 256, 256, 64, 64, 3, 3, pad=1)])
+def test_convolutions_without_a_tile_of_input_patches_keep_their_kernel(mk):
+    """Stride 1 and whole 32-channel groups of the input, but no tile of input patches fits: a variant builds, and launches of
+    any number of instances run what its parameters say."""
+    op = mk()
+    sp = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, sp, 43, n) for n in range(200)) if B.trace_validate(op, sp, t).family == B.FAM_GEMM_MFMA)
+    v = B.Variant(op, sp, t)
+    p = v.params()
+    for instances in (1, 512):
+        assert v.launch_shape(instances) == (p.body_tile, p.grid[0] * p.grid[1] * p.grid[2], p.lds_bytes)
+
+
 def test_few_long_rows_keep_their_wide_lane_groups():
     """Softmax without staging: a few long rows keep a lane group of a wavefront or more per row; many rows, short rows and
     groups that walk a row or several rows in turn go to the row kernel, as do groups narrower than a line."""
