@@ -89,7 +89,6 @@ bool takes_few(const ms_op *op, const ms_variant_params *p, const ms_variant_par
 bool fill_kernel(const ms_op *op, const ms_variant_params *p, ms_variant_params *fill);
 bool takes_fill(const ms_op *op, const ms_variant_params *p, const ms_variant_params *fill, int64_t instances);
 int fill_per_cu(const ms_op *op, const ms_variant_params *p);
-uint64_t launch_key(const ms_op *op, const ms_variant_params *p, int64_t instances); // key of the kernel that such a launch runs
 // ms_trace_validate with every rule that gives the trace another body left out
 int32_t validate_as_nest(const ms_op *op, const ms_space *space, const ms_trace *trace, ms_variant_params *out);
 int32_t make_kernel_spec(const ms_op *op, const ms_variant_params *p, KernelSpec *out);

@@ -1270,12 +1270,6 @@ bool ms::takes_fill(const ms_op *op, const ms_variant_params *p, const ms_varian
     return (gathers && !single) || tiles * 100 >= busy * (gathers ? 35 : p->compute_at >= 2 && single ? 80 : 60);
 }
 
-uint64_t ms::launch_key(const ms_op *op, const ms_variant_params *p, int64_t instances)
-{
-    ms_variant_params patch;
-    return fill_kernel(op, p, &patch) && takes_fill(op, p, &patch, instances) ? patch.key : p->key;
-}
-
 int ms::fill_per_cu(const ms_op *op, const ms_variant_params *p)
 {
     return p->body == MS_BODY_CONV_PLANES ? conv_planes_tile(op, p->body_tile).per_cu() : conv_patch_tile(op, p->body_tile).per_cu;

@@ -16,6 +16,7 @@
 #include <cmath>
 #include <cstring>
 #include <map>
+#include <set>
 #include <vector>
 
 using namespace ms;
@@ -69,8 +70,35 @@ struct Search {
     int32_t n_feat = 0;
     bool stop = false;
 
+    // Second kernels of the operator by family and body of a trace (of a trace they read nothing else); family < 0 = it has none.
+    std::map<int, ms_variant_params> fills;
+
     // key of the kernel that a measurement of the variant runs
-    uint64_t kernel(const ms_variant_params &p) const { return fake ? p.key : launch_key(op, &p, cfg->measure.instances); }
+    uint64_t kernel(const ms_variant_params &p)
+    {
+        if (fake) return p.key;
+        for (int32_t i = 0; i < n_sets; ++i) // tensors off 16-byte boundaries run what the parameters say
+            for (int k = 0; k < (op->d.has_bias ? 3 : 2); ++k)
+                if ((uintptr_t)sets[i].inputs[k] & 15u) return p.key;
+        auto at = fills.emplace(p.family * 256 + p.body, ms_variant_params{});
+        ms_variant_params &second = at.first->second;
+        if (at.second && !fill_kernel(op, &p, &second)) second.family = -1;
+        return second.family >= 0 && takes_fill(op, &p, &second, cfg->measure.instances) ? second.key : p.key;
+    }
+    // What is worth compiling ahead of a batch's measurements: one trace of each kernel that they run and none has run so far.
+    void prebuild(const std::vector<ms_trace> &batch)
+    {
+        if (fake) return;
+        std::vector<ms_trace> fresh;
+        std::set<uint64_t> have;
+        ms_variant_params p;
+        for (const ms_trace &t : batch) {
+            if (ms_trace_validate(op, space, &t, &p) != MS_OK) continue;
+            const uint64_t runs = kernel(p);
+            if (!seen.count(runs) && have.insert(runs).second) fresh.push_back(t);
+        }
+        if (!fresh.empty()) ms_prebuild(op, space, fresh.data(), (int32_t)fresh.size(), cfg->compile_threads, nullptr);
+    }
     // returns latency in us, or < 0 when the candidate produced no measurement
     double evaluate(const ms_trace &t, uint64_t *key_out)
     {
@@ -238,7 +266,8 @@ extern "C" int32_t ms_search(const ms_op *op, const ms_space *space, const ms_se
                 ++out->n_invalid;
                 continue;
             }
-            if (have.count(S.kernel(p))) {
+            const uint64_t runs = S.kernel(p);
+            if (have.count(runs)) {
                 ++out->n_duplicate;
                 continue;
             }
@@ -247,7 +276,7 @@ extern "C" int32_t ms_search(const ms_op *op, const ms_space *space, const ms_se
             if (ms_variant_features(op, &p, fv, 128, &nf) != MS_OK) continue;
             if (nf != S.n_feat) return fail(MS_ERR_BAD_ARG, "ms_search: pre-training rows have %d features, this operator's variants %d", S.n_feat, nf);
             if (ms_cost_model_predict(model, fv, 1, nf, &d.pred) != MS_OK) continue;
-            have[S.kernel(p)] = true;
+            have[runs] = true;
             drawn.push_back(d);
         }
         std::vector<size_t> by_pred(drawn.size());
@@ -261,7 +290,7 @@ extern "C" int32_t ms_search(const ms_op *op, const ms_space *space, const ms_se
         }
         for (size_t i = 0; i < drawn.size() && (int)batch.size() < want_init; ++i)
             if (!taken[i]) batch.push_back(drawn[i].t);
-        if (!fake_latency && !batch.empty()) ms_prebuild(op, space, batch.data(), (int32_t)batch.size(), cfg->compile_threads, nullptr);
+        S.prebuild(batch);
         for (auto &t : batch) {
             if (S.stop || out->n_measured >= want_init) break;
             uint64_t key = 0;
@@ -284,7 +313,7 @@ extern "C" int32_t ms_search(const ms_op *op, const ms_space *space, const ms_se
                 else ++out->n_invalid;
             }
             if (batch.empty()) return fail(MS_ERR_INVALID_TRACE, "ms_search: the sampler produced no valid trace");
-            if (!fake_latency) ms_prebuild(op, space, batch.data(), (int32_t)batch.size(), cfg->compile_threads, nullptr);
+            S.prebuild(batch);
             for (auto &t : batch) {
                 if (S.stop || out->n_measured >= want) break;
                 uint64_t key = 0;
@@ -368,7 +397,8 @@ extern "C" int32_t ms_search(const ms_op *op, const ms_space *space, const ms_se
                         ++out->n_invalid;
                         continue;
                     }
-                    if (S.seen.count(S.kernel(p)) || in_batch.count(S.kernel(p))) {
+                    const uint64_t runs = S.kernel(p);
+                    if (S.seen.count(runs) || in_batch.count(runs)) {
                         ++out->n_duplicate;
                         continue;
                     }
@@ -383,7 +413,7 @@ extern "C" int32_t ms_search(const ms_op *op, const ms_space *space, const ms_se
                         if (fc > parent_cost && !(unit_uniform(rng) < exp(-(fc - parent_cost) / (T * fbest)))) continue;
                     }
                     sc.key = p.key;
-                    in_batch[S.kernel(p)] = true;
+                    in_batch[runs] = true;
                     cand.push_back(sc);
                 }
             }
@@ -411,11 +441,9 @@ extern "C" int32_t ms_search(const ms_op *op, const ms_space *space, const ms_se
             for (size_t i = 0; i < cand.size() && (int)kids.size() < cfg->children; ++i)
                 if (!taken[i]) take(i);
         }
-        if (!fake_latency) {
-            std::vector<ms_trace> batch;
-            for (auto &k : kids) batch.push_back(k.t);
-            ms_prebuild(op, space, batch.data(), (int32_t)batch.size(), cfg->compile_threads, nullptr);
-        }
+        std::vector<ms_trace> batch;
+        for (auto &k : kids) batch.push_back(k.t);
+        S.prebuild(batch);
         std::vector<Member> snapshot = pop; // parents as they were when the children were proposed
         for (auto &k : kids) {
             if (S.stop || out->n_measured >= cfg->trials) break;

@@ -953,6 +953,42 @@ def test_a_search_measures_a_body_once():
     assert res.n_measured == 1 and res.n_duplicate > 0
 
 
+@pytest.mark.parametrize("mk,instances,offset,kernels", [
+    (lambda: B.conv2d_op(1, 16, 16, 32, 32, 3, 3, pad=1), 512, 0, 2),   # input patches and the nest of the trace that is measured
+    (lambda: B.gemm_op(16, 1024, 512, "f16"), 1, 0, 2),                 # few rows
+    (lambda: B.gemm_op(16, 1024, 512, "f16"), 1, 4, 40)])               # operands off 16-byte boundaries: nests of their own
+def test_a_search_compiles_what_its_launches_run(mk, instances, offset, kernels, tmp_path):
+    """Traces whose launches all run one second kernel are one candidate: a search compiles it once, with one nest, and ends.
+    Without a GPU every measurement fails, so the search goes through all its proposals."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the buffers are addresses only")
+    op = mk()
+    cfg = B.search_cfg_default()
+    cfg.seed, cfg.trials, cfg.init_population = 3, 2, 2
+    cfg.measure.instances = instances
+    if offset:
+        cfg.trials = cfg.init_population = 20
+    before = B.jit_stats()
+    B.set_cache_dir(str(tmp_path))
+    try:
+        stop = [0]
+
+        def failed(t):
+            assert t.status == B.MS_ERR_HIP
+            stop[0] += 1
+            return stop[0] >= 20
+
+        with pytest.raises(B.MsError) as e:
+            B.search(op, op.space(), cfg, [([4096 + offset] * 3, 4096)], on_trial=failed)
+        assert e.value.code == B.MS_ERR_HIP
+    finally:
+        B.set_cache_dir(os.path.join(os.path.dirname(B.LIB_PATH), "kcache"))
+    built = B.jit_stats()["compiled"] - before["compiled"]
+    assert built == kernels if not offset else 15 <= built <= kernels
+    assert stop[0] == (1 if not offset else 20)
+
+
 def test_unroll_budgets_that_resolve_alike_share_a_key():
     op = B.dwconv2d_op(1, 28, 28, 12)
     sp = op.space()
