@@ -493,7 +493,7 @@ int32_t ms_variant_info(const ms_variant *v, ms_variant_params *params, size_t *
  * are the fields of ms_variant_params unless the variant has a kernel of its own for many instances (body_tile_many), for
  * few tiles (MS_BODY_DOUBLE_STEPS), for launches that fill the chip (MS_BODY_CONV_PATCH) or for few rows (MS_BODY_FEW_ROWS); the last
  * two need tensors aligned to 16 bytes, others run what the parameters say.  Of MS_BODY_IMAGE_ROWS they are those of that body,
- * whether or not MS_BODY_CONV_PLANES takes its place.  Any pointer may be NULL.  BAD_ARG if instances < 1. */
+ * whether or not MS_BODY_CONV_PLANES takes its place (ms_variant_launch_kernel tells).  Any pointer may be NULL.  BAD_ARG if instances < 1. */
 int32_t ms_variant_launch_shape(const ms_variant *v, int32_t instances, int32_t *body_tile, int32_t *workgroups, int32_t *lds_bytes);
 /* What materialising a variant compiles (Section 4, building a candidate): the kernel template's file name, then the
  * -D options that specialise it, one per line.  Two parameter sets that give the same text are the same kernel and
@@ -510,6 +510,10 @@ typedef struct ms_variant_resources {
     int32_t reserved[2];
 } ms_variant_resources;
 int32_t ms_variant_resources_get(const ms_variant *v, ms_variant_resources *out);
+/* The kernel that a launch over `instances` instances runs, all tensors on 16-byte boundaries: its parameters (body, tile,
+ * workgroups, LDS) and what it occupies.  Those of ms_variant_info and ms_variant_resources_get unless that launch takes
+ * another kernel of the variant, MS_BODY_CONV_PLANES among them.  Either pointer may be NULL.  BAD_ARG if instances < 1. */
+int32_t ms_variant_launch_kernel(const ms_variant *v, int32_t instances, ms_variant_params *params, ms_variant_resources *resources);
 /* Compile the kernels of n traces ahead of use on `threads` host threads
  * (invalid traces are skipped).  *n_built = kernels now in the cache. */
 int32_t ms_prebuild(const ms_op *op, const ms_space *space, const ms_trace *traces, int32_t n,

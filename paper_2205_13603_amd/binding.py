@@ -26,7 +26,8 @@ SPACE_RFACTOR = 0x400  # opt-in: sample the split of the reduction across workgr
 SPACE_DEFAULT = 0xFF
 STATIC_WORKSPACE_BYTES = 32 << 20
 FAM_GEMM_ALU, FAM_GEMM_MFMA, FAM_DWCONV, FAM_REDUCE = range(4)
-BODY_NEST, BODY_ROW_VECTORS, BODY_STRIPS, BODY_IMAGE_ROWS, BODY_PHASES, BODY_DOUBLE_STEPS, BODY_CONV_STEPS = range(7)
+(BODY_NEST, BODY_ROW_VECTORS, BODY_STRIPS, BODY_IMAGE_ROWS, BODY_PHASES, BODY_DOUBLE_STEPS, BODY_CONV_STEPS, BODY_CONV_PATCH, BODY_CONV_PLANES,
+ BODY_FEW_ROWS) = range(10)
 MAX_SLOTS, MAX_FACTORS, MAX_CANDS, MAX_LOOPS = 16, 4, 12, 8
 
 F8E4M3 = 5
@@ -183,6 +184,7 @@ SYMBOLS = {
     "ms_variant_launch_shape": (C.c_int32, [C.c_void_p, C.c_int32, _P(C.c_int32), _P(C.c_int32), _P(C.c_int32)]),
     "ms_variant_kernel_text": (C.c_int32, [C.c_void_p, _P(ms_variant_params), C.c_char_p, C.c_size_t, _P(C.c_size_t)]),
     "ms_variant_resources_get": (C.c_int32, [C.c_void_p, _P(ms_variant_resources)]),
+    "ms_variant_launch_kernel": (C.c_int32, [C.c_void_p, C.c_int32, _P(ms_variant_params), _P(ms_variant_resources)]),
     "ms_prebuild": (C.c_int32, [C.c_void_p, _P(ms_space), _P(ms_trace), C.c_int32, C.c_int32, _P(C.c_int32)]),
     "ms_set_cache_dir": (C.c_int32, [C.c_char_p]),
     "ms_jit_stats": (C.c_int32, [_P(C.c_int64), _P(C.c_int64), _P(C.c_int64), _P(C.c_int32), _P(C.c_int32)]),
@@ -559,6 +561,12 @@ class Variant:
         r = ms_variant_resources()
         _check(lib().ms_variant_resources_get(self.handle, C.byref(r)))
         return r
+
+    def launch_kernel(self, instances):
+        """(parameters, resources) of the kernel that a launch over `instances` instances runs, tensors on 16-byte boundaries."""
+        p, r = ms_variant_params(), ms_variant_resources()
+        _check(lib().ms_variant_launch_kernel(self.handle, instances, C.byref(p), C.byref(r)))
+        return p, r
 
     def workspace_bytes(self):
         """Bytes of workspace one instance needs (0 unless the reduction is split across workgroups);

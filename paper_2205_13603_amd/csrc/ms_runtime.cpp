@@ -113,12 +113,18 @@ extern "C" int32_t ms_variant_info(const ms_variant *v, ms_variant_params *param
     return MS_OK;
 }
 
+// Which of a variant's kernels a launch over so many instances runs, tensors on 16-byte boundaries.
+static const ms_variant *kernel_of(const ms_variant *v, int32_t instances)
+{
+    if (v->few && takes_few(&v->op, &v->p, &v->few->p, instances)) return v->few;
+    return v->fill && takes_fill(&v->op, &v->p, &v->fill->p, instances) ? v->fill : v;
+}
+
 extern "C" int32_t ms_variant_launch_shape(const ms_variant *v, int32_t instances, int32_t *body_tile, int32_t *workgroups, int32_t *lds_bytes)
 {
     if (!v) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_shape: NULL variant");
     if (instances < 1) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_shape: instances = %d", instances);
-    if (v->few && takes_few(&v->op, &v->p, &v->few->p, instances)) v = v->few;
-    if (v->fill && v->fill->p.body != MS_BODY_CONV_PLANES && takes_fill(&v->op, &v->p, &v->fill->p, instances)) v = v->fill;
+    if (const ms_variant *runs = kernel_of(v, instances); runs->p.body != MS_BODY_CONV_PLANES) v = runs;
     int64_t lds = v->p.lds_bytes;
     const bool many = image_rows_many(&v->op, &v->p, instances, &lds);
     if (body_tile) *body_tile = many ? v->p.body_tile_many : v->p.body_tile;
@@ -147,20 +153,18 @@ static long meta_uint(const std::vector<char> &blob, const char *key, size_t fro
     return -1;
 }
 
-extern "C" int32_t ms_variant_resources_get(const ms_variant *v, ms_variant_resources *out)
+// of the kernel `entry` of a code object
+static int32_t resources_of(const std::vector<char> &blob, const std::string &entry, ms_variant_resources *out)
 {
-    if (!v || !out) return fail(MS_ERR_BAD_ARG, "ms_variant_resources_get: NULL argument");
     memset(out, 0, sizeof *out);
-    const std::vector<char> &blob = *v->code;
-    // the entry of the main kernel: its symbol is "<entry>.kd"
-    const std::string sym = v->spec.entry + ".kd";
+    const std::string sym = entry + ".kd"; // its symbol
     size_t at = std::string::npos;
     for (size_t i = 0; i + sym.size() <= blob.size(); ++i)
         if (memcmp(&blob[i], sym.data(), sym.size()) == 0 && i > 0 && (unsigned char)blob[i - 1] == (0xa0u | sym.size())) {
             at = i;
             break;
         }
-    if (at == std::string::npos) return fail(MS_ERR_UNSUPPORTED, "ms_variant_resources_get: no metadata entry for %s", sym.c_str());
+    if (at == std::string::npos) return fail(MS_ERR_UNSUPPORTED, "no metadata entry for %s", sym.c_str());
     // the keys of one kernel's map are sorted, so those before ".symbol" precede it in the blob: scan from the start of
     // this kernel's map, which begins at the last ".agpr_count" (its first key) before the symbol
     size_t start = 0;
@@ -169,7 +173,7 @@ extern "C" int32_t ms_variant_resources_get(const ms_variant *v, ms_variant_reso
     const long vg = meta_uint(blob, ".vgpr_count", start), ag = meta_uint(blob, ".agpr_count", start), sg = meta_uint(blob, ".sgpr_count", start);
     const long sc = meta_uint(blob, ".private_segment_fixed_size", start), sp = meta_uint(blob, ".vgpr_spill_count", start);
     const long ld = meta_uint(blob, ".group_segment_fixed_size", start);
-    if (vg < 0 || sg < 0) return fail(MS_ERR_UNSUPPORTED, "ms_variant_resources_get: register counts not found in the code object");
+    if (vg < 0 || sg < 0) return fail(MS_ERR_UNSUPPORTED, "register counts not found in the code object");
     out->vgprs = (int32_t)vg;
     out->agprs = (int32_t)(ag < 0 ? 0 : ag);
     out->sgprs = (int32_t)sg;
@@ -177,6 +181,30 @@ extern "C" int32_t ms_variant_resources_get(const ms_variant *v, ms_variant_reso
     out->spilled_vgprs = (int32_t)(sp < 0 ? 0 : sp);
     out->lds_bytes = (int32_t)(ld < 0 ? 0 : ld);
     return MS_OK;
+}
+
+extern "C" int32_t ms_variant_resources_get(const ms_variant *v, ms_variant_resources *out)
+{
+    if (!v || !out) return fail(MS_ERR_BAD_ARG, "ms_variant_resources_get: NULL argument");
+    return resources_of(*v->code, v->spec.entry, out);
+}
+
+extern "C" int32_t ms_variant_launch_kernel(const ms_variant *v, int32_t instances, ms_variant_params *params, ms_variant_resources *resources)
+{
+    if (!v) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_kernel: NULL variant");
+    if (instances < 1) return fail(MS_ERR_BAD_ARG, "ms_variant_launch_kernel: instances = %d", instances);
+    v = kernel_of(v, instances);
+    int64_t lds = v->p.lds_bytes;
+    const bool many = image_rows_many(&v->op, &v->p, instances, &lds);
+    if (params) {
+        *params = v->p;
+        if (many) {
+            params->body_tile = v->p.body_tile_many;
+            params->grid[0] = (int32_t)v->spec.many_grid;
+            params->lds_bytes = (int32_t)lds;
+        }
+    }
+    return resources ? resources_of(*v->code, v->spec.entry + (many ? "_many" : ""), resources) : MS_OK;
 }
 
 extern "C" int32_t ms_prebuild(const ms_op *op, const ms_space *space, const ms_trace *traces, int32_t n, int32_t threads,

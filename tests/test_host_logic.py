@@ -867,6 +867,27 @@ def test_convolutions_without_a_tile_of_input_patches_keep_their_kernel(mk):
         assert v.launch_shape(instances) == (p.body_tile, p.grid[0] * p.grid[1] * p.grid[2], p.lds_bytes)
 
 
+def test_first_layers_of_the_planes_tests_run_on_filter_planes():
+    """The launches that test_first_layer_planes_exact compares take the kernel it is for: all its shapes, with and without an
+    epilogue.  Fewer images than fill the chip stay on image rows."""
+    import test_gpu_conv as T
+    shapes = next(m for m in T.test_first_layer_planes_exact.pytestmark if m.args[0].startswith("N,D,H"))
+    for N, D, H, W_, Cin, Cout, k, stride, pad, dtype, R in shapes.args[1]:
+        for epilogue in (True, False):
+            args = dict(stride=stride, pad=pad, in_dtype=dtype, has_bias=epilogue, relu=epilogue)
+            op = B.conv3d_op(N, D, H, W_, Cin, Cout, k, **args) if D > 1 else B.conv2d_op(N, H, W_, Cin, Cout, k, k, **args)
+            sp = op.space()
+            t = next(t for t in (B.trace_sample_valid(op, sp, 118, n) for n in range(200))
+                     if B.trace_validate(op, sp, t).compute_at == 0 and B.trace_validate(op, sp, t).family == B.FAM_GEMM_MFMA)
+            v = B.Variant(op, sp, t)
+            assert v.params().body == B.BODY_IMAGE_ROWS
+            p, r = v.launch_kernel(R)
+            assert p.body == B.BODY_CONV_PLANES and p.lds_bytes == r.lds_bytes
+    assert v.launch_kernel(1)[0].body == B.BODY_IMAGE_ROWS
+    with pytest.raises(B.MsError):
+        v.launch_kernel(0)
+
+
 def test_few_long_rows_keep_their_wide_lane_groups():
     """Softmax without staging: a few long rows keep a lane group of a wavefront or more per row; many rows, short rows and
     groups that walk a row or several rows in turn go to the row kernel, as do groups narrower than a line."""
