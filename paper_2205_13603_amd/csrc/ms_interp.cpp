@@ -454,6 +454,8 @@ int conv_planes(const ms_op *op)
     // columns of 96 channels would leave as parts of lines (128 x 128 x 3 -> 96, 3 x 3, batch 115: 20.4 us and 26.2)
     if (op->out_size != 2 || op->in_size != 2 || op->N / 32 % 3 == 0) return 0;
     if (d.dims[1] * d.dims[2] * d.dims[3] > 0x0fffffff || op->K * op->N > 0x3fffffff) return 0; // 32-bit byte offsets, ahead of a plane and behind it too
+    // planes of few steps hide no loads (3-D, 192 x 192 x 3 -> 32, 3 x 3 x 3, x 11: 15.2 us on image rows and 17.0)
+    if (op->kd > 1 && conv_planes_tile(op, 1).steps < 4) return 0;
     int best = 0;
     double cost = 0;
     for (int tm : {4, 3, 2, 1}) {
@@ -1249,11 +1251,10 @@ bool ms::takes_fill(const ms_op *op, const ms_variant_params *p, const ms_varian
     }
     if (patch->body == MS_BODY_CONV_PLANES) {
         // Launches whose rounds leave more than a quarter of the chip idle spread better in the smaller tiles of image rows (3 x 16 x
-        // 64 x 64 -> 64, 7 x 7 x 7, x 4: 11.5 us and 18.7), and a single round of small tiles (64 x 64 x 4 -> 64, 7 x 7, batch 114: 7.4
-        // and 8.1) or planes of few steps (3-D, 192 x 192 x 3 -> 32, 3 x 3 x 3, x 11: 15.2 and 17.0) hide no loads.
+        // 64 x 64 -> 64, 7 x 7 x 7, x 4: 11.5 us and 18.7), and a single round of small tiles hides no loads (64 x 64 x 4 -> 64, 7 x 7,
+        // batch 114: 7.4 and 8.1).
         const ConvPlanes c = conv_planes_tile(op, patch->body_tile);
         const int64_t tiles = (int64_t)patch->grid[0] * instances, slots = 256 * c.per_cu(), busy = (tiles + slots - 1) / slots * slots;
-        if (op->kd > 1 && c.steps < 4) return false;
         return tiles * 100 >= busy * 75 && (c.tn == 1 || c.tm >= 3 || tiles > slots);
     }
     // its wavefronts count steps in 32 bits

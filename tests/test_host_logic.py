@@ -888,6 +888,20 @@ def test_first_layers_of_the_planes_tests_run_on_filter_planes():
         v.launch_kernel(0)
 
 
+def test_no_kernel_is_built_that_no_launch_takes(tmp_path):
+    """3-D filters of fewer than four k steps per plane stay on image rows at any number of instances: nothing else is compiled."""
+    op = B.conv3d_op(1, 4, 48, 48, 3, 32, 3, stride=2, pad=1)
+    sp = op.space()
+    before = B.jit_stats()["compiled"]
+    B.set_cache_dir(str(tmp_path))
+    try:
+        v = B.Variant(op, sp, B.trace_sample_valid(op, sp, 44, 0))
+    finally:
+        B.set_cache_dir(os.environ.get("MS_CACHE_DIR") or os.path.join(ROOT, "paper_2205_13603_amd", "kcache"))
+    assert B.jit_stats()["compiled"] - before == 1
+    assert all(v.launch_kernel(r)[0].body == B.BODY_IMAGE_ROWS for r in (1, 8, 64, 512, 4096))
+
+
 def test_few_long_rows_keep_their_wide_lane_groups():
     """Softmax without staging: a few long rows keep a lane group of a wavefront or more per row; many rows, short rows and
     groups that walk a row or several rows in turn go to the row kernel, as do groups narrower than a line."""
@@ -1004,7 +1018,7 @@ def test_a_search_compiles_what_its_launches_run(mk, instances, offset, kernels,
             B.search(op, op.space(), cfg, [([4096 + offset] * 3, 4096)], on_trial=failed)
         assert e.value.code == B.MS_ERR_HIP
     finally:
-        B.set_cache_dir(os.path.join(os.path.dirname(B.LIB_PATH), "kcache"))
+        B.set_cache_dir(os.environ.get("MS_CACHE_DIR") or os.path.join(ROOT, "paper_2205_13603_amd", "kcache"))
     built = B.jit_stats()["compiled"] - before["compiled"]
     assert built == kernels if not offset else 15 <= built <= kernels
     assert stop[0] == (1 if not offset else 20)
