@@ -84,6 +84,19 @@ __device__ __forceinline__ unsigned finish(float x, float y)
 }
 #endif
 
+// Hardware deals workgroups to the XCDs in turn, XCD f % 8 gets workgroup f.  The place of f in an order in which each XCD receives
+// runs of neighbours: of RUN workgroups, the last eight runs as long as each other but for one; RUN 0: one run for each XCD.
+template <unsigned RUN> __device__ __forceinline__ unsigned xcd_run(unsigned f, unsigned total)
+{
+    unsigned from = 0, part = total;
+    if (RUN) {
+        from = f / (RUN * 8) * (RUN * 8);
+        part = total - from < RUN * 8 ? total - from : RUN * 8;
+    }
+    const unsigned at = f - from, xcd = at % 8, left = part % 8;
+    return from + xcd * (part / 8) + (xcd < left ? xcd : left) + at / 8;
+}
+
 #ifdef I0 // kernels built from the factors of a trace
 // Workgroup -> (z, i0, j0): z = instance * batch + batch index, (i0, j0) = the two outer spatial loops.
 // REORDER 0: i outer.  1: j outer.  2: i outer, after a permutation of the launch-wide workgroup

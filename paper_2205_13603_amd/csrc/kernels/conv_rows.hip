@@ -136,12 +136,14 @@ __device__ __forceinline__ void image_rows(const void *__restrict__ x_, const vo
     __shared__ __attribute__((aligned(16))) char smem[T::LDS_B];
     int wg = blockIdx.x, z = blockIdx.z * gridDim.y + blockIdx.y; // z = instance
     {
-        // workgroup order grouped per XCD, in runs that differ by one at most: tiles that share input rows and planes meet in one L2
-        // (5 x 8 x 160 x 160 x 4 -> 32, 7 x 7 x 7: 24.6 us in the order of launch, 22.1)
-        const unsigned total = gridDim.x * gridDim.y * gridDim.z, f = wg + gridDim.x * z, left = total % 8;
-        const unsigned g = f % 8 * (total / 8) + (f % 8 < left ? f % 8 : left) + f / 8;
-        wg = (int)(g % gridDim.x);
-        z = (int)(g / gridDim.x);
+        // Workgroup order grouped per XCD: tiles that share input rows and planes meet in one L2 (5 x 8 x 160 x 160 x 4 -> 32, 7 x 7 x 7: 24.6 us
+        // in the order of launch, 22.1).  Planes are shared furthest apart, in one run for each XCD; rows in runs of 32 (114 x 96 x 96 x 3 -> 64,
+        // 5 x 5: 9.7 us in the order of launch, 10.1 in one run, 9.4 in runs of 32; 103 x 96 x 96 x 4 -> 96, 3 x 3: 12.6, 11.5, 11.2).
+        // Divisions by a constant: by gridDim.x a launch of 5 us took 0.2 to 0.7 longer.
+        constexpr unsigned GROUPS = JB * CV_OD * TILES * CV_N; // of an instance: gridDim.x
+        const unsigned g = xcd_run<CV_OD == 1 ? 32 : 0>(wg + GROUPS * z, GROUPS * gridDim.y * gridDim.z);
+        wg = (int)(g % GROUPS);
+        z = (int)(g / GROUPS);
     }
     if (z >= instances) return;
     const int jb = wg % JB, od = wg / JB % CV_OD, tile = wg / (JB * CV_OD) % TILES, n = wg / (JB * CV_OD * TILES);
@@ -255,7 +257,14 @@ __device__ __forceinline__ void image_rows(const void *__restrict__ x_, const vo
     (void)bias_;
 }
 
-extern "C" __global__ void __launch_bounds__(NT, 2)
+// Wavefronts of a SIMD that the registers are to leave room for.  Tiles of 2 x 3 intrinsics with little on its way come out at 126 to 130 of
+// the 128 registers that four of them share, by accident of the compiler: 231 x 64 x 64 x 3 -> 96, 5 x 5 with 130 13.3 us, with 128 12.6.
+template <int TM, bool SPAN> constexpr int rows_waves()
+{
+    return TM * TN == 6 && CV_KD == 1 && TM * TN * 16 + (tile_t<TM, SPAN>::XI + WI) * 4 <= 128 ? 4 : 2;
+}
+
+extern "C" __global__ void __launch_bounds__(NT, (rows_waves<CR_TM, CR_SPAN>()))
 ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *__restrict__ bias_, void *__restrict__ y_, int instances)
 {
     image_rows<CR_TM, CR_SPAN>(x_, w_, bias_, y_, instances);
@@ -263,7 +272,7 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
 
 #if CR_MANY_TM
 // the larger tile of launches over many instances; which launches take it says image_rows_many() in ms_interp.cpp
-extern "C" __global__ void __launch_bounds__(NT, 2)
+extern "C" __global__ void __launch_bounds__(NT, (rows_waves<CR_MANY_TM, CR_MANY_SPAN>()))
 ms_kernel_many(const void *__restrict__ x_, const void *__restrict__ w_, const void *__restrict__ bias_, void *__restrict__ y_, int instances)
 {
     image_rows<CR_MANY_TM, CR_MANY_SPAN>(x_, w_, bias_, y_, instances);

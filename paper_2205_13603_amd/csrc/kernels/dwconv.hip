@@ -29,6 +29,7 @@
 // 327 against 300 us on 112 x 112 x 32, stride 1).
 constexpr int SP_H = (STRIP - 1) * CV_STRIDE + CV_KH, SP_W = (STRIP - 1) * CV_STRIDE + CV_KW; // input patch of a strip
 constexpr int S_OH = (CV_OH + STRIP - 1) / STRIP, S_OW = (CV_OW + STRIP - 1) / STRIP;           // strips of an image
+constexpr unsigned S_GROUPS = (S_OH * S_OW * CV_C + STRIP_THREADS - 1) / STRIP_THREADS;          // workgroups of an image: gridDim.x
 constexpr int IMG_BYTES = CV_H * CV_W * CV_C * 4;
 
 // Results of 4 MiB and more are streamed (200 launches measured on both sides; 57 x 57 x 144, stride 2, batch 128: 56.8 us, plain 60.2).
@@ -48,12 +49,16 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
     int z = blockIdx.z * gridDim.y + blockIdx.y; // instance * N + n
     int wg = blockIdx.x;
     {
-        // workgroup order grouped per XCD, in runs that differ by one at most: strips that share input rows meet in one L2 (18 x 66 x 66 x 328,
-        // stride 1, 6678 workgroups: 52 us in the order of launch)
-        const unsigned total = gridDim.x * gridDim.y * gridDim.z, f = wg + gridDim.x * z, xcd = f % 8, left = total % 8;
-        const unsigned g = xcd * (total / 8) + (xcd < left ? xcd : left) + f / 8;
-        wg = (int)(g % gridDim.x);
-        z = (int)(g / gridDim.x);
+        // Workgroup order grouped per XCD: strips that share input rows meet in one L2 (18 x 66 x 66 x 328, stride 1, 6678 workgroups: 52 us in
+        // the order of launch, 31.7).  In one run for each XCD, or, from about 90 MB of images on, in runs of 32: the last-level cache no longer
+        // holds those for the next launch, and eight places far apart are read from HBM more slowly than one (154 x 33 x 33 x 208: one run
+        // 67.1 us, in the order of launch 64.0, runs of 32 62.1; 29 x 112 x 112 x 152, 5 x 5: 137, 131, 126; below, short runs share fewer rows:
+        // 17 x 65 x 65 x 288, 5 x 5, 83 MB: 33.8, 55.1, 35.1; 55 x 32 x 32 x 272, 61 MB: 18.2, 26.2, 19.6).
+        // Divisions by a constant: by gridDim.x a launch of 4 us took 0.3 to 0.9 longer.
+        const unsigned images = gridDim.y * gridDim.z, total = S_GROUPS * images, f = wg + S_GROUPS * z;
+        const unsigned g = images > 90000000u / IMG_BYTES ? xcd_run<32>(f, total) : xcd_run<0>(f, total);
+        wg = (int)(g % S_GROUPS);
+        z = (int)(g / S_GROUPS);
     }
     if (z >= instances * CV_N) return;
     const int item = wg * STRIP_THREADS + threadIdx.x;

@@ -902,6 +902,42 @@ def test_no_kernel_is_built_that_no_launch_takes(tmp_path):
     assert all(v.launch_kernel(r)[0].body == B.BODY_IMAGE_ROWS for r in (1, 8, 64, 512, 4096))
 
 
+def test_order_of_workgroups_is_a_permutation_in_runs(tmp_path):
+    """xcd_run() of the kernels, compiled for the host: every workgroup once for any total, and neighbours on one XCD in runs of the
+    length asked for."""
+    src = open(os.path.join(ROOT, "paper_2205_13603_amd", "csrc", "kernels", "common.h")).read()
+    fn = src[src.index("template <unsigned RUN>"):]
+    fn = fn[:fn.index("\n}\n") + 3]
+    (tmp_path / "t.cpp").write_text("""
+#include <cstdio>
+#include <vector>
+#define __device__
+#define __forceinline__
+%s
+template <unsigned RUN> int check(unsigned total)
+{
+    std::vector<unsigned> xcd(total, 8);
+    for (unsigned f = 0; f < total; ++f) {
+        const unsigned g = xcd_run<RUN>(f, total);
+        if (g >= total || xcd[g] != 8) return 1;
+        xcd[g] = f %% 8;
+    }
+    unsigned runs = 1;
+    for (unsigned g = 1; g < total; ++g) runs += xcd[g] != xcd[g - 1];
+    const unsigned pieces = RUN ? (total + RUN * 8 - 1) / (RUN * 8) : 1;
+    return runs > pieces * 8;
+}
+int main()
+{
+    for (unsigned total = 1; total < 3000; ++total)
+        if (check<0>(total) || check<32>(total)) return printf("%%u\\n", total), 1;
+    return check<0>(100003) || check<32>(100003);
+}
+""" % fn)
+    subprocess.run(["g++", "-O1", "-o", str(tmp_path / "t"), str(tmp_path / "t.cpp")], check=True)
+    subprocess.run([str(tmp_path / "t")], check=True)
+
+
 def test_few_long_rows_keep_their_wide_lane_groups():
     """Softmax without staging: a few long rows keep a lane group of a wavefront or more per row; many rows, short rows and
     groups that walk a row or several rows in turn go to the row kernel, as do groups narrower than a line."""
