@@ -549,9 +549,18 @@ int conv_patch(const ms_op *op)
                             const ConvPatch c = conv_patch_tile(op, t.code());
                             const int per_simd = (c.per_cu * (c.waves + 1) + 3) / 4;
                             if (c.waves > 15 || c.waves < 2 || c.waves >= g_limits.max_waves || (c.waves + 1) * 64 > g_limits.max_threads) continue;
-                            if (c.lds > g_limits.max_lds_bytes || c.loads > 150) continue; // a register of the loads' wavefront for each
-                            // sums, a step's weights and about 60 others
-                            if (r * tn * 4 + d.dims[5] * tn * 4 + 60 > 512 / per_simd / 8 * 8 || r * tn * 4 > g_limits.max_acc_per_thread) continue;
+                            // Registers: an address for each load, in the loads' wavefront; sums, a step's weights and at least 60 others in
+                            // those that multiply
+                            const int64_t budget = 512 / per_simd / 8 * 8, live = r * tn * 4 + d.dims[5] * tn * 4;
+                            if (c.lds > g_limits.max_lds_bytes || c.loads > std::min<int64_t>(150, budget - 40)) continue;
+                            if (live + 60 > budget || r * tn * 4 > g_limits.max_acc_per_thread) continue;
+                            // 64 channels of a wavefront take half as many again for fragments and results on their way: 254 of 256 registers for
+                            // 8 rows under 3 x 3, 276 where that is dilated, 266 for 7 rows under 5 x 5.  Their spills cost more than smaller
+                            // tiles (56 x 56 x 64 -> 64, dilation 2, x 176: 57 us and 43; 28 x 28 x 64 -> 64, 5 x 5, x 248: 39.9 and 36.0), but in
+                            // dilated layers of a batch (16 x 16 x 64 -> 128, batch 512: 22.0 and 24.7; 32 x 32 x 128 -> 256, batch 64: 32.9
+                            // and 35.3).  Two registers too many at 32 channels cost nothing (40 x 40 x 64 -> 128 x 168: 44.1 and 47.3).
+                            const bool dilated = d.dilation > 1;
+                            if (tn == 4 && live * 3 / 2 + (dilated ? 8 : -8) > budget && !(dilated && d.dims[0] > 1)) continue;
                             if (c.imgs * images + ahead > 0x3fffffff || c.tiles > 0x7fffffff) continue;
                             const int64_t slots = 256 * c.per_cu;
                             const double clocks = (double)((c.tiles + slots - 1) / slots) * c.clocks, many = (double)c.tiles / slots * c.clocks;

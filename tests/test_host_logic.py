@@ -938,6 +938,17 @@ int main()
     subprocess.run([str(tmp_path / "t")], check=True)
 
 
+@pytest.mark.parametrize("N,size,cout,k,dil,R", [(1, 56, 64, 3, 2, 512), (1, 16, 128, 3, 2, 512), (1, 28, 64, 5, 1, 512), (200, 28, 64, 5, 1, 1),
+                                                 (1, 56, 64, 3, 1, 512)])
+def test_input_patches_do_not_spill(N, size, cout, k, dil, R):
+    """The compiled kernels of residual layers whose tiles are as large as the registers allow: nothing in scratch memory."""
+    op = B.conv2d_op(N, size, size, 64, cout, k, k, pad=dil * (k - 1) // 2, dilation=dil)
+    sp = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, sp, 5, n) for n in range(200)) if B.trace_validate(op, sp, t).family == B.FAM_GEMM_MFMA)
+    p, r = B.Variant(op, sp, t).launch_kernel(R)
+    assert p.body == B.BODY_CONV_PATCH and r.scratch_bytes == 0 and r.spilled_vgprs == 0
+
+
 def test_few_long_rows_keep_their_wide_lane_groups():
     """Softmax without staging: a few long rows keep a lane group of a wavefront or more per row; many rows, short rows and
     groups that walk a row or several rows in turn go to the row kernel, as do groups narrower than a line."""
