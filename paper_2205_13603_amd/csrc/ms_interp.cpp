@@ -1256,7 +1256,13 @@ bool ms::takes_fill(const ms_op *op, const ms_variant_params *p, const ms_varian
         // nests (48 x 4096 x 2048: 7.0 us and 11.2; x 2: 10.5 and 12.2; 128 x 1024 x 1024: x 4 8.8 and 12.5; 128 x 8192 x 4096:
         // 23 and 33; 16 x 16384 x 4096: 23.1 and 23.5).  Beyond, nests fill the chip and load each operand fewer times (48 x 4096 x
         // 2048 x 8: 31 and 25; 16 x 1024 x 1024 x 64: 30 and 22; 128 x 16384 x 1024: 13.1 and 10.4).
-        return patch->grid[0] * instances <= 1024 && op->M * op->N * instances <= 1024 * 1024;
+        // Long reductions of few tiles that the trace splits over workgroups keep its nest, second kernel included: tiles leave half of the chip
+        // idle (16 x 3072 x 4096: 11.3 us and 9.2; 32 x 1280 x 4096: 9.9 and 8.1; 32 x 2048 x 4096: 9.3 and 8.7).  Up to 64 tiles the
+        // weights are read from the caches (32 x 1024 x 4096: 5.2 and 9.2; 16 x 2048 x 4096: 9.7 and 9.9), shorter reductions and more rows
+        // lose by the partial sums (16 x 4096 x 3072: 8.5 and 8.8; 32 x 2048 x 3072: 7.2 and 7.6; 48 x 1344 x 4096: 8.2 and 8.9).
+        const int64_t tiles = patch->grid[0] * instances;
+        if (p->rfactor >= 4 && tiles > 64 && tiles <= 128 && op->K >= 2560 + 48 * op->M) return false;
+        return tiles <= 1024 && op->M * op->N * instances <= 1024 * 1024;
     }
     if (patch->body == MS_BODY_CONV_PLANES) {
         // Launches whose rounds leave more than a quarter of the chip idle spread better in the smaller tiles of image rows (3 x 16 x

@@ -949,6 +949,21 @@ def test_input_patches_do_not_spill(N, size, cout, k, dil, R):
     assert p.body == B.BODY_CONV_PATCH and r.scratch_bytes == 0 and r.spilled_vgprs == 0
 
 
+@pytest.mark.parametrize("M,N,K,rf,few", [
+    (32, 2048, 4096, 4, False), (32, 2048, 4096, 2, True), (32, 2048, 3072, 4, True), (32, 1024, 4096, 4, True), (16, 3072, 4096, 4, False),
+    (48, 1344, 4096, 4, True),
+    (16, 1024, 512, 1, True), (16, 1024, 448, 1, False)])  # 1 MiB of weights and less
+def test_which_products_of_few_rows_replace_a_nest(M, N, K, rf, few):
+    """Long reductions of few tiles that the trace splits over four workgroups and more keep its nest; so do small matrices."""
+    op = B.gemm_op(M, N, K, "f16")
+    sp = op.space(B.SPACE_DEFAULT | B.SPACE_RFACTOR)
+    t = B.make_trace(sp, [[161616], [M // 16, 1, 1, 1], [N // 64, 1, 4, 1], [K // 64, 1, 4, 1], [16], [1], [8], [8], [2], [0], [1 if rf == 1 else 0], [rf]])
+    v = B.Variant(op, sp, t)
+    assert v.params().rfactor == rf and v.params().body == B.BODY_NEST
+    assert v.launch_kernel(1)[0].body == (B.BODY_FEW_ROWS if few else B.BODY_NEST)
+    assert v.workspace_bytes() == (rf * M * N * 4 if rf > 1 else 0)
+
+
 def test_few_long_rows_keep_their_wide_lane_groups():
     """Softmax without staging: a few long rows keep a lane group of a wavefront or more per row; many rows, short rows and
     groups that walk a row or several rows in turn go to the row kernel, as do groups narrower than a line."""
