@@ -1266,11 +1266,15 @@ bool ms::takes_fill(const ms_op *op, const ms_variant_params *p, const ms_varian
     }
     if (patch->body == MS_BODY_CONV_PLANES) {
         // Launches whose rounds leave more than a quarter of the chip idle spread better in the smaller tiles of image rows (3 x 16 x
-        // 64 x 64 -> 64, 7 x 7 x 7, x 4: 11.5 us and 18.7), and a single round of small tiles hides no loads (64 x 64 x 4 -> 64, 7 x 7,
-        // batch 114: 7.4 and 8.1).
+        // 64 x 64 -> 64, 7 x 7 x 7, x 4: 11.5 us and 18.7); two rounds of tiles of 3 x 2 intrinsics whose second one is less than two
+        // thirds full do so too (128 x 128 x 3 -> 64, 7 x 7, batch 75, 825 of 1024: 12.2 and 13.7; 192 x 192 x 3 -> 64, 7 x 7, batch 36, 864:
+        // 14.8 and 14.1; 4 x 2, 192 x 192 x 3 -> 64, 7 x 7, batch 47, 846: 20.4 and 18.2).  A single round hides no loads under small tiles
+        // (64 x 64 x 4 -> 64, 7 x 7, batch 114: 7.4 and 8.1) or large ones of few steps (192 x 192 x 4 -> 64, 3 x 3, batch 27: 9.3 and 10.1).
         const ConvPlanes c = conv_planes_tile(op, patch->body_tile);
         const int64_t tiles = (int64_t)patch->grid[0] * instances, slots = 256 * c.per_cu(), busy = (tiles + slots - 1) / slots * slots;
-        return tiles * 100 >= busy * 75 && (c.tn == 1 || c.tm >= 3 || tiles > slots);
+        if (c.tn == 1) return tiles * 100 >= busy * 75;
+        if (tiles <= slots && (c.tm < 3 || (c.tm == 4 && op->kd == 1 && c.steps < 4))) return false;
+        return tiles * 100 >= busy * (c.tm <= 3 && busy == 2 * slots ? 83 : 75);
     }
     // its wavefronts count steps in 32 bits
     const int64_t tiles = (int64_t)patch->grid[0] * instances;

@@ -964,6 +964,17 @@ def test_which_products_of_few_rows_replace_a_nest(M, N, K, rf, few):
     assert v.workspace_bytes() == (rf * M * N * 4 if rf > 1 else 0)
 
 
+@pytest.mark.parametrize("size,cin,k,batch,planes", [
+    (128, 3, 7, 75, False), (192, 3, 7, 36, True), (192, 3, 7, 47, True),   # two rounds: 825 and 864 of 1024 tiles of 3 x 2, 846 of 4 x 2
+    (192, 4, 3, 27, False), (224, 3, 5, 18, True),                          # a single round of few steps, of more
+    (64, 3, 5, 133, True)])
+def test_which_first_layers_fill_their_rounds(size, cin, k, batch, planes):
+    op = B.conv2d_op(batch, size, size, cin, 64, k, k, stride=2, pad=k // 2)
+    sp = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, sp, 45, n) for n in range(200)) if B.trace_validate(op, sp, t).body == B.BODY_IMAGE_ROWS)
+    assert B.Variant(op, sp, t).launch_kernel(1)[0].body == (B.BODY_CONV_PLANES if planes else B.BODY_IMAGE_ROWS)
+
+
 def test_few_long_rows_keep_their_wide_lane_groups():
     """Softmax without staging: a few long rows keep a lane group of a wavefront or more per row; many rows, short rows and
     groups that walk a row or several rows in turn go to the row kernel, as do groups narrower than a line."""
