@@ -104,10 +104,11 @@ template <unsigned RUN> __device__ __forceinline__ unsigned xcd_run(unsigned f, 
 // (x fastest, then y, z) to XCD f mod 8, so id (f mod 8) * (total / 8) + f / 8 makes the workgroups
 // one XCD receives consecutive in (z, i0, j0) order; tiles that share operand panels, and whole
 // instances, then sit behind one L2.
-// Batched products of several tiles do so under REORDER 0 and 1 too where the launch writes more than the L2s hold: tiles whose rows
-// are no whole lines then join them in one L2, and tiles of one product find its operands there (12 x 416 x 416 x 128 x 71 in fp16:
+// Batched products whose rows are split into several tiles do so under REORDER 0 and 1 too where the launch writes more than the L2s
+// hold: tiles whose rows are no whole lines then join them in one L2, and tiles of one product find its operands there (12 x 416 x 416 x 128 x 71 in fp16:
 // 139 -> 124 us; 16 x 432 x 432 x 32 x 42 in bf16: 81 -> 65; 8 x 448 x 128 x 448 x 75: 118 -> 100).  Launches below lose a little to
-// the arithmetic (12 x 384 x 384 x 32 x 2: 4.1 and 4.4).
+// the arithmetic (12 x 384 x 384 x 32 x 2: 4.1 and 4.4); tiles of whole rows lose to the order (8 x 320 x 32 x 320, 233 instances: 99.9 in that
+// of launch, 106.7; 17 of 20 such sizes).
 // RFACTOR > 1 (matrix-core kernels): RFACTOR consecutive workgroups share one output tile, workgroup ks
 // of them reduces over the ks-th run of k0 steps.
 #ifndef RFACTOR
@@ -119,7 +120,7 @@ __device__ __forceinline__ void block_to_tile(int &z, int &i0, int &j0, int &ks)
     int wg = blockIdx.x;
     z = blockIdx.z * gridDim.y + blockIdx.y;
 #if defined(DIM_B) && !IS_CONV
-    constexpr bool JOIN = REORDER < 2 && DIM_B > 1 && G > 1;
+    constexpr bool JOIN = REORDER < 2 && DIM_B > 1 && J0 > 1;
 #else
     constexpr bool JOIN = false;
 #endif
