@@ -105,10 +105,10 @@ template <unsigned RUN> __device__ __forceinline__ unsigned xcd_run(unsigned f, 
 // one XCD receives consecutive in (z, i0, j0) order; tiles that share operand panels, and whole
 // instances, then sit behind one L2.
 // Batched products whose rows are split into several tiles do so under REORDER 0 and 1 too where the launch writes more than the L2s
-// hold: tiles whose rows are no whole lines then join them in one L2, and tiles of one product find its operands there (12 x 416 x 416 x 128 x 71 in fp16:
-// 139 -> 124 us; 16 x 432 x 432 x 32 x 42 in bf16: 81 -> 65; 8 x 448 x 128 x 448 x 75: 118 -> 100).  Launches below lose a little to
+// hold: tiles whose rows are no whole lines then join them in one L2, and tiles of one product find its operands there
+// (12 x 416 x 416 x 128 x 71 in fp16: 139 -> 124 us; 16 x 432 x 432 x 32 x 42 in bf16: 81 -> 65; 8 x 448 x 128 x 448 x 75: 118 -> 100).  Launches below lose a little to
 // the arithmetic (12 x 384 x 384 x 32 x 2: 4.1 and 4.4); tiles of whole rows lose to the order (8 x 320 x 32 x 320, 233 instances: 99.9 in that
-// of launch, 106.7; 17 of 20 such sizes).
+// of launch, 106.7; 19 of 21 such sizes by 0.4 to 6 %).
 // RFACTOR > 1 (matrix-core kernels): RFACTOR consecutive workgroups share one output tile, workgroup ks
 // of them reduces over the ks-th run of k0 steps.
 #ifndef RFACTOR

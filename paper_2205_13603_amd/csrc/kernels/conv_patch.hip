@@ -11,7 +11,7 @@
 // the counter of loads and stores runs down in issue order, and behind a tile's streamed stores a load would wait for HBM.
 // What bounds it: the two wavefronts of a SIMD run through a step's first fragment reads and a tile's results at nearly the same
 // time, one waiting for the other no further than the rings allow.  56 x 56 x 64 -> 64 x 512 in fp16: 126 us, 42 % matrix-core busy
-// at 2.15 GHz; without products 102, without patch loads 108, without stores 110; 141 before, from weights and patches resident
+// at 2.15 GHz; without products 102, without patch loads 108, without stores 110; 143 before, from weights and patches resident
 // under helper wavefronts.  48 x 48 x 96 -> 32, batch 440: 180 -> 71; 32 x 32 x 256 -> 32, dilation 2, batch 144: 86 -> 34.
 #include "common.h"
 
