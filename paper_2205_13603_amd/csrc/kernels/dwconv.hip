@@ -53,10 +53,12 @@ ms_kernel(const void *__restrict__ x_, const void *__restrict__ w_, const void *
         // the order of launch, 31.7).  In one run for each XCD, or, from about 90 MB of images on, in runs of 32: the last-level cache no longer
         // holds those for the next launch, and eight places far apart are read from HBM more slowly than one (154 x 33 x 33 x 208: one run
         // 67.1 us, in the order of launch 64.0, runs of 32 62.1; 29 x 112 x 112 x 152, 5 x 5: 137, 131, 126; below, short runs share fewer rows:
-        // 17 x 65 x 65 x 288, 5 x 5, 83 MB: 33.8, 55.1, 35.1; 55 x 32 x 32 x 272, 61 MB: 18.2, 26.2, 19.6).
+        // 17 x 65 x 65 x 288, 5 x 5, 83 MB: 33.8, 55.1, 35.1; 55 x 32 x 32 x 272, 61 MB: 18.2, 26.2, 19.6).  Multiples of 8 keep one run:
+        // images that have just been written are in part still in that cache, where eight places meet more of them (57 x 57 x 144, stride 2,
+        // batch 128, first pass on new images: 71 us, runs of 32 85; again and again 57.2 and 55.1).
         // Divisions by a constant: by gridDim.x a launch of 4 us took 0.3 to 0.9 longer.
         const unsigned images = gridDim.y * gridDim.z, total = S_GROUPS * images, f = wg + S_GROUPS * z;
-        const unsigned g = images > 90000000u / IMG_BYTES ? xcd_run<32>(f, total) : xcd_run<0>(f, total);
+        const unsigned g = total % 8 && images > 90000000u / IMG_BYTES ? xcd_run<32>(f, total) : xcd_run<0>(f, total);
         wg = (int)(g % S_GROUPS);
         z = (int)(g / S_GROUPS);
     }
