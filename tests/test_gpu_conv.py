@@ -905,6 +905,20 @@ def test_conv_patch_operands_off_16_byte_boundaries():
             assert np.array_equal(got, ref), offsets
 
 
+def test_conv_patch_static_launch_exact():
+    """Input patches through the launch that allocates nothing."""
+    g = I.rng(153)
+    X, Wt = I.small_ints(g, (64, 16, 16, 32), -2, 2, "f16"), I.small_ints(g, (3, 3, 32, 32), -1, 1, "f16")
+    bias = g.integers(-3, 4, size=32).astype(np.float32)
+    op = B.conv2d_op(64, 16, 16, 32, 32, 3, 3, stride=1, pad=1)
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 114, n) for n in range(400)) if B.trace_validate(op, space, t).family == B.FAM_GEMM_MFMA)
+    assert B.Variant(op, space, t).launch_kernel(1)[0].body == B.BODY_CONV_PATCH
+    ref = O.conv2d_nhwc(X, Wt, bias=bias, relu=True, stride=1, pad=1)
+    got = run_variant_offset(op, space, t, [X, Wt, bias], "f16", ref.shape, [0, 0, 0, 0], static=True)
+    assert got is None or np.array_equal(got, ref)
+
+
 @pytest.mark.parametrize("N,D,H,W_,Cin,Cout,k,stride,pad,dtype,R", [
     (1, 6, 32, 32, 3, 64, 7, 2, 3, "f16", 512),         # planes at the ends of the depth meet fewer filter planes
     (1, 7, 21, 40, 1, 32, 7, 2, 3, "bf16", 512),        # 32 channels, the last tile of a plane in part

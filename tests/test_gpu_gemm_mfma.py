@@ -745,6 +745,19 @@ def test_few_rows_exact(M, N, K, dtype, out, R, a_row, b_row):
             assert np.array_equal(got.reshape(M, N), refs[0], equal_nan=True), "offset"
 
 
+@pytest.mark.parametrize("static,output", [(True, 0), (False, 1), (True, 3)])
+def test_few_rows_static_launches_and_outputs_off_16_byte_boundaries(static, output):
+    """The second kernel through the launch that allocates nothing, and its results at any address: integers, exact."""
+    g = I.rng(151)
+    op = B.gemm_op(48, 1024, 512, "f16")
+    space = op.space()
+    t = next(t for t in (B.trace_sample_valid(op, space, 152, n) for n in range(400)) if B.trace_validate(op, space, t).body == B.BODY_NEST)
+    assert B.Variant(op, space, t).launch_kernel(1)[0].body == B.BODY_FEW_ROWS
+    a, b = I.small_ints(g, (48, 512), -1, 1, "f16"), I.small_ints(g, (512, 1024), -1, 1, "f16")
+    got = run_variant_offset(op, space, t, [a, b], "f16", (48, 1024), [0, 0, output], static=static)
+    assert got is None or np.array_equal(got, O.gemm(a, b))
+
+
 @pytest.mark.parametrize("trans_b", [True, False])
 @pytest.mark.parametrize("reorder", [0, 1])
 @pytest.mark.parametrize("many", [48, 49, 50])
